@@ -6,8 +6,8 @@
 // chunk into a partial [dphi][d] + [dphi], and a second kernel sums the partials of a head
 // in chunk order, so the result does not depend on scheduling.
 //
-// bf16 caches use the matrix cores for both contractions (features = K Wk^T, then
-// S = Phi^T [V | 1]); other storage types use a generic fp32 kernel.
+// bf16 caches with d_phi = d use bf16 matrix instructions for both contractions (features = K Wk^T, then
+// S = Phi^T [V | 1]); other storage types and feature widths the fp32 ones.
 #include "block_utils.h"
 #include "tkphi_internal.h"
 
@@ -298,19 +298,29 @@ void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __
 }
 
 // ------------------------------------------------------------------------------------
-// generic kernel (any storage type, fp32 arithmetic): grid (n_build_chunks, Hkv, n_problems)
-// threads form a 16 x 16 grid over (feature block, channel block).
+// fp32 arithmetic on the matrix cores (any storage type, any d_phi): grid (n_build_chunks, Hkv, n_problems),
+// 4 wavefronts; wavefront w owns the feature tiles w, w + 4, ... (FTW = ceil(d_phi / 64) of them).
+//
+// Tiles of 64 tokens: the key and value rows are widened to fp32 into LDS (the next tile's loads are in flight while
+// one is contracted).  Per 16 tokens:
+//   GEMM1  P[16 tokens][16 features] = K Wk^T with v_mfma_f32_16x16x4_f32: the four inner indices of step
+//          (jj, e) are the channels 16 jj + 4 kg + e, so one 16-byte read per lane feeds four steps
+//   GEMM2  S[16 features][channels] += Phi^T V: GEMM1 leaves lane (r, kg) with feature r of the tokens
+//          4 kg + i, which is the A operand of step i over the tokens {i, 4 + i, 8 + i, 12 + i}: the features never
+//          touch LDS
+// Rows are padded by 4 floats: the 16-byte reads of GEMM1 and the 4-byte reads of GEMM2 then spread over all banks.
+// What bounds it: latency for the few tokens fp32 caches come with.  A VALU version with 16-token batches that read the
+// Wk rows again for every batch, on chunks of 256 tokens, took 325 us for one head of 4028 tokens at d = 64
+// (16 workgroups); this one, 63 chunks of 64 tokens, 8.5 us, and the call 328 -> 11.4 us.
 // ------------------------------------------------------------------------------------
-constexpr int kTB = 16;   // tokens per batch
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void build_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                         char* __restrict__ ws) {
-  __shared__ float kf[kTB][kMaxDim];
-  __shared__ float vf[kTB][kMaxDim];
-  __shared__ float ph[kTB][kMaxDim];
-  constexpr int FJmax = kMaxDim / 16, FCmax = 128 / 16;
-
+template <typename T, int D, int FTW>
+__global__ __launch_bounds__(kThreads) void build_f32_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+                                                             char* __restrict__ ws) {
+  constexpr int TT = 64, ROWF = D + 4, EPL = Elem<T>::per16, SEGS = D / EPL, NLD = TT * SEGS / kThreads;
+  constexpr int CT = D / 16;
+  extern __shared__ __attribute__((aligned(16))) float lds_f[];      // keys [TT][ROWF], values [TT][ROWF]
+  float* k_s = lds_f;
+  float* v_s = lds_f + TT * ROWF;
   const int ch = blockIdx.x, h = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
@@ -318,84 +328,151 @@ __global__ __launch_bounds__(kThreads) void build_kernel(Geom g, const tkphi_pro
   const int c0 = ch * g.build_chunk;
   if (c0 >= n) return;
   const int c1 = min(n, c0 + g.build_chunk);
-  const int d = g.d, dphi = g.dphi;
-  const int FJ = dphi / 16, FC = d / 16;
-  const int tj = tid / 16, tc = tid % 16;
+  const int dphi = g.dphi, NFT = dphi / 16;
+  const int lane = tid & 63, wv = tid >> 6, r = lane & 15, kg = lane >> 4;
 
-  float acc[FJmax][FCmax];
-  float uacc[FJmax];
+  const int64_t base = (int64_t)h * pr.stride_head + (int64_t)g.n_sink * pr.stride_tok;
+  u32x4 kr[NLD], vr[NLD];
+  auto request = [&](int t0) {                       // rows past the end repeat the last one
 #pragma unroll
-  for (int a = 0; a < FJmax; ++a) {
-    uacc[a] = 0.f;
-#pragma unroll
-    for (int b = 0; b < FCmax; ++b) acc[a][b] = 0.f;
-  }
-  const int64_t head_off = (int64_t)h * pr.stride_head;
-
-  for (int base = c0; base < c1; base += kTB) {
-    const int nt = min(kTB, c1 - base);
-    __syncthreads();
-    for (int i = tid; i < kTB * d; i += kThreads) {
-      const int t = i / d, c = i % d;
-      float kv = 0.f, vv = 0.f;
-      if (t < nt) {
-        const int64_t off = head_off + (int64_t)(g.n_sink + base + t) * pr.stride_tok + c;
-        kv = Elem<T>::load1(pr.K, off);
-        vv = Elem<T>::load1(pr.V, off);
-      }
-      kf[t][c] = kv; vf[t][c] = vv;
+    for (int i = 0; i < NLD; ++i) {
+      const int idx = tid + i * kThreads;
+      const int64_t off = base + (int64_t)min(t0 + idx / SEGS, c1 - 1) * pr.stride_tok + (idx % SEGS) * EPL;
+      kr[i] = gload128((const char*)pr.K + off * sizeof(T));
+      vr[i] = gload128((const char*)pr.V + off * sizeof(T));
     }
+  };
+  auto commit = [&](int t0) {                        // -> LDS as fp32; rows past the end as zeros
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int idx = tid + i * kThreads, row = idx / SEGS;
+      const bool ok = t0 + row < c1;
+      float x[EPL], y[EPL];
+      Elem<T>::unpack(make_uint4(kr[i].x, kr[i].y, kr[i].z, kr[i].w), x);
+      Elem<T>::unpack(make_uint4(vr[i].x, vr[i].y, vr[i].z, vr[i].w), y);
+      float* kd = k_s + row * ROWF + (idx % SEGS) * EPL;
+      float* vd = v_s + row * ROWF + (idx % SEGS) * EPL;
+#pragma unroll
+      for (int e = 0; e < EPL; e += 4) {
+        *(floatx4*)(kd + e) = ok ? (floatx4){x[e], x[e + 1], x[e + 2], x[e + 3]} : (floatx4){0.f, 0.f, 0.f, 0.f};
+        *(floatx4*)(vd + e) = ok ? (floatx4){y[e], y[e + 1], y[e + 2], y[e + 3]} : (floatx4){0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  };
+  request(c0);
+
+  // this wavefront's slice of Wk (lane (r, kg): feature r of a tile, channels 16 jj + 4 kg ..); at d_phi > 128 it does not
+  // fit the registers beside S and is read again per 16 tokens (from L1 / L2)
+  constexpr bool W_REG = FTW * D <= 256;
+  constexpr int WN = W_REG ? FTW : 1;
+  floatx4 wk[WN][CT];
+  float bias[FTW];
+  auto load_w = [&](int k, floatx4 (&w)[CT]) {
+    const int64_t wrow = ((int64_t)h * dphi + min(wv + 4 * k, NFT - 1) * 16 + r) * D;
+#pragma unroll
+    for (int jj = 0; jj < CT; ++jj) {
+      if (sizeof(T) == 4) {
+        const u32x4 t = gload128((const char*)pr.Wk + (wrow + jj * 16 + kg * 4) * 4);
+        w[jj] = (floatx4){__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)};
+      } else {
+        const u32x2 t = *(const __attribute__((address_space(1))) u32x2*)((const char*)pr.Wk + (wrow + jj * 16 + kg * 4) * 2);
+        w[jj] = (floatx4){__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16),
+                          __uint_as_float(t.y & 0xffff0000u)};
+      }
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < FTW; ++k) {
+    if (W_REG) load_w(k, wk[W_REG ? k : 0]);
+    bias[k] = pr.bk[(int64_t)h * dphi + min(wv + 4 * k, NFT - 1) * 16 + r];
+  }
+  floatx4 sacc[FTW][CT];
+  float uacc[FTW];
+#pragma unroll
+  for (int k = 0; k < FTW; ++k) {
+    uacc[k] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) sacc[k][ct] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  }
+
+  for (int t0 = c0; t0 < c1; t0 += TT) {
+    if (t0 != c0) __syncthreads();                   // the previous tile's readers are done
+    commit(t0);
     __syncthreads();
-    // features: thread (t = tid / 16, j = tid % 16 + 16 * i)
-    {
-      const int t = tid / 16;
+    if (t0 + TT < c1) request(t0 + TT);
+    float ut[FTW];                                   // this tile's share of u
+#pragma unroll
+    for (int k = 0; k < FTW; ++k) ut[k] = 0.f;
+#pragma unroll 1
+    for (int mt = 0; mt < TT / 16; ++mt) {
+      if (t0 + mt * 16 >= c1) break;
+      floatx4 a[CT];
       float nrm = 0.f;
-      for (int c = 0; c < d; ++c) nrm = fmaf(kf[t][c], kf[t][c], nrm);
-      for (int i = 0; i < FJ; ++i) {
-        const int j = (tid % 16) + 16 * i;
-        const int64_t wbase = ((int64_t)h * dphi + j) * d;
-        float dot = 0.f;
-        constexpr int EPL = Elem<T>::per16;
-        for (int c = 0; c < d; c += EPL) {       // 16-byte pieces of the Wk row
-          const u32x4 wv4 = gload128((const char*)pr.Wk + (wbase + c) * sizeof(T));
-          float wx[EPL];
-          Elem<T>::unpack(make_uint4(wv4.x, wv4.y, wv4.z, wv4.w), wx);
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) dot = fmaf(wx[e], kf[t][c + e], dot);
+      for (int jj = 0; jj < CT; ++jj) {
+        a[jj] = *(const floatx4*)(k_s + (mt * 16 + r) * ROWF + jj * 16 + kg * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nrm = fmaf(a[jj][e], a[jj][e], nrm);
+      }
+      nrm += __shfl_xor(nrm, 16);
+      nrm += __shfl_xor(nrm, 32);                    // |k|^2 of token r
+      float cn[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cn[i] = g.c * __shfl(nrm, 4 * kg + i);
+      const int tok = t0 + mt * 16 + 4 * kg;
+      floatx4 f[FTW];                                // feature (wv + 4 k) 16 + r of tokens 4 kg + i
+#pragma unroll
+      for (int k = 0; k < FTW; ++k) {
+        if (!W_REG) load_w(k, wk[0]);
+        // (four chains of D / 16 steps instead of one of D / 4: shorter to wait for, and less rounding in the exponent)
+        floatx4 acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int jj = 0; jj < CT; ++jj)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[jj][e], wk[W_REG ? k : 0][jj][e], acc[e], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float dot = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+          f[k][i] = tok + i < c1 ? expf(g.a * dot - cn[i] + bias[k]) : 0.f;
         }
-        const float f = expf(g.a * dot - g.c * nrm + pr.bk[(int64_t)h * dphi + j]);
-        ph[t][j] = t < nt ? f : 0.f;
-        if (g.cache && t < nt) pr.phi_cache[((size_t)h * n + base + t) * dphi + j] = f;
+        ut[k] += (f[k][0] + f[k][1]) + (f[k][2] + f[k][3]);
+        if (g.cache && wv + 4 * k < NFT) {
+          float* cp = pr.phi_cache + ((size_t)h * n + tok) * dphi + (wv + 4 * k) * 16 + r;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (tok + i < c1) cp[(size_t)i * dphi] = f[k][i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float* vrow = v_s + (mt * 16 + 4 * kg + i) * ROWF + r;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          const float v = vrow[ct * 16];
+#pragma unroll
+          for (int k = 0; k < FTW; ++k) sacc[k][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[k][i], v, sacc[k][ct], 0, 0, 0);
+        }
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int a = 0; a < FJmax; ++a) {
-      if (a < FJ) {
-        const int j = tj * FJ + a;
-        float ub = 0.f;                    // this batch's share of u
-        for (int t = 0; t < kTB; ++t) {
-          const float f = ph[t][j];
-          ub += f;
-#pragma unroll
-          for (int b = 0; b < FCmax; ++b)
-            if (b < FC) acc[a][b] = fmaf(f, vf[t][tc * FC + b], acc[a][b]);
-        }
-        uacc[a] += ub;
-      }
-    }
+    for (int k = 0; k < FTW; ++k) uacc[k] += ut[k];
   }
 
-  float* bp = (float*)(ws + g.off_bpart) +
-              ((size_t)(p * g.Hkv + h) * g.n_build_chunks + ch) * ((size_t)dphi * (d + 1));
+  float* bp = (float*)(ws + g.off_bpart) + ((size_t)(p * g.Hkv + h) * g.n_build_chunks + ch) * ((size_t)dphi * (D + 1));
 #pragma unroll
-  for (int a = 0; a < FJmax; ++a) {
-    if (a < FJ) {
-      const int j = tj * FJ + a;
+  for (int k = 0; k < FTW; ++k) {
+    const int ft = wv + 4 * k;
+    if (ft < NFT) {
 #pragma unroll
-      for (int b = 0; b < FCmax; ++b)
-        if (b < FC) bp[(size_t)j * d + tc * FC + b] = acc[a][b];
-      if (tc == 0) bp[(size_t)dphi * d + j] = uacc[a];
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bp[(size_t)(ft * 16 + 4 * kg + i) * D + ct * 16 + r] = sacc[k][ct][i];
+      float x = uacc[k];
+      x += __shfl_xor(x, 16);
+      x += __shfl_xor(x, 32);
+      if (kg == 0) bp[(size_t)dphi * D + ft * 16 + r] = x;
     }
   }
 }
@@ -460,6 +537,23 @@ static void launch_build_mfma(const Geom& g, const tkphi_problem* probs, char* w
   else launch_build_mfma_as<64, false, NS>(g, probs, ws, grid, s);
 }
 
+template <typename T, int D>
+static void launch_build_f32_d(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
+  constexpr size_t lds = (size_t)2 * 64 * (D + 4) * sizeof(float);
+  const int ftw = (g.dphi + 63) / 64;    // feature tiles per wavefront: 1, 2 or (3, 4 ->) 4
+  const auto fn = ftw <= 1 ? build_f32_kernel<T, D, 1> : ftw == 2 ? build_f32_kernel<T, D, 2> : build_f32_kernel<T, D, 4>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
+  }
+  TKPHI_LAUNCH(ST_UNTIMED, fn, grid, dim3(kThreads), lds, s, g, probs, ws);
+}
+template <typename T>
+static void launch_build_f32(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
+  if (g.d == 128) launch_build_f32_d<T, 128>(g, probs, ws, grid, s);
+  else launch_build_f32_d<T, 64>(g, probs, ws, grid, s);
+}
+
 void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   if (g.max_mid > 0) {
     dim3 grid(g.n_build_chunks, g.Hkv, g.n_problems);
@@ -468,9 +562,9 @@ void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream
     } else if (g.use_mfma) {
       launch_build_mfma(g, probs, ws, grid, s);
     } else if (g.dtype == TKPHI_BF16) {
-      TKPHI_LAUNCH(ST_UNTIMED, build_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws);
+      launch_build_f32<uint16_t>(g, probs, ws, grid, s);
     } else {
-      TKPHI_LAUNCH(ST_UNTIMED, build_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws);
+      launch_build_f32<float>(g, probs, ws, grid, s);
     }
   }
   const int per4 = g.dphi * (g.d + 1) / 4;

@@ -136,8 +136,10 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
   g->sg_split = g->filtered ? std::clamp(256 / std::max(1, g->Hq * std::max(n_problems, 1)), 1, 16) : 0;
   g->n_atiles = (int)std::max<int64_t>(1, ceil_div(std::min<int64_t>((int64_t)cfg->n_sink + cfg->n_tail, max_L) + cfg->max_gen, 64));
   // summary_build: 512 workgroups fill the chip (2 per CU); larger jobs get about 2048 chunks of at
-  // least 2048 tokens so that the last, partly filled round of workgroups stays a small share
-  const int64_t bc_small = std::clamp<int64_t>(ceil_div(units, 512), 256, 2048);
+  // least 2048 tokens so that the last, partly filled round of workgroups stays a small share.  The fp32-arithmetic
+  // kernel spends 32 times the bf16 one's time on a token: there a workgroup takes as little as one tile of 64
+  const bool f32_build = !g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE;
+  const int64_t bc_small = std::clamp<int64_t>(ceil_div(units, 512), f32_build ? 64 : 256, 2048);
   int bc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 2048), bc_small, 1 << 20), 64);
   if (!g->use_mfma) bc = std::min(bc, 4096);    // fp32 FMA chains stay short on the generic kernel
   // Several resident rounds of the matrix-core kernel (512 workgroup slots at d = 128, 1024 at d = 64): among the

@@ -1,0 +1,38 @@
+"""The fp32-arithmetic summary build at the edges of its tiles (64 tokens, 16-token rows of them), feature tiles per
+wavefront (d_phi up to 64, 128, 256, off multiples of 64) and chunks, both storage types and head dimensions."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2604_05438_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cache", [False, True])
+@pytest.mark.parametrize("dtype,d,dphi,chunk", [("f32", 64, 64, 0), ("f32", 64, 16, 128), ("f32", 128, 80, 64), ("f32", 128, 256, 192),
+                                                ("bf16", 64, 128, 64), ("bf16", 128, 48, 0), ("bf16", 64, 192, 128)])
+def test_build_f32_edges(dtype, d, dphi, chunk, cache):
+    """S, u (and the cached features) of a batch whose mid-regions end on, before and behind every kind of edge, against the
+    float64 oracle: relative Frobenius error 2e-5, the bar of the fp32 arithmetic (fp32 sums of at most 4096 tokens per
+    chunk; a feature's exponent carries |logit| 2^-23, below 1e-5 for the logits of these inputs)."""
+    import parity_utils as PU
+    from oracle import tkphi_oracle as orc
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype=dtype, n_q_heads=4, n_kv_heads=2, d_head=d, d_phi=dphi, seed=91)
+    mids = [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 300, 1000]
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(mids)]
+    b = H.Batch(H.config_of(w, cache_features=cache, tuning={"build_chunk": chunk}), layers, [1] * len(layers), debug=True)
+    b.build()
+    assert b.status() == 0
+    for i, P in enumerate(layers):
+        O = PU.oracle_inputs(P)
+        S, u = orc.build_summaries(O["K"], O["V"], O["Wk"], O["bk"], w.phi_in_scale, w.phi_norm_coef, w.n_sink, w.n_tail)
+        PU.check_summaries(b.result(i, "S"), b.result(i, "u"), S, u, 2e-5)
+        if cache:
+            _, M = orc.partition(int(P["L"]), w.n_sink, w.n_tail)
+            for h in range(w.n_kv_heads):
+                F = orc.phi(O["K"][h, M], O["Wk"][h], O["bk"][h], w.phi_in_scale, w.phi_norm_coef)
+                rel = np.abs(b.result(i, "phi_cache")[h].astype(np.float64) - F) / F
+                assert rel.max() <= 2e-5, f"mid {mids[i]} head {h}: feature rel err {rel.max():.3e}"
