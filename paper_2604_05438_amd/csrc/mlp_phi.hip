@@ -6,16 +6,16 @@
 // Keys: every 64-token tile runs the chain
 //   stem  G = X Ws^T + bs            (X = bf16 key rows: exact, single MFMA pass)
 //   hid   H = GeLU(G W1^T + b1)
-//   res   G = G + alpha (H W2^T + b2)    (in place: a tile reads only its own G entries)
+//   res   G = G + alpha (H W2^T + b2)
 //   out   Phi = exp(G Wo^T + bo)     -> tkphi_problem::phi_cache
-// with one tiled matrix-core GEMM (mlp_gemm_tile).  A tile's layers depend only on the tile's own
-// rows: by default one persistent launch per group of up to Geom::mlp_group problems takes each
-// workgroup's tiles through stem, hid and res + out (g1 stays on chip); widths that do not fuse run
-// the layers as separate launches per problem and block of Geom::mlp_block tokens.
+// A tile's layers depend only on the tile's own rows: by default one persistent launch per group of up to
+// Geom::mlp_group problems takes each workgroup's tiles through all four with the activations in registers and LDS
+// (mlp_chain_kernel); widths it is not built for run the layers as separate launches of one tiled matrix-core GEMM
+// (mlp_gemm_tile) per problem and block of Geom::mlp_block tokens, with fp32 activations in the workspace.
 // Without cfg.cache_features the features of a group go to a workspace buffer that the summary
 // contraction of the group consumes, and decode recomputes the features of the retrieved keys
 // (Sec. "Retrieved-token subtraction") by sending their rows through the same chain.
-// Activations are fp32 in the workspace; as MFMA operands they are split into a bf16 hi + lo
+// Activations are fp32; as MFMA operands they are split into a bf16 hi + lo
 // pair (16 significant bits, two MFMAs per product), weights are bf16 as stored, accumulation
 // is fp32.  With ~1.3 MFLOP per token and KV head against 256 bytes of key the chain is bound by
 // the matrix cores, not by HBM.
@@ -38,7 +38,11 @@ enum { EPI_STEM = 0, EPI_HID = 1, EPI_RES = 2, EPI_OUT = 3, EPI_RESOUT = 4 };
 // ------------------------------------------------------------------------------------
 // Weights in MFMA-fragment order.  A matrix W [N][Kd] (row-major bf16) is cut into blocks of 16
 // outputs x 32 inputs; block (ct, ks) is stored as the 1 KB a wavefront loads as one operand:
-// lane (r, kg) -> the 16 bytes W[16 ct + r][32 ks + 8 kg .. + 7], at byte ((ct Kd/32 + ks) 64 + lane) 16.
+// lane (r, kg) -> the 16 bytes W[16 ct + r][32 ks + 8 kg .. + 7], at byte 16 lane of the block.  Blocks of the d_emb-wide
+// matrices lie in groups of four output tiles, K step by K step: block (ct, ks) at KB (ct / 4 Kd/32 + ks) 4 + ct mod 4
+// (a wavefront's four operands of a K step are 4 KB in a row); those of Wo at KB ct Kd/32 + ks.
+// `chain`: for W1, W2 and Wo lane (r, kg) takes the inputs 32 ks + 4 kg + {0 .. 3} and 32 ks + 16 + 4 kg + {0 .. 3} instead:
+// the order in which a lane of the persistent chain holds the outputs of two neighbouring tiles.
 // The GEMM's operand loads then are whole 1 KB lines instead of 16 pieces of 64 B (measured 19 %
 // faster).  One launch packs the four matrices of every KV head of the problems p0 .. p0 + gridDim.z - 1
 // into the workspace, problem p0 + z into slot z: grid (ceil(pieces / 256), Hkv, problems); per head
@@ -59,7 +63,7 @@ __device__ __forceinline__ float* key_feature_rows(const Geom& g, const tkphi_pr
 }
 
 __global__ __launch_bounds__(kThreads) void mlp_pack_weights_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                    char* __restrict__ ws, int p0) {
+                                                                    char* __restrict__ ws, int p0, bool chain) {
   const int h = blockIdx.y, slot = blockIdx.z;
   const tkphi_problem pr = probs[p0 + slot];
   if (pr.L < 1 || pr.L > g.max_L) return;
@@ -77,8 +81,16 @@ __global__ __launch_bounds__(kThreads) void mlp_pack_weights_kernel(Geom g, cons
   else { W = (const char*)mp.Wo; Kd = E; q -= n_s + 2 * n_1; }
   const int lane = (int)(q & 63), r = lane & 15, kg = lane >> 4;
   const size_t blk = q >> 6;
-  const int ks = (int)(blk % (Kd / 32)), ct = (int)(blk / (Kd / 32));
-  *(u32x4*)dst = gload128(W + ((size_t)(ct * 16 + r) * Kd + ks * 32 + kg * 8) * 2);
+  const int KS = Kd / 32;
+  const bool grouped = W != (const char*)mp.Wo;
+  const int ks = (int)(grouped ? blk / 4 % KS : blk % KS), ct = (int)(grouped ? blk / 4 / KS * 4 + blk % 4 : blk / KS);
+  const char* row = W + ((size_t)(ct * 16 + r) * Kd + ks * 32) * 2;
+  if (chain && W != (const char*)mp.Ws) {
+    const u32x2 a = *(const u32x2*)(row + kg * 8), b = *(const u32x2*)(row + 32 + kg * 8);
+    *(u32x4*)dst = (u32x4){a.x, a.y, b.x, b.y};
+  } else {
+    *(u32x4*)dst = gload128(row + kg * 16);
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -145,7 +157,11 @@ __device__ __forceinline__ void mlp_gemm_tile(const Geom& g, const tkphi_problem
   const int colw = n0 + wv * NT * 16;
   const char* w_src[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) w_src[nt] = W + ((size_t)min(colw / 16 + nt, Nout / 16 - 1) * (Kd / 32) * 64 + lane) * 16;
+  for (int nt = 0; nt < NT; ++nt) {
+    const int ct = min(colw / 16 + nt, Nout / 16 - 1);
+    w_src[nt] = W + (EPI == EPI_OUT ? (size_t)ct * (Kd / 32) : (size_t)(ct / 4) * (Kd / 32) * 4 + ct % 4) * 1024 + lane * 16;
+  }
+  constexpr int w_step = EPI == EPI_OUT ? 1024 : 4096;  // bytes from one K step of an output tile to the next
 
   floatx4 acc[4][NT];
 #pragma unroll
@@ -163,7 +179,7 @@ __device__ __forceinline__ void mlp_gemm_tile(const Geom& g, const tkphi_problem
       ar[1] = gload128(a_src + (size_t)k0 * 4 + 16);
     }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) br[nt].u = gload128(w_src[nt] + (size_t)(k0 / KB) * 1024);
+    for (int nt = 0; nt < NT; ++nt) br[nt].u = gload128(w_src[nt] + (size_t)(k0 / KB) * w_step);
   };
 
   const int n_stages = Kd / KB;
@@ -352,70 +368,304 @@ __global__ __launch_bounds__(kThreads, 2) void mlp_gemm_kernel(Geom g, const tkp
                               Hb + (size_t)row0 * g.d_emb, (int)blockIdx.y * 64 * NT, 0, key_feature_rows(g, pr, ws, 0, h, n));
 }
 
-// The whole chain in one launch (d_emb == 64 NT, d_phi == 64 NTO): a tile's layers depend only on the
-// tile's own rows, so a persistent workgroup takes a 64-token tile through stem, hidden layer and
-// residual + output with workgroup barriers in between; its activations (2 x 64 x d_emb floats of the
-// workspace per workgroup) never leave L2.  grid (n_wg); the tiles of the np problems p0 .. p0 + np - 1:
-// tile T = blockIdx.x + k n_wg -> problem slot T / tpp, KV head (T % tpp) % Hkv, tokens
-// [64 ((T % tpp) / Hkv), + 64), tpp = Hkv ceil(max_mid / 64) (tiles past a shorter problem's end are skipped).
-// No launch gaps and one cold start per workgroup (4 % faster than the layer-wise launches; holding back
-// every other workgroup at the start so that neighbours on a CU run different phases was measured to
-// change nothing).
-template <int NT, int NTO>
-__global__ __launch_bounds__(kThreads, 2) void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                char* __restrict__ ws, int p0, int np) {
-  __shared__ __attribute__((aligned(16))) char lds_raw[mlp_lds_bytes<NT>()];
-  const int tpp = ((g.max_mid + 63) / 64) * g.Hkv;
-  float* Gt = (float*)(ws + g.off_act) + (size_t)blockIdx.x * 2 * 64 * g.d_emb;
-  float* Ht = Gt + (size_t)64 * g.d_emb;
-  for (int T = blockIdx.x; T < tpp * np; T += gridDim.x) {
-    const int slot = T / tpp, rem = T % tpp;
-    const tkphi_problem pr = probs[p0 + slot];
-    if (pr.L < 1 || pr.L > g.max_L) continue;          // (uniform over the workgroup)
-    const int n = mid_size(pr.L, g.n_sink, g.n_tail);
-    const int h = rem % g.Hkv, tok0 = (rem / g.Hkv) * 64;
-    if (tok0 >= n) continue;
-    const int rows_valid = min(64, n - tok0);
-    const tkphi_mlp mp = pr.mlp_k[h];
-    float* feat = key_feature_rows(g, pr, ws, slot, h, n);
-    mlp_gemm_tile<EPI_STEM, NT, 0>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat);
-    __syncthreads();                                   // g0 of the tile is visible to the workgroup; LDS is free
-    mlp_gemm_tile<EPI_HID, NT, 0>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat);
-    __syncthreads();
-    mlp_gemm_tile<EPI_RESOUT, NT, NTO>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat);
-    __syncthreads();                                   // the next tile overwrites g, h and the planes
-  }
-}
+// ------------------------------------------------------------------------------------
+// The whole chain in one launch, d_emb == 128 NT, d_phi <= 64 NTO.  A tile's layers depend only on the tile's own
+// rows: a persistent workgroup of 8 wavefronts takes 64 tokens through all four of them, and no activation leaves the
+// CU.  Wavefront w owns the outputs [16 NT w, 16 NT (w + 1)) of every layer for all 64 tokens:
+//   stem    g0 = Ws x + bs stays in registers, fp32, until the residual; its bf16 hi / lo split goes to two LDS planes
+//   hid     h = GeLU(W1 g0 + b1), split in registers, replaces g0 in the planes
+//   res     g1 = g0 + alpha (W2 h + b2) replaces h
+//   out     phi = exp(Wo g1 + bo) goes to memory (wavefront w: 32 tokens x a quarter of the outputs)
+// Weights are the MFMA row operand, streamed from L2 in fragment order two K steps ahead; planes are token-major with
+// rows padded by 16 B (conflict-free 16-byte reads).  The keys of the next tile are requested behind the stem.
+//
+// What bounds it: of 70 K cycles per tile (8 heads of 131004 tokens, d_emb 512, at the 2.0 GHz the card holds under this
+// load) the MFMAs, two per product (hi, lo), need 39 K; the two hidden GEMMs run at 88 % of that rate, GeLU and the splits of
+// the wavefronts that finish a GEMM last are exposed (10 K and 3 K), the output layer waits for L1 and LDS (11 K for
+// 4 K of MFMA).  64 tokens because their planes (133 KB at d_emb 512) are what LDS holds; each wavefront spans all
+// tokens so that a tile streams the weights once (1.3 MB: half the L2 rate at full MFMA rate).  A chain of 256-thread
+// workgroups that handed fp32 activations from layer to layer through L2 took 3.6-3.75 ms for these tokens and 132 us
+// for the 31440 retrieved rows of a decode step; this one 2.2 ms and 85 us.
+//
+// SEL false (build): tile T of the np problems p0 .. -> problem slot T / tpp, KV head (T % tpp) % Hkv, tokens
+// [64 ((T % tpp) / Hkv), + 64), tpp = Hkv ceil(max_mid / 64).  With 8 KV heads each XCD's L2 serves one head's weights.
+// SEL true (decode without a feature cache): KV head (T % tpp) % Hkv, query head G h + ((T % tpp) / Hkv) % G, entries
+// [64 ((T % tpp) / Hq), + 64) of that head's retrieved list; row i of a head is mid token sel_idx[i], its features go to
+// row i of the head's block of Geom::off_selphi.
+// ------------------------------------------------------------------------------------
+constexpr int kChainThreads = 512;
+template <int NT, int D>
+constexpr size_t chain_lds_bytes() { return (size_t)2 * 64 * (128 * NT * 2 + 16) + (size_t)64 * (D * 2 + 16); }
 
-// Decode without a feature cache: the same chain over the retrieved keys.  Tile T -> problem slot T / tpp, query
-// head (T % tpp) % Hq, entries [64 ((T % tpp) / Hq), + 64) of that head's retrieved list (tpp = Hq ceil(max_K / 64));
-// row i of a head is mid token sel_idx[i], its features go to row i of the head's block of Geom::off_selphi.
-template <int NT, int NTO>
-__global__ __launch_bounds__(kThreads, 2) void mlp_chain_sel_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                    char* __restrict__ ws, int p0, int np) {
-  __shared__ __attribute__((aligned(16))) char lds_raw[mlp_lds_bytes<NT>()];
-  const int tpp = ((g.max_K + 63) / 64) * g.Hq;
-  float* Gt = (float*)(ws + g.off_act) + (size_t)blockIdx.x * 2 * 64 * g.d_emb;
-  float* Ht = Gt + (size_t)64 * g.d_emb;
-  for (int T = blockIdx.x; T < tpp * np; T += gridDim.x) {
-    const int slot = T / tpp, rem = T % tpp;
-    const tkphi_problem pr = probs[p0 + slot];
-    if (pr.L < 1 || pr.L > g.max_L) continue;
-    const int n = mid_size(pr.L, g.n_sink, g.n_tail);
-    const int gq = rem % g.Hq, tok0 = (rem / g.Hq) * 64, h = gq / g.G;
-    char* blk = problem_block(g, ws, p0 + slot);
-    const int Ksel = min(((const SelPlan*)(blk + g.off_plan))[gq].n_sel, g.max_K);
-    if (n == 0 || tok0 >= Ksel) continue;
-    const int rows_valid = min(64, Ksel - tok0);
-    const tkphi_mlp mp = pr.mlp_k[h];
-    const int32_t* rowmap = (const int32_t*)(blk + g.off_selidx) + (size_t)gq * g.max_K;
-    float* feat = (float*)(blk + g.off_selphi) + (size_t)gq * g.max_K * g.dphi;
-    mlp_gemm_tile<EPI_STEM, NT, 0>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat, rowmap);
-    __syncthreads();
-    mlp_gemm_tile<EPI_HID, NT, 0>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat, rowmap);
-    __syncthreads();
-    mlp_gemm_tile<EPI_RESOUT, NT, NTO>(g, pr, mp, ws, lds_raw, h, n, tok0, rows_valid, Gt, Ht, 0, slot, feat, rowmap);
-    __syncthreads();
+template <int NT, int NTO, int D, bool SEL>
+__global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws, int p0, int np) {
+  constexpr int E = 128 * NT, PROW = E * 2 + 16, KROW = D * 2 + 16, KSE = E / 32, KSD = D / 32;
+  constexpr int NKL = 64 * (D / 8) / kChainThreads;    // 16-byte pieces of the key tile per thread
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  char* const p_hi = lds;
+  char* const p_lo = lds + 64 * PROW;
+  char* const kbuf = lds + 2 * 64 * PROW;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tpp = SEL ? ((g.max_K + 63) / 64) * g.Hq : ((g.max_mid + 63) / 64) * g.Hkv;
+  const int n_tiles = tpp * np;
+
+  struct Tile { int T, slot, h, rows; float* feat; };
+  u32x4 kreg[NKL];
+  // the first tile with rows at or after T of this workgroup's sequence: its key rows -> kreg
+  auto request_tile = [&](int T) -> Tile {
+#pragma unroll
+    for (int i = 0; i < NKL; ++i) kreg[i] = (u32x4){0u, 0u, 0u, 0u};
+    for (; T < n_tiles; T += gridDim.x) {
+      const int slot = T / tpp, rem = T % tpp;
+      const tkphi_problem& pr = probs[p0 + slot];
+      const int L = pr.L;
+      if (L < 1 || L > g.max_L) continue;
+      const int n = mid_size(L, g.n_sink, g.n_tail);
+      const int h = rem % g.Hkv;
+      char* blk = problem_block(g, ws, p0 + slot);
+      int tok0, rows;
+      const int32_t* rowmap = nullptr;
+      float* feat;
+      if (SEL) {
+        const int gq = h * g.G + (rem / g.Hkv) % g.G;
+        tok0 = (rem / g.Hq) * 64;
+        rows = n == 0 ? 0 : min(((const SelPlan*)(blk + g.off_plan))[gq].n_sel, g.max_K) - tok0;
+        rowmap = (const int32_t*)(blk + g.off_selidx) + (size_t)gq * g.max_K + tok0;
+        feat = (float*)(blk + g.off_selphi) + ((size_t)gq * g.max_K + tok0) * g.dphi;
+      } else {
+        tok0 = (rem / g.Hkv) * 64;
+        rows = n - tok0;
+        feat = (g.cache ? pr.phi_cache + (size_t)h * n * g.dphi
+                        : (float*)(ws + g.off_feat) + ((size_t)slot * g.Hkv + h) * (size_t)g.max_mid * g.dphi) + (size_t)tok0 * g.dphi;
+      }
+      if (rows <= 0) continue;
+      rows = min(rows, 64);
+      const char* Kh = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2;
+#pragma unroll
+      for (int i = 0; i < NKL; ++i) {
+        const int idx = tid + i * kChainThreads, row = min(idx / (D / 8), rows - 1);      // rows past the end repeat the last one
+        const int tok = SEL ? min(max(rowmap[row], 0), n - 1) : tok0 + row;
+        kreg[i] = gload128(Kh + ((size_t)tok * pr.stride_tok + (idx % (D / 8)) * 8) * 2);
+      }
+      return Tile{T, slot, h, rows, feat};
+    }
+    return Tile{n_tiles, 0, 0, 0, nullptr};
+  };
+  // K steps of a layer: operand blocks of this wavefront's output tiles, two steps ahead
+  Frag wf[2][NT];
+  const uint32_t lane16 = lane * 16;
+  auto load_w = [&](const char* W, int ks_n, int ks, Frag (&f)[NT]) {
+    const char* base = W + ((size_t)((wv * NT / 4) * ks_n + ks) * 4 + wv * NT % 4) * 1024;       // (uniform)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) f[nt].u = gload128(base + nt * 1024 + lane16);
+  };
+  floatx4 acc[4][NT], g0[4][NT];
+  u32x4 bias[NT];
+  auto load_bias = [&](const float* b) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) bias[nt] = gload128(b + (wv * NT + nt) * 16 + 4 * kg);
+  };
+  auto init_bias = [&]() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+        acc[mt][nt] = (floatx4){__uint_as_float(bias[nt].x), __uint_as_float(bias[nt].y), __uint_as_float(bias[nt].z), __uint_as_float(bias[nt].w)};
+  };
+  // acc += W (planes): steps of 16 tokens x 32 inputs; the plane operands of a step are read while the step before it
+  // multiplies.  Lo products before hi products: no MFMA waits for the previous one's sum.
+  const char* const frag_hi = p_hi + r * PROW + kg * 16;
+  const char* const frag_lo = p_lo + r * PROW + kg * 16;
+  auto gemm_planes = [&](const char* W) {
+    Frag b_hi[2], b_lo[2];
+    b_lo[0].u = *(const u32x4*)frag_lo;
+    b_hi[0].u = *(const u32x4*)frag_hi;
+#pragma unroll 2
+    for (int ks = 0; ks < KSE; ++ks) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const int nx = mt == 3 ? (ks + 1) * 64 : (mt + 1) * 16 * PROW + ks * 64;     // (one K step past the end is read, not used)
+        b_lo[(mt + 1) & 1].u = *(const u32x4*)(frag_lo + nx);
+        b_hi[(mt + 1) & 1].u = *(const u32x4*)(frag_hi + nx);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks & 1][nt].v, b_lo[mt & 1].v, acc[mt][nt], 0, 0, 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks & 1][nt].v, b_hi[mt & 1].v, acc[mt][nt], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // the next step's LDS reads, then this step's MFMAs
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NT, 0);
+      }
+      load_w(W, KSE, min(ks + 2, KSE - 1), wf[ks & 1]);
+    }
+  };
+  // a lane's 4 consecutive outputs of a token, as hi / lo pairs
+  auto split4 = [](const floatx4& x, u32x2* hi, u32x2* lo) {
+    uint32_t h01, l01, h23, l23;
+    split_bf16_pair(x[0], x[1], &h01, &l01);
+    split_bf16_pair(x[2], x[3], &h23, &l23);
+    *hi = (u32x2){h01, h23};
+    *lo = (u32x2){l01, l23};
+  };
+  // outputs 16 ct + 4 kg + {0 .. 3} of a token lie at byte 64 (ct / 2) + 16 kg + 8 (ct mod 2) of its row: two neighbouring tiles
+  // of a lane are 16 bytes in a row, and what a lane reads back for K step ks is inputs 32 ks + 4 kg + .. and 32 ks + 16 + 4 kg + ..
+  const uint32_t out_at = r * PROW + (wv * NT / 2) * 64 + kg * 16 + (NT == 1 ? (wv & 1) * 8 : 0);
+  auto store_planes = [&](int mt, const u32x2 (&hi)[NT], const u32x2 (&lo)[NT]) {
+    char* const d_hi = p_hi + mt * 16 * PROW + out_at;
+    char* const d_lo = p_lo + mt * 16 * PROW + out_at;
+    if constexpr (NT == 1) {
+      *(u32x2*)d_hi = hi[0];
+      *(u32x2*)d_lo = lo[0];
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < NT; nt += 2) {
+        *(u32x4*)(d_hi + nt * 32) = (u32x4){hi[nt].x, hi[nt].y, hi[nt + 1].x, hi[nt + 1].y};
+        *(u32x4*)(d_lo + nt * 32) = (u32x4){lo[nt].x, lo[nt].y, lo[nt + 1].x, lo[nt + 1].y};
+      }
+    }
+  };
+  // acc -> f(acc), split in registers; into the planes once every wavefront has read what they hold
+  auto replace_planes = [&](auto&& f) {
+    u32x2 s_hi[4][NT], s_lo[4][NT];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        floatx4 x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = f(acc[mt][nt][i], mt, nt, i);
+        split4(x, &s_hi[mt][nt], &s_lo[mt][nt]);
+      }
+    lds_barrier();
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) store_planes(mt, s_hi[mt], s_lo[mt]);
+    lds_barrier();
+  };
+
+  const int n_otiles = g.dphi / 16, og = wv & 3, mg = wv >> 2;
+  // the maps of the current (problem, KV head): read again only when it changes
+  const char* Ws = nullptr;
+  const float *bs = nullptr, *b1 = nullptr, *b2 = nullptr, *bo = nullptr;
+  float alpha = 0.f;
+  Frag wst[KSD][NT];                                   // the stem's weights, all K steps
+  auto preload_stem = [&](const Tile& x, bool same) {
+    if (!same) {
+      const tkphi_mlp& mp = probs[p0 + x.slot].mlp_k[x.h];
+      Ws = packed_weights(g, ws, x.slot, x.h);
+      bs = mp.bs; b1 = mp.b1; b2 = mp.b2; bo = mp.bo;
+      alpha = mp.alpha;
+    }
+#pragma unroll
+    for (int ks = 0; ks < KSD; ++ks) load_w(Ws, KSD, ks, wst[ks]);
+    load_bias(bs);
+  };
+  Tile t = request_tile(blockIdx.x);
+  if (t.T >= n_tiles) return;
+  preload_stem(t, false);
+  while (t.T < n_tiles) {
+    const char* W1 = Ws + (size_t)E * D * 2;
+    const char* W2 = W1 + (size_t)E * E * 2;
+    const char* Wo = W2 + (size_t)E * E * 2;
+    const Tile cur = t;
+#pragma unroll
+    for (int i = 0; i < NKL; ++i) {
+      const int idx = tid + i * kChainThreads;
+      *(u32x4*)(kbuf + (idx / (D / 8)) * KROW + (idx % (D / 8)) * 16) = kreg[i];
+    }
+    lds_barrier();                                     // the keys are staged; every wavefront is done with the previous tile's planes
+    // ---- stem (bf16 keys: one MFMA per product); 16 tokens are split and stored while the next 16 multiply ----
+    init_bias();
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int ks = 0; ks < KSD; ++ks) {
+        Frag b;
+        b.u = *(const u32x4*)(kbuf + (mt * 16 + r) * KROW + ks * 64 + kg * 16);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wst[ks][nt].v, b.v, acc[mt][nt], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      u32x2 hi[NT], lo[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        g0[mt][nt] = acc[mt][nt];
+        split4(g0[mt][nt], &hi[nt], &lo[nt]);
+      }
+      store_planes(mt, hi, lo);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(W1, KSE, 0, wf[0]);
+    load_w(W1, KSE, 1, wf[1]);
+    load_bias(b1);
+    t = request_tile(cur.T + gridDim.x);
+    lds_barrier();
+    // ---- hidden layer ----
+    __builtin_amdgcn_sched_barrier(0);
+    init_bias();
+    gemm_planes(W1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(W2, KSE, 0, wf[0]);
+    load_w(W2, KSE, 1, wf[1]);
+    load_bias(b2);
+    replace_planes([&](float x, int, int, int) { return gelu_erf(x); });
+    // ---- residual ----
+    __builtin_amdgcn_sched_barrier(0);
+    init_bias();
+    gemm_planes(W2);
+    __builtin_amdgcn_sched_barrier(0);
+    // output layer: NTO output tiles x 2 token tiles per wavefront, operands 4 K steps ahead
+    constexpr int WD = 4;
+    Frag wo[WD][NTO];
+    auto wo_block = [&](int ks, int j) { return Wo + ((size_t)(min(og * NTO + j, n_otiles - 1) * KSE + ks) * 64 + lane) * 16; };
+#pragma unroll
+    for (int st = 0; st < WD; ++st)
+#pragma unroll
+      for (int j = 0; j < NTO; ++j) wo[st][j].u = gload128(wo_block(st, j));
+    replace_planes([&](float x, int mt, int nt, int i) { return fmaf(alpha, x, g0[mt][nt][i]); });
+    // ---- output layer ----
+    floatx4 acco[2][NTO];
+#pragma unroll
+    for (int j = 0; j < NTO; ++j) {
+      const u32x4 b = gload128(bo + min(og * NTO + j, n_otiles - 1) * 16 + 4 * kg);
+#pragma unroll
+      for (int m2 = 0; m2 < 2; ++m2)
+        acco[m2][j] = (floatx4){__uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+    }
+#pragma unroll
+    for (int ks = 0; ks < KSE; ++ks) {
+#pragma unroll
+      for (int m2 = 0; m2 < 2; ++m2) {
+        Frag b_hi, b_lo;
+        b_lo.u = *(const u32x4*)(frag_lo + (mg * 2 + m2) * 16 * PROW + ks * 64);
+        b_hi.u = *(const u32x4*)(frag_hi + (mg * 2 + m2) * 16 * PROW + ks * 64);
+#pragma unroll
+        for (int j = 0; j < NTO; ++j) acco[m2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[ks % WD][j].v, b_lo.v, acco[m2][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NTO; ++j) acco[m2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[ks % WD][j].v, b_hi.v, acco[m2][j], 0, 0, 0);
+      }
+      if (ks + WD < KSE) {
+#pragma unroll
+        for (int j = 0; j < NTO; ++j) wo[ks % WD][j].u = gload128(wo_block(ks + WD, j));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {                                                  // (unconditional: the registers' old contents need not live on)
+      const Tile& nx = t.T < n_tiles ? t : cur;
+      preload_stem(nx, nx.slot == cur.slot && nx.h == cur.h);
+    }
+#pragma unroll
+    for (int j = 0; j < NTO; ++j) {
+      if (og * NTO + j >= n_otiles) continue;
+#pragma unroll
+      for (int m2 = 0; m2 < 2; ++m2) {
+        const int row = (mg * 2 + m2) * 16 + r;
+        if (row >= cur.rows) continue;
+        *(float4*)(cur.feat + (size_t)row * g.dphi + (og * NTO + j) * 16 + 4 * kg) =
+            make_float4(expf(acco[m2][j][0]), expf(acco[m2][j][1]), expf(acco[m2][j][2]), expf(acco[m2][j][3]));
+      }
+    }
   }
 }
 
@@ -445,31 +695,42 @@ static void launch_mlp_resout_nt(const Geom& g, const tkphi_problem* probs, char
   else hipLaunchKernelGGL((mlp_gemm_kernel<EPI_RESOUT, NT, 4>), grid, dim3(kThreads), 0, s, g, probs, ws, p, t0);
 }
 
-template <int NT>
-static void launch_mlp_chain_nt(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np, bool sel) {
-  const int64_t tiles = sel ? (int64_t)(g.max_K + 63) / 64 * g.Hq * np : (int64_t)(g.max_mid + 63) / 64 * g.Hkv * np;
-  dim3 grid((unsigned)std::min<int64_t>(tiles, kMlpChainWGs));
-  if (sel) {
-    if (g.dphi == 64) hipLaunchKernelGGL((mlp_chain_sel_kernel<NT, 1>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
-    else if (g.dphi == 128) hipLaunchKernelGGL((mlp_chain_sel_kernel<NT, 2>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
-    else hipLaunchKernelGGL((mlp_chain_sel_kernel<NT, 4>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
+template <int NT, int NTO, int D, bool SEL>
+static void launch_mlp_chain_as(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np) {
+  constexpr size_t lds = chain_lds_bytes<NT, D>();
+  const auto fn = mlp_chain_kernel<NT, NTO, D, SEL>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
+  }
+  const int64_t tiles = SEL ? (int64_t)(g.max_K + 63) / 64 * g.Hq * np : (int64_t)(g.max_mid + 63) / 64 * g.Hkv * np;
+  hipLaunchKernelGGL(fn, dim3((unsigned)std::min<int64_t>(tiles, kMlpChainWGs)), dim3(kChainThreads), lds, s, g, probs, ws, p0, np);
+}
+
+template <int NT, int D, bool SEL>
+static void launch_mlp_chain_nt(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np) {
+  if (g.dphi <= 64) launch_mlp_chain_as<NT, 1, D, SEL>(g, probs, ws, s, p0, np);
+  else if (g.dphi <= 128) launch_mlp_chain_as<NT, 2, D, SEL>(g, probs, ws, s, p0, np);
+  else launch_mlp_chain_as<NT, 4, D, SEL>(g, probs, ws, s, p0, np);
+}
+
+template <bool SEL>
+static void launch_mlp_chain(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np) {
+  if (g.d == 128) {
+    if (g.d_emb == 512) launch_mlp_chain_nt<4, 128, SEL>(g, probs, ws, s, p0, np);
+    else if (g.d_emb == 256) launch_mlp_chain_nt<2, 128, SEL>(g, probs, ws, s, p0, np);
+    else launch_mlp_chain_nt<1, 128, SEL>(g, probs, ws, s, p0, np);
   } else {
-    if (g.dphi == 64) hipLaunchKernelGGL((mlp_chain_kernel<NT, 1>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
-    else if (g.dphi == 128) hipLaunchKernelGGL((mlp_chain_kernel<NT, 2>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
-    else hipLaunchKernelGGL((mlp_chain_kernel<NT, 4>), grid, dim3(kThreads), 0, s, g, probs, ws, p0, np);
+    if (g.d_emb == 512) launch_mlp_chain_nt<4, 64, SEL>(g, probs, ws, s, p0, np);
+    else if (g.d_emb == 256) launch_mlp_chain_nt<2, 64, SEL>(g, probs, ws, s, p0, np);
+    else launch_mlp_chain_nt<1, 64, SEL>(g, probs, ws, s, p0, np);
   }
 }
 
-static void launch_mlp_chain(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np, bool sel) {
-  if (g.d_emb == 512) launch_mlp_chain_nt<8>(g, probs, ws, s, p0, np, sel);
-  else if (g.d_emb == 256) launch_mlp_chain_nt<4>(g, probs, ws, s, p0, np, sel);
-  else launch_mlp_chain_nt<2>(g, probs, ws, s, p0, np, sel);
-}
-
-static void launch_mlp_pack(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np) {
+static void launch_mlp_pack(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s, int p0, int np, bool chain) {
   const size_t pieces = ((size_t)g.d_emb * g.d + (size_t)2 * g.d_emb * g.d_emb + (size_t)g.dphi * g.d_emb) / 8;
   hipLaunchKernelGGL(mlp_pack_weights_kernel, dim3((unsigned)((pieces + kThreads - 1) / kThreads), g.Hkv, np), dim3(kThreads), 0, s,
-                     g, probs, ws, p0);
+                     g, probs, ws, p0, chain);
 }
 
 // Build with the MLP maps: the key features of every problem's mid-region (-> phi_cache, or the workspace buffer of
@@ -482,9 +743,9 @@ void launch_mlp_build(const Geom& g, const tkphi_problem* probs, char* ws, hipSt
   const int group = chain ? g.mlp_group : 1;
   for (int p0 = 0; p0 < g.n_problems; p0 += group) {
     const int np = std::min(group, g.n_problems - p0);
-    launch_mlp_pack(g, probs, ws, s, p0, np);
+    launch_mlp_pack(g, probs, ws, s, p0, np, chain);
     if (chain) {
-      launch_mlp_chain(g, probs, ws, s, p0, np, false);
+      launch_mlp_chain<false>(g, probs, ws, s, p0, np);
     } else {
       for (int t0 = 0; t0 < g.max_mid; t0 += g.mlp_block) {
         const int rows = std::min(g.mlp_block, g.max_mid - t0);
@@ -509,8 +770,8 @@ void launch_mlp_sel_features(const Geom& g, const tkphi_problem* probs, char* ws
   if (g.max_mid == 0 || g.max_K == 0) return;
   for (int p0 = 0; p0 < g.n_problems; p0 += g.mlp_group) {
     const int np = std::min(g.mlp_group, g.n_problems - p0);
-    launch_mlp_pack(g, probs, ws, s, p0, np);
-    launch_mlp_chain(g, probs, ws, s, p0, np, true);
+    launch_mlp_pack(g, probs, ws, s, p0, np, true);
+    launch_mlp_chain<true>(g, probs, ws, s, p0, np);
   }
 }
 

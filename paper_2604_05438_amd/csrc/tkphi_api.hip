@@ -226,8 +226,10 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
     // (the activations, the packed weights and the feature buffer lie behind the decode blocks as well: a decode
     // without a feature cache sends the retrieved keys through the same chain)
     g->off_act = align_up(std::max(build_total, decode_total), 256);
-    // (or, for the one-launch build, 2 x 64 x d_emb floats per persistent workgroup)
-    const size_t act_bytes = std::max((size_t)2 * g->Hkv * g->mlp_block, (size_t)2 * 64 * kMlpChainWGs) * g->d_emb * sizeof(float);
+    // (the one-launch chain keeps its activations on chip)
+    const bool chain_build = tn.mlp_mode == 0 && (cfg->d_emb == 128 || cfg->d_emb == 256 || cfg->d_emb == 512) &&
+                             (g->dphi == 64 || g->dphi == 128 || g->dphi == 256);
+    const size_t act_bytes = chain_build ? 0 : (size_t)2 * g->Hkv * g->mlp_block * g->d_emb * sizeof(float);
     g->off_wpack = align_up(g->off_act + act_bytes, 256);
     // Problems per chain launch: their packed weights (and, without a feature cache, the features of their
     // mid-regions, fp32) are held together; up to 16 problems, the feature buffer at most 1 GiB (one problem if a
@@ -238,7 +240,7 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
     if (feat_one > 0) g->mlp_group = (int)std::clamp<size_t>(((size_t)1 << 30) / feat_one, 1, (size_t)g->mlp_group);
     g->off_feat = align_up(g->off_wpack + (size_t)g->mlp_group * wpack_one, 256);
     build_all = g->off_feat + (size_t)g->mlp_group * feat_one;
-    if (g->sel_feat) decode_all = g->off_feat;          // activations and packed weights
+    if (g->sel_feat) decode_all = g->off_feat;          // (up to the end of the packed weights)
   }
   g->decode_bytes = align_up(decode_all, 256);
   g->build_bytes = align_up(build_all, 256);

@@ -127,7 +127,7 @@ struct SelPlan {
   int32_t nb;      // tokens in the boundary bin
   int32_t n_sel;   // retrieved tokens K' = min(topk, |M|, max_K)
 };
-constexpr int kMlpChainWGs = 512;       // persistent workgroups of the one-launch MLP build (two per CU)
+constexpr int kMlpChainWGs = 256;       // persistent workgroups of the one-launch MLP chain (one per CU)
 constexpr int kMaxScanChunks = 2048;   // chunk offsets are scanned in LDS by `plan`
 
 // kernel launchers (each defined next to its kernels)
@@ -184,10 +184,14 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 // values and what the decode side subtracts for a retrieved token.
 // Two features at a time with the packed hardware conversion (v_cvt_pk_bf16_f32, round to
 // nearest even): *hi / *lo hold (f0, f1) in their (low, high) halves.
+// (the empty asm keeps the packed pair in one register: without it the compiler converts f0 once more for the shift.
+// The conversion itself stays a compiler instruction: the wait states it needs behind a matrix instruction are
+// not inserted in front of inline assembly)
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 __device__ __forceinline__ void split_bf16_pair(float f0, float f1, uint32_t* hi, uint32_t* lo) {
   const bf16x2_t h = {(__bf16)f0, (__bf16)f1};
-  const uint32_t hb = __builtin_bit_cast(uint32_t, h);
+  uint32_t hb = __builtin_bit_cast(uint32_t, h);
+  asm("" : "+v"(hb));
   const bf16x2_t l = {(__bf16)(f0 - __uint_as_float(hb << 16)), (__bf16)(f1 - __uint_as_float(hb & 0xffff0000u))};
   *hi = hb;
   *lo = __builtin_bit_cast(uint32_t, l);
@@ -337,17 +341,18 @@ __device__ __forceinline__ void gemv_bf16_rows(const void* W, int N, int Kd, con
   }
 }
 
-// GeLU(x) = x Phi(x) with Phi(x) = erfc(-x / sqrt 2) / 2.  erfc(z) for z >= 0 by the classical
+// GeLU(x) = x Phi(x) = max(x, 0) - |x| erfc(|x| / sqrt 2) / 2.  erfc(z) for z >= 0 by the classical
 // five-term rational approximation erfc(z) ~ t (a1 + t (a2 + ... + t a5)) exp(-z^2), t = 1 / (1 + p z)
 // (Abramowitz & Stegun 7.1.26: absolute error <= 1.5e-7 on erfc, hence <= 0.75e-7 |x| on GeLU, and
-// no cancellation for x < 0): a reciprocal, an exponential and seven FMAs instead of the library
-// erff, which dominated the hidden layer's epilogue.
+// no cancellation for x < 0), with the factors 1/2 and 1 / sqrt 2 in the constants: 12 ordinary instructions, a
+// 1-ulp reciprocal and an exp2 (the correctly rounded division and the select of the first form: 31).  The epilogue of
+// the MLP chain's hidden layer is mostly this.
 __device__ __forceinline__ float gelu_erf(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __frcp_rn(fmaf(0.3275911f, z, 1.0f));
-  const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
-  const float erfc_z = poly * __expf(-z * z);                       // erfc(|x| / sqrt 2)
-  return 0.5f * x * (x < 0.f ? erfc_z : 2.0f - erfc_z);
+  const float xa = fminf(fabsf(x), 1e18f);                          // (finite: infinity times a vanished erfc would be NaN)
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.23164189f, xa, 1.0f));
+  const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0.5307027145f, -0.7265760135f), 0.7107068705f), -0.142248368f), 0.127414796f);
+  const float y = x * 0.84932180f;                                  // exp(-x^2 / 2) = exp2(-y^2)
+  return fmaf(-xa, poly * __builtin_amdgcn_exp2f(-y * y), fmaxf(x, 0.f));
 }
 
 // device status word: recomputed from the problem lengths by one workgroup per call (decode also
