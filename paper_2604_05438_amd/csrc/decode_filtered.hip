@@ -53,7 +53,10 @@ __device__ __forceinline__ int sample_row(int si, int n, int m) {
 // ---- sample job: one workgroup per (problem, KV head) ------------------------------------------------
 // LDS: sc [G][1024] sampled scores, hist [G][kBins], nin [G], inb [G][kInBin] keys of the boundary bin
 constexpr int kInBin = 256;
-constexpr int kSigmas = 4;             // margin of the sampled bound in standard deviations (a miss costs one rescan)
+// Margin of the sampled bound in standard deviations.  A miss costs a rescan of the head (2.3 ms for a 128K head): at four it
+// came up once per 40 000 heads - every fourth call of a batch of 8192 heads (select 540 -> 690 us on average) -, at five
+// once per 800 000 for 11 % more candidates, which cost nothing measurable.
+constexpr int kSigmas = 5;
 template <int D, int TPI>
 __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& pr, char* blk, int h, float* sc, uint32_t* hist,
                                             uint32_t* inb, int* nin, char* stage_all) {
@@ -380,9 +383,13 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
   }
 }
 
-// grid (n_scan_chunks, Hkv, n_problems), 256 threads: wavefront w is slot w of the workgroup's chunk.
-template <int D, int TPI, bool STREAM>
-__global__ __launch_bounds__(kThreads) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+// grid (n_scan_chunks, Hkv, n_problems), 256 threads: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
+// caches, by the latency of a few round trips for short ones.  A wavefront holds two groups of TPI / 4 tiles, one on its way
+// while the other is contracted: whole units at a time (16 loads, wait, 16 tiles' scores, next unit) took 49.5 us
+// against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
+// as large, gain nothing at 128K and lose 2 us at 32K (the first group is consumed later).
+template <int D, int TPI, bool STREAM, bool STRIP>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                   char* __restrict__ ws) {
   const int p = blockIdx.z, h = blockIdx.y;
   const tkphi_problem pr = probs[p];
@@ -397,11 +404,11 @@ __global__ __launch_bounds__(kThreads) void score_filtered_kernel(Geom g, const 
   const int r = threadIdx.x & 15;
   ScoreFrag bq[D / 32];
   load_query_frags<D>(g, pr, h, bq);
-  const uint32_t edge_r = r < g.G ? ((const uint32_t*)(blk + g.off_thr))[h * g.G + r] : 0xffffffffu;
-  extern __shared__ __attribute__((aligned(16))) uint2 sh_heads[];      // [4 wavefronts][G][cand_T]
-  const int wv = (int)(threadIdx.x >> 6);
-  scan_wave_slot<D, TPI, TPI, STREAM>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r, -1, false,
-                         g.head_strip ? sh_heads + (size_t)wv * g.G * g.cand_T : nullptr);
+  const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
+  extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  scan_wave_slot<D, TPI, TPI / 4, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r, -1, false,
+                                                       (lds_u32x2)sh_heads + (STRIP ? wv * g.G * g.cand_T : 0));
 }
 
 // The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query
@@ -444,9 +451,10 @@ void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, 
   if (g.max_mid == 0) return;
   dim3 grid(g.n_scan_chunks, g.Hkv, g.n_problems);
   const size_t lds = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
-  if (g.d == 128 && g.stream_keys) TKPHI_LAUNCH(ST_SCORE, (score_filtered_kernel<128, 4, true>), grid, dim3(kThreads), lds, s, g, probs, ws);
-  else if (g.d == 128) TKPHI_LAUNCH(ST_SCORE, (score_filtered_kernel<128, 4, false>), grid, dim3(kThreads), lds, s, g, probs, ws);
-  else TKPHI_LAUNCH(ST_SCORE, (score_filtered_kernel<64, 8, false>), grid, dim3(kThreads), lds, s, g, probs, ws);
+  const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
+  if (g.d == 128 && g.stream_keys) { if (g.head_strip) launch(score_filtered_kernel<128, 4, true, true>); else launch(score_filtered_kernel<128, 4, true, false>); }
+  else if (g.d == 128) { if (g.head_strip) launch(score_filtered_kernel<128, 4, false, true>); else launch(score_filtered_kernel<128, 4, false, false>); }
+  else { if (g.head_strip) launch(score_filtered_kernel<64, 8, false, true>); else launch(score_filtered_kernel<64, 8, false, false>); }
 }
 
 }  // namespace tkphi

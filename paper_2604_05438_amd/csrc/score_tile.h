@@ -9,6 +9,10 @@ namespace tkphi {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 st_bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float st_floatx4;
+typedef unsigned int st_u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) st_u32x2* lds_u32x2;
+typedef __attribute__((address_space(1))) st_u32x2* glb_u32x2;
+typedef __attribute__((address_space(1))) float* glb_f32;
 union ScoreFrag {
   u32x4 u;
   st_bf16x8 v;
@@ -22,7 +26,7 @@ __device__ __forceinline__ void load_query_frags(const Geom& g, const tkphi_prob
 #pragma unroll
   for (int j = 0; j < D / 32; ++j) {
     bq[j].u = (u32x4){0u, 0u, 0u, 0u};
-    if (r < g.G) bq[j].u = *(const u32x4*)((const uint16_t*)pr.q + (size_t)(h * g.G + r) * D + j * 32 + kg * 8);
+    if (r < g.G) bq[j].u = gload128((const uint16_t*)pr.q + (size_t)(h * g.G + r) * D + j * 32 + kg * 8);
   }
 }
 
@@ -47,78 +51,109 @@ __device__ __forceinline__ size_t cand_region(const Geom& g, int gq, int chunk, 
 //            only that set, so what a first attempt reads is never overwritten while another workgroup reads it)
 // Lane (r, kg) ends up with the scores of head r for tokens base + t 16 + 4 kg + i, so each list is
 // written by the four lanes of its column, in the order (unit, t, i, kg).
-// SUB: 16-token tiles whose loads are in flight together (the rescan keeps registers low); STREAM: non-temporal key loads
-template <int D, int TPI, int SUB = TPI, bool STREAM = false>
+// SUB: 16-token tiles loaded and contracted together; NB: groups of SUB tiles in registers, NB - 1 of them on their way while one
+// is contracted (the rescan, which must not cost the kernel around it registers, runs one tile at a time); STREAM: non-temporal key loads
+// STRIP: `strip` is used (a template parameter, and address spaces spelled out on every pointer stored through: a store that
+// might go to LDS or to memory becomes a flat store, after which the compiler waits for every load in flight)
+template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP>
 __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks,
                                                int chunk, int wslot, const ScoreFrag (&bq)[D / 32], uint32_t edge_r,
-                                               int only_gl, bool rescan = false, uint2* strip = nullptr) {
+                                               int only_gl, bool rescan, lds_u32x2 strip) {
   constexpr int KS = D / 32;
   constexpr int TOK = TPI * 16;         // tokens per wavefront and unit
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int G = g.G;
   const bool col_live = r < G && (only_gl < 0 || r == only_gl);
   const int gq = h * G + min(r, G - 1);
-  uint2* list = (uint2*)(blk + (rescan ? g.off_resf : g.off_candf)) + cand_region(g, gq, chunk, wslot);
-  uint2* head = (uint2*)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)g.cand_T;
+  const glb_u32x2 list = (glb_u32x2)(blk + (rescan ? g.off_resf : g.off_candf)) + cand_region(g, gq, chunk, wslot);
+  const glb_u32x2 head = (glb_u32x2)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)g.cand_T;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
   const uint64_t col_lanes = 0x0001000100010001ull << r;     // the four lanes of this column
   const uint64_t lanes_below = (1ull << lane) - 1ull;
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
-  const char* Kb = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + (size_t)kg * 16;
+  const char* Kb = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2;
   const float scale = g.score_scale;
-  float* export_row = pr.scores ? pr.scores + (size_t)gq * n : nullptr;
+  const glb_f32 export_row = pr.scores ? (glb_f32)(pr.scores + (size_t)gq * n) : (glb_f32) nullptr;
   int cnt = 0;                          // length of this column's list (the same in its four lanes)
 
-  const int n_units = g.scan_chunk / (4 * TOK);
-  for (int k = 0; k < n_units; ++k) {
-    const int base = chunk_unit_token(g, n_chunks, chunk, k) + wslot * TOK;
-    if (base >= n) { if (g.interleave) break; else continue; }
+  // A score is first compared as a float with the bound: false for what cannot be a candidate (NaN and the columns of no
+  // head aside), two instructions and a branch; the branch decides exactly, by key.
+  float edge_s;
+  auto float_bound = [&]() { edge_s = !col_live || edge_r == 0xffffffffu ? INFINITY : edge_r == 0u ? -INFINITY : key_score(edge_r); };
+
+  ScoreFrag a[NB][SUB][KS];
+  const char* const Kl = Kb + kg * 16;
+  auto request = [&](int base, ScoreFrag (&f)[SUB][KS]) {
 #pragma unroll
-    for (int t0 = 0; t0 < TPI; t0 += SUB) {
-      ScoreFrag a[SUB][KS];
+    for (int t = 0; t < SUB; ++t) {
+      const char* rp = Kl + (uint64_t)(uint32_t)min(base + t * 16 + r, n - 1) * row_bytes;     // rows past the end repeat the last one
 #pragma unroll
-      for (int t = 0; t < SUB; ++t) {
-        const int row = min(base + (t0 + t) * 16 + r, n - 1);
-        const char* rp = Kb + (size_t)row * row_bytes;
+      for (int j = 0; j < KS; ++j) f[t][j].u = STREAM ? gload128_stream(rp + j * 64) : gload128(rp + j * 64);
+    }
+  };
+  auto contract = [&](int base, const ScoreFrag (&f)[SUB][KS]) {
+    st_floatx4 acc[SUB];
 #pragma unroll
-        for (int j = 0; j < KS; ++j) a[t][j].u = STREAM ? gload128_stream(rp + j * 64) : gload128(rp + j * 64);
-      }
-      __builtin_amdgcn_sched_barrier(0);   // all loads of the group are in flight before the first MFMA
-      st_floatx4 acc[SUB];
+    for (int t = 0; t < SUB; ++t) {
+      acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int t = 0; t < SUB; ++t) {
-        acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][j].v, bq[j].v, acc[t], 0, 0, 0);
+    }
 #pragma unroll
-        for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][j].v, bq[j].v, acc[t], 0, 0, 0);
-      }
+    for (int t = 0; t < SUB; ++t) {
 #pragma unroll
-      for (int t = 0; t < SUB; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tok = base + (t0 + t) * 16 + 4 * kg + i;
-          const float s = acc[t][i] * scale + 0.0f;            // + 0.0f: -0 -> +0, equal scores get equal keys
-          const bool live = col_live && tok < n;
-          if (export_row && live) export_row[tok] = s;
-          const bool pass = live && score_key(s) >= edge_r;
-          const uint64_t mask = __ballot(pass);
-          if (mask) {
-            const uint64_t mine = mask & col_lanes;
-            const int at = cnt + __popcll(mine & lanes_below);
-            if (pass) {
-              const uint2 e = make_uint2(__float_as_uint(s), (uint32_t)tok);
-              if (at < T) { if (strip) strip[min(r, G - 1) * T + at] = e; else head[at] = e; }
-              else if (at < cap) list[at] = e;
-            }
-            cnt += __popcll(mine);
+      for (int i = 0; i < 4; ++i) {
+        const int tok = base + t * 16 + 4 * kg + i;
+        const float s = fmaf(acc[t][i], scale, 0.0f);          // + 0.0f: -0 -> +0, equal scores get equal keys
+        if (export_row && col_live && tok < n) export_row[tok] = s;
+        if (__ballot(!(s < edge_s))) {
+          const bool pass = col_live && tok < n && score_key(s) >= edge_r;
+          const uint64_t mine = __ballot(pass) & col_lanes;
+          const int at = cnt + __popcll(mine & lanes_below);
+          if (pass) {
+            const st_u32x2 e = (st_u32x2){__float_as_uint(s), (uint32_t)tok};
+            if (at < T) { if constexpr (STRIP) strip[min(r, G - 1) * T + at] = e; else head[at] = e; }
+            else if (at < cap) list[at] = e;
           }
+          cnt += __popcll(mine);
         }
       }
     }
+  };
+  // groups of SUB tiles in the order (unit, group of the unit); units past the end of a chunk's tokens end the pass (their
+  // first tokens only grow with k)
+  constexpr int GPU = TPI / SUB;
+  const int n_groups = g.scan_chunk / (4 * TOK) * GPU;
+  auto group_base = [&](int q) { return q < n_groups ? chunk_unit_token(g, n_chunks, chunk, q / GPU) + wslot * TOK + (q % GPU) * SUB * 16 : n; };
+  if constexpr (NB > 1) {
+    // (requests and contractions are unconditional - past the end they repeat the last row, whose tokens are then dead - so that
+    // the compiler can count the loads in flight on every path)
+    int bases[NB];
+#pragma unroll
+    for (int u = 0; u < NB - 1; ++u) { bases[u] = group_base(u); request(bases[u], a[u]); }
+    float_bound();                       // (behind the first requests: the bound itself is still on its way)
+    for (int q = 0; bases[0] < n; q += NB) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        constexpr int kAhead = NB - 1;
+        bases[(u + kAhead) % NB] = group_base(q + u + kAhead);
+        request(bases[(u + kAhead) % NB], a[(u + kAhead) % NB]);
+        __builtin_amdgcn_sched_barrier(0);
+        contract(bases[u], a[u]);
+      }
+    }
+  } else {
+    float_bound();
+    for (int q = 0, base = group_base(0); base < n; base = group_base(++q)) {
+      request(base, a[0]);
+      __builtin_amdgcn_sched_barrier(0);   // all loads of the group are in flight before the first MFMA
+      contract(base, a[0]);
+    }
   }
-  if (strip) {                          // (LDS operations of one wavefront execute in order: no barrier)
+  if constexpr (STRIP) {                // (LDS operations of one wavefront execute in order: no barrier)
     for (int gl = 0; gl < G; ++gl) {
       const int c = min(__shfl(cnt, gl), T);          // lane gl is lane (r = gl, kg = 0) of column gl
-      uint2* hd = (uint2*)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)(h * G + gl) * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)T;
+      const glb_u32x2 hd = (glb_u32x2)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)(h * G + gl) * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)T;
       for (int i = lane; i < c; i += 64) hd[i] = strip[gl * T + i];
     }
   }

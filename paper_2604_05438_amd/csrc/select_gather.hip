@@ -50,11 +50,11 @@ template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 // (one 16-token tile in flight per wavefront: the rare path must not cost the common one registers)
 template <int D, int TPI, int NTHR>
 __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int n, int n_chunks) {
-  const int h = gq / g.G, wv = threadIdx.x >> 6;
+  const int h = gq / g.G, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   ScoreFrag bq[D / 32];
   load_query_frags<D>(g, pr, h, bq);
   for (int reg = wv; reg < n_chunks * 4; reg += NTHR / 64)
-    scan_wave_slot<D, TPI, 1>(g, pr, blk, h, n, n_chunks, reg >> 2, reg & 3, bq, 0u, gq % g.G, true);
+    scan_wave_slot<D, TPI, 1, 1, false, false>(g, pr, blk, h, n, n_chunks, reg >> 2, reg & 3, bq, 0u, gq % g.G, true, (lds_u32x2) nullptr);
 }
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
