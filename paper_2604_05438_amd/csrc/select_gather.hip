@@ -34,14 +34,13 @@
 namespace tkphi {
 
 constexpr int kBCap = 1024;            // boundary-bin candidates ranked in LDS
-constexpr int kSweepEntries = 12;      // entries per thread and sweep (Geom::cand_T is a multiple)
 constexpr int kSweepLoads = kSweepEntries / 2;
 // winners gathered per round: 16-token tile t of a round goes to wavefront t mod 16.  Two tiles per wavefront at
 // d = 64 (one round for most heads of a batch of short sequences); at d = 128 the second tile's rows do not fit
 // the registers
 template <int D, int NTHR> constexpr int kBatchOf = (D == 64 && NTHR == 1024) ? 512 : 256;
-// candidates of a head that the select phase packs into LDS
-template <int NTHR> constexpr int kDenseOf = NTHR == 1024 ? 8192 : 4096;
+// candidates of a head that the select phase packs into LDS (what the staged Wk leaves room for; 512 threads: two workgroups per CU)
+template <int D, int NTHR> constexpr int kDenseOf = NTHR == 512 ? 4096 : D == 64 ? 12288 : 10240;
 // winners of a workgroup kept in LDS (the rest are re-read from the retrieved list)
 template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 
@@ -66,7 +65,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // select phase: histogram (8 KB) + boundary candidates (8 KB); gather phase: reduction scratch of the value sums
   __shared__ __attribute__((aligned(16))) char lds_a[16384];
   __shared__ __attribute__((aligned(16))) char wk_lds[D * WROW];
-  constexpr int kDense = kDenseOf<NTHR>, kWinLds = kWinLdsOf<NTHR>, NWV = NTHR / 64;
+  constexpr int kDense = kDenseOf<D, NTHR>, kWinLds = kWinLdsOf<NTHR>, NWV = NTHR / 64;
   __shared__ uint2 dense[kDense];                   // the candidates of the head, packed (select phase)
   __shared__ int w_tok[kWinLds];
   __shared__ float w_s[kWinLds];
@@ -75,7 +74,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   __shared__ float sh_bk[D], sh_pq[D];              // bk[h] and phi_q of the head, staged with Wk
   __shared__ int sh_scan[NWV];
   __shared__ uint64_t sh_prefix, sh_thr;
-  __shared__ int sh_want, sh_tot, sh_r0, sh_r1;
+  __shared__ int sh_want, sh_tot;
   __shared__ int sh_bstar, sh_krem, sh_chi, sh_nb, sh_nbc;
   __shared__ uint32_t sh_total, sh_ovp;
   __shared__ float sh_m, sh_Z, sh_zs;
@@ -196,56 +195,91 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 
   // (have_e0 is false exactly after a rescan: those lists were written without a bound)
   const SelBins bin_of{edge0, have_e0 && edge0 != 0u && edge0 != 0xffffffffu};
-  // This workgroup's share of the gather: the winners of lists [l0, l1), in list order
   const int split = g.sg_split;
-  const int per_part = (n_reg + split - 1) / split;
-  const int l0 = part * per_part, l1 = min(n_reg, l0 + per_part);
-  int my_base = 0, my_count = 0;                    // winners in earlier lists; winners of this workgroup
-  // Common case: one sweep holds every candidate and there are at most kDense of them (about 2.5 K per head at a
-  // 1 % budget, against 12 K list slots).  They are first packed, in list order, into an LDS array (64 KB that
-  // is otherwise unused: a workgroup of 1024 threads has a CU to itself); histogram, threshold and winners then
-  // walk 3-4 entries per thread instead of 12 slots.
-  if (n_sweeps == 1 && have_e0 && total <= (uint32_t)kDense) {
-    const int n_cand = (int)total;
-    const Share sh0 = share_of(0, tid, (int)min(c0, cap_w));
-    const int nv = sh0.nvalid;
+  int my_base = 0, my_count = 0;                    // winners ahead of this workgroup's; winners of this workgroup
+  // The candidates are packed, sweep by sweep, into an LDS array (80 KB that are otherwise unused: a workgroup of 1024
+  // threads has a CU to itself); histogram, threshold and winners then walk 3-4 entries per thread (about 3 K candidates per
+  // head at a 1 % budget of 128K) instead of 12 list slots per sweep, and workgroup `part` takes the winners of an equal
+  // share of the array.  More candidates than it holds: a first pass over the sweeps finds the boundary bin, and only
+  // what lies in it or above is packed.
+  auto clear_hist = [&]() {
     for (int i = tid; i < kFineBins; i += NTHR) sh_hist[i] = 0u;
-    if (tid == 0) {
-      sh_bstar = -1; sh_krem = 0; sh_chi = 0; sh_nb = 0; sh_nbc = 0; sh_thr = 0ull;
-      sh_r0 = l0 < n_reg ? 0 : n_cand; sh_r1 = n_cand;
-    }
-    const int off = sel_scan_incl(nv, sh_scan) - nv;       // (its barriers also publish the initial values above)
+    if (tid == 0) { sh_bstar = -1; sh_krem = 0; sh_chi = 0; sh_nb = 0; sh_nbc = 0; sh_thr = 0ull; }
+  };
+  // histogram -> boundary bin: thread t takes the BPT bins below kFineBins - BPT t, highest first: a prefix sum over the
+  // threads is a suffix sum over the bins
+  auto boundary_bin = [&]() {
+    constexpr int BPT = kFineBins / NTHR;
+    int cb[BPT], own = 0;
 #pragma unroll
-    for (int i = 0; i < kSweepEntries; ++i)
-      if (i < nv) dense[off + i] = entry(e0, i);
-    {
-      const int s0 = kSweepEntries * tid, list = s0 / T;
-      if (s0 % T == 0 && list < n_reg) {               // first slot of a list: where the list starts in the packed array
-        if (list == l0) sh_r0 = off;
-        if (list == l1) sh_r1 = off;
-      }
+    for (int e = 0; e < BPT; ++e) { cb[e] = (int)sh_hist[kFineBins - 1 - BPT * tid - e]; own += cb[e]; }
+    int gt = sel_scan_incl(own, sh_scan) - own;              // candidates in bins above this thread's
+#pragma unroll
+    for (int e = 0; e < BPT; ++e) {
+      if (gt + cb[e] >= Ksel && gt < Ksel) { sh_bstar = kFineBins - 1 - BPT * tid - e; sh_krem = Ksel - gt; sh_chi = gt; sh_nb = cb[e]; }
+      gt += cb[e];
     }
     lds_barrier();
-    const int r0 = sh_r0, r1 = sh_r1;
+  };
+  auto sweep_histogram = [&]() {
+    for (int sw = 0; sw < n_sweeps; ++sw) {
+      const Share sh = share_of(sw, tid);
+      u32x4 e[kSweepLoads];
+      load_share(sh, e);
+#pragma unroll
+      for (int i = 0; i < kSweepEntries; ++i)
+        if (i < sh.nvalid) atomicAdd(&sh_hist[bin_of(score_key(__uint_as_float(entry(e, i).x)))], 1u);
+    }
+    lds_barrier();                                    // (the histogram is LDS traffic; the Wk loads stay in flight)
+  };
+  bool packed = total <= (uint32_t)kDense;
+  int min_bin = 0;                                  // candidates in lower bins are not packed
+  if (!packed) {
+    clear_hist();
+    __syncthreads();
+    sweep_histogram();
+    boundary_bin();
+    min_bin = sh_bstar;
+    packed = min_bin >= 0 && sh_chi + sh_nb <= kDense;       // (else all scores (nearly) equal, or a budget beyond the array)
+    lds_barrier();
+  }
+  if (packed) {
+    int n_cand = 0;
+    clear_hist();
+    if (n_sweeps == 1 && have_e0 && min_bin == 0) {  // the usual case, straight from the registers of the speculative sweep
+      const int nv = share_of(0, tid, (int)min(c0, cap_w)).nvalid;
+      const int off = sel_scan_incl(nv, sh_scan) - nv;       // (its barriers also publish the cleared histogram)
+#pragma unroll
+      for (int i = 0; i < kSweepEntries; ++i)
+        if (i < nv) dense[off + i] = entry(e0, i);
+      n_cand = (int)total;
+      lds_barrier();
+    } else {
+      for (int sw = 0; sw < n_sweeps; ++sw) {
+        const Share sh = share_of(sw, tid);
+        u32x4 e[kSweepLoads];
+        load_share(sh, e);
+        uint32_t keep = 0;
+#pragma unroll
+        for (int i = 0; i < kSweepEntries; ++i)
+          if (i < sh.nvalid && (min_bin == 0 || bin_of(score_key(__uint_as_float(entry(e, i).x))) >= min_bin)) keep |= 1u << i;
+        const int nw = __popc(keep);
+        const int incl = sel_scan_incl(nw, sh_scan);
+        int at = n_cand + incl - nw;
+#pragma unroll
+        for (int i = 0; i < kSweepEntries; ++i)
+          if (keep & (1u << i)) dense[at++] = entry(e, i);
+        if (tid == NTHR - 1) sh_tot = incl;
+        lds_barrier();
+        n_cand += sh_tot;
+      }
+    }
+    const int r0 = (int)((uint32_t)(n_cand * part) / (uint32_t)split), r1 = (int)((uint32_t)(n_cand * (part + 1)) / (uint32_t)split);
     // ---- histogram -> boundary bin ----------------------------------------------------------------------------
     for (int idx = tid; idx < n_cand; idx += NTHR) atomicAdd(&sh_hist[bin_of(score_key(__uint_as_float(dense[idx].x)))], 1u);
     lds_barrier();
     TKPHI_PHASE(ws, 12);
-    {
-      // thread t takes the BPT bins below kFineBins - BPT t, highest first: a prefix sum over the threads is a
-      // suffix sum over the bins
-      constexpr int BPT = kFineBins / NTHR;
-      int cb[BPT], own = 0;
-#pragma unroll
-      for (int e = 0; e < BPT; ++e) { cb[e] = (int)sh_hist[kFineBins - 1 - BPT * tid - e]; own += cb[e]; }
-      int gt = sel_scan_incl(own, sh_scan) - own;          // candidates in bins above this thread's
-#pragma unroll
-      for (int e = 0; e < BPT; ++e) {
-        if (gt + cb[e] >= Ksel && gt < Ksel) { sh_bstar = kFineBins - 1 - BPT * tid - e; sh_krem = Ksel - gt; sh_chi = gt; sh_nb = cb[e]; }
-        gt += cb[e];
-      }
-      lds_barrier();
-    }
+    boundary_bin();
     const int bstar = sh_bstar, krem = sh_krem, c_hi = sh_chi, nb = sh_nb;
     if (bstar < 0) {                                  // cannot happen: total >= Ksel
       if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
@@ -338,37 +372,17 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       }
     }
   } else {
-    // (the general path: several sweeps, more candidates than the packed array holds, or the lists of a rescan;
-    // every phase reads its entries from the lists again)
+    // (the general path: the candidates that may be winners do not fit the packed array; every phase reads its entries from the
+    // lists again)
     // ---- pass A: histogram of the candidates' fine bins ----------------------------------------------------------
-    for (int i = tid; i < kFineBins; i += NTHR) sh_hist[i] = 0u;
-    if (tid == 0) { sh_bstar = -1; sh_krem = 0; sh_chi = 0; sh_nb = 0; sh_nbc = 0; sh_thr = 0ull; }
+    // (this workgroup's share of the gather: the winners of lists [l0, l1), in list order)
+    const int per_part = (n_reg + split - 1) / split;
+    const int l0 = part * per_part, l1 = min(n_reg, l0 + per_part);
+    clear_hist();
     __syncthreads();
-    for (int sw = 0; sw < n_sweeps; ++sw) {
-      const Share sh = share_of(sw, tid);
-      u32x4 e[kSweepLoads];
-      load_share(sh, e);
-#pragma unroll
-      for (int i = 0; i < kSweepEntries; ++i)
-        if (i < sh.nvalid) atomicAdd(&sh_hist[bin_of(score_key(__uint_as_float(entry(e, i).x)))], 1u);
-    }
-    lds_barrier();                                    // (the histogram is LDS traffic; the Wk loads stay in flight)
+    sweep_histogram();
     TKPHI_PHASE(ws, 12);
-    {
-      // thread t takes the BPT bins below kFineBins - BPT t, highest first: a prefix sum over the threads is a
-      // suffix sum over the bins
-      constexpr int BPT = kFineBins / NTHR;
-      int cb[BPT], own = 0;
-#pragma unroll
-      for (int e = 0; e < BPT; ++e) { cb[e] = (int)sh_hist[kFineBins - 1 - BPT * tid - e]; own += cb[e]; }
-      int gt = sel_scan_incl(own, sh_scan) - own;          // candidates in bins above this thread's
-#pragma unroll
-      for (int e = 0; e < BPT; ++e) {
-        if (gt + cb[e] >= Ksel && gt < Ksel) { sh_bstar = kFineBins - 1 - BPT * tid - e; sh_krem = Ksel - gt; sh_chi = gt; sh_nb = cb[e]; }
-        gt += cb[e];
-      }
-      lds_barrier();
-    }
+    boundary_bin();
     const int bstar = sh_bstar, krem = sh_krem, c_hi = sh_chi, nb = sh_nb;
     if (bstar < 0) {                                  // cannot happen: total >= Ksel
       if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
@@ -692,11 +706,8 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
   dim3 grid(g.sg_split, g.Hq, g.n_problems);       // (Geom::n_tiles of this pipeline: one partial per workgroup)
-  // Batches of short sequences at d = 64 (one workgroup per head, at least two heads per CU): 512-thread workgroups,
-  // two per CU, so that one head's memory round trips hide behind the other's arithmetic
-  const bool small_wg = g.d == 64 && g.sg_split == 1 && (long)g.Hq * g.n_problems >= 512 && g.max_K <= 1024;
   if (g.d == 128) TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<128, 4, 1024>), grid, dim3(1024), 0, s, g, probs, ws, mode);
-  else if (small_wg) TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<64, 8, 512>), grid, dim3(512), 0, s, g, probs, ws, mode);
+  else if (g.sg_threads == 512) TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<64, 8, 512>), grid, dim3(512), 0, s, g, probs, ws, mode);
   else TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<64, 8, 1024>), grid, dim3(1024), 0, s, g, probs, ws, mode);
 }
 

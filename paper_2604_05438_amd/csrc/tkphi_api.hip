@@ -24,7 +24,21 @@ void set_error(const char* fmt, ...) {
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g) {
+// Entries of the compact part of a candidate list (a quarter of a chunk of scan_chunk tokens) for a budget of K in n: the expected
+// number of its tokens above the sampled bound (estimated as for the smallest sample of 512 rows, whose bound is the
+// loosest) and five standard deviations, no more than one sweep of the select kernel holds for every list, at least 24.
+// Whatever the sweep has room for instead: 1 us slower at 32K and 52K (the entries are read whether they are filled or not);
+// 24 for lists of 256 tokens: one overflows in most calls, and the select kernel takes 28 or 35 us instead of 23.
+static int list_head(int scan_chunk, int64_t K, int64_t n, int sweep, int64_t n_chunks) {
+  const double share = n <= 0 ? 0.0 : (double)K / (double)n, mu = 512.0 * share;
+  const double mean = std::min(1.0, (mu + 5.0 * std::sqrt(mu) + 2.0) / 512.0) * scan_chunk / 4;
+  const int want = (int)std::min<double>(mean + 5.0 * std::sqrt(mean) + 4.0, scan_chunk / 4);
+  const int fit = (int)(sweep / (4 * n_chunks)) / kSweepEntries * kSweepEntries;
+  return std::max(kMinListHead, std::min(fit, (int)align_up((size_t)want, kSweepEntries)));
+}
+
+// compact: the chunks and candidate lists of the filtered pipeline as small as they get (callers with a scratch limit)
+static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, bool compact, Geom* g) {
   if (!cfg) { set_error("cfg is null"); return TKPHI_EINVAL; }
   if (n_problems < 0 || max_L < 1 || max_K < 0) {
     set_error("n_problems=%d max_L=%d max_K=%d out of range", n_problems, max_L, max_K);
@@ -103,12 +117,49 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
   g->score_scale = cfg->score_scale; g->a = cfg->phi_in_scale; g->c = cfg->phi_norm_coef;
 
   const int64_t units = (int64_t)g->max_mid * g->Hkv * std::max(n_problems, 1);
-  // score_mid: about 1024 workgroups, 256..8192 tokens each (uint16 chunk histograms: < 65536)
-  int sc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 1024), 256, 8192), 256);
-  if (tn.scan_chunk > 0) sc = tn.scan_chunk;
+  // filtered pipeline: where the matrix-core score kernel applies, for budgets of at most 1/12 of the mid-region, the range it
+  // measured faster than the spill pipeline in (3B layer at 128K, 1 / 2 / 4 / 7 %: 84 / 93 / 110 / 127 against 98 / 108 /
+  // 122 / 143 us; 1B layer at 32K 38 / 39 / 41 / 44 against 42 / 43 / 45 / 48; 16 sequences of 4K to 16K at d = 64, 4 %: 94
+  // against 114)
+  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
+                 (tn.select_mode == 2 || (int64_t)max_K * 12 <= g->max_mid)) ? 1 : 0;
+  // filtered pipeline: the workgroups that share a query head in the fused select + gather kernel, one partial each: about one
+  // workgroup per CU for a single layer, one per head in big batches; batches of short sequences at d = 64 (one workgroup
+  // per head, at least two heads per CU) take 512-thread workgroups, two per CU, so that one head's memory round trips
+  // hide behind the other's arithmetic
+  g->sg_split = g->filtered ? std::clamp(256 / std::max(1, g->Hq * std::max(n_problems, 1)), 1, 16) : 0;
+  g->sg_threads = g->d == 64 && g->sg_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
+  const int sweep = g->sg_threads * kSweepEntries;   // candidate slots of a head that kernel reads in one go
   // matrix-core score kernel: 4 wavefronts x 64 (d = 128) or 128 (d = 64) tokens per iteration;
   // a chunk is a whole number of such units
   g->scan_unit = g->use_mfma ? (g->d == 128 ? 256 : 512) : 256;
+  // spill pipeline: about 1024 workgroups, 256..8192 tokens each (uint16 chunk histograms: < 65536)
+  int sc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 1024), 256, 8192), 256);
+  if (g->filtered && !compact) {
+    if (n_problems > 1) {
+      // Filtered pipeline, batches: 4096 workgroups by the bounds of the call, a power of two of tokens each.  Ragged batches have
+      // far fewer, which then still even out over the CUs (8 sequences of 8K to 32K at d = 128: score pass 74 -> 58 us against a
+      // target of 1024, 16 of 16K to 64K at d = 64: 168 -> 152)
+      sc = 256;
+      while (sc < 8192 && (int64_t)sc * 4096 < units) sc *= 2;
+      while (sc < 32768 && ceil_div(g->max_mid, std::max(sc, g->scan_unit)) * 4 * kMinListHead > sweep) sc *= 2;
+    } else {
+      // One problem: the pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (3B layer
+      // at 50 K tokens: 232 workgroups of 1792 tokens 22.4 us, 400 of 1024 25.0, 312 of 1280 29.2); one workgroup per CU
+      // streams 7 % slower at d = 128 and, with 2.7 times the score work per byte, 40 % at d = 64.  Against that stands what the
+      // select kernel pays for more lists: 0.35 us per 1000 slots of their compact heads.
+      const double ideal_us = (double)units * g->d * 2 / 6.2e6;
+      double best = 0.0;
+      for (int c = g->scan_unit; c <= std::max(8192, g->scan_unit); c += g->scan_unit) {
+        const int64_t chunks = std::max<int64_t>(1, ceil_div(g->max_mid, c)), rounds = ceil_div(chunks * g->Hkv, 256);
+        if (chunks * 4 * kMinListHead > sweep && c + g->scan_unit <= 8192) continue;
+        const double eff = (double)units / ((double)rounds * 256 * c) * (rounds > 1 ? 1.0 : g->d == 128 ? 0.93 : 0.7);
+        const double cost = ideal_us / eff + 0.35e-3 * (double)(chunks * 4 * list_head(c, std::min<int64_t>(max_K, g->max_mid), g->max_mid, sweep, chunks));
+        if (best == 0.0 || cost <= best) { best = cost; sc = c; }
+      }
+    }
+  }
+  if (tn.scan_chunk > 0) sc = tn.scan_chunk;
   g->scan_chunk = std::clamp((int)align_up((size_t)std::max(sc, 1), g->scan_unit), g->scan_unit, 32768);
   while (ceil_div(g->max_mid, g->scan_chunk) > kMaxScanChunks && g->scan_chunk < 32768) g->scan_chunk *= 2;
   if (ceil_div(g->max_mid, g->scan_chunk) > kMaxScanChunks) {
@@ -117,23 +168,14 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
   }
   g->n_scan_chunks = (int)std::max<int64_t>(1, ceil_div(g->max_mid, g->scan_chunk));
   // with many chunks per head (one long sequence) the workgroups read neighbouring rows at any
-  // moment instead of 1024 far-apart ranges: measured 5 % faster; with few chunks per head
-  // (many problems) contiguous ranges are faster
-  g->interleave = tn.interleave ? (tn.interleave == 1 ? 1 : 0) : (g->use_mfma && g->scan_unit < g->scan_chunk && g->n_scan_chunks >= 64) ? 1 : 0;
+  // moment instead of far-apart ranges (3B layer at 128K: 47.9 against 49.5 us); with few chunks per head or
+  // several problems contiguous ranges are as fast or faster (16 ragged sequences at d = 64, chunks of 1024: 137 against 153 us)
+  g->interleave = tn.interleave ? (tn.interleave == 1 ? 1 : 0)
+                                : (g->use_mfma && g->scan_unit < g->scan_chunk && g->n_scan_chunks >= 64 && (n_problems == 1 || !g->filtered)) ? 1 : 0;
   if (!g->use_mfma || g->scan_unit >= g->scan_chunk) g->interleave = 0;
-  // filtered pipeline: where the matrix-core score kernel applies.  Chosen by default where it measured faster
-  // than the spill pipeline: a budget of at most 1/64 of the mid-region (128K layer: 86 / 89 against 95 / 100 us
-  // per step at 0.5 / 1 %; 32K layer 42.5 against 44.5 us; 28 layers per call 1.62 against 1.87 ms; the ragged
-  // 256-problem batch 3.36 against 3.65 ms).  At 2 % and 4 % candidate lists overflow their compact heads and the
-  // fused select falls back to its general path: 110 / 124 against 108 / 123 us
-  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
-                 (tn.select_mode == 2 || (int64_t)max_K * 64 <= g->max_mid)) ? 1 : 0;
   g->sel_test = tn.select_test;
   // gather: tiles of kPairsPerWG retrieved tokens per query head
   g->n_tiles = (int)ceil_div(std::min<int64_t>(max_K, g->max_mid), kPairsPerWG);
-  // (filtered pipeline: the workgroups that share a query head in the fused select + gather kernel, one
-  // partial each: about one workgroup per CU for a single layer, one per head in big batches)
-  g->sg_split = g->filtered ? std::clamp(256 / std::max(1, g->Hq * std::max(n_problems, 1)), 1, 16) : 0;
   g->n_atiles = (int)std::max<int64_t>(1, ceil_div(std::min<int64_t>((int64_t)cfg->n_sink + cfg->n_tail, max_L) + cfg->max_gen, 64));
   // summary_build: 512 workgroups fill the chip (2 per CU); larger jobs get about 2048 chunks of at
   // least 2048 tokens so that the last, partly filled round of workgroups stays a small share.  The fp32-arithmetic
@@ -176,10 +218,8 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
   g->off_candf = p;     // (the two pipelines never run in the same call)
   p = align_up(p + std::max((size_t)g->Hq * g->mid_stride * sizeof(float),
                             g->filtered ? (size_t)g->Hq * g->n_scan_chunks * g->scan_chunk * sizeof(uint2) : (size_t)0), 256);
-  // compact part of a candidate list: 24 entries, or 3/32 of the list's capacity if that is more (about three
-  // times the expected length); with 128 chunks per head the compact lists of a head are one sweep of the
-  // fused select + gather kernel
-  g->cand_T = (int)align_up((size_t)std::max(24, g->scan_chunk / 4 * 3 / 32), 12);
+  g->cand_T = compact || !g->filtered ? (int)align_up((size_t)std::max(kMinListHead, g->scan_chunk / 4 * 3 / 32), kSweepEntries)
+                                      : list_head(g->scan_chunk, std::min(max_K, g->max_mid), g->max_mid, sweep, g->n_scan_chunks);
   g->head_strip = (size_t)4 * g->G * g->cand_T * sizeof(uint2) <= 32768 ? 1 : 0;
   // Non-temporal key loads leave the candidate lists, phi_q and the problem record in the caches for the select kernel
   // (l3b_128k: score pass unchanged, select 25.5 -> 24.9 us, step -1.4 us).  Only for one problem of 256-byte rows:
@@ -246,6 +286,13 @@ tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int m
   g->build_bytes = align_up(build_all, 256);
   g->total_bytes = align_up(std::max(decode_all, build_all), 256);
   return TKPHI_OK;
+}
+
+// scratch_limit: where a decode's scratch would exceed it (0: none), the compact geometry
+tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t scratch_limit) {
+  const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, false, g);
+  if (st != TKPHI_OK || scratch_limit == 0 || g->decode_bytes <= scratch_limit) return st;
+  return make_geom_as(cfg, n_problems, max_L, max_K, true, g);
 }
 
 static tkphi_status check_call(const tkphi_problem* problems, int n_problems, const void* ws,
@@ -427,7 +474,7 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg, const tkphi_problem* p
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, TKPHI_STATIC_SCRATCH_BYTES);
   if (st != TKPHI_OK) return st;
   g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
   if (g.phi_kind == TKPHI_PHI_MLP) {      // that path creates a stream and events on first use

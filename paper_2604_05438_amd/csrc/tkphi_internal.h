@@ -24,6 +24,8 @@ constexpr int kExpHi = 134;
 constexpr int kMagBins = (kExpHi - kExpLo + 1) * 16;   // 256
 constexpr int kBins = 2 * kMagBins;                     // 512
 constexpr int kCandCap = 4096;         // boundary-bin candidates resolved in LDS
+constexpr int kSweepEntries = 12;      // select + gather kernel: candidate entries per thread and sweep (Geom::cand_T is a multiple)
+constexpr int kMinListHead = 24;       // smallest Geom::cand_T
 constexpr int kPairsPerWG = 64;        // gather: retrieved tokens per workgroup (16 per wavefront)
 
 // ---- launch geometry + workspace layout -------------------------------------------
@@ -53,6 +55,7 @@ struct Geom {
   int n_tiles;           // gather: ceil(max_K / kPairsPerWG) retrieved-token tiles per query head; one partial each
   int sg_split;          // filtered pipeline: workgroups per query head of the fused select + gather kernel (0 if it cannot run);
                          // that pipeline's launchers get a Geom whose n_tiles is this number
+  int sg_threads;        // its workgroup size: 1024 or 512
   int n_atiles;          // gather: ceil((n_sink + n_tail + max_gen) / 64) tiles of exact anchors + generated tokens per query head (>= 1)
   int build_chunk, n_build_chunks;   // summary_build: mid tokens per workgroup
   int part_stride;       // floats per partial: 2*d + 4
@@ -97,7 +100,7 @@ struct Geom {
 };
 
 // Fills g for the given bounds; returns TKPHI_OK or the reason the config is unsupported.
-tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g);
+tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t scratch_limit = 0);
 void set_error(const char* fmt, ...);
 
 // Optional per-kernel timing: while g_kernel_timer is set (by tkphi_decode_stage_times, on

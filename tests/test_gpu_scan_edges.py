@@ -25,3 +25,35 @@ def test_score_groups_at_every_end(shape, chunk, interleave):
     for i, (P, k) in enumerate(zip(layers, ks)):
         PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
+
+@pytest.mark.parametrize("shape,n_mid,k,select_test", [
+    ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # a hot stretch overflows the compact heads of its lists: several sweeps
+    ("l3b_128k", 13000, 400, 2), ("l1b_32k", 14000, 1500, 2),     # every token a candidate, more than the packed array: boundary bin first
+    ("l1b_32k", 14000, 13500, 2),                                 # a budget beyond the packed array: every phase from the lists
+    ("l3b_128k", 13000, 900, 1)])                                 # nothing passes the bound: rescan, then as above
+def test_candidate_packing(shape, n_mid, k, select_test):
+    """The select kernel's ways of bringing the candidates of a head together, where neighbouring tokens score alike (rows
+    [2000, 2400) lean towards a query of their group, so their lists hold far more than the expected share).  One problem
+    (several workgroups per head share the packed array) and a batch of three (one each), against the oracle."""
+    import numpy as np
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    layers = []
+    for i, m in enumerate((n_mid, n_mid // 2 + 5, 700)):
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i)
+        if m > 2400:
+            K, q = I.bf16_bits_to_f32(P["K"]), I.bf16_bits_to_f32(P["q"])
+            for h in range(w.n_kv_heads):
+                lean = q[h * w.group + h % w.group]
+                K[h, 2000:2400] = 0.6 * K[h, 2000:2400] + np.float32(0.35) * lean
+            P["K"] = I.f32_to_bf16_bits(K)
+        layers.append(P)
+    ks = [k, max(1, k // 3), min(k, 650) // 7]
+    for n in (1, 3):
+        b = H.Batch(H.config_of(w, tuning={"select_mode": 2, "select_test": select_test}), layers[:n], ks[:n], debug=True)
+        b.build()
+        b.decode()
+        assert b.status() & ~2 == 0      # (the residual clamp may fire where nearly every mid token is retrieved)
+        for i in range(n):
+            PU.check_layer(w, layers[i], ks[i], b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
