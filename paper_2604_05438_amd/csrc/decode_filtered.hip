@@ -428,6 +428,44 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
   }
 }
 
+// The front end of short contexts (Geom::direct) in one launch: grid (G (1 + n_atiles) + n_scan_chunks, Hkv, n_problems), 256
+// threads; first the phi and anchor jobs (as in decode_side_kernel), then the score chunks, which store every score: the
+// select kernel takes the exact threshold from all of them, and the sample job, a launch that nothing could overlap with
+// (7-9 us), is not needed.
+template <int D, int TPI>
+__global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
+  __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
+  const int n_side = g.G * (1 + g.n_atiles);
+  const int x = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
+  if (x == 0 && h == 0 && p == 0) write_device_status(g, probs, ws, true);
+  const tkphi_problem pr = probs[p];
+  if (pr.L < 1 || pr.L > g.max_L) return;
+  char* blk = problem_block(g, ws, p);
+  if (x < n_side) {
+    if (x < g.G) {
+      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
+      side_phi(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+    } else {
+      const int j = x - g.G;
+      side_anchor(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+    }
+    return;
+  }
+  const int n = mid_size(pr.L, g.n_sink, g.n_tail);
+  const int chunk = x - n_side, n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
+  if (chunk >= n_chunks) return;
+  ScoreFrag bq[D / 32];
+  load_query_frags<D>(g, pr, h, bq);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  scan_wave_slot<D, TPI, TPI / 4, 2, false, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, -1, false, (lds_u32x2) nullptr);
+}
+
+void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
+  dim3 grid(g.G * (1 + g.n_atiles) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
+  if (g.d == 128) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4>), grid, dim3(kThreads), 0, s, g, probs, ws);
+  else TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<64, 8>), grid, dim3(kThreads), 0, s, g, probs, ws);
+}
+
 void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   dim3 grid(1 + g.G * (1 + g.n_atiles), g.Hkv, g.n_problems);
   // <= 56 KB at G = 8, plus 68 KB (d = 128) / 36 KB (d = 64) of staging strips

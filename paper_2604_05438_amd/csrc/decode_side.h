@@ -28,6 +28,18 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
 #pragma unroll
   for (int e = 0; e < 8; ++e) nrm = fmaf(qx[e], qx[e], nrm);
   for (int o = LPR >> 1; o >= 1; o >>= 1) nrm += __shfl_xor(nrm, o);
+  // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels; its rows of S are requested first
+  // (they depend on nothing: one round trip for S and Wq together instead of two or three in a row)
+  const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
+  const int jg = tid / QPR, c4 = tid % QPR;
+  const int per = (dphi + NG - 1) / NG, sj0 = jg * per, sj1 = min(dphi, sj0 + per);
+  const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
+  constexpr int MAXS = 16;                            // rows of S held at once (all of them for d_phi = d)
+  u32x4 sv[MAXS];
+#pragma unroll
+  for (int k = 0; k < MAXS; ++k)
+    if (k < per) sv[k] = gload128(S + (size_t)min(sj0 + k, dphi - 1) * d + c4 * 4);
+  const float uj = pr.u[(size_t)h * dphi + min(tid, dphi - 1)];
   float* phiq = (float*)(blk + g.off_phiq) + (size_t)gq * dphi;
   constexpr int MAXP = 8;
   for (int j0 = 0; j0 < dphi; j0 += rows_pp * MAXP) {
@@ -58,20 +70,16 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
     }
   }
   __syncthreads();
-  // S^T phi_q: thread (jg, c4) takes the features of group jg for 4 value channels, 8 rows of S in flight
-  const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
-  const int jg = tid / QPR, c4 = tid % QPR;
-  const int per = (dphi + NG - 1) / NG, j0 = jg * per, j1 = min(dphi, j0 + per);
-  const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
   float4 sacc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int jb = j0; jb < j1; jb += 8) {
-    u32x4 sv[8];
+  for (int jb = sj0; jb < sj1; jb += MAXS) {
+    if (jb != sj0) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (jb + k < j1) sv[k] = gload128(S + (size_t)(jb + k) * d + c4 * 4);
+      for (int k = 0; k < MAXS; ++k)
+        if (jb + k < sj1) sv[k] = gload128(S + (size_t)(jb + k) * d + c4 * 4);
+    }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (jb + k < j1) {
+    for (int k = 0; k < MAXS; ++k) {
+      if (jb + k < sj1) {
         const float pj = sh_phiq[jb + k];
         sacc.x = fmaf(pj, __uint_as_float(sv[k].x), sacc.x); sacc.y = fmaf(pj, __uint_as_float(sv[k].y), sacc.y);
         sacc.z = fmaf(pj, __uint_as_float(sv[k].z), sacc.z); sacc.w = fmaf(pj, __uint_as_float(sv[k].w), sacc.w);
@@ -79,7 +87,7 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
     }
   }
   if (act) *(float4*)(red + jg * d + c4 * 4) = sacc;  // NG d = 1024 floats
-  for (int j = tid; j < dphi && act; j += kThreads) pu[j] = sh_phiq[j] * pr.u[(size_t)h * dphi + j];
+  if (tid < dphi) pu[tid] = sh_phiq[tid] * uj;        // (d_phi <= kMaxDim = the threads)
   __syncthreads();
   if (tid < d) {
     float a = 0.f;

@@ -55,7 +55,8 @@ __device__ __forceinline__ size_t cand_region(const Geom& g, int gq, int chunk, 
 // is contracted (the rescan, which must not cost the kernel around it registers, runs one tile at a time); STREAM: non-temporal key loads
 // STRIP: `strip` is used (a template parameter, and address spaces spelled out on every pointer stored through: a store that
 // might go to LDS or to memory becomes a flat store, after which the compiler waits for every load in flight)
-template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP>
+// DIRECT: no bound and no lists; every score goes to the head's row of Geom::off_scores
+template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP, bool DIRECT = false>
 __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks,
                                                int chunk, int wslot, const ScoreFrag (&bq)[D / 32], uint32_t edge_r,
                                                int only_gl, bool rescan, lds_u32x2 strip) {
@@ -68,6 +69,7 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
   const glb_u32x2 list = (glb_u32x2)(blk + (rescan ? g.off_resf : g.off_candf)) + cand_region(g, gq, chunk, wslot);
   const glb_u32x2 head = (glb_u32x2)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)g.cand_T;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
+  const glb_f32 score_row = (glb_f32)(blk + g.off_scores) + (size_t)gq * g.mid_stride;   // (DIRECT)
   const uint64_t col_lanes = 0x0001000100010001ull << r;     // the four lanes of this column
   const uint64_t lanes_below = (1ull << lane) - 1ull;
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
@@ -98,6 +100,24 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
       acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][j].v, bq[j].v, acc[t], 0, 0, 0);
+    }
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int t = 0; t < SUB; ++t) {
+        const int tok = base + t * 16 + 4 * kg;
+        if (col_live && tok < n) {
+          uint32_t e[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float s = fmaf(acc[t][i], scale, 0.0f);        // + 0.0f: -0 -> +0, equal scores get equal keys
+            e[i] = __float_as_uint(s);
+            if (export_row && tok + i < n) export_row[tok + i] = s;
+          }
+          typedef __attribute__((address_space(1))) u32x4* glb_u32x4;
+          *(glb_u32x4)(score_row + tok) = (u32x4){e[0], e[1], e[2], e[3]};       // (the row is padded to whole groups of 64)
+        }
+      }
+      return;
     }
 #pragma unroll
     for (int t = 0; t < SUB; ++t) {
@@ -157,6 +177,7 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
       for (int i = lane; i < c; i += 64) hd[i] = strip[gl * T + i];
     }
   }
+  if constexpr (DIRECT) return;
   if (col_live && kg == 0)
     ((uint32_t*)(blk + (rescan ? g.off_rescount : g.off_ccount)))[((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot] = (uint32_t)min(cnt, cap);
 }

@@ -15,12 +15,14 @@
 //   * histogram of a fine monotone binning of the score keys -> boundary bin b* (tokens in higher bins
 //     are retrieved); the candidates in b* are ranked by counting (or, beyond kBCap of them, by radix
 //     passes over the sweeps) -> the K-th best composite (score key, lower index first), `thr`
-//   * fewer than K candidates (the sampled bound was too high: a ~1e-5 event per head by design, and what
+//   * fewer than K candidates (the sampled bound was too high: a ~1e-6 event per head by design, and what
 //     tkphi_tuning::select_test = 1 forces): the workgroup first rescans its head's keys with no bound,
 //     which makes every mid token a candidate
-// Then workgroup `part` takes the lists [part, part + 1) n_lists / split: their winners (composite >=
-// thr), in list order, are written to the head's retrieved list at the offset given by the winners in
-// earlier lists, and gathered 256 or 512 at a time (16-token tiles, one or two per wavefront):
+// Short contexts (Geom::direct) come without a bound and without lists: the score pass stored a row of scores per head, which
+// is loaded whole and packed as it is.
+// Then workgroup `part` takes an equal share of the packed candidates (of the lists, where they are too many to pack): its
+// winners (composite >= thr) go to the head's retrieved list, in order, behind those of the shares before
+// it, and are gathered 256 or 512 at a time (16-token tiles, one or two per wavefront):
 //     m_loc = max s_i,  Z_loc = sum exp(s_i - m_loc),  nu_loc = sum exp(s_i - m_loc) v_i     (eq. (exact_terms))
 //     zsum = sum z_i,  zv = sum z_i v_i,  z_i = phi_q . phi_k(k_i) recomputed                (eq. (subtraction))
 // into one partial per workgroup, [m, Z, zsum, count, nu[d], zv[d]], which the merge kernel combines in
@@ -39,8 +41,6 @@ constexpr int kSweepLoads = kSweepEntries / 2;
 // d = 64 (one round for most heads of a batch of short sequences); at d = 128 the second tile's rows do not fit
 // the registers
 template <int D, int NTHR> constexpr int kBatchOf = (D == 64 && NTHR == 1024) ? 512 : 256;
-// candidates of a head that the select phase packs into LDS (what the staged Wk leaves room for; 512 threads: two workgroups per CU)
-template <int D, int NTHR> constexpr int kDenseOf = NTHR == 512 ? 4096 : D == 64 ? 12288 : 10240;
 // winners of a workgroup kept in LDS (the rest are re-read from the retrieved list)
 template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 
@@ -57,7 +57,8 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
 }
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
-template <int D, int TPI, int NTHR>
+// DIRECT: Geom::direct (a row of scores per head instead of candidate lists)
+template <int D, int TPI, int NTHR, bool DIRECT>
 __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
                                                    int part, int gq, int p) {
   constexpr int KS = D / 32;
@@ -65,7 +66,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // select phase: histogram (8 KB) + boundary candidates (8 KB); gather phase: reduction scratch of the value sums
   __shared__ __attribute__((aligned(16))) char lds_a[16384];
   __shared__ __attribute__((aligned(16))) char wk_lds[D * WROW];
-  constexpr int kDense = kDenseOf<D, NTHR>, kWinLds = kWinLdsOf<NTHR>, NWV = NTHR / 64;
+  constexpr int kDense = packed_candidates(D, NTHR), kWinLds = kWinLdsOf<NTHR>, NWV = NTHR / 64;
   __shared__ uint2 dense[kDense];                   // the candidates of the head, packed (select phase)
   __shared__ int w_tok[kWinLds];
   __shared__ float w_s[kWinLds];
@@ -97,8 +98,13 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // ---- first sweep, speculatively: addresses depend on the launch geometry only --------------------------
   u32x4 e0[kSweepLoads];
   uint32_t c0 = 0;
-  const uint32_t edge0 = ((const uint32_t*)(blk + g.off_thr))[gq];   // the bound the score pass pruned this head with
-  {
+  const uint32_t edge0 = DIRECT ? 0u : ((const uint32_t*)(blk + g.off_thr))[gq];   // the bound the score pass pruned this head with
+  if constexpr (DIRECT) {                         // the head's row of scores, 4 tokens per load
+    const float* row = (const float*)(blk + g.off_scores) + (size_t)gq * g.mid_stride;
+#pragma unroll
+    for (int k = 0; k < kSweepEntries / 4; ++k)
+      if (4 * (tid + k * NTHR) < g.mid_stride) e0[k] = gload128(row + 4 * (tid + k * NTHR));
+  } else {
     const int s = kSweepEntries * tid, list = s / T;
     if (list < n_reg_max) {
       c0 = ccount[list];
@@ -145,7 +151,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // ---- candidate count, overflow depth (and, on a threshold miss, the rescan) ---------------------------
   bool have_e0 = true;
   int n_sweeps = 0;
-  for (int attempt = 0;; ++attempt) {
+  if constexpr (!DIRECT) for (int attempt = 0;; ++attempt) {
     if (tid == 0) { sh_total = 0u; sh_ovp = 0u; }
     __syncthreads();
     uint32_t tot = 0, ovp = 0;
@@ -173,7 +179,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     have_e0 = false;
     __syncthreads();
   }
-  const uint32_t total = sh_total;
+  if (DIRECT) n_sweeps = 1;
+  const uint32_t total = DIRECT ? (uint32_t)n : sh_total;
   TKPHI_PHASE(ws, 11);
   float* partial = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + part) * g.part_stride;
   auto empty_partial = [&]() {
@@ -246,7 +253,19 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   if (packed) {
     int n_cand = 0;
     clear_hist();
-    if (n_sweeps == 1 && have_e0 && min_bin == 0) {  // the usual case, straight from the registers of the speculative sweep
+    if constexpr (DIRECT) {                        // entry i = token i, straight from the registers of the speculative loads
+#pragma unroll
+      for (int k = 0; k < kSweepEntries / 4; ++k) {
+        const uint32_t sc[4] = {e0[k].x, e0[k].y, e0[k].z, e0[k].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int tok = 4 * (tid + k * NTHR) + i;
+          if (tok < n) dense[tok] = make_uint2(sc[i], (uint32_t)tok);
+        }
+      }
+      n_cand = n;
+      lds_barrier();
+    } else if (n_sweeps == 1 && have_e0 && min_bin == 0) {  // the usual case, straight from the registers of the speculative sweep
       const int nv = share_of(0, tid, (int)min(c0, cap_w)).nvalid;
       const int off = sel_scan_incl(nv, sh_scan) - nv;       // (its barriers also publish the cleared histogram)
 #pragma unroll
@@ -679,12 +698,12 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // with its first 256 threads: no separate merge launch.  The counters are cleared by the prep kernel of the same
 // call.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
 // wavefronts of the workgroup that are still running.)
-template <int D, int TPI, int NTHR>
+template <int D, int TPI, int NTHR, bool DIRECT>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
   const int part = blockIdx.x, gq = blockIdx.y, p = blockIdx.z;
-  select_gather_body<D, TPI, NTHR>(g, probs, ws, part, gq, p);
+  select_gather_body<D, TPI, NTHR, DIRECT>(g, probs, ws, part, gq, p);
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
   // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads; the
@@ -706,9 +725,10 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
   dim3 grid(g.sg_split, g.Hq, g.n_problems);       // (Geom::n_tiles of this pipeline: one partial per workgroup)
-  if (g.d == 128) TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<128, 4, 1024>), grid, dim3(1024), 0, s, g, probs, ws, mode);
-  else if (g.sg_threads == 512) TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<64, 8, 512>), grid, dim3(512), 0, s, g, probs, ws, mode);
-  else TKPHI_LAUNCH(ST_SELECT, (select_gather_kernel<64, 8, 1024>), grid, dim3(1024), 0, s, g, probs, ws, mode);
+  const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SELECT, fn, grid, dim3(threads), 0, s, g, probs, ws, mode); };
+  if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 4, 1024, true>, 1024); else launch(select_gather_kernel<128, 4, 1024, false>, 1024); }
+  else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 8, 512, true>, 512); else launch(select_gather_kernel<64, 8, 512, false>, 512); }
+  else { if (g.direct) launch(select_gather_kernel<64, 8, 1024, true>, 1024); else launch(select_gather_kernel<64, 8, 1024, false>, 1024); }
 }
 
 }  // namespace tkphi

@@ -25,6 +25,8 @@ constexpr int kMagBins = (kExpHi - kExpLo + 1) * 16;   // 256
 constexpr int kBins = 2 * kMagBins;                     // 512
 constexpr int kCandCap = 4096;         // boundary-bin candidates resolved in LDS
 constexpr int kSweepEntries = 12;      // select + gather kernel: candidate entries per thread and sweep (Geom::cand_T is a multiple)
+// candidates of a head that kernel packs into LDS: what the staged Wk leaves room for (512 threads: two workgroups per CU)
+constexpr int packed_candidates(int d, int threads) { return threads == 512 ? 4096 : d == 64 ? 12288 : 10240; }
 constexpr int kMinListHead = 24;       // smallest Geom::cand_T
 constexpr int kPairsPerWG = 64;        // gather: retrieved tokens per workgroup (16 per wavefront)
 
@@ -48,6 +50,7 @@ struct Geom {
                          // (all workgroups sweep the key cache together); 0: one contiguous range
   int filtered;          // 1: decode may run the filtered pipeline (prep, score_filtered, select_gather, merge):
                          // bf16 matrix-core shapes, exp-affine maps, budgets well below the mid-region size
+  int direct;            // 1: filtered pipeline for short contexts: all scores stored (off_scores), no bound, no prep launch
   int cand_T;            // filtered pipeline: entries of a candidate list kept in the compact array (multiple of 12)
   int head_strip;        // 1: the score pass collects the compact list heads in LDS (4 G cand_T entries fit 32 KB)
   int stream_keys;       // 1: the filtered score pass reads the keys with non-temporal loads
@@ -137,6 +140,7 @@ constexpr int kMaxScanChunks = 2048;   // chunk offsets are scanned in LDS by `p
 void launch_score_mid(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);              // filtered pipeline
+void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);      // filtered pipeline, Geom::direct
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);  // includes the merge
 void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);

@@ -57,3 +57,32 @@ def test_candidate_packing(shape, n_mid, k, select_test):
         assert b.status() & ~2 == 0      # (the residual clamp may fire where nearly every mid token is retrieved)
         for i in range(n):
             PU.check_layer(w, layers[i], ks[i], b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
+@pytest.mark.parametrize("shape,max_mid", [("l1b_32k", 12288), ("l1b_32k", 12289), ("l3b_128k", 10240), ("l3b_128k", 10241), ("l1b_32k", 4096)])
+@pytest.mark.parametrize("n_problems", [1, 2, 18])
+def test_short_contexts(shape, max_mid, n_problems):
+    """Contexts whose scores the select kernel takes as a whole (no sampled bound, one launch less): the largest mid-region
+    of that path and one token more, one problem, two, and a batch whose heads take the 512-thread select (limit 4096); lengths
+    down to one token, budgets from one token to the largest of the filtered pipeline, generated tokens, ties."""
+    import numpy as np
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    max_gen = 70
+    mids = ([max_mid, 1, 63, 64, 65, 255, 257, 511, 513, 700, 1023, 1500] * 2)[:n_problems]
+    ks = [max(1, m // (12 if i % 2 == 0 else 90)) for i, m in enumerate(mids)]
+    layers = []
+    for i, m in enumerate(mids):
+        gen = (i * 37 + 3) % (max_gen + 1)
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + m + gen, seq=i)
+        P["L"], P["n_gen"] = w.n_sink + w.n_tail + m, gen
+        if i == 0:                       # equal rows: ties across the whole region, taken by lower index
+            P["K"][:, 100:900] = P["K"][:, 100:101]
+        layers.append(P)
+    b = H.Batch(H.config_of(w, max_gen=max_gen), layers, ks, debug=True)
+    b.build()
+    b.decode()
+    assert b.status() & ~2 == 0          # (the residual clamp may fire where nearly every mid token is retrieved)
+    for i, (P, k) in enumerate(zip(layers, ks)):
+        PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
