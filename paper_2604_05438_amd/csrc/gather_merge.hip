@@ -257,20 +257,21 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
 
 // ------------------------------------------------------------------------------------
 // gather, generic (any storage type, fp32 arithmetic): same grid.  The key rows of the tile's
-// (at most 64) tokens are staged in LDS as fp32; thread (token t = tid % 64, group fg = tid / 64)
-// evaluates the features j = fg, fg + 4, ... of token t (Wk rows are read with 16-byte loads
-// that all 64 lanes of a wavefront share), so the 64 tokens advance together.
+// (at most 64) tokens are staged in LDS as fp32; wavefront w evaluates the features of its 16 tokens with
+// v_mfma_f32_16x16x4_f32, the arithmetic of the fp32 summary build (the inner indices of step (jj, e) are the channels
+// 16 jj + 4 kg + e), Wk from global memory with the next feature tile's rows on their way.  Bound by latency: with a
+// thread per (token, every fourth feature) on the vector ALU, one Wk row after the other, the kernel took 16 us for 40
+// tokens at d = d_phi = 64; this one 10 us.
 // ------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                           char* __restrict__ ws) {
   constexpr int EPL = Elem<T>::per16;
-  constexpr int KFS = 128 + 1;                     // padded row stride (d <= 128): conflict-free column reads
-  __shared__ float kf[kPairsPerWG * KFS];
+  constexpr int KFS = 128 + 4;                     // padded row stride (d <= 128): conflict-free 16-byte reads
+  __shared__ __attribute__((aligned(16))) float kf[kPairsPerWG * KFS];
   __shared__ float red[2 * kThreads * 8];
   __shared__ int p_tok[kPairsPerWG];
   __shared__ float p_s[kPairsPerWG], p_w[kPairsPerWG], p_z[kPairsPerWG];
-  __shared__ float z_part[4][kPairsPerWG];
   __shared__ float acc_part[2 * 128 + 4];
   __shared__ float sh_m;
   const int tile = blockIdx.x, gq = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
@@ -314,32 +315,78 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
     for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if (tid == 0) sh_m = m;
   }
-  {
-    // z_t = phi_q . phi_k(k_t): thread (t, fg) sums its features in ascending order
-    const int t = tid % kPairsPerWG, fg = tid / kPairsPerWG;
-    const float* kt = kf + t * KFS;
-    float nrm = 0.f;
-    for (int c = 0; c < d; ++c) nrm = fmaf(kt[c], kt[c], nrm);
-    float z = 0.f;
-    for (int j = fg; j < dphi; j += kThreads / kPairsPerWG) {
-      const char* wrow = (const char*)pr.Wk + ((int64_t)h * dphi + j) * d * sizeof(T);
-      float dot = 0.f;
-      for (int c0 = 0; c0 < d; c0 += EPL) {
-        const u32x4 wv4 = gload128(wrow + c0 * sizeof(T));
-        float wx[EPL];
-        Elem<T>::unpack(make_uint4(wv4.x, wv4.y, wv4.z, wv4.w), wx);
+  // z_t = phi_q . phi_k(k_t) of this wavefront's 16 tokens
+  const int lane = tid & 63, wv = tid >> 6, r = lane & 15, kg = lane >> 4;
+  if (wv * 16 < cnt) {
+    typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int CTM = 8;                         // 16-channel steps of a row at d = 128
+    const int CT = d / 16, NT = dphi / 16;
+    // lane (r, kg): feature 16 nt + r, channels 16 jj + 4 kg ..
+    auto load_w = [&](int nt, floatx4 (&w)[CTM], float* bias, float* pq) {
+      const int j = min(nt, NT - 1) * 16 + r;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) dot = fmaf(wx[e], kt[c0 + e], dot);
+      for (int jj = 0; jj < CTM; ++jj) {
+        if (jj >= CT) break;                       // (uniform)
+        const char* src = (const char*)pr.Wk + (((int64_t)h * dphi + j) * d + jj * 16 + kg * 4) * sizeof(T);
+        if (sizeof(T) == 4) {
+          const u32x4 t = gload128(src);
+          w[jj] = (floatx4){__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)};
+        } else {
+          const u32x2 t = *(const __attribute__((address_space(1))) u32x2*)src;
+          w[jj] = (floatx4){__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u)};
+        }
       }
-      z = fmaf(expf(g.a * dot - g.c * nrm + pr.bk[(int64_t)h * dphi + j]), phiq[j], z);
+      *bias = pr.bk[(int64_t)h * dphi + j];
+      *pq = phiq[j];
+    };
+    floatx4 a[CTM], w[2][CTM];
+    float bias[2], pq[2];
+    load_w(0, w[0], &bias[0], &pq[0]);
+    float nrm = 0.f;
+#pragma unroll
+    for (int jj = 0; jj < CTM; ++jj) {
+      if (jj >= CT) break;
+      a[jj] = *(const floatx4*)(kf + (wv * 16 + r) * KFS + jj * 16 + kg * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) nrm = fmaf(a[jj][e], a[jj][e], nrm);
     }
-    z_part[fg][t] = z;
+    nrm += __shfl_xor(nrm, 16);
+    nrm += __shfl_xor(nrm, 32);                    // |k|^2 of token r
+    float cn[4], z[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { cn[i] = g.c * __shfl(nrm, 4 * kg + i); z[i] = 0.f; }
+    for (int nt0 = 0; nt0 < NT; nt0 += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int nt = nt0 + u;
+        load_w(nt + 1, w[u ^ 1], &bias[u ^ 1], &pq[u ^ 1]);
+        if (nt >= NT) break;
+        floatx4 acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int jj = 0; jj < CTM; ++jj) {
+          if (jj >= CT) break;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[jj][e], w[u][jj][e], acc[e], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float dot = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+          z[i] = fmaf(expf(g.a * dot - cn[i] + bias[u]), pq[u], z[i]);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int o = 8; o >= 1; o >>= 1) z[i] += __shfl_xor(z[i], o);
+      if (r == 0) p_z[wv * 16 + 4 * kg + i] = wv * 16 + 4 * kg + i < cnt ? z[i] : 0.f;
+    }
   }
   __syncthreads();
-  if (tid < kPairsPerWG) {
-    p_z[tid] = tid < cnt ? (z_part[0][tid] + z_part[1][tid]) + (z_part[2][tid] + z_part[3][tid]) : 0.f;
-    p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
-  }
+  if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
   weighted_value_sums<T>(g, pr, head_off, p_tok, p_w, p_z, cnt, red, acc_part, true);

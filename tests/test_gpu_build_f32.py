@@ -36,3 +36,22 @@ def test_build_f32_edges(dtype, d, dphi, chunk, cache):
                 F = orc.phi(O["K"][h, M], O["Wk"][h], O["bk"][h], w.phi_in_scale, w.phi_norm_coef)
                 rel = np.abs(b.result(i, "phi_cache")[h].astype(np.float64) - F) / F
                 assert rel.max() <= 2e-5, f"mid {mids[i]} head {h}: feature rel err {rel.max():.3e}"
+
+
+@pytest.mark.parametrize("dtype,d,dphi", [("f32", 64, 64), ("f32", 128, 16), ("f32", 128, 256), ("bf16", 64, 80), ("bf16", 128, 48)])
+def test_gather_f32_edges(dtype, d, dphi):
+    """Decode on the fp32-arithmetic kernels: retrieved counts around the 16-token rows and 64-token tiles of the gather, feature
+    widths of an odd and an even number of 16-feature tiles, mid-regions that make the score pass run with 256 and (few
+    workgroups) 1024 threads.  The bars of parity_utils: scores 1e-5, outputs 2e-3, residual terms 1e-4."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype=dtype, n_q_heads=6, n_kv_heads=2, d_head=d, d_phi=dphi, seed=92)
+    ks = [1, 15, 16, 17, 63, 64, 65, 129]
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + 300 + 211 * i, seq=i) for i in range(len(ks))]
+    for sel in (slice(0, 8), slice(6, 7)):
+        b = H.Batch(H.config_of(w), layers[sel], ks[sel], debug=True)
+        b.build()
+        b.decode()
+        assert b.status() == 0
+        for i, (P, k) in enumerate(zip(layers[sel], ks[sel])):
+            PU.check_layer(w, P, k, b, i, sum_tol=2e-5)
