@@ -37,7 +37,10 @@ static int list_head(int scan_chunk, int64_t K, int64_t n, int sweep, int64_t n_
   return std::max(kMinListHead, std::min(fit, (int)align_up((size_t)want, kSweepEntries)));
 }
 
-// compact: the chunks and candidate lists of the filtered pipeline as small as they get (callers with a scratch limit)
+// compact: the geometry for scratch memory that the faster one does not fit in.  Its needs grow with max_L, max_K and the
+// number of problems (one chunk rule for all lengths, the filtered pipeline with its two full-length lists per head for budgets
+// up to 1/64 only), so a workspace sized for larger bounds serves the smaller calls (but for a budget of at most 1/64 where the
+// workspace was sized for one beyond 1/12).
 static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, bool compact, Geom* g) {
   if (!cfg) { set_error("cfg is null"); return TKPHI_EINVAL; }
   if (n_problems < 0 || max_L < 1 || max_K < 0) {
@@ -121,8 +124,9 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // measured faster than the spill pipeline in (3B layer at 128K, 1 / 2 / 4 / 7 %: 84 / 93 / 110 / 127 against 98 / 108 /
   // 122 / 143 us; 1B layer at 32K 38 / 39 / 41 / 44 against 42 / 43 / 45 / 48; 16 sequences of 4K to 16K at d = 64, 4 %: 94
   // against 114)
+  const int min_inverse_budget = compact ? 64 : 12;
   g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
-                 (tn.select_mode == 2 || (int64_t)max_K * 12 <= g->max_mid)) ? 1 : 0;
+                 (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
   // filtered pipeline: the workgroups that share a query head in the fused select + gather kernel, one partial each: about one
   // workgroup per CU for a single layer, one per head in big batches; batches of short sequences at d = 64 (one workgroup
   // per head, at least two heads per CU) take 512-thread workgroups, two per CU, so that one head's memory round trips
@@ -189,7 +193,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // least 2048 tokens so that the last, partly filled round of workgroups stays a small share.  The fp32-arithmetic
   // kernel spends 32 times the bf16 one's time on a token: there a workgroup takes as little as one tile of 64
   const bool f32_build = !g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE;
-  const int64_t bc_small = std::clamp<int64_t>(ceil_div(units, 512), f32_build ? 64 : 256, 2048);
+  const int64_t bc_small = std::clamp<int64_t>(ceil_div(units, 512), f32_build && !compact ? 64 : 256, 2048);
   int bc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 2048), bc_small, 1 << 20), 64);
   if (!g->use_mfma) bc = std::min(bc, 4096);    // fp32 FMA chains stay short on the generic kernel
   // Several resident rounds of the matrix-core kernel (512 workgroup slots at d = 128, 1024 at d = 64): among the
@@ -296,10 +300,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   return TKPHI_OK;
 }
 
-// scratch_limit: where a decode's scratch would exceed it (0: none), the compact geometry
-tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t scratch_limit) {
+// have / need: the scratch bytes that the caller has and the member that says what its call takes (null: no limit)
+tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have, size_t Geom::*need) {
   const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, false, g);
-  if (st != TKPHI_OK || scratch_limit == 0 || g->decode_bytes <= scratch_limit) return st;
+  if (st != TKPHI_OK || !need || g->*need <= have) return st;
   return make_geom_as(cfg, n_problems, max_L, max_K, true, g);
 }
 
@@ -332,14 +336,16 @@ extern "C" {
 size_t tkphi_workspace_bytes(const tkphi_config* cfg, int32_t n_problems, int32_t max_L, int32_t max_K) {
   Geom g;
   if (make_geom(cfg, n_problems, max_L, max_K, &g) != TKPHI_OK) return 0;
-  return g.total_bytes;
+  const size_t bytes = g.total_bytes;      // (enough for the compact geometry too, which a call with smaller bounds may fall back to)
+  if (make_geom_as(cfg, n_problems, max_L, max_K, true, &g) != TKPHI_OK) return 0;
+  return std::max(bytes, g.total_bytes);
 }
 
 tkphi_status tkphi_build_summaries(const tkphi_config* cfg, const tkphi_problem* problems,
                                    int32_t n_problems, int32_t max_L, void* workspace,
                                    size_t workspace_bytes, void* hip_stream) {
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, 0, &g);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, 0, &g, workspace_bytes, &Geom::build_bytes);
   if (st != TKPHI_OK) return st;
   st = check_call(problems, n_problems, workspace, workspace_bytes, g, g.build_bytes);   // (the decode scratch depends on max_K)
   if (st != TKPHI_OK) return st;
@@ -437,7 +443,7 @@ tkphi_status tkphi_decode(const tkphi_config* cfg, const tkphi_problem* problems
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes);
   g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
   if (st != TKPHI_OK) return st;
   st = check_call(problems, n_problems, workspace, workspace_bytes, g, g.decode_bytes);
@@ -486,7 +492,7 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg, const tkphi_problem* p
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, TKPHI_STATIC_SCRATCH_BYTES);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, TKPHI_STATIC_SCRATCH_BYTES, &Geom::decode_bytes);
   if (st != TKPHI_OK) return st;
   g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
   if (g.phi_kind == TKPHI_PHI_MLP) {      // that path creates a stream and events on first use
@@ -521,7 +527,7 @@ tkphi_status tkphi_decode_stage_times(const tkphi_config* cfg, const tkphi_probl
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes);
   g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
   if (st != TKPHI_OK) return st;
   st = check_call(problems, n_problems, workspace, workspace_bytes, g, g.decode_bytes);

@@ -86,3 +86,45 @@ def test_short_contexts(shape, max_mid, n_problems):
     assert b.status() & ~2 == 0          # (the residual clamp may fire where nearly every mid token is retrieved)
     for i, (P, k) in enumerate(zip(layers, ks)):
         PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
+@pytest.mark.parametrize("shape,big_L,big_K,calls", [
+    # shorter sequences and smaller budgets than the workspace was sized for: other chunks, one-launch selection, other pipeline
+    ("l3b_128k", 65536, 655, [(50000, 500), (50000, 3000), (12000, 120), (10308, 100), (300, 20)]),
+    ("l1b_32k", 65536, 1310, [(65536, 1000), (50000, 1000), (40000, 320), (13000, 1000), (12356, 123), (700, 600)]),
+    ("l1b_32k", 40000, 20000, [(40000, 700), (40000, 3000), (39000, 3900)])])
+@pytest.mark.parametrize("exact", [False, True])
+def test_workspace_sized_for_larger_bounds(shape, big_L, big_K, calls, exact):
+    """A workspace sized for a call's largest bounds serves the smaller ones, with its own size (exact) or more than that, and
+    an index set and output that match the oracle; what the call itself reports as needed is enough as well."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    for L, k in calls:
+        P = I.make_layer(w, L=L, seq=0)
+        k = min(k, big_K)
+        b = H.Batch(H.config_of(w), [P], [k], debug=True)
+        if not exact:
+            b.ws_bytes = B.tkphi_workspace_bytes(b.cfg, 1, big_L, big_K)
+            b.ws = B.alloc_workspace(b.ws_bytes, "cuda")
+        b.build()
+        b.decode()
+        assert b.status() & ~2 == 0
+        PU.check_layer(w, P, k, b, 0, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
+@pytest.mark.parametrize("shape,L,k", [("l1b_32k", 60000, 1200), ("l1b_32k", 60000, 4500), ("l3b_128k", 50000, 1500), ("l1b_32k", 30000, 300)])
+def test_static_scratch_budgets(shape, L, k):
+    """Budgets of 2 to 7.5 % whose faster pipeline needs more than the 32 MiB of static scratch run with the smaller one."""
+    import torch
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    P = I.make_layer(w, L=L, seq=0)
+    b = H.Batch(H.config_of(w), [P], [k], debug=True)
+    b.build()
+    B.tkphi_decode_static(b.cfg, b.table.data_ptr(), 1, b.max_L, b.max_K, 0, B.current_stream_ptr())
+    torch.cuda.synchronize()
+    PU.check_layer(w, P, k, b, 0, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
