@@ -130,7 +130,7 @@ typedef struct tkphi_mlp {
 typedef struct tkphi_tuning {
   int32_t force_generic;  /* 1: run the generic fp32-arithmetic kernels where the matrix-core ones apply  */
   int32_t scan_chunk;     /* score_mid: mid tokens per workgroup (rounded up to the kernel's unit of
-                             256 / 512 rows, at most 32768); 0 = about 1024 workgroups per call           */
+                             256 / 512 rows, at most 32768); 0 = by the shape and the pipeline            */
   int32_t interleave;     /* score_mid chunk-to-row mapping: 1 = chunk c takes the units c, c + n_chunks,
                              ..., 2 = one contiguous range per chunk; 0 = by the number of chunks         */
   int32_t build_chunk;    /* summary build: mid tokens per workgroup (multiple of 64); 0 = auto          */
@@ -139,7 +139,7 @@ typedef struct tkphi_tuning {
                              1 = layer-wise launches per token block (residual + output fused),
                              2 = all four layers as separate launches                                    */
   int32_t select_mode;    /* decode pipeline of the bf16 matrix-core shapes: 0 = by the bounds (filtered where it
-                             measured faster: max_K at most 1/64 of the largest mid-region),
+                             measured faster: max_K at most 1/12 of the largest mid-region),
                              1 = spill (score_mid writes
                              every score and chunk histograms; plan / emit / resolve select from them),
                              2 = filtered (a sampled lower bound of the K-th score prunes what the score pass
@@ -252,7 +252,8 @@ typedef struct tkphi_problem {
 } tkphi_problem;
 
 /* Bytes of DEVICE workspace tkphi_build_summaries / tkphi_decode need for the given
- * launch bounds (the larger of the two).  Returns 0 if the config is invalid.
+ * launch bounds (the larger of the two; a decode that is handed less may still run, in a smaller and slower
+ * launch geometry).  Returns 0 if the config is invalid.
  * The workspace must be 256-byte aligned.  Its contents need not be preserved between
  * calls and need not be initialised.  Two calls that overlap in time (different
  * streams) must not share a workspace. */
@@ -291,11 +292,12 @@ tkphi_status tkphi_decode(const tkphi_config* cfg /*HOST*/,
 
 /* tkphi_decode for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments (minus
- * the workspace), same validation, same kernels and bit-identical results; the scratch memory is a
+ * the workspace), same validation and the same kernels, with bit-identical results where the scratch of
+ * tkphi_decode's launch geometry fits the array too; a call that only fits with smaller candidate lists
+ * or score chunks takes those (same retrieved sets, sums in another order).  The scratch memory is a
  * static device array of TKPHI_STATIC_SCRATCH_BYTES inside the library, of which every GPU the
  * library runs on holds one copy until the process ends.  A request whose decode scratch does not
- * fit (tkphi_workspace_bytes is an upper bound of it; one 128K-token layer of 24 query heads needs
- * about 17 MiB) fails with TKPHI_EWORKSPACE and enqueues nothing; TKPHI_PHI_MLP is refused with
+ * fit (a 128K-token layer of 24 query heads, for one) fails with TKPHI_EWORKSPACE and enqueues nothing; TKPHI_PHI_MLP is refused with
  * TKPHI_EUNSUPPORTED (that path creates a stream on first use).  The call allocates nothing and frees
  * nothing.  The first call on a device resolves the array's address (with that device current: the
  * device of hip_stream must be the current device); a caller that captures calls into a HIP graph makes

@@ -2,12 +2,12 @@
 //
 // The exhaustive Top-K over the mid-region (Sec. "Models, tasks, and protocol") needs every score
 // s_i = q . k_i / sqrt(d_h) once, but only the scores that can still reach the top K have to
-// leave the chip.  Two kernels:
+// leave the chip.  Two kernels (one for short contexts):
 //
 //   decode_prep     one small launch of independent jobs that need no selection:
 //                   * sample: per KV head, the scores of an evenly spaced sample of mid-region rows
 //                     -> per query head a lower bound of the K-th largest score (a bin edge chosen so
-//                     that the sample count above it exceeds its expectation at the K-th score by six
+//                     that the sample count above it exceeds its expectation at the K-th score by five
 //                     standard deviations); the bound only prunes: the select kernel verifies that at
 //                     least K tokens passed and otherwise rescans the head without a bound
 //                   * phi:    phi_q(q) of a query head (App. "Head-wise phi architecture": per query
@@ -18,6 +18,8 @@
 //   score_filtered  the streaming pass over all mid-region keys, each KV head read once for its G
 //                   query heads; a score goes to memory only if its key is >= the head's bound
 //                   (about 2-3 K tokens per head instead of |M|), appended to per-wavefront lists.
+//   score_direct    instead of both where contexts are short (Geom::direct): every score stored, one row per head,
+//                   with the phi and anchor jobs in the same launch.
 #include <algorithm>
 
 #include "decode_side.h"

@@ -94,7 +94,7 @@ struct Geom {
                          //                                       in the order of the retrieved list
   size_t off_part;       // float    [Hq][n_tiles + n_atiles][part_stride]  (retrieved tiles, then anchor tiles)
   size_t off_bpart;      // float    [Hkv][n_build_chunks][dphi*(d+1)]   (build only; aliases the block)
-  size_t off_act;        // float    2 x [Hkv][mlp_block][d_emb]          (MLP build only: activations g, h of a token block)
+  size_t off_act;        // float    2 x [Hkv][mlp_block][d_emb]          (layer-wise MLP build only: activations g, h of a token block)
   size_t off_wpack;      // bf16     [mlp_group][Hkv][Ws | W1 | W2 | Wo]  (MLP maps: a group's key-side weights in MFMA-fragment order)
   size_t off_feat;       // float    [mlp_group][Hkv][max_mid][d_phi]     (MLP build without a feature cache: a group's key features)
   size_t decode_bytes;   // what a decode call alone uses (status word + per-problem blocks)

@@ -128,3 +128,32 @@ def test_static_scratch_budgets(shape, L, k):
     B.tkphi_decode_static(b.cfg, b.table.data_ptr(), 1, b.max_L, b.max_K, 0, B.current_stream_ptr())
     torch.cuda.synchronize()
     PU.check_layer(w, P, k, b, 0, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
+@pytest.mark.parametrize("shape,L,k", [("l3b_128k", 14000, 139), ("l1b_32k", 5000, 49)])
+def test_each_decode_route_replays_from_a_hip_graph(shape, L, k):
+    """The sampled-bound route (three launches) and the short-context one (two), captured and replayed with eager work between."""
+    import numpy as np
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    b = H.Batch(H.config_of(w), [I.make_layer(w, L=L)], [k], debug=True)
+    b.build(); b.decode()
+    torch.cuda.synchronize()
+    eager = {n: b.result(0, n).copy() for n in ("out", "topk_idx")}
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        b.decode()
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            b.decode()
+    torch.cuda.synchronize()
+    for rep in range(3):
+        b.dev[0]["out"].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for n, y in eager.items():
+            assert np.array_equal(b.result(0, n), y), f"replay {rep}: {n} differs from the eager result"
+        b.decode()
+        torch.cuda.synchronize()
