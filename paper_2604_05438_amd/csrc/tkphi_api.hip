@@ -132,6 +132,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // per head, at least two heads per CU) take 512-thread workgroups, two per CU, so that one head's memory round trips
   // hide behind the other's arithmetic
   g->sg_split = g->filtered ? std::clamp(256 / std::max(1, g->Hq * std::max(n_problems, 1)), 1, 16) : 0;
+  const int max_split = g->sg_split;
   g->sg_threads = g->d == 64 && g->sg_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
   const int sweep = g->sg_threads * kSweepEntries;   // candidate slots of a head that kernel reads in one go
   // matrix-core score kernel: 4 wavefronts x 64 (d = 128) or 128 (d = 64) tokens per iteration;
@@ -230,7 +231,8 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->off_candf = p;     // (the two pipelines never run in the same call)
   p = align_up(p + std::max((size_t)g->Hq * g->mid_stride * sizeof(float),
                             g->filtered ? (size_t)g->Hq * g->n_scan_chunks * g->scan_chunk * sizeof(uint2) : (size_t)0), 256);
-  g->cand_T = compact || !g->filtered ? (int)align_up((size_t)std::max(kMinListHead, g->scan_chunk / 4 * 3 / 32), kSweepEntries)
+  // (short contexts have no lists: there the layout is the compact geometry's)
+  g->cand_T = compact || !g->filtered || g->direct ? (int)align_up((size_t)std::max(kMinListHead, g->scan_chunk / 4 * 3 / 32), kSweepEntries)
                                       : list_head(g->scan_chunk, std::min(max_K, g->max_mid), g->max_mid, sweep, g->n_scan_chunks);
   g->head_strip = (size_t)4 * g->G * g->cand_T * sizeof(uint2) <= 32768 ? 1 : 0;
   // Non-temporal key loads leave the candidate lists, phi_q and the problem record in the caches for the select kernel
@@ -259,7 +261,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->sel_feat = cfg->phi_kind == TKPHI_PHI_MLP && !g->cache;
   g->off_selphi = p;  p = align_up(p + (g->sel_feat ? (size_t)g->Hq * std::max(max_K, 1) * g->dphi * sizeof(float) : (size_t)0), 256);
   g->off_part = p;
-  p = align_up(p + (size_t)g->Hq * (std::max(g->n_tiles, g->sg_split) + g->n_atiles) * g->part_stride * sizeof(float), 256);
+  p = align_up(p + (size_t)g->Hq * (std::max(g->n_tiles, max_split) + g->n_atiles) * g->part_stride * sizeof(float), 256);
   g->per_problem = p;
   const size_t decode_total = g->off_problem0 + (size_t)std::max(n_problems, 1) * g->per_problem;
   size_t decode_all = decode_total;
