@@ -73,19 +73,17 @@ __global__ __launch_bounds__(kThreads) void mlp_pack_weights_kernel(Geom g, cons
   size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x;
   if (q >= n_s + 2 * n_1 + n_o) return;
   char* dst = ws + g.off_wpack + ((size_t)slot * g.Hkv + h) * packed_bytes_per_head(g) + q * 16;
-  const char* W;
-  int Kd;
-  if (q < n_s) { W = (const char*)mp.Ws; Kd = g.d; }
-  else if (q < n_s + n_1) { W = (const char*)mp.W1; Kd = E; q -= n_s; }
-  else if (q < n_s + 2 * n_1) { W = (const char*)mp.W2; Kd = E; q -= n_s + n_1; }
-  else { W = (const char*)mp.Wo; Kd = E; q -= n_s + 2 * n_1; }
+  // (the layer says how a matrix is packed; two layers may share one buffer)
+  const bool stem = q < n_s, out = q >= n_s + 2 * n_1;
+  const char* W = (const char*)(stem ? mp.Ws : out ? mp.Wo : q < n_s + n_1 ? mp.W1 : mp.W2);
+  const int Kd = stem ? g.d : E;
+  q -= stem ? 0 : out ? n_s + 2 * n_1 : q < n_s + n_1 ? n_s : n_s + n_1;
   const int lane = (int)(q & 63), r = lane & 15, kg = lane >> 4;
   const size_t blk = q >> 6;
   const int KS = Kd / 32;
-  const bool grouped = W != (const char*)mp.Wo;
-  const int ks = (int)(grouped ? blk / 4 % KS : blk % KS), ct = (int)(grouped ? blk / 4 / KS * 4 + blk % 4 : blk / KS);
+  const int ks = (int)(out ? blk % KS : blk / 4 % KS), ct = (int)(out ? blk / KS : blk / 4 / KS * 4 + blk % 4);
   const char* row = W + ((size_t)(ct * 16 + r) * Kd + ks * 32) * 2;
-  if (chain && W != (const char*)mp.Ws) {
+  if (chain && !stem) {
     const u32x2 a = *(const u32x2*)(row + kg * 8), b = *(const u32x2*)(row + 32 + kg * 8);
     *(u32x4*)dst = (u32x4){a.x, a.y, b.x, b.y};
   } else {

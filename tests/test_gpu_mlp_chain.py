@@ -40,3 +40,33 @@ def test_chain_tile_edges(d, dphi, d_emb, cache):
                 F = fk[h](I.to_f64(P["K"])[h, M])
                 rel = np.abs(b.result(i, "phi_cache")[h].astype(np.float64) - F) / F
                 assert rel.max() <= PU.MLP_FEATURE_EPS, f"mid {mids[i]} head {h}: feature rel err {rel.max():.3e}"
+
+
+@pytest.mark.parametrize("d,dphi,d_emb,mode", [(128, 128, 128, ""), (64, 128, 128, ""), (64, 64, 64, ""), (128, 128, 128, "unfused")])
+def test_tied_weights(d, dphi, d_emb, mode):
+    """Maps whose matrices are one buffer (Ws = W1 = W2 = Wo where the widths agree, else W1 = W2 = Wo): the packed copies of a
+    matrix differ by the layer it serves, so the layer has to decide, not the address.  Against the float64 oracle, bounds
+    as above."""
+    import torch
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l1b_32k"], n_q_heads=4, n_kv_heads=2, d_head=d, d_phi=dphi, seed=613)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 200)
+    P["mlp"] = I.make_mlp_phi(w, layer=0, d_emb=d_emb)
+    tied = [n for n, rows, cols in (("Ws", d_emb, d), ("W2", d_emb, d_emb), ("Wo", dphi, d_emb)) if (rows, cols) == (d_emb, d_emb)]
+    assert "W2" in tied and len(tied) >= 2
+    for side in ("q", "k"):
+        for n in tied:
+            P["mlp"][side][n] = P["mlp"][side]["W1"]
+    b = H.Batch(H.config_of(w, cache_features=True, d_emb=d_emb, tuning={"mlp_mode": B.MLP_MODES[mode]}), [P], [40], debug=True)
+    for side in ("q", "k"):                            # one buffer on the device as well
+        t = b.dev[0][f"mlp_{side}_w"]
+        for n in tied:
+            t[n] = t["W1"]
+        b.dev[0]["mlp_" + side].copy_(B.upload_mlp(t))
+    torch.cuda.synchronize()
+    b.build()
+    b.decode()
+    assert b.status() & ~2 == 0
+    PU.check_layer(w, P, 40, b, 0)
