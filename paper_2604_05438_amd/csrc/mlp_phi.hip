@@ -465,12 +465,20 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) bias[nt] = gload128(b + (wv * NT + nt) * 16 + 4 * kg);
   };
-  auto init_bias = [&]() {
+  // A layer's sum runs from zero and takes the bias once, at its end: in the accumulator from the start, every product added
+  // would round at the size of the bias.
+  auto clear_acc = [&]() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  };
+  auto add_bias = [&]() {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
-        acc[mt][nt] = (floatx4){__uint_as_float(bias[nt].x), __uint_as_float(bias[nt].y), __uint_as_float(bias[nt].z), __uint_as_float(bias[nt].w)};
+        acc[mt][nt] += (floatx4){__uint_as_float(bias[nt].x), __uint_as_float(bias[nt].y), __uint_as_float(bias[nt].z), __uint_as_float(bias[nt].w)};
   };
   // acc += W (planes): steps of 16 tokens x 32 inputs; the plane operands of a step are read while the step before it
   // multiplies.  Lo products before hi products: no MFMA waits for the previous one's sum.
@@ -572,7 +580,7 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
     }
     lds_barrier();                                     // the keys are staged; every wavefront is done with the previous tile's planes
     // ---- stem (bf16 keys: one MFMA per product); 16 tokens are split and stored while the next 16 multiply ----
-    init_bias();
+    clear_acc();
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
@@ -583,6 +591,7 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wst[ks][nt].v, b.v, acc[mt][nt], 0, 0, 0);
       }
     }
+    add_bias();
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
       u32x2 hi[NT], lo[NT];
@@ -601,8 +610,9 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
     lds_barrier();
     // ---- hidden layer ----
     __builtin_amdgcn_sched_barrier(0);
-    init_bias();
+    clear_acc();
     gemm_planes(W1);
+    add_bias();
     __builtin_amdgcn_sched_barrier(0);
     load_w(W2, KSE, 0, wf[0]);
     load_w(W2, KSE, 1, wf[1]);
@@ -610,8 +620,9 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
     replace_planes([&](float x, int, int, int) { return gelu_erf(x); });
     // ---- residual ----
     __builtin_amdgcn_sched_barrier(0);
-    init_bias();
+    clear_acc();
     gemm_planes(W2);
+    add_bias();
     __builtin_amdgcn_sched_barrier(0);
     // output layer: NTO output tiles x 2 token tiles per wavefront, operands 4 K steps ahead
     constexpr int WD = 4;
@@ -624,12 +635,12 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
     replace_planes([&](float x, int mt, int nt, int i) { return fmaf(alpha, x, g0[mt][nt][i]); });
     // ---- output layer ----
     floatx4 acco[2][NTO];
+    u32x4 ob[NTO];
 #pragma unroll
     for (int j = 0; j < NTO; ++j) {
-      const u32x4 b = gload128(bo + min(og * NTO + j, n_otiles - 1) * 16 + 4 * kg);
+      ob[j] = gload128(bo + min(og * NTO + j, n_otiles - 1) * 16 + 4 * kg);
 #pragma unroll
-      for (int m2 = 0; m2 < 2; ++m2)
-        acco[m2][j] = (floatx4){__uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+      for (int m2 = 0; m2 < 2; ++m2) acco[m2][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int ks = 0; ks < KSE; ++ks) {
@@ -661,7 +672,8 @@ void mlp_chain_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __r
         const int row = (mg * 2 + m2) * 16 + r;
         if (row >= cur.rows) continue;
         *(float4*)(cur.feat + (size_t)row * g.dphi + (og * NTO + j) * 16 + 4 * kg) =
-            make_float4(expf(acco[m2][j][0]), expf(acco[m2][j][1]), expf(acco[m2][j][2]), expf(acco[m2][j][3]));
+            make_float4(expf(acco[m2][j][0] + __uint_as_float(ob[j].x)), expf(acco[m2][j][1] + __uint_as_float(ob[j].y)),
+                        expf(acco[m2][j][2] + __uint_as_float(ob[j].z)), expf(acco[m2][j][3] + __uint_as_float(ob[j].w)));
       }
     }
   }

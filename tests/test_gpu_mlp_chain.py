@@ -70,3 +70,29 @@ def test_tied_weights(d, dphi, d_emb, mode):
     b.decode()
     assert b.status() & ~2 == 0
     PU.check_layer(w, P, 40, b, 0)
+
+
+@pytest.mark.parametrize("d,d_emb", [(128, 512), (64, 256), (64, 128)])
+def test_large_output_bias_is_rounded_once(d, d_emb):
+    """Output biases near -60: a sum that has the bias in it from the start rounds every one of its 2 d_emb / 32 steps at the ulp of
+    60 (2^-18), one that takes it at the end rounds once.  The logarithm of a stored feature then carries what it carries
+    with small biases (measured on the same weights), that one rounding (2^-19 / sqrt 3 rms) and the rounding of the
+    bias itself and of exp's argument reduction in the float64 comparison (nothing and 2^-24 relative): 1.2 times the root of
+    the sum of squares is allowed."""
+    from oracle import tkphi_oracle as orc
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l1b_32k"], n_q_heads=4, n_kv_heads=2, d_head=d, d_phi=d, seed=617)
+    rms = []
+    for shift in (0.0, -60.0):
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + 2000)
+        P["mlp"] = I.make_mlp_phi(w, layer=0, d_emb=d_emb)
+        P["mlp"]["k"]["bo"] = (P["mlp"]["k"]["bo"] + np.float32(shift)).astype(np.float32)
+        b = H.Batch(H.config_of(w, cache_features=True, d_emb=d_emb), [P], [20])
+        b.build()
+        _, fk = PU.mlp_feature_fns(P)
+        _, M = orc.partition(int(P["L"]), w.n_sink, w.n_tail)
+        e = [np.log(b.result(0, "phi_cache")[h].astype(np.float64)) - np.log(fk[h](I.to_f64(P["K"])[h, M])) for h in range(w.n_kv_heads)]
+        rms.append(float(np.sqrt(np.mean(np.square(e)))))
+    print("log-feature error, rms:", d, d_emb, rms, flush=True)
+    assert rms[1] <= 1.2 * np.hypot(rms[0], 2.0 ** -19 / np.sqrt(3.0)), rms
