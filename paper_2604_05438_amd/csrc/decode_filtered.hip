@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
   char* blk = problem_block(g, ws, p);
   if (job < g.G) {
     if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + job] = 0u;
-    side_phi(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+    side_phi<0>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
   } else {
     const int j = job - g.G;
     side_anchor(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
 // threads; first the phi and anchor jobs (as in decode_side_kernel), then the score chunks, which store every score: the
 // select kernel takes the exact threshold from all of them, and the sample job, a launch that nothing could overlap with
 // (7-9 us), is not needed.
-template <int D, int TPI>
+template <int D, int TPI, int EARLY>
 __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
   const int n_side = g.G * (1 + g.n_atiles);
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   if (x < n_side) {
     if (x < g.G) {
       if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
-      side_phi(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+      side_phi<EARLY>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
     } else {
       const int j = x - g.G;
       side_anchor(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
@@ -466,8 +466,11 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
 
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   dim3 grid(g.G * (1 + g.n_atiles) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
-  if (g.d == 128) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4>), grid, dim3(kThreads), 0, s, g, probs, ws);
-  else TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<64, 8>), grid, dim3(kThreads), 0, s, g, probs, ws);
+  // (the phi job's rows of S ahead of everything else: 0.3 us off one 3B layer of 4K or 9K tokens, but at 158 registers instead of
+  // 73 the whole launch of 256 problems of 1.5K takes 258 us instead of 224 at d = 128, 154 instead of 128 at d = 64)
+  if (g.d == 128 && g.n_problems == 1) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4, 16>), grid, dim3(kThreads), 0, s, g, probs, ws);
+  else if (g.d == 128) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4, 0>), grid, dim3(kThreads), 0, s, g, probs, ws);
+  else TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<64, 8, 0>), grid, dim3(kThreads), 0, s, g, probs, ws);
 }
 
 void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {

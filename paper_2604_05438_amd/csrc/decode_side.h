@@ -15,6 +15,10 @@ namespace tkphi {
 // ---- phi job: one workgroup per query head ----------------------------------------------------------------
 // phi_q -> workspace; sphi[c] = sum_j phi_q[j] S[h][j][c]; uphi = sum_j phi_q[j] u[h][j].  Sums run in a fixed
 // order.    LDS: sh_phiq, pu [kMaxDim], red [1024]
+// EARLY: rows of S a thread requests before anything else (16: all it takes at d_phi = d = 128; one round trip for S and Wq
+// together, for a launch of few workgroups), 0: none, eight at a time behind phi_q (16 rows ahead cost batches two of three
+// wavefronts: decode_side_kernel over 6400 heads 99 us instead of 59).
+template <int EARLY>
 __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* sh_phiq, float* pu,
                                          float* red) {
   const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
@@ -28,16 +32,15 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
 #pragma unroll
   for (int e = 0; e < 8; ++e) nrm = fmaf(qx[e], qx[e], nrm);
   for (int o = LPR >> 1; o >= 1; o >>= 1) nrm += __shfl_xor(nrm, o);
-  // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels; its rows of S are requested first
-  // (they depend on nothing: one round trip for S and Wq together instead of two or three in a row)
+  // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels
   const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR;
   const int per = (dphi + NG - 1) / NG, sj0 = jg * per, sj1 = min(dphi, sj0 + per);
   const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
-  constexpr int MAXS = 16;                            // rows of S held at once (all of them for d_phi = d)
+  constexpr int MAXS = EARLY ? EARLY : 8;             // rows of S held at once
   u32x4 sv[MAXS];
 #pragma unroll
-  for (int k = 0; k < MAXS; ++k)
+  for (int k = 0; k < EARLY; ++k)
     if (k < per) sv[k] = gload128(S + (size_t)min(sj0 + k, dphi - 1) * d + c4 * 4);
   const float uj = pr.u[(size_t)h * dphi + min(tid, dphi - 1)];
   float* phiq = (float*)(blk + g.off_phiq) + (size_t)gq * dphi;
@@ -72,7 +75,7 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
   __syncthreads();
   float4 sacc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int jb = sj0; jb < sj1; jb += MAXS) {
-    if (jb != sj0) {
+    if (!EARLY || jb != sj0) {
 #pragma unroll
       for (int k = 0; k < MAXS; ++k)
         if (jb + k < sj1) sv[k] = gload128(S + (size_t)(jb + k) * d + c4 * 4);
