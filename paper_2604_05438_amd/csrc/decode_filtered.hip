@@ -389,10 +389,9 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
 // caches, by the latency of a few round trips for short ones.  A wavefront holds two groups of TPI / 4 tiles, one on its way
 // while the other is contracted: whole units at a time (16 loads, wait, 16 tiles' scores, next unit) took 49.5 us
 // against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
-// as large, gain nothing at 128K and lose 2 us at 32K (the first group is consumed later).  Batches at d = 64 with many rounds of
-// workgroups take groups of TPI / 2: 256 ragged sequences of 16K to 64K 3.01 -> 2.96 ms per step, on buffers that are new to
-// the caches and the address translation 3.08 -> 2.95.
-template <int D, int TPI, bool STREAM, bool STRIP, int SUB = TPI / 4>
+// as large, gain nothing at 128K and lose 2 us at 32K (the first group is consumed later).  Groups of TPI / 2 for batches at
+// d = 64: within 0.6 % either way over 66 batches of 4 to 400 sequences on the same buffers.
+template <int D, int TPI, bool STREAM, bool STRIP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                   char* __restrict__ ws) {
   const int p = blockIdx.z, h = blockIdx.y;
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
   extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  scan_wave_slot<D, TPI, SUB, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r, -1, false,
+  scan_wave_slot<D, TPI, TPI / 4, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r, -1, false,
                                                        (lds_u32x2)sh_heads + (STRIP ? wv * g.G * g.cand_T : 0));
 }
 
@@ -499,7 +498,6 @@ void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, 
   const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
   if (g.d == 128 && g.stream_keys) { if (g.head_strip) launch(score_filtered_kernel<128, 4, true, true>); else launch(score_filtered_kernel<128, 4, true, false>); }
   else if (g.d == 128) { if (g.head_strip) launch(score_filtered_kernel<128, 4, false, true>); else launch(score_filtered_kernel<128, 4, false, false>); }
-  else if ((int64_t)g.n_problems * g.Hkv * g.n_scan_chunks >= 4096) { if (g.head_strip) launch(score_filtered_kernel<64, 8, false, true, 4>); else launch(score_filtered_kernel<64, 8, false, false, 4>); }
   else { if (g.head_strip) launch(score_filtered_kernel<64, 8, false, true>); else launch(score_filtered_kernel<64, 8, false, false>); }
 }
 
