@@ -144,9 +144,13 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
     if (n_problems > 1) {
       // Filtered pipeline, batches: 4096 workgroups by the bounds of the call, a power of two of tokens each.  Ragged batches have
       // far fewer, which then still even out over the CUs (8 sequences of 8K to 32K at d = 128: score pass 74 -> 58 us against a
-      // target of 1024, 16 of 16K to 64K at d = 64: 168 -> 152)
+      // target of 1024, 16 of 16K to 64K at d = 64: 168 -> 152).  At most 4096 tokens where sequences may be longer than 32K: a
+      // workgroup of 8192 that starts last alone on its CU ends 30 us late (64 sequences of 16K to 64K: step 743 -> 708 us at
+      // d = 64, 1364 -> 1280 at d = 128; 28 of 128K, where the last round is full: 1472 -> 1486), below that at most 8192 (200 of
+      // 16K: 966 against 990 us with 4096).
+      const int most = g->max_mid > 32768 ? 4096 : 8192;
       sc = 256;
-      while (sc < 8192 && (int64_t)sc * 4096 < units) sc *= 2;
+      while (sc < most && (int64_t)sc * 4096 < units) sc *= 2;
       while (sc < 32768 && ceil_div(g->max_mid, std::max(sc, g->scan_unit)) * 4 * kMinListHead > sweep) sc *= 2;
     } else {
       // One problem: the pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (3B layer
