@@ -37,6 +37,27 @@ static int list_head(int scan_chunk, int64_t K, int64_t n, int sweep, int64_t n_
   return std::max(kMinListHead, std::min(fit, (int)align_up((size_t)want, kSweepEntries)));
 }
 
+// The filtered pipeline runs for budgets of at most 1 / (this number) of the mid-region.  Against the spill pipeline it saves the
+// write-back of the scores, and pays for a larger budget with what one workgroup of its select kernel gathers alone.  Measured
+// over 1000 combinations of shape, batch, length and budget (spill / filtered, us):
+//   * short contexts: always faster (1.07 to 1.6x)
+//   * up to 1/64: as it always was (faster wherever the score pass lasts)
+//   * beyond, where the select kernel's workgroups fill the last of their rounds over the 256 CUs to 4/5: up to 1/12 (3B layer
+//     at 128K and 6 % 135 / 123; 28 3B sequences of 64K and 8 % 1530 / 1403); to 3/4: up to 1/16 (18 1B sequences of 40K, 576 heads:
+//     4 % 352 / 349, 8 % 443 / 475); to 3/5 and long sequences: up to 1/25 (5 1B sequences of 40K, 160 heads: 2.8 % 114 / 98,
+//     8 % 150 / 158; 11 3B sequences of 16K, 264 heads, the second round nearly empty: 2 % 147 / 149, 6 % 175 / 190);
+//     512-thread workgroups, of which the next takes a CU's place as soon as one ends: up to 1/12
+//   * not with fewer than 16 heads, which leave CUs without a workgroup, and more than 2048 retrieved (3 / 1 heads at 128K and
+//     4 % 53 / 64), nor where the winners nearly fill the packed array (3B layer at 128K and 8 % 147 / 158: beyond it every
+//     phase reads the lists again)
+static int filtered_min_inverse_budget(bool short_context, int64_t heads, int split, int threads, int packed, int max_mid, int max_K) {
+  if (short_context) return 12;
+  if (max_K > packed / 5 * 4 || (heads < 16 && max_K > 2048)) return 64;
+  const int64_t wgs = heads * split, slots = (wgs + 255) / 256 * 256;
+  if (threads == 512 || heads < 16 || wgs * 5 >= slots * 4) return 12;
+  return wgs * 4 >= slots * 3 ? 16 : wgs * 5 >= slots * 3 && max_mid > 32768 ? 25 : 64;
+}
+
 // compact: the geometry for scratch memory that the faster one does not fit in.  Its needs grow with max_L, max_K and the
 // number of problems (one chunk rule for all lengths, the filtered pipeline with its two full-length lists per head for budgets
 // up to 1/64 only), so a workspace sized for larger bounds serves the smaller calls (but for a budget of at most 1/64 where the
@@ -120,21 +141,20 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->score_scale = cfg->score_scale; g->a = cfg->phi_in_scale; g->c = cfg->phi_norm_coef;
 
   const int64_t units = (int64_t)g->max_mid * g->Hkv * std::max(n_problems, 1);
-  // filtered pipeline: where the matrix-core score kernel applies, for budgets of at most 1/12 of the mid-region, the range it
-  // measured faster than the spill pipeline in (3B layer at 128K, 1 / 2 / 4 / 7 %: 84 / 93 / 110 / 127 against 98 / 108 /
-  // 122 / 143 us; 1B layer at 32K 38 / 39 / 41 / 44 against 42 / 43 / 45 / 48; 16 sequences of 4K to 16K at d = 64, 4 %: 94
-  // against 114)
-  const int min_inverse_budget = compact ? 64 : 12;
-  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
-                 (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
-  // filtered pipeline: the workgroups that share a query head in the fused select + gather kernel, one partial each: about one
-  // workgroup per CU for a single layer, one per head in big batches; batches of short sequences at d = 64 (one workgroup
+  // fused select + gather kernel of the filtered pipeline: the workgroups that share a query head, one partial each (about one
+  // workgroup per CU for a single layer, one per head in big batches); batches of short sequences at d = 64 (one workgroup
   // per head, at least two heads per CU) take 512-thread workgroups, two per CU, so that one head's memory round trips
   // hide behind the other's arithmetic
-  g->sg_split = g->filtered ? std::clamp(256 / std::max(1, g->Hq * std::max(n_problems, 1)), 1, 16) : 0;
-  const int max_split = g->sg_split;
-  g->sg_threads = g->d == 64 && g->sg_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
+  const int64_t heads = (int64_t)g->Hq * std::max(n_problems, 1);
+  const int max_split = (int)std::clamp<int64_t>(256 / heads, 1, 16);
+  g->sg_threads = g->d == 64 && max_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
   const int sweep = g->sg_threads * kSweepEntries;   // candidate slots of a head that kernel reads in one go
+  const int packed = packed_candidates(g->d, g->sg_threads);
+  const bool short_context = !compact && tn.scan_chunk == 0 && tn.select_test == 0 && g->max_mid <= std::min(sweep, packed);
+  const int min_inverse_budget = compact ? 64 : filtered_min_inverse_budget(short_context, heads, max_split, g->sg_threads, packed, g->max_mid, max_K);
+  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
+                 (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
+  g->sg_split = g->filtered ? max_split : 0;
   // matrix-core score kernel: 4 wavefronts x 64 (d = 128) or 128 (d = 64) tokens per iteration;
   // a chunk is a whole number of such units
   g->scan_unit = g->use_mfma ? (g->d == 128 ? 256 : 512) : 256;
@@ -172,7 +192,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // Short contexts, as long as every token fits one sweep and the packed array of the select kernel: one unit per chunk, all
   // scores stored, no bound and no prep launch (1B layer at 4K 34.5 -> 22.6 us, at 10K 34.9 -> 24.6; 3B layer 34.6 -> 26.0 and 37.5 -> 31.8).  Few
   // winners then, and what workgroups of a head hand each other costs more than a gather round: one per 64 of the budget
-  g->direct = g->filtered && !compact && tn.scan_chunk == 0 && tn.select_test == 0 && g->max_mid <= std::min(sweep, packed_candidates(g->d, g->sg_threads)) ? 1 : 0;
+  g->direct = g->filtered && short_context ? 1 : 0;
   if (g->direct) {
     sc = g->scan_unit;
     g->sg_split = std::min(g->sg_split, std::max(1, (int)ceil_div(std::min(max_K, g->max_mid), 64)));
@@ -265,7 +285,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->sel_feat = cfg->phi_kind == TKPHI_PHI_MLP && !g->cache;
   g->off_selphi = p;  p = align_up(p + (g->sel_feat ? (size_t)g->Hq * std::max(max_K, 1) * g->dphi * sizeof(float) : (size_t)0), 256);
   g->off_part = p;
-  p = align_up(p + (size_t)g->Hq * (std::max(g->n_tiles, max_split) + g->n_atiles) * g->part_stride * sizeof(float), 256);
+  p = align_up(p + (size_t)g->Hq * (std::max(g->n_tiles, g->filtered ? max_split : 0) + g->n_atiles) * g->part_stride * sizeof(float), 256);
   g->per_problem = p;
   const size_t decode_total = g->off_problem0 + (size_t)std::max(n_problems, 1) * g->per_problem;
   size_t decode_all = decode_total;

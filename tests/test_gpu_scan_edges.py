@@ -157,3 +157,26 @@ def test_each_decode_route_replays_from_a_hip_graph(shape, L, k):
             assert np.array_equal(b.result(0, n), y), f"replay {rep}: {n} differs from the eager result"
         b.decode()
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,max_mid,max_K,filtered", [
+    (24, 8, 128, 1, 131004, 1310, True), (24, 8, 128, 1, 131004, 7800, True), (24, 8, 128, 1, 131004, 10400, False),     # winners beyond the packed array
+    (3, 1, 128, 1, 131004, 1310, True), (3, 1, 128, 1, 131004, 5240, False), (3, 1, 128, 1, 32000, 2040, True),          # few heads
+    (4, 1, 64, 1, 12000, 1000, True), (4, 1, 64, 1, 12000, 1001, False),                                                 # short context, 1/12
+    (32, 8, 64, 18, 40000, 1600, True), (32, 8, 64, 18, 40000, 3200, False),                                             # 576 heads: 3/4 of three rounds
+    (24, 8, 128, 11, 16000, 250, True), (24, 8, 128, 11, 16000, 320, False)])                                            # 264 heads: second round empty
+def test_pipeline_by_bounds(hq, hkv, d, n, max_mid, max_K, filtered):
+    """Which pipeline a call takes follows from its bounds (the problems themselves are short here): the stages that ran say it;
+    either way the result is the oracle's."""
+    import dataclasses
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l3b_128k" if d == 128 else "l1b_32k"], n_q_heads=hq, n_kv_heads=hkv)
+    layers = [I.make_layer(w, L=700 + 13 * i, seq=i) for i in range(n)]
+    b = H.Batch(H.config_of(w), layers, [40] * n, debug=True, max_L=max_mid + w.n_sink + w.n_tail, max_K=max_K)
+    b.build()
+    stages = dict(zip(B.STAGES, b.decode_stage_times()))
+    assert (stages["select"] > 0) == filtered and (stages["merge"] > 0) == (not filtered), stages
+    for i in (0, n - 1):
+        PU.check_layer(w, layers[i], 40, b, i, heads=[0, hq - 1])
