@@ -62,7 +62,7 @@ static int filtered_min_inverse_budget(bool short_context, int64_t heads, int sp
 // number of problems (one chunk rule for all lengths, the filtered pipeline with its two full-length lists per head for budgets
 // up to 1/64 only), so a workspace sized for larger bounds serves the smaller calls (but for a budget of at most 1/64 where the
 // workspace was sized for one beyond 1/12).
-static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, bool compact, Geom* g) {
+static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, bool compact, bool diag, Geom* g) {
   if (!cfg) { set_error("cfg is null"); return TKPHI_EINVAL; }
   if (n_problems < 0 || max_L < 1 || max_K < 0) {
     set_error("n_problems=%d max_L=%d max_K=%d out of range", n_problems, max_L, max_K);
@@ -152,7 +152,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   const int packed = packed_candidates(g->d, g->sg_threads);
   const bool short_context = !compact && tn.scan_chunk == 0 && tn.select_test == 0 && g->max_mid <= std::min(sweep, packed);
   const int min_inverse_budget = compact ? 64 : filtered_min_inverse_budget(short_context, heads, max_split, g->sg_threads, packed, g->max_mid, max_K);
-  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 &&
+  // (a step with the diagnostics runs the spill pipeline; of one problem also on its chunks: on the few long ones that the
+  // filtered pass likes a 3B layer at 128K took 107.5 us instead of 101.5, batches are as fast or faster on theirs)
+  g->diag = diag ? 1 : 0;
+  g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 && !(diag && n_problems <= 1) &&
                  (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
   g->sg_split = g->filtered ? max_split : 0;
   // matrix-core score kernel: 4 wavefronts x 64 (d = 128) or 128 (d = 64) tokens per iteration;
@@ -327,10 +330,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
 }
 
 // have / need: the scratch bytes that the caller has and the member that says what its call takes (null: no limit)
-tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have, size_t Geom::*need) {
-  const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, false, g);
+tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have, size_t Geom::*need, bool diag) {
+  const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, false, diag, g);
   if (st != TKPHI_OK || !need || g->*need <= have) return st;
-  return make_geom_as(cfg, n_problems, max_L, max_K, true, g);
+  return make_geom_as(cfg, n_problems, max_L, max_K, true, diag, g);
 }
 
 static tkphi_status check_call(const tkphi_problem* problems, int n_problems, const void* ws,
@@ -363,7 +366,7 @@ size_t tkphi_workspace_bytes(const tkphi_config* cfg, int32_t n_problems, int32_
   Geom g;
   if (make_geom(cfg, n_problems, max_L, max_K, &g) != TKPHI_OK) return 0;
   const size_t bytes = g.total_bytes;      // (enough for the compact geometry too, which a call with smaller bounds may fall back to)
-  if (make_geom_as(cfg, n_problems, max_L, max_K, true, &g) != TKPHI_OK) return 0;
+  if (make_geom_as(cfg, n_problems, max_L, max_K, true, false, &g) != TKPHI_OK) return 0;
   return std::max(bytes, g.total_bytes);
 }
 
@@ -469,8 +472,7 @@ tkphi_status tkphi_decode(const tkphi_config* cfg, const tkphi_problem* problems
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes);
-  g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes, (mode & TKPHI_FLAG_DIAG) != 0);
   if (st != TKPHI_OK) return st;
   st = check_call(problems, n_problems, workspace, workspace_bytes, g, g.decode_bytes);
   if (st != TKPHI_OK) return st;
@@ -518,9 +520,8 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg, const tkphi_problem* p
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, TKPHI_STATIC_SCRATCH_BYTES, &Geom::decode_bytes);
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, TKPHI_STATIC_SCRATCH_BYTES, &Geom::decode_bytes, (mode & TKPHI_FLAG_DIAG) != 0);
   if (st != TKPHI_OK) return st;
-  g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
   if (g.phi_kind == TKPHI_PHI_MLP) {      // that path creates a stream and events on first use
     set_error("tkphi_decode_static does not run the MLP feature maps");
     return TKPHI_EUNSUPPORTED;
@@ -553,8 +554,7 @@ tkphi_status tkphi_decode_stage_times(const tkphi_config* cfg, const tkphi_probl
     return TKPHI_EINVAL;
   }
   Geom g;
-  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes);
-  g.diag = (mode & TKPHI_FLAG_DIAG) ? 1 : 0;
+  tkphi_status st = make_geom(cfg, n_problems, max_L, max_K, &g, workspace_bytes, &Geom::decode_bytes, (mode & TKPHI_FLAG_DIAG) != 0);
   if (st != TKPHI_OK) return st;
   st = check_call(problems, n_problems, workspace, workspace_bytes, g, g.decode_bytes);
   if (st != TKPHI_OK) return st;

@@ -103,7 +103,7 @@ struct Geom {
 };
 
 // Fills g for the given bounds; returns TKPHI_OK or the reason the config is unsupported.
-tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have = 0, size_t Geom::*need = nullptr);
+tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have = 0, size_t Geom::*need = nullptr, bool diag = false);
 void set_error(const char* fmt, ...);
 
 // Optional per-kernel timing: while g_kernel_timer is set (by tkphi_decode_stage_times, on

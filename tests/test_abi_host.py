@@ -151,3 +151,30 @@ def test_calls_reject_bad_arguments_before_any_launch():
     assert "null" in B.tkphi_last_error()
     # zero problems is a no-op
     assert lib.tkphi_decode(C.byref(cfg), None, 0, 1000, 9, 0, 4096, nbytes, None) == B.TKPHI_OK
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_reported_workspace_serves_every_mode_and_smaller_bounds(seed):
+    """What tkphi_workspace_bytes reports for some bounds is accepted by decode calls in every mode, the diagnostics flag
+    included, and by calls with smaller bounds whose budget is smaller in proportion (an empty table: the call stops after
+    its checks, so no GPU is needed)."""
+    import random
+    r = random.Random(seed)
+    lib = B.lib()
+    for _ in range(300):
+        d, hkv = r.choice([64, 128]), r.choice([1, 2, 4, 8])
+        cfg = _cfg(n_q_heads=hkv * r.choice([1, 3, 4, 8]), n_kv_heads=hkv, d_head=d, d_phi=r.choice([d, d, 48]), dtype=r.choice(["bf16", "bf16", "f32"]),
+                   cache_features=int(r.random() < 0.2))
+        L = int(2 ** r.uniform(5, 17.3))
+        K = int(L * 10 ** r.uniform(-3, -0.3))
+        size = B.tkphi_workspace_bytes(cfg, 1, L, K)
+        assert size > 0
+        part = r.uniform(0.05, 1.0)
+        calls = [(L, K, m | f) for m in (0, 1, 2) for f in (0, B.TKPHI_FLAG_DIAG)]
+        if K * 12 > L or K * 64 <= L // 2:             # (a budget between 1/12 and 1/64 may become one of at most 1/64, which is laid out differently)
+            calls.append((max(1, int(L * part)), int(K * part), 0))
+        for l, k, mode in calls:
+            if l != L and ((k * 64 <= l - 68) != (K * 64 <= L - 68)):
+                continue
+            st = lib.tkphi_decode(C.byref(cfg), None, 0, l, k, mode, 4096, size, None)
+            assert st == B.TKPHI_OK, (L, K, l, k, mode, B.tkphi_last_error())

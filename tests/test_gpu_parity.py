@@ -473,6 +473,24 @@ def test_entropy_and_mass_diagnostics(shape, L, k, interleave):
     assert all(np.array_equal(b1.result(i, "out"), y1[i]) for i in range(2))
 
 
+@pytest.mark.parametrize("shape,L,k", [("l3b_128k", 40000, 400), ("l1b_32k", 60000, 600), ("l3b_128k", 9000, 90)])
+def test_diagnostics_of_one_problem_run_on_the_spill_chunks(shape, L, k):
+    """A step with the diagnostics runs the spill pipeline; for one problem also in the spill pipeline's launch geometry, so that
+    its output is that of a step forced through it bit for bit, whatever pipeline the plain step takes."""
+    from paper_2604_05438_amd import binding as B
+    w = I.WORKLOADS[shape]
+    P = I.make_layer(w, L=L)
+    y = []
+    for tuning, flag in ((None, B.TKPHI_FLAG_DIAG), ({"select_mode": 1}, 0)):
+        b = _batch(w, [P], [k], tuning=tuning)
+        b.build(); b.decode(B.TKPHI_MODE_SUB | flag)
+        assert b.status() == 0
+        y.append(b.result(0, "out").copy())
+        if flag:
+            _check_diag(w, P, k, b, 0, [0, w.n_q_heads - 1])
+    assert np.array_equal(y[0], y[1])
+
+
 @pytest.mark.parametrize("shape,L,k", [("l3b_128k", 9000, 360), ("l1b_32k", 5000, 49), ("tiny_f32", 4096, 40),
                                        ("f32_gqa", 1500, 33)])
 def test_cached_key_features(shape, L, k):
