@@ -154,8 +154,9 @@ __global__ __launch_bounds__(kThreads) void score_mid_mfma_kernel(Geom g, const 
 // bytes and forms the partial dot products for all G query heads; the partials are summed
 // across the LPR lanes with butterfly shuffles.
 // ------------------------------------------------------------------------------------
-// NTHR = 1024 for at most one workgroup per CU (a chunk of 256 fp32 rows at d = 64 is then one batch of loads: 15.7 -> 11.4 us for
-// one head of 4028 tokens), 256 otherwise.
+// NTHR = 1024 for at most one workgroup per CU and rows of 256 bytes or more (a chunk of 256 fp32 rows at d = 64 is then one batch of
+// loads: 15.7 -> 11.4 us for one head of 4028 tokens; steps of bf16 layers at d = 128 7 to 25 % faster), 256 otherwise (of
+// 128-byte rows 1024 threads request four chunks' worth at once: steps 4 % slower).
 template <typename T, int NTHR>
 __global__ __launch_bounds__(NTHR) void score_mid_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                              char* __restrict__ ws) {
@@ -244,7 +245,7 @@ void launch_score_mid(const Geom& g, const tkphi_problem* probs, char* ws, hipSt
       TKPHI_LAUNCH(ST_SCORE, (score_mid_mfma_kernel<64, 8>), grid, dim3(kThreads), hist_lds + (size_t)4 * g.G * 128 * 4, s,
                          g, probs, ws);
   } else {
-    const bool wide = (int64_t)g.n_scan_chunks * g.Hkv * g.n_problems <= 256;     // at most one workgroup per CU
+    const bool wide = (int64_t)g.n_scan_chunks * g.Hkv * g.n_problems <= 256 && g.d * (g.dtype == TKPHI_BF16 ? 2 : 4) >= 256;
     const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(threads), hist_lds, s, g, probs, ws); };
     if (g.dtype == TKPHI_BF16) { if (wide) launch(score_mid_kernel<uint16_t, 1024>, 1024); else launch(score_mid_kernel<uint16_t, kThreads>, kThreads); }
     else if (wide) launch(score_mid_kernel<float, 1024>, 1024);
