@@ -171,7 +171,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     if (sh_total >= (uint32_t)Ksel || attempt > 0) break;
     __syncthreads();
     // (every workgroup of the head takes this branch, the counts it depends on being the score pass's, and writes
-    // the same values to the rescan set: no ordering between them is needed)
+    // the same values to the rescan set: no ordering between them is needed.  A head's only workgroup may write the first set
+    // over: every thread has read its counts before the barrier above, and nothing else of that set is read again)
     rescan_head<D, TPI, NTHR>(g, pr, blk, gq, n, n_chunks);
     ccount = (const uint32_t*)(blk + g.off_rescount) + (size_t)gq * n_reg_max;
     compact = (const uint2*)(blk + g.off_resc) + (size_t)gq * n_reg_max * T;

@@ -256,9 +256,13 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   size_t p = 0;
   g->off_scores = p;
   g->off_candf = p;     // (the two pipelines never run in the same call)
-  p = align_up(p + std::max((size_t)g->Hq * g->mid_stride * sizeof(float),
-                            g->filtered ? (size_t)g->Hq * g->n_scan_chunks * g->scan_chunk * sizeof(uint2) : (size_t)0), 256);
-  // (short contexts have no lists: there the layout is the compact geometry's)
+  // The second set of candidate lists, which a rescan writes while other workgroups of the head may still read the first, is the
+  // first one where a head has one workgroup: a batch of 256 sequences of 50K at 2 % needs 4.4 GB so, 8.2 with two sets (the
+  // spill pipeline 2.1).  (The compact geometry keeps the room; short contexts have no lists, but keep it too, so that the
+  // reported size stays the smallest accepted for one problem.)
+  const size_t lists = g->filtered ? (size_t)g->Hq * g->n_scan_chunks : 0;
+  const bool one_set = !compact && max_split == 1;
+  p = align_up(p + std::max((size_t)g->Hq * g->mid_stride * sizeof(float), lists * g->scan_chunk * sizeof(uint2)), 256);
   g->cand_T = compact || !g->filtered || g->direct ? (int)align_up((size_t)std::max(kMinListHead, g->scan_chunk / 4 * 3 / 32), kSweepEntries)
                                       : list_head(g->scan_chunk, std::min(max_K, g->max_mid), g->max_mid, sweep, g->n_scan_chunks);
   g->head_strip = (size_t)4 * g->G * g->cand_T * sizeof(uint2) <= 32768 ? 1 : 0;
@@ -267,11 +271,15 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // with 128-byte rows the two loads that share a cache line fetch it twice (ragged batch: score pass +20 %), and
   // the 28-layer call measured 2 % slower
   g->stream_keys = (n_problems == 1 && g->d == 128) ? 1 : 0;
-  g->off_candc = p;   p = align_up(p + (g->filtered ? (size_t)g->Hq * g->n_scan_chunks * 4 * g->cand_T * sizeof(uint2) : (size_t)0), 256);
-  g->off_ccount = p;  p = align_up(p + (g->filtered ? (size_t)g->Hq * g->n_scan_chunks * 4 * sizeof(uint32_t) : (size_t)0), 256);
-  g->off_resf = p;    p = align_up(p + (g->filtered ? (size_t)g->Hq * g->n_scan_chunks * g->scan_chunk * sizeof(uint2) : (size_t)0), 256);
-  g->off_resc = p;    p = align_up(p + (g->filtered ? (size_t)g->Hq * g->n_scan_chunks * 4 * g->cand_T * sizeof(uint2) : (size_t)0), 256);
-  g->off_rescount = p; p = align_up(p + (g->filtered ? (size_t)g->Hq * g->n_scan_chunks * 4 * sizeof(uint32_t) : (size_t)0), 256);
+  g->off_candc = p;   p = align_up(p + lists * 4 * g->cand_T * sizeof(uint2), 256);
+  g->off_ccount = p;  p = align_up(p + lists * 4 * sizeof(uint32_t), 256);
+  if (one_set) {
+    g->off_resf = g->off_candf; g->off_resc = g->off_candc; g->off_rescount = g->off_ccount;
+  } else {
+    g->off_resf = p;    p = align_up(p + lists * g->scan_chunk * sizeof(uint2), 256);
+    g->off_resc = p;    p = align_up(p + lists * 4 * g->cand_T * sizeof(uint2), 256);
+    g->off_rescount = p; p = align_up(p + lists * 4 * sizeof(uint32_t), 256);
+  }
   g->off_thr = p;     p = align_up(p + (size_t)g->Hq * sizeof(uint32_t), 256);
   g->off_mcount = p;  p = align_up(p + (size_t)g->Hq * sizeof(uint32_t), 256);
   g->off_sphi = p;    p = align_up(p + (size_t)g->Hq * g->d * sizeof(float), 256);
@@ -365,9 +373,16 @@ extern "C" {
 size_t tkphi_workspace_bytes(const tkphi_config* cfg, int32_t n_problems, int32_t max_L, int32_t max_K) {
   Geom g;
   if (make_geom(cfg, n_problems, max_L, max_K, &g) != TKPHI_OK) return 0;
-  const size_t bytes = g.total_bytes;      // (enough for the compact geometry too, which a call with smaller bounds may fall back to)
-  if (make_geom_as(cfg, n_problems, max_L, max_K, true, false, &g) != TKPHI_OK) return 0;
-  return std::max(bytes, g.total_bytes);
+  size_t bytes = 0;
+  // enough for the compact geometry too, which a call with smaller bounds may fall back to, and for the largest number of problems
+  // whose heads have two workgroups (and two sets of candidate lists): it may need more than a few problems beyond it
+  const int fewer = std::min(n_problems, 128 / cfg->n_q_heads);
+  for (int n : {n_problems, fewer})
+    for (bool compact : {false, true}) {
+      if (make_geom_as(cfg, n, max_L, max_K, compact, false, &g) != TKPHI_OK) return 0;
+      bytes = std::max(bytes, g.total_bytes);
+    }
+  return bytes;
 }
 
 tkphi_status tkphi_build_summaries(const tkphi_config* cfg, const tkphi_problem* problems,

@@ -75,7 +75,8 @@ struct Geom {
   size_t off_candc;      // uint2    [Hq][n_scan_chunks][4][cand_T]  the first cand_T entries of every list
   size_t off_ccount;     // uint32   [Hq][n_scan_chunks][4]      lengths of the candidate lists
   size_t off_resf, off_resc, off_rescount;  // the rescan set: a second candf / candc / ccount, written when the select kernel
-                         //                                       rescans a head without a bound, read by its second attempt
+                         //                                       rescans a head without a bound, read by its second attempt; the
+                         //                                       first set itself where one workgroup takes a head (sg_split 1)
   size_t off_thr;        // uint32   [Hq]                        lower bound of the score key per query head
   size_t off_mcount;     // uint32   [Hq]                        filtered pipeline: workgroups of the fused select + gather kernel
                          //                                       that have finished their share of the head (cleared by prep)

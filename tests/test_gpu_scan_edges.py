@@ -180,3 +180,34 @@ def test_pipeline_by_bounds(hq, hkv, d, n, max_mid, max_K, filtered):
     assert (stages["select"] > 0) == filtered and (stages["merge"] > 0) == (not filtered), stages
     for i in (0, n - 1):
         PU.check_layer(w, layers[i], 40, b, i, heads=[0, hq - 1])
+
+
+@pytest.mark.parametrize("shape,n_mid,n_problems", [("l1b_32k", 14000, 1), ("l1b_32k", 14000, 9), ("l1b_32k", 5000, 17), ("l3b_128k", 11000, 1), ("l3b_128k", 11000, 11)])
+def test_sampled_rows_above_all_others(shape, n_mid, n_problems):
+    """The rows that the bound is sampled from lean towards one query of their group, so that its K best are among them and the
+    bound lies above its K-th score: that head misses and rescans, its neighbours, scanned in the same pass, do not.  One
+    problem (several workgroups per head, which write a second set of lists) and batches (one each, which writes its lists
+    over; 512 threads from 512 heads on): index sets, scores and outputs against the oracle."""
+    import numpy as np
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    layers, k = [], n_mid // 100
+    m = min(1024, max(512, n_mid // 64)) // 16 * 16                     # the sample: groups of 16 rows at equal distances
+    rows = np.array([(s >> 4) * (n_mid // (m >> 4)) + (s & 15) for s in range(m)]) + w.n_sink
+    for i in range(n_problems):
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + n_mid, seq=i % 3)
+        K, q = I.bf16_bits_to_f32(P["K"]), I.bf16_bits_to_f32(P["q"])
+        h, g = i % w.n_kv_heads, i % w.group
+        K[h, rows] = 0.5 * K[h, rows] + np.float32(0.6) * q[h * w.group + g]
+        P["K"] = I.f32_to_bf16_bits(K)
+        layers.append(P)
+    b = H.Batch(H.config_of(w, tuning={"select_mode": 2, "scan_chunk": 1024}), layers, [k] * n_problems, debug=True)
+    b.build()
+    for _ in range(2):
+        b.decode()
+    assert b.status() & ~2 == 0
+    for i in sorted({0, 1 % n_problems, n_problems - 1}):
+        hot = (i % w.n_kv_heads) * w.group + i % w.group
+        PU.check_layer(w, layers[i], k, b, i, heads=sorted({hot, hot ^ 1, (hot + w.group) % w.n_q_heads}))
+        assert np.isin(b.result(i, "topk_idx")[hot, :k], rows).mean() > 0.9        # (the case is what it says: the bound misses)
