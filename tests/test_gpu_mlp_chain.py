@@ -96,3 +96,24 @@ def test_large_output_bias_is_rounded_once(d, d_emb):
         rms.append(float(np.sqrt(np.mean(np.square(e)))))
     print("log-feature error, rms:", d, d_emb, rms, flush=True)
     assert rms[1] <= 1.2 * np.hypot(rms[0], 2.0 ** -19 / np.sqrt(3.0)), rms
+
+
+@pytest.mark.parametrize("d_emb,cache", [(128, True), (512, False), (1024, True)])
+def test_hidden_units_far_outside(d_emb, cache):
+    """Hidden biases of minus infinity and of -1e30 switch their units off (GeLU is zero there, not NaN): features, summaries and
+    outputs are those of the maps whose second layer has zeros in these columns, on the chain, the layer-wise launches
+    (d_emb 1024) and the query side."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l1b_32k"], n_q_heads=4, n_kv_heads=2, d_head=64, d_phi=64, seed=619)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 300)
+    P["mlp"] = I.make_mlp_phi(w, layer=0, d_emb=d_emb)
+    O = dict(P, mlp={side: {n: t.copy() for n, t in P["mlp"][side].items()} for side in ("q", "k")})
+    for side in ("q", "k"):
+        P["mlp"][side]["b1"][:, [0, 17]], P["mlp"][side]["b1"][:, d_emb - 1] = -np.inf, -1e30
+        O["mlp"][side]["W2"][:, :, [0, 17, d_emb - 1]] = 0
+    b = H.Batch(H.config_of(w, cache_features=cache, d_emb=d_emb), [P], [40], debug=True)
+    b.build()
+    b.decode()
+    assert b.status() & ~2 == 0
+    PU.check_layer(w, O, 40, b, 0)

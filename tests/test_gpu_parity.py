@@ -177,7 +177,8 @@ def test_degenerate_budgets_and_lengths():
 
 SELECT_VARIANTS = {
     "spill": {"select_mode": 1},                            # every score written, plan / emit / resolve
-    "filtered": {"select_mode": 2},                         # sampled bound, candidate lists, one select kernel
+    "direct": {"select_mode": 2},                           # short contexts: all scores in a row, one select kernel (longer: as filtered)
+    "filtered": {"select_mode": 2, "scan_chunk": 1024},     # sampled bound, candidate lists (a chunk of its own rules the row out)
     "rescan": {"select_mode": 2, "select_test": 1},         # ... with a bound nothing passes: every head rescans
     "no_pruning": {"select_mode": 2, "select_test": 2},     # ... with a bound everything passes
 }
@@ -186,8 +187,8 @@ SELECT_VARIANTS = {
 @pytest.mark.parametrize("variant", list(SELECT_VARIANTS))
 @pytest.mark.parametrize("shape,L,k", [("l3b_128k", 9000, 360), ("l1b_32k", 5000, 49), ("l1b_32k", 20011, 200)])
 def test_select_pipelines(shape, L, k, variant):
-    """Both decode pipelines of the matrix-core shapes, and the filtered one's rare paths (threshold
-    miss -> rescan of the head; no pruning -> every mid token a candidate), forced through
+    """The decode routes of the matrix-core shapes (spill; direct up to 12288 / 10240 mid tokens; filtered), and the filtered one's
+    rare paths (threshold miss -> rescan of the head; no pruning -> every mid token a candidate), forced through
     tkphi_tuning at sizes the oracle checks in full; single problem, then a ragged batch with a tiny
     and an empty mid-region and budgets from 0 to most of the mid-region."""
     import parity_utils as PU
@@ -207,7 +208,7 @@ def test_select_pipelines(shape, L, k, variant):
         PU.check_layer(w, P, kk, b, i, heads=[0, w.n_q_heads // 2, w.n_q_heads - 1])
 
 
-@pytest.mark.parametrize("variant", ["spill", "filtered"])
+@pytest.mark.parametrize("variant", ["spill", "direct", "filtered"])
 def test_graph_replay_matches_eager(variant):
     """A decode call captured into a HIP graph (it allocates nothing, synchronises nothing and records no
     memset) replayed several times, with eager decodes and synchronisations in between and the query changed
@@ -282,7 +283,8 @@ def test_batch_of_many_heads_uses_small_workgroups(shape, variant):
         ks += [30, 20, 10, 1400, 25, 40]
     layers = [I.make_layer(w, L=l, seq=i) for i, l in enumerate(Ls)]
     layers[8]["K"][:, :, :] = layers[8]["K"][:, 100:101, :]           # every score of problem 8 equal: Top-1 = first mid token
-    b = H.Batch(H.config_of(w, tuning=SELECT_VARIANTS[variant]), layers, ks, debug=True)
+    tuning = dict(SELECT_VARIANTS[variant], scan_chunk=0)              # (a batch with 12000 tokens has lists at the default chunk)
+    b = H.Batch(H.config_of(w, tuning=tuning), layers, ks, debug=True)
     assert w.n_q_heads * len(layers) >= 512
     b.build(); b.decode()
     assert b.status() == 0
@@ -293,11 +295,13 @@ def test_batch_of_many_heads_uses_small_workgroups(shape, variant):
 
 
 @pytest.mark.parametrize("variant", list(SELECT_VARIANTS))
-@pytest.mark.parametrize("shape,L", [("l1b_32k", 7000), ("l3b_128k", 3000)])
+@pytest.mark.parametrize("shape,L", [("l1b_32k", 7000), ("l3b_128k", 3000), ("l1b_32k", 14000), ("l3b_128k", 12000)])
 def test_all_scores_equal_slow_path(variant, shape, L):
-    """Every key identical: the boundary bin holds the whole mid-region (more than the
-    in-LDS candidate capacity), so the radix passes run (7000 tokens: over the lists in global memory;
-    3000 tokens at head dimension 128: over the candidates packed in LDS); Top-K = first K."""
+    """Every key identical: the boundary bin holds the whole mid-region (more than the in-LDS candidate capacity), so the radix
+    passes run; Top-K = first K.  7000 tokens at head dimension 64 and 3000 at 128 fit the array of packed candidates
+    (12288, 10240): radix passes in LDS, also over the row of scores ("direct").  14000 and 12000 do not, and the
+    boundary bin cannot be packed either: passes over the lists in global memory, of the score pass (filtered, no_pruning; the
+    sampled bound equals every score) or of the rescan."""
     from paper_2604_05438_amd import harness as H
     w = I.WORKLOADS[shape]
     P = I.make_layer(w, L=L)
@@ -311,6 +315,69 @@ def test_all_scores_equal_slow_path(variant, shape, L):
     import parity_utils as PU
     rep = PU.check_layer(w, P, k, b, 0, heads=[0, 9])
     print("all-equal", rep)
+
+
+@pytest.mark.parametrize("variant", ["filtered", "rescan", "no_pruning"])
+def test_all_scores_equal_in_a_batch(variant):
+    """The same in 512-thread workgroups (16 problems of 32 heads), whose packed array takes 4096 candidates: identical keys on
+    5000 and 6100 tokens go through the lists in global memory, on 3000 through LDS."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS["l1b_32k"]
+    Ls = [5000, 3000, 6100] + [700 + 50 * i for i in range(13)]
+    ks = [49, 30, 700] + [7] * 13
+    layers = [I.make_layer(w, L=l, seq=i) for i, l in enumerate(Ls)]
+    for P in layers[:3]:
+        P["K"][:, :, :] = P["K"][:, 100:101, :]
+    b = H.Batch(H.config_of(w, tuning=SELECT_VARIANTS[variant]), layers, ks, debug=True)
+    b.build(); b.decode()
+    assert b.status() == 0
+    for i in range(3):
+        assert (b.result(i, "topk_idx")[:, :ks[i]] == np.arange(w.n_sink, w.n_sink + ks[i])).all()
+    for i in (0, 1, 2, 3, 15):
+        PU.check_layer(w, layers[i], ks[i], b, i, heads=[0, 13, 31])
+
+
+@pytest.mark.parametrize("variant", ["spill", "direct", "filtered", "rescan", "no_pruning"])
+@pytest.mark.parametrize("shape,L", [("l1b_32k", 3000), ("l3b_128k", 3000)])
+def test_infinite_and_undefined_keys(variant, shape, L):
+    """One infinite channel in some key rows of KV head 1, a row of NaN in KV head 2.  Scores of +infinity are retrieved first (by
+    index), of -infinity never; selection-only outputs of the heads that see nothing but -infinity match an oracle that sees
+    very negative scores in their place; the indices of KV head 2 are a valid set; every other head is as ever."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    w = I.WORKLOADS[shape]
+    k, G = 30, w.group
+    P = I.make_layer(w, L=L)
+    q = I.to_f64(P["q"])
+    c = int(np.argmin(np.abs(np.sign(q[G:2 * G]).sum(0))))             # a channel in which the group's queries have both signs
+    Q = dict(P, K=P["K"].copy())                                       # the oracle's copy: 3e4 for infinity, the row of NaN as it was
+    rows = np.array([w.n_sink, 77, 400, 401, 1999, L - w.n_tail - 1])
+    P["K"][1, rows, c] = 0x7F80
+    Q["K"][1, rows, c] = I.f32_to_bf16_bits(np.array([3e4], np.float32))[0]
+    P["K"][2, 555, :] = 0x7FC0
+    b = _batch(w, [P], [k], tuning=SELECT_VARIANTS[variant])
+    b.build(); b.decode()
+    S = [I.to_f64(x) for x in (b.result(0, "S"), b.result(0, "u"))]
+    others = [g for g in range(w.n_q_heads) if g // G not in (1, 2)]
+    assert all(np.isfinite(x[[h for h in range(w.n_kv_heads) if h not in (1, 2)]]).all() for x in S)
+    res, S_or, u_or, _ = PU.oracle_layer(w, Q, k, heads=others[::5])
+    PU.check_layer(w, Q, k, b, 0, heads=others[::5], summaries=(S_or, u_or))
+    idx = b.result(0, "topk_idx")
+    neg = []
+    for g in range(G, 2 * G):
+        got = idx[g, :k]
+        assert (np.diff(got) > 0).all() and got[0] >= w.n_sink and got[-1] < L - w.n_tail
+        assert np.isin(rows, got).all() if q[g, c] > 0 else not np.isin(rows, got).any(), (g, q[g, c])
+        neg += [g] if q[g, c] < 0 else []
+    for g in range(2 * G, 3 * G):
+        got = idx[g, :k]
+        assert (np.diff(got) > 0).all() and got[0] >= w.n_sink and got[-1] < L - w.n_tail
+    assert neg
+    b.decode(B.TKPHI_MODE_TOPK_ONLY)
+    y = b.result(0, "out")
+    for g, r in zip(neg, PU.oracle_layer(w, Q, k, heads=neg, S=S_or, u=u_or)[0]):
+        PU.check_output(y[g], r["y_topk"], f"head {g} beside infinite keys")
 
 
 def test_large_scores_use_the_max_shift():

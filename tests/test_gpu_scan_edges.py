@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape", ["l3b_128k", "l1b_32k"])
 @pytest.mark.parametrize("chunk,interleave", [(0, 0), (512, 1), (1024, 2), (2048, 1)])
 def test_score_groups_at_every_end(shape, chunk, interleave):
-    """Every score (exported), index set and output of a ragged batch, filtered pipeline forced; scores to 1e-5, the bar of
-    parity_utils.  The longest problem fills several chunks; budgets from one token to a fifth of the mid-region."""
+    """Every score (exported), index set and output of a ragged batch, filtered pipeline forced (with chunk 0 the pass of short
+    contexts, which scores the same groups and stores all of them); scores to 1e-5, the bar of parity_utils.  The longest problem fills several chunks; budgets from one token to a fifth of the mid-region."""
     import parity_utils as PU
     from paper_2604_05438_amd import harness as H
     w = I.WORKLOADS[shape]
@@ -27,7 +27,8 @@ def test_score_groups_at_every_end(shape, chunk, interleave):
 
 
 @pytest.mark.parametrize("shape,n_mid,k,select_test", [
-    ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # a hot stretch overflows the compact heads of its lists: several sweeps
+    ("l3b_128k", 11000, 100, 0), ("l1b_32k", 13000, 700, 0),      # a hot stretch overflows the compact heads of its lists: several sweeps
+    ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # short contexts: no lists, the row of scores is packed as it is
     ("l3b_128k", 13000, 400, 2), ("l1b_32k", 14000, 1500, 2),     # every token a candidate, more than the packed array: boundary bin first
     ("l1b_32k", 14000, 13500, 2),                                 # a budget beyond the packed array: every phase from the lists
     ("l3b_128k", 13000, 900, 1)])                                 # nothing passes the bound: rescan, then as above
@@ -211,3 +212,19 @@ def test_sampled_rows_above_all_others(shape, n_mid, n_problems):
         hot = (i % w.n_kv_heads) * w.group + i % w.group
         PU.check_layer(w, layers[i], k, b, i, heads=sorted({hot, hot ^ 1, (hot + w.group) % w.n_q_heads}))
         assert np.isin(b.result(i, "topk_idx")[hot, :k], rows).mean() > 0.9        # (the case is what it says: the bound misses)
+
+
+@pytest.mark.parametrize("hq,hkv,d,L,k", [(3, 1, 128, 70000, 700), (8, 1, 64, 70000, 1500), (1, 1, 128, 20000, 100), (4, 2, 64, 50000, 400)])
+def test_few_kv_heads(hq, hkv, d, L, k):
+    """One or two KV heads over a long context: at most 128 chunks per head, fewer workgroups than CUs.  All heads against the
+    oracle, at the library's own geometry."""
+    import dataclasses
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l3b_128k" if d == 128 else "l1b_32k"], n_q_heads=hq, n_kv_heads=hkv)
+    P = I.make_layer(w, L=L)
+    b = H.Batch(H.config_of(w), [P], [k], debug=True)
+    b.build()
+    b.decode()
+    assert b.status() == 0
+    PU.check_layer(w, P, k, b, 0)
