@@ -55,9 +55,10 @@ __device__ __forceinline__ int sample_row(int si, int n, int m) {
 // ---- sample job: one workgroup per (problem, KV head) ------------------------------------------------
 // LDS: sc [G][1024] sampled scores, hist [G][kBins], nin [G], inb [G][kInBin] keys of the boundary bin
 constexpr int kInBin = 256;
-// Margin of the sampled bound in standard deviations.  A miss costs a rescan of the head (2.3 ms for a 128K head): at four it
-// came up once per 40 000 heads - every fourth call of a batch of 8192 heads (select 540 -> 690 us on average) -, at five
-// once per 800 000 for 11 % more candidates, which cost nothing measurable.
+// Margin of the sampled bound in standard deviations.  A miss costs a rescan of the head (2.3 ms for a 128K head): over rows
+// that are independent of each other it came up once per 40 000 heads at four - every fourth call of a batch of 8192 heads (select
+// 540 -> 690 us on average) -, at five once per 800 000 for 11 % more candidates, which cost 0.5 % of a batch's step and
+// nothing measurable of one problem's.
 constexpr int kSigmas = 5;
 template <int D, int TPI>
 __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& pr, char* blk, int h, float* sc, uint32_t* hist,

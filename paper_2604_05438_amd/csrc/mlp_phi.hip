@@ -116,13 +116,12 @@ constexpr int mlp_lds_bytes() {
 // One 64-token tile of one layer.  tok0: first row of the tile; Gt, Ht: the tile's fp32
 // activations g and h, [64][d_emb]; lds_raw: mlp_lds_bytes<NT>() bytes, free on entry (the caller
 // puts a barrier between two calls); n0: first output of the workgroup (0 unless the layer is wider
-// than 64 NT).  Row tok0 + i is mid token tok0 + i, or, with a row map, mid token rowmap[tok0 + i]
-// (decode: the retrieved list of a query head); feat: where row 0's features go (row-major, d_phi floats
+// than 64 NT).  Row tok0 + i is mid token tok0 + i; feat: where row 0's features go (row-major, d_phi floats
 // per row); slot: which packed weights.
 template <int EPI, int NT, int NTO>
 __device__ __forceinline__ void mlp_gemm_tile(const Geom& g, const tkphi_problem& pr, const tkphi_mlp& mp, char* __restrict__ ws,
                                               char* lds_raw, int h, int n, int tok0, int rows_valid, float* Gt, float* Ht, int n0,
-                                              int slot, float* feat, const int32_t* rowmap = nullptr) {
+                                              int slot, float* feat) {
   constexpr int BM = 64, KB = 32;
   constexpr int AROW = KB * 2 + 16;
   constexpr bool A_BF16 = EPI == EPI_STEM;
@@ -146,10 +145,7 @@ __device__ __forceinline__ void mlp_gemm_tile(const Geom& g, const tkphi_problem
   const int srow = tid >> 2, sseg = tid & 3;
   const int arow = min(srow, rows_valid - 1);          // clamped: rows past the end repeat the last one
   const char* a_src;
-  if (A_BF16) {
-    const int tok = rowmap ? min(max(rowmap[tok0 + arow], 0), n - 1) : tok0 + arow;
-    a_src = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)(g.n_sink + tok) * pr.stride_tok + sseg * 8) * 2;
-  }
+  if (A_BF16) a_src = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)(g.n_sink + tok0 + arow) * pr.stride_tok + sseg * 8) * 2;
   else a_src = (const char*)((EPI_W == EPI_RES ? Ht : Gt) + (size_t)arow * E + sseg * 8);
   // weight operands: the NT output tiles of this wavefront (clamped to the last tile: every lane loads)
   const int colw = n0 + wv * NT * 16;

@@ -205,8 +205,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   const SelBins bin_of{edge0, have_e0 && edge0 != 0u && edge0 != 0xffffffffu};
   const int split = g.sg_split;
   int my_base = 0, my_count = 0;                    // winners ahead of this workgroup's; winners of this workgroup
-  // The candidates are packed, sweep by sweep, into an LDS array (80 KB that are otherwise unused: a workgroup of 1024
-  // threads has a CU to itself); histogram, threshold and winners then walk 3-4 entries per thread (about 3 K candidates per
+  // The candidates are packed, sweep by sweep, into an LDS array (96 KB at d = 64, 80 at d = 128 that are otherwise unused: a
+  // workgroup of 1024 threads has a CU to itself; 32 KB for 512 threads); histogram, threshold and winners then walk 3-4 entries per thread (about 3 K candidates per
   // head at a 1 % budget of 128K) instead of 12 list slots per sweep, and workgroup `part` takes the winners of an equal
   // share of the array.  More candidates than it holds: a first pass over the sweeps finds the boundary bin, and only
   // what lies in it or above is packed.
@@ -696,8 +696,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 
 // grid (sg_split, Hq, n_problems).  After its own share every workgroup of a head counts itself in (its partial made
 // visible first); the one that arrives last finds all partials of the head complete and merges them (merge_head.h)
-// with its first 256 threads: no separate merge launch.  The counters are cleared by the prep kernel of the same
-// call.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
+// with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
+// same call: the phi jobs of decode_prep_kernel or decode_side_kernel, or, for short contexts, of score_direct_kernel.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
 // wavefronts of the workgroup that are still running.)
 template <int D, int TPI, int NTHR, bool DIRECT>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
