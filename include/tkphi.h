@@ -139,7 +139,8 @@ typedef struct tkphi_tuning {
                              1 = layer-wise launches per token block (residual + output fused),
                              2 = all four layers as separate launches                                    */
   int32_t select_mode;    /* decode pipeline of the bf16 matrix-core shapes: 0 = by the bounds (filtered where it
-                             measured faster: max_K at most 1/12 of the largest mid-region),
+                             measured faster: max_K at most 1/64 of the largest mid-region, or, by the
+                             number of heads and for short contexts, up to 1/12),
                              1 = spill (score_mid writes
                              every score and chunk histograms; plan / emit / resolve select from them),
                              2 = filtered (a sampled lower bound of the K-th score prunes what the score pass
@@ -253,7 +254,8 @@ typedef struct tkphi_problem {
 
 /* Bytes of DEVICE workspace tkphi_build_summaries / tkphi_decode need for the given
  * launch bounds (the larger of the two; a decode that is handed less may still run, in a smaller and slower
- * launch geometry).  Returns 0 if the config is invalid.
+ * launch geometry).  For long contexts, per problem, query head and mid token: about 5 bytes where the spill pipeline
+ * runs, 10 (budgets beyond 1/64 of batches of more than 128 heads) or 20 with the candidate lists of the filtered one.  Returns 0 if the config is invalid.
  * The workspace must be 256-byte aligned.  Its contents need not be preserved between
  * calls and need not be initialised.  Two calls that overlap in time (different
  * streams) must not share a workspace. */
@@ -297,8 +299,9 @@ tkphi_status tkphi_decode(const tkphi_config* cfg /*HOST*/,
  * or score chunks takes those (same retrieved sets, sums in another order).  The scratch memory is a
  * static device array of TKPHI_STATIC_SCRATCH_BYTES inside the library, of which every GPU the
  * library runs on holds one copy until the process ends.  A request whose decode scratch does not
- * fit (a 128K-token layer of 24 query heads, for one) fails with TKPHI_EWORKSPACE and enqueues nothing; TKPHI_PHI_MLP is refused with
- * TKPHI_EUNSUPPORTED (that path creates a stream on first use).  The call allocates nothing and frees
+ * fit (a 128K-token layer of 24 query heads at a budget of at most 1/64 of the mid-region, whose candidate lists take 60 MB, or of
+ * more than a fifth; between these it runs, on the spill pipeline) fails with TKPHI_EWORKSPACE and enqueues nothing; TKPHI_PHI_MLP
+ * is refused with TKPHI_EUNSUPPORTED (that path creates a stream on first use).  The call allocates nothing and frees
  * nothing.  The first call on a device resolves the array's address (with that device current: the
  * device of hip_stream must be the current device); a caller that captures calls into a HIP graph makes
  * one call outside the capture first.  All calls on one GPU share the array, which keeps the last call's contents

@@ -120,7 +120,7 @@ constexpr int mlp_lds_bytes() {
 // per row); slot: which packed weights.
 template <int EPI, int NT, int NTO>
 __device__ __forceinline__ void mlp_gemm_tile(const Geom& g, const tkphi_problem& pr, const tkphi_mlp& mp, char* __restrict__ ws,
-                                              char* lds_raw, int h, int n, int tok0, int rows_valid, float* Gt, float* Ht, int n0,
+                                              char* lds_raw, int h, int tok0, int rows_valid, float* Gt, float* Ht, int n0,
                                               int slot, float* feat) {
   constexpr int BM = 64, KB = 32;
   constexpr int AROW = KB * 2 + 16;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kThreads, 2) void mlp_gemm_kernel(Geom g, const tkp
   const tkphi_mlp mp = pr.mlp_k[h];
   float* Gb = (float*)(ws + g.off_act) + (size_t)h * g.mlp_block * g.d_emb;
   float* Hb = Gb + (size_t)g.Hkv * g.mlp_block * g.d_emb;
-  mlp_gemm_tile<EPI, NT, NTO>(g, pr, mp, ws, lds_raw, h, n, t0 + row0, rows_valid, Gb + (size_t)row0 * g.d_emb,
+  mlp_gemm_tile<EPI, NT, NTO>(g, pr, mp, ws, lds_raw, h, t0 + row0, rows_valid, Gb + (size_t)row0 * g.d_emb,
                               Hb + (size_t)row0 * g.d_emb, (int)blockIdx.y * 64 * NT, 0, key_feature_rows(g, pr, ws, 0, h, n));
 }
 

@@ -79,7 +79,7 @@ struct Geom {
                          //                                       first set itself where one workgroup takes a head (sg_split 1)
   size_t off_thr;        // uint32   [Hq]                        lower bound of the score key per query head
   size_t off_mcount;     // uint32   [Hq]                        filtered pipeline: workgroups of the fused select + gather kernel
-                         //                                       that have finished their share of the head (cleared by prep)
+                         //                                       that have finished their share of the head (cleared by the phi jobs)
   size_t off_sphi;       // float    [Hq][d]                     S_M^T phi_q
   size_t off_uphi;       // float    [Hq]                        phi_q . u_M
   size_t off_hist;       // uint16   [n_scan_chunks][Hq][kBins]  per-chunk histograms

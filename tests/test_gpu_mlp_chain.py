@@ -117,3 +117,34 @@ def test_hidden_units_far_outside(d_emb, cache):
     b.decode()
     assert b.status() & ~2 == 0
     PU.check_layer(w, O, 40, b, 0)
+
+
+def test_recomputing_decode_replays_from_a_hip_graph():
+    """A decode step without a feature cache (weight packing and the chain over the retrieved rows on the caller's stream, phi_q on
+    the library's, 150 KB of LDS asked for at each launch) captured after one call outside, replayed with eager steps between:
+    bit for bit the eager result."""
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS["l3b_128k"]
+    P = I.make_layer(w, L=3000)
+    P["mlp"] = I.make_mlp_phi(w, d_emb=512)
+    b = H.Batch(H.config_of(w, cache_features=False, d_emb=512), [P], [100], debug=True)
+    b.build()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        b.decode()
+        side.synchronize()
+        eager = b.result(0, "out").copy()
+        with torch.cuda.graph(graph, stream=side):
+            b.decode()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        b.dev[0]["out"].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(b.result(0, "out"), eager)
+        b.decode()
+        torch.cuda.synchronize()
+        assert np.array_equal(b.result(0, "out"), eager)
