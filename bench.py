@@ -229,7 +229,8 @@ def main() -> int:
     bytes_const = probs_per_step * (w.n_kv_heads * w.d_phi * (w.d_head + 1) * 4          # S, u
                                     + (w.n_q_heads + w.n_kv_heads) * w.d_phi * w.d_head * esz)   # Wq, Wk
     bytes_step = bytes_scan + bytes_gather + bytes_anchor + bytes_const
-    scan_kernel = "score_filtered_kernel" if stage_us.get("prep", 0.0) > 0 else "score_mid_kernel"
+    scan_kernel = ("score_mid_kernel" if stage_us.get("select", 0.0) == 0 else
+                   "score_filtered_kernel" if stage_us.get("prep", 0.0) > 0 else "score_fused_kernel")
     scan_s = stage_us["score_mid"] * 1e-6
     achieved = bytes_scan / scan_s / 1e9
 

@@ -323,8 +323,8 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg /*HOST*/,
  *   select_resolve, gather (exact branch + subtraction sums), merge (spill pipeline), phi_q (the
  *   three phi_q launches of the MLP feature maps, begin of the first to end of the third; or, for a
  *   batch on the filtered pipeline, the phi / anchor jobs of prep as a launch of their own), and the
- *   two kernels only the filtered pipeline has: prep (sampled score bound; for a few problems also phi_q,
- *   the summary terms and the anchors; runs first) and select (selection, gather and merge)
+ *   two kernels only the filtered pipeline has: prep (sampled score bound, for some calls also phi_q,
+ *   the summary terms and the anchors; runs first; for one or a few problems part of score_mid) and select (selection, gather and merge)
  * (0 for a stage that the given configuration and bounds do not launch).  Same validation and results as
  * tkphi_decode; creates and destroys HIP events (no device memory). */
 #define TKPHI_N_STAGES 9

@@ -2,7 +2,7 @@
 //
 // The exhaustive Top-K over the mid-region (Sec. "Models, tasks, and protocol") needs every score
 // s_i = q . k_i / sqrt(d_h) once, but only the scores that can still reach the top K have to
-// leave the chip.  Two kernels (one for short contexts):
+// leave the chip.  Two kernels (for batches; one otherwise):
 //
 //   decode_prep     one small launch of independent jobs that need no selection:
 //                   * sample: per KV head, the scores of an evenly spaced sample of mid-region rows
@@ -18,6 +18,8 @@
 //   score_filtered  the streaming pass over all mid-region keys, each KV head read once for its G
 //                   query heads; a score goes to memory only if its key is >= the head's bound
 //                   (about 2-3 K tokens per head instead of |M|), appended to per-wavefront lists.
+//   score_fused     both in one launch for one problem or a few (Geom::fused): the scan keeps its scores in LDS until the sample's
+//                   bound, which the sample workgroups hand over inside the launch, has come.
 //   score_direct    instead of both where contexts are short (Geom::direct): every score stored, one row per head,
 //                   with the phi and anchor jobs in the same launch.
 #include <algorithm>
@@ -60,31 +62,37 @@ constexpr int kInBin = 256;
 // 540 -> 690 us on average) -, at five once per 800 000 for 11 % more candidates, which cost 0.5 % of a batch's step and
 // nothing measurable of one problem's.
 constexpr int kSigmas = 5;
-template <int D, int TPI>
-__device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& pr, char* blk, int h, float* sc, uint32_t* hist,
-                                            uint32_t* inb, int* nin, char* stage_all) {
+// Heads gl0 .. gl0 + G - 1 of the group, by NTHR threads; FUSED: the bounds are also handed to the score workgroups of the same
+// launch (await_bounds).
+template <int D, int TPI, int NTHR, bool FUSED>
+__device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& pr, char* blk, int h, int gl0, int G, float* sc,
+                                            uint32_t* hist, uint32_t* inb, int* nin, char* stage_all) {
+  constexpr int NWV = NTHR / 64;
   constexpr int KS = D / 32, TOK = TPI * 16;
   // The sampled key rows are loaded whole-row-wise (a load instruction covers 64 / LPRW complete rows: one
   // workgroup pulls 2.6 times the bytes per second that it gets with the 16 rows x 64 bytes of the MFMA operand
   // layout) and pass through a wavefront-private LDS strip of one 16-row tile into the operand layout.
   constexpr int LPRW = D / 8, RPI = 64 / LPRW, NLD = TOK / RPI, ROWP = D * 2 + 16;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, kg = lane >> 4;
-  const int G = g.G;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int Ksel = max(0, min(min(pr.topk, n), g.max_K));
-  uint32_t* thr = (uint32_t*)(blk + g.off_thr) + h * G;
+  auto publish = [&](int gl, uint32_t edge) {
+    const int gq = h * g.G + gl0 + gl;
+    ((uint32_t*)(blk + g.off_thr))[gq] = edge;
+    if (FUSED) store_agent((uint64_t*)(blk + g.off_hand) + gq, ((uint64_t)g.tag << 32) | edge);
+  };
   if (n == 0 || Ksel == 0 || g.sel_test == 1) {         // nothing to retrieve (or test: a bound nothing passes)
-    if (tid < G) thr[tid] = 0xffffffffu;
+    if (tid < G) publish(tid, 0xffffffffu);
     return;
   }
   if (g.sel_test == 2) {                                // test: no pruning at all
-    if (tid < G) thr[tid] = 0u;
+    if (tid < G) publish(tid, 0u);
     return;
   }
   const int m = sample_size(n);
   TKPHI_PHASE((blk - g.off_problem0), 3);
   TKPHI_WAVE_MARK((blk - g.off_problem0), 64);       // sample job entered
-  for (int i = tid; i < G * kBins; i += kPrepThreads) hist[i] = 0u;
+  for (int i = tid; i < G * kBins; i += NTHR) hist[i] = 0u;
   if (tid < G) nin[tid] = 0;
   ScoreFrag bq[KS];
   load_query_frags<D>(g, pr, h, bq);
@@ -92,7 +100,7 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
   const char* K0 = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + (size_t)(lane % LPRW) * 16;
   char* stage = stage_all + (size_t)wv * 16 * ROWP;
   TKPHI_WAVE_MARK((blk - g.off_problem0), 80);       // before the key loads
-  for (int i0 = wv * TOK; i0 < m; i0 += kPrepWaves * TOK) {
+  for (int i0 = wv * TOK; i0 < m; i0 += NWV * TOK) {
     u32x4 raw[NLD];
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
@@ -118,20 +126,24 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
       st_floatx4 acc = (st_floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < KS; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].v, bq[j].v, acc, 0, 0, 0);
-      // lane (r < G, kg) holds head r's scores of samples i0 + t 16 + 4 kg + {0..3}: to LDS, so that every lane
+      // lane (r, kg) holds head r's scores of samples i0 + t 16 + 4 kg + {0..3}: to LDS, so that every lane
       // takes part in what follows (12 of 64 lanes hold all the scores here)
-      if (r < G) *(st_floatx4*)(sc + r * 1024 + i0 + t * 16 + 4 * kg) = acc;
+      if (r >= gl0 && r < gl0 + G) *(st_floatx4*)(sc + (r - gl0) * 1024 + i0 + t * 16 + 4 * kg) = acc;
     }
   }
   __syncthreads();
   TKPHI_PHASE((blk - g.off_problem0), 4);
-  // thread t <-> sample t: first-level histogram per head
-  uint32_t key[kMaxGroup];
+  // thread t <-> samples t, t + NTHR, ..: first-level histogram per head
+  constexpr int SPT = 1024 / NTHR, MG = FUSED ? 1 : kMaxGroup;
+  uint32_t key[SPT][MG];
 #pragma unroll
-  for (int gl = 0; gl < kMaxGroup; ++gl) {
-    if (gl < G && tid < m) {
-      key[gl] = score_key(sc[gl * 1024 + tid] * g.score_scale + 0.0f);
-      atomicAdd(&hist[gl * kBins + key_bin(key[gl])], 1u);
+  for (int k = 0; k < SPT; ++k) {
+#pragma unroll
+    for (int gl = 0; gl < MG; ++gl) {
+      if (gl < G && tid + k * NTHR < m) {
+        key[k][gl] = score_key(sc[gl * 1024 + tid + k * NTHR] * g.score_scale + 0.0f);
+        atomicAdd(&hist[gl * kBins + key_bin(key[k][gl])], 1u);
+      }
     }
   }
   __syncthreads();
@@ -172,10 +184,13 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
   __syncthreads();
   // inside that bin: the rem-th largest sampled key is the bound (ranked by counting; the bin holds a few dozen samples)
 #pragma unroll
-  for (int gl = 0; gl < kMaxGroup; ++gl) {
-    if (gl < G && tid < m && sh_bin[gl] >= 0 && key_bin(key[gl]) == sh_bin[gl]) {
-      const int at = atomicAdd(&nin[gl], 1);
-      if (at < kInBin) inb[gl * kInBin + at] = key[gl];
+  for (int k = 0; k < SPT; ++k) {
+#pragma unroll
+    for (int gl = 0; gl < MG; ++gl) {
+      if (gl < G && tid + k * NTHR < m && sh_bin[gl] >= 0 && key_bin(key[k][gl]) == sh_bin[gl]) {
+        const int at = atomicAdd(&nin[gl], 1);
+        if (at < kInBin) inb[gl * kInBin + at] = key[k][gl];
+      }
     }
   }
   __syncthreads();
@@ -196,7 +211,7 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) edge = max(edge, (uint32_t)__shfl_xor((int)edge, o));
     }
-    if (lane == 0) thr[gl] = edge;
+    if (lane == 0) publish(gl, edge);
   }
 }
 
@@ -371,7 +386,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
 #endif
   if (job == 0) {
     uint32_t* hist = (uint32_t*)(sh_dyn + g.G * 1024);
-    prep_sample<D, TPI>(g, pr, blk, h, sh_dyn, hist, hist + g.G * kBins, sh_nin, (char*)(hist + g.G * (kBins + kInBin)));
+    prep_sample<D, TPI, kPrepThreads, false>(g, pr, blk, h, 0, g.G, sh_dyn, hist, hist + g.G * kBins, sh_nin, (char*)(hist + g.G * (kBins + kInBin)));
     TKPHI_PHASE(ws, 2);
 #ifdef TKPHI_PHASE_CLOCK
     if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) ((unsigned long long*)(ws + 16))[27] = clock64();
@@ -392,7 +407,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
 // against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
 // as large, gain nothing at 128K and lose 2 us at 32K (the first group is consumed later).  Groups of TPI / 2 for batches at
 // d = 64: within 0.6 % either way over 66 batches of 4 to 400 sequences on the same buffers.
-template <int D, int TPI, bool STREAM, bool STRIP>
+template <int D, int TPI, bool STRIP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                   char* __restrict__ ws) {
   const int p = blockIdx.z, h = blockIdx.y;
@@ -411,8 +426,75 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
   extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  scan_wave_slot<D, TPI, TPI / 4, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r, -1, false,
+  scan_wave_slot<D, TPI, TPI / 4, 2, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r,
                                                        (lds_u32x2)sh_heads + (STRIP ? wv * g.G * g.cand_T : 0));
+}
+
+// ---- sample and score pass in one launch ------------------------------------------------------------------------------
+// The bounds of KV head h (lane gl < G: head h G + gl) from the sample workgroups, which lie ahead of every score workgroup in
+// the launch and wait for nothing, so the words arrive; the polls are counted all the same, and a head whose bound has not come
+// by then goes unpruned (every score a candidate: slower, nothing else).  A word is (tag, bound): tags differ from call to call,
+// and the merging workgroup of the select kernel clears the word, for replays of a captured call.
+constexpr int kBoundPolls = 1 << 14;     // of a microsecond or so
+__device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk, int h) {
+  const uint64_t* word = (const uint64_t*)(blk + g.off_hand) + h * g.G + min((int)(threadIdx.x & 63), g.G - 1);
+  uint64_t w = 0;
+  for (int k = 0; k < kBoundPolls; ++k) {
+    w = load_agent(word);
+    if (__all((uint32_t)(w >> 32) == g.tag)) break;
+    __builtin_amdgcn_s_sleep(4);
+  }
+  return (uint32_t)(w >> 32) == g.tag ? (uint32_t)w : 0u;
+}
+
+// grid (Hq (2 + n_atiles) + Hkv n_scan_chunks, n_problems), 512 threads: a sample job per query head, the phi and anchor jobs
+// (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks.  A score workgroup keeps its scores in LDS (G scan_chunk floats) and lists those that reach the bound at
+// its end, when the sample is long since done: the launch that only sampled had nothing to run beside it.  Bound by HBM for long
+// contexts (3B layer at 128K: 268 MB in 45 us behind 2 us of prologue; CUs that also sample end 3 us late, the lists take 1.6), by
+// the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10.7).  Prep + score
+// launches / this one: 11.1 + 48.7 / 52.5 us and 7.6 + 9.6 / 13.5 us.
+constexpr int kFusedThreads = 512;
+template <int D, int TPI>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+                                                                                                              char* __restrict__ ws) {
+  extern __shared__ __attribute__((aligned(16))) float sh_dyn[];
+  __shared__ int sh_n;
+  constexpr int NWV = kFusedThreads / 64;
+  const int p = blockIdx.y;
+  int x = blockIdx.x;
+  if (x == 0 && p == 0) write_device_status(g, probs, ws, true);
+  const tkphi_problem pr = probs[p];
+  if (pr.L < 1 || pr.L > g.max_L) return;
+  char* blk = problem_block(g, ws, p);
+  if (x < g.Hq) {
+    uint32_t* hist = (uint32_t*)(sh_dyn + 1024);
+    prep_sample<D, TPI, kFusedThreads, true>(g, pr, blk, x / g.G, x % g.G, 1, sh_dyn, hist, hist + kBins, &sh_n, (char*)(hist + kBins + kInBin));
+    return;
+  }
+  x -= g.Hq;
+  if (x < g.Hq) {
+    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
+    side_phi<0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+    return;
+  }
+  x -= g.Hq;
+  if (x < g.Hq * g.n_atiles) {
+    side_anchor(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
+    return;
+  }
+  x -= g.Hq * g.n_atiles;
+  const int n = mid_size(pr.L, g.n_sink, g.n_tail);
+  const int n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
+  const int h = x / g.n_scan_chunks, chunk = (x % g.n_scan_chunks + h + p * g.Hkv) % g.n_scan_chunks;
+  if (chunk >= n_chunks) return;
+  if (threadIdx.x == 0) sh_n = NWV;
+  ScoreFrag bq[D / 32];
+  load_query_frags<D>(g, pr, h, bq);
+  lds_barrier();
+  scan_keep<D, TPI / 4, NWV>(g, pr, h, n, n_chunks, chunk, bq, (lds_f32)sh_dyn, &sh_n);
+  const uint32_t edge = await_bounds(g, blk, h);
+  lds_barrier();
+  list_kept<D, NWV>(g, pr, blk, h, n, n_chunks, chunk, (lds_f32)sh_dyn, edge);
 }
 
 // The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query
@@ -461,7 +543,20 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   ScoreFrag bq[D / 32];
   load_query_frags<D>(g, pr, h, bq);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  scan_wave_slot<D, TPI, TPI / 4, 2, false, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, -1, false, (lds_u32x2) nullptr);
+  scan_wave_slot<D, TPI, TPI / 4, 2, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, (lds_u32x2) nullptr);
+}
+
+void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
+  dim3 grid(g.Hq + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0) + g.Hq * (1 + g.n_atiles), g.n_problems);
+  const size_t sample = (size_t)(1024 + kBins + kInBin) * 4 + (size_t)(kFusedThreads / 64) * 16 * (g.d * 2 + 16);
+  const size_t lds = std::max(sample, (size_t)g.G * g.scan_chunk * sizeof(float));       // (more than the 6 KB of the phi jobs)
+  const auto launch = [&](auto fn) {
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
+    TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kFusedThreads), lds, s, g, probs, ws);
+  };
+  if (g.d == 128) launch(score_fused_kernel<128, 4>);
+  else launch(score_fused_kernel<64, 8>);
 }
 
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
@@ -497,9 +592,8 @@ void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, 
   dim3 grid(g.n_scan_chunks, g.Hkv, g.n_problems);
   const size_t lds = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
   const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
-  if (g.d == 128 && g.stream_keys) { if (g.head_strip) launch(score_filtered_kernel<128, 4, true, true>); else launch(score_filtered_kernel<128, 4, true, false>); }
-  else if (g.d == 128) { if (g.head_strip) launch(score_filtered_kernel<128, 4, false, true>); else launch(score_filtered_kernel<128, 4, false, false>); }
-  else { if (g.head_strip) launch(score_filtered_kernel<64, 8, false, true>); else launch(score_filtered_kernel<64, 8, false, false>); }
+  if (g.d == 128) { if (g.head_strip) launch(score_filtered_kernel<128, 4, true>); else launch(score_filtered_kernel<128, 4, false>); }
+  else { if (g.head_strip) launch(score_filtered_kernel<64, 8, true>); else launch(score_filtered_kernel<64, 8, false>); }
 }
 
 }  // namespace tkphi

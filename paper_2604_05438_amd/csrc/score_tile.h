@@ -13,6 +13,8 @@ typedef unsigned int st_u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) st_u32x2* lds_u32x2;
 typedef __attribute__((address_space(1))) st_u32x2* glb_u32x2;
 typedef __attribute__((address_space(1))) float* glb_f32;
+typedef __attribute__((address_space(3))) float* lds_f32;
+typedef __attribute__((address_space(3))) st_floatx4* lds_f32x4;
 union ScoreFrag {
   u32x4 u;
   st_bf16x8 v;
@@ -42,32 +44,28 @@ __device__ __forceinline__ size_t cand_region(const Geom& g, int gq, int chunk, 
 
 // One wavefront: slot `wslot` of chunk `chunk` of KV head h (n mid tokens, n_chunks chunks).
 //   edge_r   lower bound of the score key for the query head of this lane's column r (ignored for r >= G)
-//   only_gl  -1: every head of the group; else only head h G + only_gl is written
 //   strip    null, or this wavefront's LDS strip of G x cand_T entries: the compact heads of the G lists are
 //            collected there and go to memory at the end as whole lines (a head is cand_T contiguous entries, the
 //            four slots of a chunk adjoin), instead of one 8-byte store per candidate scattered through the scan:
 //            fewer partly written lines for the L2 to write back in the middle of the read stream
-//   rescan   write the rescan set of lists, compact heads and counts (the select kernel's second attempt reads
-//            only that set, so what a first attempt reads is never overwritten while another workgroup reads it)
 // Lane (r, kg) ends up with the scores of head r for tokens base + t 16 + 4 kg + i, so each list is
 // written by the four lanes of its column, in the order (unit, t, i, kg).
 // SUB: 16-token tiles loaded and contracted together; NB: groups of SUB tiles in registers, NB - 1 of them on their way while one
-// is contracted (the rescan, which must not cost the kernel around it registers, runs one tile at a time); STREAM: non-temporal key loads
+// is contracted
 // STRIP: `strip` is used (a template parameter, and address spaces spelled out on every pointer stored through: a store that
 // might go to LDS or to memory becomes a flat store, after which the compiler waits for every load in flight)
 // DIRECT: no bound and no lists; every score goes to the head's row of Geom::off_scores
-template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP, bool DIRECT = false>
+template <int D, int TPI, int SUB, int NB, bool STRIP, bool DIRECT = false>
 __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks,
-                                               int chunk, int wslot, const ScoreFrag (&bq)[D / 32], uint32_t edge_r,
-                                               int only_gl, bool rescan, lds_u32x2 strip) {
+                                               int chunk, int wslot, const ScoreFrag (&bq)[D / 32], uint32_t edge_r, lds_u32x2 strip) {
   constexpr int KS = D / 32;
   constexpr int TOK = TPI * 16;         // tokens per wavefront and unit
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int G = g.G;
-  const bool col_live = r < G && (only_gl < 0 || r == only_gl);
+  const bool col_live = r < G;
   const int gq = h * G + min(r, G - 1);
-  const glb_u32x2 list = (glb_u32x2)(blk + (rescan ? g.off_resf : g.off_candf)) + cand_region(g, gq, chunk, wslot);
-  const glb_u32x2 head = (glb_u32x2)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)g.cand_T;
+  const glb_u32x2 list = (glb_u32x2)(blk + g.off_candf) + cand_region(g, gq, chunk, wslot);
+  const glb_u32x2 head = (glb_u32x2)(blk + g.off_candc) + (((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)g.cand_T;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
   const glb_f32 score_row = (glb_f32)(blk + g.off_scores) + (size_t)gq * g.mid_stride;   // (DIRECT)
   const uint64_t col_lanes = 0x0001000100010001ull << r;     // the four lanes of this column
@@ -90,7 +88,7 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
     for (int t = 0; t < SUB; ++t) {
       const char* rp = Kl + (uint64_t)(uint32_t)min(base + t * 16 + r, n - 1) * row_bytes;     // rows past the end repeat the last one
 #pragma unroll
-      for (int j = 0; j < KS; ++j) f[t][j].u = STREAM ? gload128_stream(rp + j * 64) : gload128(rp + j * 64);
+      for (int j = 0; j < KS; ++j) f[t][j].u = gload128(rp + j * 64);
     }
   };
   auto contract = [&](int base, const ScoreFrag (&f)[SUB][KS]) {
@@ -145,41 +143,160 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
   constexpr int GPU = TPI / SUB;
   const int n_groups = g.scan_chunk / (4 * TOK) * GPU;
   auto group_base = [&](int q) { return q < n_groups ? chunk_unit_token(g, n_chunks, chunk, q / GPU) + wslot * TOK + (q % GPU) * SUB * 16 : n; };
-  if constexpr (NB > 1) {
-    // (requests and contractions are unconditional - past the end they repeat the last row, whose tokens are then dead - so that
-    // the compiler can count the loads in flight on every path)
-    int bases[NB];
+  static_assert(NB > 1, "one group on its way while another is contracted");
+  // (requests and contractions are unconditional - past the end they repeat the last row, whose tokens are then dead - so that
+  // the compiler can count the loads in flight on every path)
+  int bases[NB];
 #pragma unroll
-    for (int u = 0; u < NB - 1; ++u) { bases[u] = group_base(u); request(bases[u], a[u]); }
-    float_bound();                       // (behind the first requests: the bound itself is still on its way)
-    for (int q = 0; bases[0] < n; q += NB) {
+  for (int u = 0; u < NB - 1; ++u) { bases[u] = group_base(u); request(bases[u], a[u]); }
+  float_bound();                         // (behind the first requests: the bound itself is still on its way)
+  for (int q = 0; bases[0] < n; q += NB) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        constexpr int kAhead = NB - 1;
-        bases[(u + kAhead) % NB] = group_base(q + u + kAhead);
-        request(bases[(u + kAhead) % NB], a[(u + kAhead) % NB]);
-        __builtin_amdgcn_sched_barrier(0);
-        contract(bases[u], a[u]);
-      }
-    }
-  } else {
-    float_bound();
-    for (int q = 0, base = group_base(0); base < n; base = group_base(++q)) {
-      request(base, a[0]);
-      __builtin_amdgcn_sched_barrier(0);   // all loads of the group are in flight before the first MFMA
-      contract(base, a[0]);
+    for (int u = 0; u < NB; ++u) {
+      constexpr int kAhead = NB - 1;
+      bases[(u + kAhead) % NB] = group_base(q + u + kAhead);
+      request(bases[(u + kAhead) % NB], a[(u + kAhead) % NB]);
+      __builtin_amdgcn_sched_barrier(0);
+      contract(bases[u], a[u]);
     }
   }
   if constexpr (STRIP) {                // (LDS operations of one wavefront execute in order: no barrier)
     for (int gl = 0; gl < G; ++gl) {
       const int c = min(__shfl(cnt, gl), T);          // lane gl is lane (r = gl, kg = 0) of column gl
-      const glb_u32x2 hd = (glb_u32x2)(blk + (rescan ? g.off_resc : g.off_candc)) + (((size_t)(h * G + gl) * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)T;
+      const glb_u32x2 hd = (glb_u32x2)(blk + g.off_candc) + (((size_t)(h * G + gl) * g.n_scan_chunks + chunk) * 4 + wslot) * (size_t)T;
       for (int i = lane; i < c; i += 64) hd[i] = strip[gl * T + i];
     }
   }
   if constexpr (DIRECT) return;
   if (col_live && kg == 0)
-    ((uint32_t*)(blk + (rescan ? g.off_rescount : g.off_ccount)))[((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot] = (uint32_t)min(cnt, cap);
+    ((uint32_t*)(blk + g.off_ccount))[((size_t)gq * g.n_scan_chunks + chunk) * 4 + wslot] = (uint32_t)min(cnt, cap);
+}
+
+// The score pass of a workgroup of NWV wavefronts that learns the bounds only at its end (Geom::fused): all unscaled scores of
+// the chunk stay in LDS, keep[head of the group][position], position = token's place in the order of the chunk's units.
+// The wavefronts draw groups of SUB tiles from a counter in LDS: of two workgroups that share a CU the older one gets its loads
+// served first, so that with a fixed share for each the second half ran alone for the last quarter of the pass (3B layer at 128K: the
+// older ones done after 33 us, the younger after 44).  Rows of 256 bytes are read with non-temporal loads: the pass itself takes as
+// long, but the lists, phi_q and the problem record are still in the caches when the select kernel starts (25.5 -> 24.9 us); of rows
+// of 128 bytes the two loads that share a cache line would fetch it twice (a batch's pass 20 % longer).
+template <int D, int SUB, int NWV>
+__device__ __forceinline__ void scan_keep(const Geom& g, const tkphi_problem& pr, int h, int n, int n_chunks, int chunk,
+                                          const ScoreFrag (&bq)[D / 32], lds_f32 keep, int* next /*LDS, NWV*/) {
+  constexpr int KS = D / 32, GT = SUB * 16;
+  const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const size_t row_bytes = (size_t)pr.stride_tok * 2;
+  const char* const Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + kg * 16;
+  constexpr int per_unit = keep_unit(D) / GT;
+  const int n_groups = g.scan_chunk / GT;
+  auto group_base = [&](int q) { return q < n_groups ? chunk_unit_token(g, n_chunks, chunk, q / per_unit) + (q % per_unit) * GT : n; };
+  auto draw = [&]() {
+    int q = 0;
+    if (lane == 0) q = atomicAdd(next, 1);
+    return __builtin_amdgcn_readfirstlane(q);
+  };
+  ScoreFrag a[2][SUB][KS];
+  auto request = [&](int base, ScoreFrag (&f)[SUB][KS]) {      // (unconditional: rows past the end repeat the last one)
+#pragma unroll
+    for (int t = 0; t < SUB; ++t) {
+      const char* rp = Kl + (uint64_t)(uint32_t)min(base + t * 16 + r, n - 1) * row_bytes;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) f[t][j].u = D == 128 ? gload128_stream(rp + j * 64) : gload128(rp + j * 64);
+    }
+  };
+  auto contract = [&](int q, int base, const ScoreFrag (&f)[SUB][KS]) {
+    st_floatx4 acc[SUB];
+#pragma unroll
+    for (int t = 0; t < SUB; ++t) {
+      acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][j].v, bq[j].v, acc[t], 0, 0, 0);
+    }
+    if (r < g.G && base < n) {
+#pragma unroll
+      for (int t = 0; t < SUB; ++t) *(lds_f32x4)(keep + r * g.scan_chunk + q * GT + t * 16 + 4 * kg) = acc[t];
+    }
+  };
+  int q[2], base[2];
+  q[0] = wv;
+  base[0] = group_base(q[0]);
+  request(base[0], a[0]);
+  while (base[0] < n) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      q[u ^ 1] = draw();
+      base[u ^ 1] = group_base(q[u ^ 1]);
+      request(base[u ^ 1], a[u ^ 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      contract(q[u], base[u], a[u]);
+    }
+  }
+}
+
+// The lists of a chunk whose scores scan_keep left in LDS, once the bounds are known (lane gl < G: the bound of head h G + gl):
+// list (head, slot) takes the positions [slot, slot + 1) scan_chunk / 4, 1024 of them at a time: a lane marks which of its 16 (4 of
+// every 256) pass, one prefix sum over the lanes places them (a ballot and a store per four positions took 5 us of the pass of
+// a 3B layer at 128K instead of 1).  A list is in the order (1024 positions, lane, position).
+template <int D, int NWV>
+__device__ __forceinline__ void list_kept(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks, int chunk,
+                                          lds_f32 keep, uint32_t edge_lane) {
+  const int lane = threadIdx.x & 63, slot = g.scan_chunk / 4, T = g.cand_T;
+  constexpr int U = keep_unit(D);        // = g.scan_unit
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int first = chunk_unit_token(g, n_chunks, chunk, 0), step = chunk_unit_token(g, n_chunks, chunk, 1) - first;
+  auto token = [&](int pos) { return first + pos / U * step + pos % U; };
+  auto score = [&](float x) { return fmaf(x, g.score_scale, 0.0f); };        // + 0.0f: -0 -> +0, equal scores get equal keys
+  if (pr.scores) {
+    for (int gl = 0; gl < g.G; ++gl)
+      for (int pos = threadIdx.x; pos < g.scan_chunk; pos += NWV * 64)
+        if (token(pos) < n) ((glb_f32)pr.scores)[(size_t)(h * g.G + gl) * n + token(pos)] = score(keep[gl * g.scan_chunk + pos]);
+  }
+  for (int job = wv; job < 4 * g.G; job += NWV) {
+    const int gl = job >> 2, ws = job & 3, gq = h * g.G + gl, pos0 = ws * slot + 4 * lane;
+    const uint32_t edge = (uint32_t)__builtin_amdgcn_readlane((int)edge_lane, gl);
+    const size_t idx = ((size_t)gq * g.n_scan_chunks + chunk) * 4 + ws;
+    const glb_u32x2 list = (glb_u32x2)(blk + g.off_candf) + idx * (size_t)slot;
+    const glb_u32x2 head = (glb_u32x2)(blk + g.off_candc) + idx * (size_t)T;
+    const lds_f32 row = keep + gl * g.scan_chunk + ws * slot;
+    const bool plain = edge >= 0x80000000u;      // the bound is a score >= 0: keys compare as the scores' bits do, as integers
+    const int edge_bits = (int)(edge & 0x7fffffffu);
+    int cnt = 0;
+    for (int o = 0; o < slot; o += 1024) {
+      st_floatx4 s4[4];
+      uint32_t live = 0, pass = 0;         // bit 4 k + i: position o + 256 k + 4 lane + i
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int at4 = o + 256 * k + 4 * lane;
+        s4[k] = *(lds_f32x4)(row + min(at4, slot - 4));
+        const int left = at4 < slot ? n - token(pos0 + o + 256 * k) : 0;      // (positions of dead tokens may hold anything)
+        live |= ((1u << min(max(left, 0), 4)) - 1u) << (4 * k);
+      }
+      if (plain) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pass |= __float_as_int(score(s4[k][i])) >= edge_bits ? 1u << (4 * k + i) : 0u;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pass |= score_key(score(s4[k][i])) >= edge ? 1u << (4 * k + i) : 0u;
+      }
+      pass &= live;
+      const int mine = __popc(pass), incl = wave_scan_incl(mine);
+      int at = cnt + incl - mine;
+      while (pass) {
+        const int b = __builtin_ctz(pass), in_slot = o + 64 * (b & 12) + 4 * lane + (b & 3);
+        const st_u32x2 e = (st_u32x2){__float_as_uint(score(row[in_slot])), (uint32_t)token(ws * slot + in_slot)};
+        if (at < T) head[at] = e;
+        else list[at] = e;
+        ++at;
+        pass &= pass - 1;
+      }
+      cnt += __builtin_amdgcn_readlane(incl, 63);
+    }
+    if (lane == 0) ((uint32_t*)(blk + g.off_ccount))[idx] = (uint32_t)cnt;
+  }
 }
 
 // Smallest score key whose first-level bin is >= t (key_bin is monotone in the key), so that

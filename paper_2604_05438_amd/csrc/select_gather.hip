@@ -44,21 +44,47 @@ template <int D, int NTHR> constexpr int kBatchOf = (D == 64 && NTHR == 1024) ? 
 // winners of a workgroup kept in LDS (the rest are re-read from the retrieved list)
 template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 
-// every mid token of query head gq becomes a candidate: the head's lists are written again with no bound, into
-// the rescan set (what the score pass wrote stays as it is: other workgroups of the head may still be reading it)
+// every mid token of query head gq becomes a candidate: list k of the rescan set takes the tokens [k cap, (k + 1) cap), cap =
+// scan_chunk / 4 (what the score pass wrote stays as it is: other workgroups of the head may still be reading it)
 // (one 16-token tile in flight per wavefront: the rare path must not cost the common one registers)
-template <int D, int TPI, int NTHR>
-__device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int n, int n_chunks) {
+template <int D, int NTHR>
+__device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int n, int n_reg) {
   const int h = gq / g.G, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
+  const int cap = g.scan_chunk / 4, T = g.cand_T;
   ScoreFrag bq[D / 32];
   load_query_frags<D>(g, pr, h, bq);
-  for (int reg = wv; reg < n_chunks * 4; reg += NTHR / 64)
-    scan_wave_slot<D, TPI, 1, 1, false, false>(g, pr, blk, h, n, n_chunks, reg >> 2, reg & 3, bq, 0u, gq % g.G, true, (lds_u32x2) nullptr);
+  const char* Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + kg * 16;
+  for (int reg = wv; reg < n_reg; reg += NTHR / 64) {
+    const size_t idx = (size_t)gq * g.n_scan_chunks * 4 + reg;
+    const glb_u32x2 list = (glb_u32x2)(blk + g.off_resf) + idx * (size_t)cap;
+    const glb_u32x2 head = (glb_u32x2)(blk + g.off_resc) + idx * (size_t)T;
+    const int t0 = reg * cap, cnt = max(0, min(cap, n - t0));
+    for (int o = 0; o < cnt; o += 16) {
+      const char* rp = Kl + (uint64_t)(uint32_t)min(t0 + o + r, n - 1) * (uint64_t)(pr.stride_tok * 2);
+      ScoreFrag a[D / 32];
+#pragma unroll
+      for (int j = 0; j < D / 32; ++j) a[j].u = gload128(rp + j * 64);
+      st_floatx4 acc = (st_floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < D / 32; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].v, bq[j].v, acc, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int at = o + 4 * kg + i;
+        const st_u32x2 e = (st_u32x2){__float_as_uint(fmaf(acc[i], g.score_scale, 0.0f)), (uint32_t)(t0 + at)};
+        if (r == gq % g.G && at < cnt) {
+          if (at < T) head[at] = e;
+          else list[at] = e;
+        }
+      }
+    }
+    if (lane == 0) ((uint32_t*)(blk + g.off_rescount))[idx] = (uint32_t)cnt;
+  }
 }
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
 // DIRECT: Geom::direct (a row of scores per head instead of candidate lists)
-template <int D, int TPI, int NTHR, bool DIRECT>
+template <int D, int NTHR, bool DIRECT>
 __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
                                                    int part, int gq, int p) {
   constexpr int KS = D / 32;
@@ -173,7 +199,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     // (every workgroup of the head takes this branch, the counts it depends on being the score pass's, and writes
     // the same values to the rescan set: no ordering between them is needed.  A head's only workgroup may write the first set
     // over: every thread has read its counts before the barrier above, and nothing else of that set is read again)
-    rescan_head<D, TPI, NTHR>(g, pr, blk, gq, n, n_chunks);
+    rescan_head<D, NTHR>(g, pr, blk, gq, n, n_reg);
     ccount = (const uint32_t*)(blk + g.off_rescount) + (size_t)gq * n_reg_max;
     compact = (const uint2*)(blk + g.off_resc) + (size_t)gq * n_reg_max * T;
     sparse = (const uint2*)(blk + g.off_resf) + (size_t)gq * n_reg_max * cap_w;
@@ -699,12 +725,12 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
 // same call: the phi jobs of decode_prep_kernel or decode_side_kernel, or, for short contexts, of score_direct_kernel.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
 // wavefronts of the workgroup that are still running.)
-template <int D, int TPI, int NTHR, bool DIRECT>
+template <int D, int NTHR, bool DIRECT>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
   const int part = blockIdx.x, gq = blockIdx.y, p = blockIdx.z;
-  select_gather_body<D, TPI, NTHR, DIRECT>(g, probs, ws, part, gq, p);
+  select_gather_body<D, NTHR, DIRECT>(g, probs, ws, part, gq, p);
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
   // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads; the
@@ -721,15 +747,17 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   __syncthreads();
   if (!sh_last || threadIdx.x >= kThreads) return;
   if (exports) __threadfence();
+  // (the handed-over bound has been read: a replay of this call from a graph, whose tag is the same, must not find it)
+  if (g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;
   merge_head<true, true>(g, probs, ws, gq, p, mode);
 }
 
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
   dim3 grid(g.sg_split, g.Hq, g.n_problems);       // (Geom::n_tiles of this pipeline: one partial per workgroup)
   const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SELECT, fn, grid, dim3(threads), 0, s, g, probs, ws, mode); };
-  if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 4, 1024, true>, 1024); else launch(select_gather_kernel<128, 4, 1024, false>, 1024); }
-  else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 8, 512, true>, 512); else launch(select_gather_kernel<64, 8, 512, false>, 512); }
-  else { if (g.direct) launch(select_gather_kernel<64, 8, 1024, true>, 1024); else launch(select_gather_kernel<64, 8, 1024, false>, 1024); }
+  if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
+  else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 512, true>, 512); else launch(select_gather_kernel<64, 512, false>, 512); }
+  else { if (g.direct) launch(select_gather_kernel<64, 1024, true>, 1024); else launch(select_gather_kernel<64, 1024, false>, 1024); }
 }
 
 }  // namespace tkphi

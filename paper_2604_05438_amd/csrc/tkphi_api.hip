@@ -1,6 +1,7 @@
 // Host layer of libtkphi: argument validation, launch geometry / workspace planning and
 // the extern "C" entry points declared in include/tkphi.h.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -163,33 +164,34 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->scan_unit = g->use_mfma ? (g->d == 128 ? 256 : 512) : 256;
   // spill pipeline: about 1024 workgroups, 256..8192 tokens each (uint16 chunk histograms: < 65536)
   int sc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 1024), 256, 8192), 256);
-  if (g->filtered && !compact) {
-    if (n_problems > 1) {
-      // Filtered pipeline, batches: 4096 workgroups by the bounds of the call, a power of two of tokens each.  Ragged batches have
-      // far fewer, which then still even out over the CUs (8 sequences of 8K to 32K at d = 128: score pass 74 -> 58 us against a
-      // target of 1024, 16 of 16K to 64K at d = 64: 168 -> 152).  At most 4096 tokens where sequences may be longer than 32K: a
-      // workgroup of 8192 that starts last alone on its CU ends 30 us late (64 sequences of 16K to 64K: step 743 -> 708 us at
-      // d = 64, 1364 -> 1280 at d = 128; 28 of 128K, where the last round is full: 1472 -> 1486), below that at most 8192 (200 of
-      // 16K: 966 against 990 us with 4096).
-      const int most = g->max_mid > 32768 ? 4096 : 8192;
-      sc = 256;
-      while (sc < most && (int64_t)sc * 4096 < units) sc *= 2;
-      while (sc < 32768 && ceil_div(g->max_mid, std::max(sc, g->scan_unit)) * 4 * kMinListHead > sweep) sc *= 2;
-    } else {
-      // One problem: the pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (3B layer
-      // at 50 K tokens: 232 workgroups of 1792 tokens 22.4 us, 400 of 1024 25.0, 312 of 1280 29.2); one workgroup per CU
-      // streams 7 % slower at d = 128 and, with 2.7 times the score work per byte, 40 % at d = 64.  Against that stands what the
-      // select kernel pays for more lists: 0.35 us per 1000 slots of their compact heads.
-      const double ideal_us = (double)units * g->d * 2 / 6.2e6;
-      double best = 0.0;
-      for (int c = g->scan_unit; c <= std::max(8192, g->scan_unit); c += g->scan_unit) {
-        const int64_t chunks = std::max<int64_t>(1, ceil_div(g->max_mid, c)), rounds = ceil_div(chunks * g->Hkv, 256);
-        if (chunks * 4 * kMinListHead > sweep && c + g->scan_unit <= 8192) continue;
-        const double eff = (double)units / ((double)rounds * 256 * c) * (rounds > 1 ? 1.0 : g->d == 128 ? 0.93 : 0.7);
-        const double cost = ideal_us / eff + 0.35e-3 * (double)(chunks * 4 * list_head(c, std::min<int64_t>(max_K, g->max_mid), g->max_mid, sweep, chunks));
-        if (best == 0.0 || cost <= best) { best = cost; sc = c; }
-      }
-    }
+  // Filtered pipeline, one or a few problems: sample and score pass in one launch, whose workgroups hold the scores of their chunk in
+  // LDS (at most half of it: two workgroups per CU).  One problem: the pass lasts as long as its busiest CU and wants one
+  // workgroup on each.  A few (ragged: up to half of the chunks that the bounds allow for are empty): about 1024 workgroups.  At most
+  // 128 chunks per KV head (one sweep of the select kernel).  Two launches / one, us per step: 3B layer at 16K 41 / 35, 50K 56 / 48,
+  // 128K 84 / 77; 1B layer at 32K 37.5 / 34, 96K 52 / 43; 1B sequences of 4K to 16K, 2 of them 35 / 32, 4 of them 50 / 42; 2 3B
+  // sequences of 32K to 64K 75 / 70.  Beyond 32 KV heads the sample is a small part and the workgroups that wait for it cost more:
+  // 8 3B sequences of 16K to 64K 193 / 200, 16 1B ones 206 / 224.
+  const int unit = keep_unit(g->d), keep_most = 79872 / (g->G * (int)sizeof(float)) / unit * unit;
+  int64_t keep_chunk = ceil_div(g->max_mid, std::clamp(256 / g->Hkv, 1, 128));
+  if (n_problems > 1)
+    for (keep_chunk = 1024; keep_chunk * 1024 < units || ceil_div(g->max_mid, keep_chunk) > 128;) keep_chunk *= 2;
+  keep_chunk = std::min<int64_t>(align_up((size_t)std::max<int64_t>(keep_chunk, 1), unit), keep_most);
+  g->fused = g->filtered && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
+             (tn.scan_chunk > 0 ? tn.scan_chunk <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128) ? 1 : 0;
+  if (g->fused) {
+    g->scan_unit = unit;
+    sc = (int)keep_chunk;
+  } else if (g->filtered && !compact) {
+    // Filtered pipeline, batches: 4096 workgroups by the bounds of the call, a power of two of tokens each.  Ragged batches have
+    // far fewer, which then still even out over the CUs (8 sequences of 8K to 32K at d = 128: score pass 74 -> 58 us against a
+    // target of 1024, 16 of 16K to 64K at d = 64: 168 -> 152).  At most 4096 tokens where sequences may be longer than 32K: a
+    // workgroup of 8192 that starts last alone on its CU ends 30 us late (64 sequences of 16K to 64K: step 743 -> 708 us at
+    // d = 64, 1364 -> 1280 at d = 128; 28 of 128K, where the last round is full: 1472 -> 1486), below that at most 8192 (200 of
+    // 16K: 966 against 990 us with 4096).
+    const int most = g->max_mid > 32768 ? 4096 : 8192;
+    sc = 256;
+    while (sc < most && (int64_t)sc * 4096 < units) sc *= 2;
+    while (sc < 32768 && ceil_div(g->max_mid, std::max(sc, g->scan_unit)) * 4 * kMinListHead > sweep) sc *= 2;
   }
   if (tn.scan_chunk > 0) sc = tn.scan_chunk;
   // Short contexts, as long as every token fits one sweep and the packed array of the select kernel: one unit per chunk, all
@@ -211,7 +213,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // moment instead of far-apart ranges (3B layer at 128K: 47.9 against 49.5 us); with few chunks per head or
   // several problems contiguous ranges are as fast or faster (16 ragged sequences at d = 64, chunks of 1024: 137 against 153 us)
   g->interleave = tn.interleave ? (tn.interleave == 1 ? 1 : 0)
-                                : (g->use_mfma && g->scan_unit < g->scan_chunk && g->n_scan_chunks >= 64 && (n_problems == 1 || !g->filtered)) ? 1 : 0;
+                                : (g->use_mfma && g->scan_unit < g->scan_chunk && (g->fused || (g->n_scan_chunks >= 64 && (n_problems == 1 || !g->filtered)))) ? 1 : 0;
   if (!g->use_mfma || g->scan_unit >= g->scan_chunk) g->interleave = 0;
   g->sel_test = tn.select_test;
   // gather: tiles of kPairsPerWG retrieved tokens per query head
@@ -266,11 +268,6 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->cand_T = compact || !g->filtered || g->direct ? (int)align_up((size_t)std::max(kMinListHead, g->scan_chunk / 4 * 3 / 32), kSweepEntries)
                                       : list_head(g->scan_chunk, std::min(max_K, g->max_mid), g->max_mid, sweep, g->n_scan_chunks);
   g->head_strip = (size_t)4 * g->G * g->cand_T * sizeof(uint2) <= 32768 ? 1 : 0;
-  // Non-temporal key loads leave the candidate lists, phi_q and the problem record in the caches for the select kernel
-  // (l3b_128k: score pass unchanged, select 25.5 -> 24.9 us, step -1.4 us).  Only for one problem of 256-byte rows:
-  // with 128-byte rows the two loads that share a cache line fetch it twice (ragged batch: score pass +20 %), and
-  // the 28-layer call measured 2 % slower
-  g->stream_keys = (n_problems == 1 && g->d == 128) ? 1 : 0;
   g->off_candc = p;   p = align_up(p + lists * 4 * g->cand_T * sizeof(uint2), 256);
   g->off_ccount = p;  p = align_up(p + lists * 4 * sizeof(uint32_t), 256);
   if (one_set) {
@@ -284,7 +281,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->off_mcount = p;  p = align_up(p + (size_t)g->Hq * sizeof(uint32_t), 256);
   g->off_sphi = p;    p = align_up(p + (size_t)g->Hq * g->d * sizeof(float), 256);
   g->off_uphi = p;    p = align_up(p + (size_t)g->Hq * sizeof(float), 256);
-  g->off_hist = p;    p = align_up(p + (size_t)g->n_scan_chunks * g->Hq * kBins * sizeof(uint16_t), 256);
+  g->off_hist = g->off_hand = p;    p = align_up(p + (size_t)g->n_scan_chunks * g->Hq * kBins * sizeof(uint16_t), 256);
   g->off_plan = p;    p = align_up(p + (size_t)g->Hq * sizeof(SelPlan), 256);
   g->off_diag = p;    p = align_up(p + (size_t)g->n_scan_chunks * g->Hq * 4 * sizeof(float), 256);
   g->off_chunkoff = p; p = align_up(p + (size_t)g->Hq * g->n_scan_chunks * 2 * sizeof(int32_t), 256);
@@ -437,12 +434,25 @@ static tkphi_status side_stream(SideStream** out) {
   return TKPHI_OK;
 }
 
+// Marks the bounds that one call's sample workgroups hand to its score workgroups: another one for every call, spread over 32
+// bits so that what other calls leave in the same scratch memory is not taken for it, never 0 (what a finished call leaves)
+static uint32_t next_tag() {
+  static std::atomic<uint32_t> calls{0};
+  uint32_t x = calls.fetch_add(1, std::memory_order_relaxed);
+  x = (x ^ 0x5bd1e995u) * 0x9e3779b1u;               // (one to one)
+  x ^= x >> 15;
+  return x ? x : 0x9e3779b1u;
+}
+
 static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems, char* ws, int acct, hipStream_t s) {
   if (g.filtered && !g.diag) {         // (the diagnostics are by-products of the spill pipeline's emit pass)
     Geom gf = g;
     gf.n_tiles = g.sg_split;           // one partial per workgroup of the fused select + gather kernel
     if (gf.direct) {
       launch_score_direct(gf, problems, ws, s);
+    } else if (gf.fused) {
+      gf.tag = next_tag();
+      launch_score_fused(gf, problems, ws, s);
     } else {
       launch_prep(gf, problems, ws, s);
       launch_score_filtered(gf, problems, ws, s);

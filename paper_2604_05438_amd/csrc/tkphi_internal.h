@@ -31,6 +31,8 @@ constexpr int kMinListHead = 24;       // smallest Geom::cand_T
 constexpr int kPairsPerWG = 64;        // gather: retrieved tokens per workgroup (16 per wavefront)
 
 // ---- launch geometry + workspace layout -------------------------------------------
+constexpr int keep_unit(int d) { return d == 128 ? 64 : 128; }   // Geom::scan_unit where Geom::fused
+
 struct Geom {
   int Hq, Hkv, G, d, dphi, n_sink, n_tail, dtype;
   int use_mfma;          // bf16 storage with d_phi == d_head: matrix-core kernels
@@ -51,9 +53,10 @@ struct Geom {
   int filtered;          // 1: decode may run the filtered pipeline (prep, score_filtered, select_gather, merge):
                          // bf16 matrix-core shapes, exp-affine maps, budgets well below the mid-region size
   int direct;            // 1: filtered pipeline for short contexts: all scores stored (off_scores), no bound, no prep launch
+  int fused;             // 1: filtered pipeline, sample and score pass in one launch: the scores wait in LDS for the bound (off_hand)
+  uint32_t tag;          // fused: the bounds of this call carry it (not 0)
   int cand_T;            // filtered pipeline: entries of a candidate list kept in the compact array (multiple of 12)
   int head_strip;        // 1: the score pass collects the compact list heads in LDS (4 G cand_T entries fit 32 KB)
-  int stream_keys;       // 1: the filtered score pass reads the keys with non-temporal loads
   int sel_test;          // tkphi_tuning::select_test (0 unless a test forces the rescan or the no-pruning path)
   int n_tiles;           // gather: ceil(max_K / kPairsPerWG) retrieved-token tiles per query head; one partial each
   int sg_split;          // filtered pipeline: workgroups per query head of the fused select + gather kernel (0 if it cannot run);
@@ -78,6 +81,8 @@ struct Geom {
                          //                                       rescans a head without a bound, read by its second attempt; the
                          //                                       first set itself where one workgroup takes a head (sg_split 1)
   size_t off_thr;        // uint32   [Hq]                        lower bound of the score key per query head
+  size_t off_hand;       // uint64   [Hq]                        fused: (tag, bound) of a head, handed from its sample workgroup to the
+                         //                                       score workgroups of the running launch (shares off_hist's memory)
   size_t off_mcount;     // uint32   [Hq]                        filtered pipeline: workgroups of the fused select + gather kernel
                          //                                       that have finished their share of the head (cleared by the phi jobs)
   size_t off_sphi;       // float    [Hq][d]                     S_M^T phi_q
@@ -141,6 +146,7 @@ constexpr int kMaxScanChunks = 2048;   // chunk offsets are scanned in LDS by `p
 void launch_score_mid(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);              // filtered pipeline
+void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);       // filtered pipeline, Geom::fused
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);      // filtered pipeline, Geom::direct
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);  // includes the merge
@@ -389,6 +395,17 @@ __device__ __forceinline__ void write_device_status(const Geom& g, const tkphi_p
 #define TKPHI_PHASE_VALUE(ws, slot, v) do {} while (0)
 #endif
 
+// Inclusive prefix sum over the lanes of a wavefront by data-parallel-primitive moves (inside rows of 16 lanes, then across them)
+__device__ __forceinline__ int wave_scan_incl(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+  return x;
+}
+
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every global load the wavefront
 // has in flight (its fences cover global memory); where a barrier only hands LDS data from one wavefront to
 // another, this one lets prefetched global loads stay in flight across it.  Not for data exchanged through
@@ -432,6 +449,9 @@ __device__ __forceinline__ void wait_vm_loads() {   // at most N vector memory o
 // whole L2.
 __device__ __forceinline__ void store_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__device__ __forceinline__ void store_agent(uint64_t* p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint64_t load_agent(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // mid-region size of a problem; 0 if the anchors cover everything
 __device__ __forceinline__ int mid_size(int L, int n_sink, int n_tail) {

@@ -26,6 +26,29 @@ def test_score_groups_at_every_end(shape, chunk, interleave):
         PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+@pytest.mark.parametrize("shape,unit", [("l3b_128k", 64), ("l1b_32k", 128)])
+@pytest.mark.parametrize("units,interleave", [(1, 0), (3, 1), (5, 2), (17, 1)])
+def test_kept_scores_at_every_end(shape, unit, units, interleave):
+    """One launch for the sample and the scores of one problem or a few: chunks of 1, 3, 5 and 17 units (a list is a quarter of a chunk:
+    16 to 544 positions), mid-regions that end around units and
+    chunks, and bounds of either sign (budgets beyond half of the mid-region).  Scores, index sets and outputs against the oracle."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    chunk = units * unit
+    for mids in ([1], [unit - 1], [unit + 1], [chunk], [chunk + 1], [3 * chunk + unit // 2 + 1], [2500, 37, 2 * chunk - 1]):
+        layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(mids)]
+        for share in (0.02, 0.6):
+            ks = [max(1, int(m * share)) for m in mids]
+            b = H.Batch(H.config_of(w, tuning={"select_mode": 2, "scan_chunk": chunk, "interleave": interleave}), layers, ks, debug=True)
+            b.build()
+            for _ in range(2):
+                b.decode()
+            assert b.status() & ~2 == 0  # (the residual clamp may fire where nearly every mid token is retrieved)
+            for i, (P, k) in enumerate(zip(layers, ks)):
+                PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
 @pytest.mark.parametrize("shape,n_mid,k,select_test", [
     ("l3b_128k", 11000, 100, 0), ("l1b_32k", 13000, 700, 0),      # a hot stretch overflows the compact heads of its lists: several sweeps
     ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # short contexts: no lists, the row of scores is packed as it is
