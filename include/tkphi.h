@@ -98,14 +98,15 @@ typedef enum tkphi_mode { TKPHI_MODE_SUB = 0, TKPHI_MODE_NOSUB = 1, TKPHI_MODE_T
  *               the build keeps a group's features in the workspace until they are contracted
  *               into S, u, and every decode step sends the retrieved key rows through the same
  *               chain (Sec. "Retrieved-token subtraction": retrieved-key feature
- *               recomputation).  tkphi_decode evaluates phi_q with
- *               three small launches on a second stream that the library creates per device
- *               on first use (default priority, kept until the process ends): forked from the
- *               caller's stream at the start of the call and joined to it before the gather, so
- *               the caller still sees one in-order unit of work; such calls serialise on a
- *               mutex while they enqueue.  The device of hip_stream must be the current device;
- *               a caller that captures decode calls into a HIP graph makes one call outside the
- *               capture first (the stream and its two events are created then). */
+ *               recomputation).  tkphi_decode evaluates phi_q in three stages.  For several
+ *               problems they are small launches on a second stream that the library creates per
+ *               device on the first MLP call (default priority, kept until the process ends):
+ *               forked from the caller's stream at the start of the call and joined to it before
+ *               the gather, so the caller still sees one in-order unit of work; for one problem
+ *               they run on the caller's stream.  Such calls serialise on a mutex while they
+ *               enqueue.  The device of hip_stream must be the current device; a caller that
+ *               captures decode calls into a HIP graph makes one call outside the capture first
+ *               (the stream and its two events are created then). */
 typedef enum tkphi_phi_kind { TKPHI_PHI_EXP_AFFINE = 0, TKPHI_PHI_MLP = 1 } tkphi_phi_kind;
 
 /* One head's MLP feature map.  DEVICE struct (arrays of it live in device memory); weights are
@@ -321,7 +322,7 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg /*HOST*/,
  * duration in milliseconds of each stage:
  *   score_mid (either pipeline's score pass), select_plan (+ the exp-affine phi_q), select_emit,
  *   select_resolve, gather (exact branch + subtraction sums), merge (spill pipeline), phi_q (the
- *   three phi_q launches of the MLP feature maps, begin of the first to end of the third; or, for a
+ *   phi_q launches of the MLP feature maps, begin of the first to end of the last; or, for a
  *   batch on the filtered pipeline, the phi / anchor jobs of prep as a launch of their own), and the
  *   two kernels only the filtered pipeline has: prep (sampled score bound, for some calls also phi_q,
  *   the summary terms and the anchors; runs first; for one or a few problems part of score_mid) and select (selection, gather and merge)

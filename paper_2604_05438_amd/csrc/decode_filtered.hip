@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "decode_side.h"
+#include "mlp_query.h"
 #include "score_tile.h"
 #include "tkphi_internal.h"
 
@@ -449,6 +450,7 @@ __device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk,
 
 // grid (Hq (2 + n_atiles) + Hkv n_scan_chunks, n_problems), 512 threads: a sample job per query head, the phi and anchor jobs
 // (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks.  A score workgroup keeps its scores in LDS (G scan_chunk floats) and lists those that reach the bound at
+// (With MLP maps, Geom::list, the first stage of phi_q instead of the phi and anchor jobs, behind the score chunks.)
 // its end, when the sample is long since done: the launch that only sampled had nothing to run beside it.  Bound by HBM for long
 // contexts (3B layer at 128K: 268 MB in 45 us behind 2 us of prologue; CUs that also sample end 3 us late, the lists take 1.6), by
 // the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10.7).  Prep + score
@@ -472,17 +474,23 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
     return;
   }
   x -= g.Hq;
-  if (x < g.Hq) {
-    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
-    side_phi<0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+  if (!g.list) {
+    if (x < g.Hq) {
+      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
+      side_phi<0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+      return;
+    }
+    x -= g.Hq;
+    if (x < g.Hq * g.n_atiles) {
+      side_anchor(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
+      return;
+    }
+    x -= g.Hq * g.n_atiles;
+  } else if (x >= g.Hkv * g.n_scan_chunks) {
+    x -= g.Hkv * g.n_scan_chunks;
+    mlp_phi_q_slice<0>(g, pr, blk, x % g.Hq, x / g.Hq);
     return;
   }
-  x -= g.Hq;
-  if (x < g.Hq * g.n_atiles) {
-    side_anchor(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
-    return;
-  }
-  x -= g.Hq * g.n_atiles;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
   const int h = x / g.n_scan_chunks, chunk = (x % g.n_scan_chunks + h + p * g.Hkv) % g.n_scan_chunks;
@@ -521,7 +529,7 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
 template <int D, int TPI, int EARLY>
 __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
-  const int n_side = g.G * (1 + g.n_atiles);
+  const int n_side = g.list ? 0 : g.G * (1 + g.n_atiles);
   const int x = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
   if (x == 0 && h == 0 && p == 0) write_device_status(g, probs, ws, true);
   const tkphi_problem pr = probs[p];
@@ -547,7 +555,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
 }
 
 void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(g.Hq + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0) + g.Hq * (1 + g.n_atiles), g.n_problems);
+  dim3 grid(g.Hq * (g.list ? 1 + g.d_emb / 64 : 2 + g.n_atiles) + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0), g.n_problems);
   const size_t sample = (size_t)(1024 + kBins + kInBin) * 4 + (size_t)(kFusedThreads / 64) * 16 * (g.d * 2 + 16);
   const size_t lds = std::max(sample, (size_t)g.G * g.scan_chunk * sizeof(float));       // (more than the 6 KB of the phi jobs)
   const auto launch = [&](auto fn) {
@@ -560,7 +568,7 @@ void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hip
 }
 
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(g.G * (1 + g.n_atiles) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
+  dim3 grid((g.list ? 0 : g.G * (1 + g.n_atiles)) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
   // (the phi job's rows of S ahead of everything else: 0.3 us off one 3B layer of 4K or 9K tokens, but at 158 registers instead of
   // 73 the whole launch of 256 problems of 1.5K takes 258 us instead of 224 at d = 128, 154 instead of 128 at d = 64)
   if (g.d == 128 && g.n_problems == 1) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4, 16>), grid, dim3(kThreads), 0, s, g, probs, ws);

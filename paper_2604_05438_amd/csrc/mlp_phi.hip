@@ -21,6 +21,8 @@
 // the matrix cores, not by HBM.
 #include <algorithm>
 
+#include "mlp_pack.h"
+#include "mlp_query.h"
 #include "tkphi_internal.h"
 
 namespace tkphi {
@@ -35,26 +37,6 @@ union Frag {
 
 enum { EPI_STEM = 0, EPI_HID = 1, EPI_RES = 2, EPI_OUT = 3, EPI_RESOUT = 4 };
 
-// ------------------------------------------------------------------------------------
-// Weights in MFMA-fragment order.  A matrix W [N][Kd] (row-major bf16) is cut into blocks of 16
-// outputs x 32 inputs; block (ct, ks) is stored as the 1 KB a wavefront loads as one operand:
-// lane (r, kg) -> the 16 bytes W[16 ct + r][32 ks + 8 kg .. + 7], at byte 16 lane of the block.  Blocks of the d_emb-wide
-// matrices lie in groups of four output tiles, K step by K step: block (ct, ks) at KB (ct / 4 Kd/32 + ks) 4 + ct mod 4
-// (a wavefront's four operands of a K step are 4 KB in a row); those of Wo at KB ct Kd/32 + ks.
-// `chain`: for W1, W2 and Wo lane (r, kg) takes the inputs 32 ks + 4 kg + {0 .. 3} and 32 ks + 16 + 4 kg + {0 .. 3} instead:
-// the order in which a lane of the persistent chain holds the outputs of two neighbouring tiles.
-// The GEMM's operand loads then are whole 1 KB lines instead of 16 pieces of 64 B (measured 19 %
-// faster).  One launch packs the four matrices of every KV head of the problems p0 .. p0 + gridDim.z - 1
-// into the workspace, problem p0 + z into slot z: grid (ceil(pieces / 256), Hkv, problems); per head
-// Ws | W1 | W2 | Wo, in this order.
-// ------------------------------------------------------------------------------------
-__device__ __forceinline__ size_t packed_bytes_per_head(const Geom& g) {
-  return ((size_t)g.d_emb * g.d + (size_t)2 * g.d_emb * g.d_emb + (size_t)g.dphi * g.d_emb) * 2;
-}
-
-__device__ __forceinline__ const char* packed_weights(const Geom& g, const char* ws, int slot, int h) {
-  return ws + g.off_wpack + ((size_t)slot * g.Hkv + h) * packed_bytes_per_head(g);
-}
 // Where the key features of KV head h of a problem (n mid tokens) live: the caller's cache, or, without one, the
 // workspace buffer of the problem's slot in the group being built.
 __device__ __forceinline__ float* key_feature_rows(const Geom& g, const tkphi_problem& pr, char* ws, int slot, int h, int n) {
@@ -62,33 +44,14 @@ __device__ __forceinline__ float* key_feature_rows(const Geom& g, const tkphi_pr
   return (float*)(ws + g.off_feat) + ((size_t)slot * g.Hkv + h) * (size_t)g.max_mid * g.dphi;
 }
 
+// grid (ceil(pieces / 256), Hkv, problems): packs problem p0 + z into slot z
 __global__ __launch_bounds__(kThreads) void mlp_pack_weights_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int p0, bool chain) {
   const int h = blockIdx.y, slot = blockIdx.z;
   const tkphi_problem pr = probs[p0 + slot];
   if (pr.L < 1 || pr.L > g.max_L) return;
-  const tkphi_mlp mp = pr.mlp_k[h];
-  const int E = g.d_emb;
-  const size_t n_s = (size_t)E * g.d / 8, n_1 = (size_t)E * E / 8, n_o = (size_t)g.dphi * E / 8;   // 16-byte pieces
-  size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  if (q >= n_s + 2 * n_1 + n_o) return;
-  char* dst = ws + g.off_wpack + ((size_t)slot * g.Hkv + h) * packed_bytes_per_head(g) + q * 16;
-  // (the layer says how a matrix is packed; two layers may share one buffer)
-  const bool stem = q < n_s, out = q >= n_s + 2 * n_1;
-  const char* W = (const char*)(stem ? mp.Ws : out ? mp.Wo : q < n_s + n_1 ? mp.W1 : mp.W2);
-  const int Kd = stem ? g.d : E;
-  q -= stem ? 0 : out ? n_s + 2 * n_1 : q < n_s + n_1 ? n_s : n_s + n_1;
-  const int lane = (int)(q & 63), r = lane & 15, kg = lane >> 4;
-  const size_t blk = q >> 6;
-  const int KS = Kd / 32;
-  const int ks = (int)(out ? blk % KS : blk / 4 % KS), ct = (int)(out ? blk / KS : blk / 4 / KS * 4 + blk % 4);
-  const char* row = W + ((size_t)(ct * 16 + r) * Kd + ks * 32) * 2;
-  if (chain && !stem) {
-    const u32x2 a = *(const u32x2*)(row + kg * 8), b = *(const u32x2*)(row + 32 + kg * 8);
-    *(u32x4*)dst = (u32x4){a.x, a.y, b.x, b.y};
-  } else {
-    *(u32x4*)dst = gload128(row + kg * 16);
-  }
+  const size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (q < packed_pieces(g)) pack_piece(g, ws, pr.mlp_k[h], slot, h, q, chain);
 }
 
 // ------------------------------------------------------------------------------------
@@ -771,12 +734,13 @@ void launch_mlp_build(const Geom& g, const tkphi_problem* probs, char* ws, hipSt
   }
 }
 
-// Decode without a feature cache: phi_k of every query head's retrieved keys -> Geom::off_selphi (after the select)
+// Decode without a feature cache: phi_k of every query head's retrieved keys -> Geom::off_selphi (after the select, which has packed
+// the weights where Geom::list)
 void launch_mlp_sel_features(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   if (g.max_mid == 0 || g.max_K == 0) return;
   for (int p0 = 0; p0 < g.n_problems; p0 += g.mlp_group) {
     const int np = std::min(g.mlp_group, g.n_problems - p0);
-    launch_mlp_pack(g, probs, ws, s, p0, np, true);
+    if (!g.list) launch_mlp_pack(g, probs, ws, s, p0, np, true);
     launch_mlp_chain<true>(g, probs, ws, s, p0, np);
   }
 }
@@ -926,74 +890,29 @@ __global__ __launch_bounds__(kThreads) void summary_from_cache_kernel(Geom g, co
   }
 }
 
-// ------------------------------------------------------------------------------------
-// phi_q of every query head (decode side): the same chain as matrix-vector products in fp32,
-// three launches so that each layer is spread over the chip.  grid (slices, Hq, n_problems),
-// 1024 threads; a workgroup owns 64 output rows of its layer:
-//   stage 0: g0 = Ws q + bs (every workgroup of the head recomputes it: 2 d d_emb bytes from L2),
-//            h[rows] = GeLU(W1[rows] g0 + b1[rows]); slice 0 also stores g0
-//   stage 1: g[rows] = g0[rows] + alpha (W2[rows] h + b2[rows])
-//   stage 2: phi_q[rows] = exp(Wo[rows] g + bo[rows])
-// ------------------------------------------------------------------------------------
-// Every global load of a workgroup (weights of its first row groups, biases, input vector) is
-// issued before anything is consumed: one memory round trip per launch.
-template <int STAGE, int SPL>   // SPL = 1 for d_emb <= 512, 2 for 1024
+// grid (slices, Hq, n_problems), 1024 threads
+template <int STAGE, int SPL>
 __global__ __launch_bounds__(kSelThreads) void mlp_phi_q_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                 char* __restrict__ ws) {
-  __shared__ float xs[128];
-  __shared__ float vin[1024], sb[1024];
-  __shared__ float sb2[64], sg[64];
-  const int gq = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
-  const tkphi_problem pr = probs[p];
+  const tkphi_problem pr = probs[blockIdx.z];
   if (pr.L < 1 || pr.L > g.max_L) return;
-  char* blk = problem_block(g, ws, p);
-  const int E = g.d_emb;
-  float* gbuf = (float*)(blk + g.off_mlpq) + (size_t)gq * 2 * E;
-  float* hbuf = gbuf + E;
-  const tkphi_mlp mp = pr.mlp_q[gq];
-  const int j0 = blockIdx.x * 64;
-  const int nrows = min(64, (STAGE == 2 ? g.dphi : E) - j0);
-  const char* Wslice = (const char*)(STAGE == 0 ? mp.W1 : STAGE == 1 ? mp.W2 : mp.Wo) + (size_t)j0 * E * 2;
-  const float* bslice = (STAGE == 0 ? mp.b1 : STAGE == 1 ? mp.b2 : mp.bo) + j0;
-  u32x4 ts[8], tw[8];
-  if (STAGE == 0) gemv_load<1>(mp.Ws, E, g.d, 0, ts);
-  gemv_load<SPL>(Wslice, nrows, E, 0, tw);
-  if (tid < 64) sb2[tid] = bslice[min(tid, nrows - 1)];
-  if (STAGE == 0) {
-    if (tid < g.d) xs[tid] = Elem<uint16_t>::load1(pr.q, (int64_t)gq * g.d + tid);
-    if (tid < E) sb[tid] = mp.bs[tid];
-    __syncthreads();
-    gemv_bf16_rows<1>(mp.Ws, E, g.d, xs, ts, [&](int j, float dot) { vin[j] = dot + sb[j]; });
-    __syncthreads();
-    if (blockIdx.x == 0 && tid < E) gbuf[tid] = vin[tid];
-    gemv_bf16_rows<SPL>(Wslice, nrows, E, vin, tw, [&](int j, float dot) { hbuf[j0 + j] = gelu_erf(dot + sb2[j]); });
-  } else if (STAGE == 1) {
-    if (tid < E) vin[tid] = hbuf[tid];
-    if (tid < 64) sg[tid] = gbuf[j0 + min(tid, nrows - 1)];
-    __syncthreads();
-    gemv_bf16_rows<SPL>(Wslice, nrows, E, vin, tw, [&](int j, float dot) { gbuf[j0 + j] = fmaf(mp.alpha, dot + sb2[j], sg[j]); });
-  } else {
-    if (tid < E) vin[tid] = gbuf[tid];
-    __syncthreads();
-    float* phiq = (float*)(blk + g.off_phiq) + (size_t)gq * g.dphi;
-    gemv_bf16_rows<SPL>(Wslice, nrows, E, vin, tw, [&](int j, float dot) { phiq[j0 + j] = expf(dot + sb2[j]); });
-  }
+  mlp_phi_q_slice<STAGE, SPL>(g, pr, problem_block(g, ws, blockIdx.z), blockIdx.y, blockIdx.x);
 }
 
+// all three stages, or those that have not ridden in the score and select launches (Geom::list); one timed stage
 void launch_mlp_phi_q(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   dim3 ge(g.d_emb / 64, g.Hq, g.n_problems), go((g.dphi + 63) / 64, g.Hq, g.n_problems);
-  KernelTimer* t = g_kernel_timer;            // the three launches are one timed stage
+  KernelTimer* t = g_kernel_timer;
   if (t) t->used[ST_PHIQ] = true;
   hipEvent_t e0 = t ? t->start[ST_PHIQ] : nullptr, e1 = t ? t->stop[ST_PHIQ] : nullptr;
-  if (g.d_emb <= 512) {
-    hipExtLaunchKernelGGL((mlp_phi_q_kernel<0, 1>), ge, dim3(kSelThreads), 0, s, e0, nullptr, 0, g, probs, ws);
-    hipLaunchKernelGGL((mlp_phi_q_kernel<1, 1>), ge, dim3(kSelThreads), 0, s, g, probs, ws);
-    hipExtLaunchKernelGGL((mlp_phi_q_kernel<2, 1>), go, dim3(kSelThreads), 0, s, nullptr, e1, 0, g, probs, ws);
-  } else {
-    hipExtLaunchKernelGGL((mlp_phi_q_kernel<0, 2>), ge, dim3(kSelThreads), 0, s, e0, nullptr, 0, g, probs, ws);
-    hipLaunchKernelGGL((mlp_phi_q_kernel<1, 2>), ge, dim3(kSelThreads), 0, s, g, probs, ws);
-    hipExtLaunchKernelGGL((mlp_phi_q_kernel<2, 2>), go, dim3(kSelThreads), 0, s, nullptr, e1, 0, g, probs, ws);
-  }
+  const auto launch = [&](auto k0, auto k1, auto k2) {
+    const int first = !g.list ? 0 : g.direct ? 1 : 2;
+    if (first == 0) hipExtLaunchKernelGGL(k0, ge, dim3(kSelThreads), 0, s, e0, nullptr, 0, g, probs, ws);
+    if (first <= 1) hipExtLaunchKernelGGL(k1, ge, dim3(kSelThreads), 0, s, first == 1 ? e0 : nullptr, nullptr, 0, g, probs, ws);
+    hipExtLaunchKernelGGL(k2, go, dim3(kSelThreads), 0, s, first == 2 ? e0 : nullptr, e1, 0, g, probs, ws);
+  };
+  if (g.d_emb <= 512) launch(mlp_phi_q_kernel<0, 1>, mlp_phi_q_kernel<1, 1>, mlp_phi_q_kernel<2, 1>);
+  else launch(mlp_phi_q_kernel<0, 2>, mlp_phi_q_kernel<1, 2>, mlp_phi_q_kernel<2, 2>);
 }
 
 template <int D, int FTW>

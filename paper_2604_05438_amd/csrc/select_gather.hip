@@ -27,8 +27,12 @@
 //     zsum = sum z_i,  zv = sum z_i v_i,  z_i = phi_q . phi_k(k_i) recomputed                (eq. (subtraction))
 // into one partial per workgroup, [m, Z, zsum, count, nu[d], zv[d]], which the merge kernel combines in
 // part order.  No atomics on global memory; every sum runs in a fixed order.
+#include <algorithm>
+
 #include "gather_tile.h"
 #include "merge_head.h"
+#include "mlp_pack.h"
+#include "mlp_query.h"
 #include "score_tile.h"
 #include "select_utils.h"
 #include "tkphi_internal.h"
@@ -83,8 +87,9 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
 }
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
-// DIRECT: Geom::direct (a row of scores per head instead of candidate lists)
-template <int D, int NTHR, bool DIRECT>
+// DIRECT: Geom::direct (a row of scores per head instead of candidate lists).  LIST: Geom::list (ends with the retrieved list of the head,
+// whose only workgroup this is)
+template <int D, int NTHR, bool DIRECT, bool LIST>
 __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
                                                    int part, int gq, int p) {
   constexpr int KS = D / 32;
@@ -211,6 +216,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   TKPHI_PHASE(ws, 11);
   float* partial = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + part) * g.part_stride;
   auto empty_partial = [&]() {
+    if (LIST) return;
     if (tid == 0) { store_agent(partial, -INFINITY); store_agent(partial + 1, 0.f); store_agent(partial + 2, 0.f); store_agent(partial + 3, 0.f); }
     if (tid < D) { store_agent(partial + 4 + tid, 0.f); store_agent(partial + 4 + D + tid, 0.f); }
   };
@@ -223,9 +229,9 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // to LDS right before the gather (the barrier after the histogram pass orders LDS only, so it does not wait
   // for these loads)
   WkPieces<D, NTHR> wkp;
-  wkp.request(pr.Wk, h);
   float bk_t = 0.f, pq_t = 0.f;
-  if (tid < D) { bk_t = pr.bk[(size_t)h * D + tid]; pq_t = ((const float*)(blk + g.off_phiq))[(size_t)gq * D + tid]; }
+  if constexpr (!LIST) wkp.request(pr.Wk, h);
+  if (!LIST && tid < D) { bk_t = pr.bk[(size_t)h * D + tid]; pq_t = ((const float*)(blk + g.off_phiq))[(size_t)gq * D + tid]; }
 
   // (have_e0 is false exactly after a rescan: those lists were written without a bound)
   const SelBins bin_of{edge0, have_e0 && edge0 != 0u && edge0 != 0xffffffffu};
@@ -388,7 +394,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       for (int e = 0; e < per; ++e) {
         uint2 en;
         if (is_winner(first + e, r1, &en)) {
-          if (at < kWinLds) { w_tok[at] = (int)en.y; w_s[at] = __uint_as_float(en.x); }
+          if (LIST) { if (at < min(Ksel, g.max_K)) { sel_idx[at] = (int32_t)en.y; sel_score[at] = __uint_as_float(en.x); } }
+          else if (at < kWinLds) { w_tok[at] = (int)en.y; w_s[at] = __uint_as_float(en.x); }
           ++at;
         }
       }
@@ -396,7 +403,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       my_count = sh_tot;
     }
     // the retrieved list of the head, for the export of the merge and for winners beyond the LDS stage
-    if (my_count > kWinLds || pr.topk_idx) {
+    if (!LIST && (my_count > kWinLds || pr.topk_idx)) {
       int before = 0;
       for (int idx = tid; idx < r0; idx += NTHR) { uint2 en; before += is_winner(idx, r0, &en) ? 1 : 0; }
       const int incl_b = sel_scan_incl(before, sh_scan);
@@ -523,7 +530,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
         for (int i = 0; i < kSweepEntries; ++i) {
           if (fw & (1u << i)) {
             const uint2 en = entry(e, i);
-            if (at < kWinLds) { w_tok[at] = (int)en.y; w_s[at] = __uint_as_float(en.x); }
+            if (!LIST && at < kWinLds) { w_tok[at] = (int)en.y; w_s[at] = __uint_as_float(en.x); }
             // (global position: filled in below, once the winners of earlier lists in later sweeps are known)
             ++at;
           }
@@ -541,7 +548,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       for (int sw = 0; sw < n_sweeps; ++sw) {
         const Share sh = share_of(sw, tid);
         const bool mine = sh.list >= l0 && sh.list < l1;
-        if (n_sweeps == 1 && !need_global && !pr.topk_idx) break;     // (nothing reads the list)
+        if (!LIST && n_sweeps == 1 && !need_global && !pr.topk_idx) break;     // (nothing reads the list)
         u32x4 e[kSweepLoads];
         load_share(sh, e);
         uint32_t fw = 0;
@@ -571,6 +578,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     }
   }
   TKPHI_PHASE(ws, 15);
+  if constexpr (LIST) return;
 
   // ---- gather: kBatch winners per round, one or two 16-token tiles per wavefront -----------------------------
   const int r = lane & 15, kg = lane >> 4;
@@ -725,12 +733,35 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
 // same call: the phi jobs of decode_prep_kernel or decode_side_kernel, or, for short contexts, of score_direct_kernel.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
 // wavefronts of the workgroup that are still running.)
-template <int D, int NTHR, bool DIRECT>
+template <int D, int NTHR, bool DIRECT, bool LIST = false>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
+  if constexpr (LIST) {
+    // grid (Hq + Hq d_emb / 64 + ..): behind a workgroup per head, on the CUs that the selection leaves idle, a stage of phi_q (the second, where
+    // the first rode in a score launch long enough for it) and, for a step that recomputes features, the weights of the chain over the retrieved keys (a single problem: slot
+    // 0).  As a launch between select and chain the packing took 9 us of a 3B layer's step; phi_q on a second stream, joined before the
+    // gather, held a step with a feature cache at 65 us at any context length (now 45 at 4K).
+    const int idx = blockIdx.x, n_phi = g.d_emb / 64 * g.Hq, p = 0;
+    if (idx >= g.Hq) {
+      const tkphi_problem& pr = probs[p];
+      if (pr.L < 1 || pr.L > g.max_L) return;
+      if (idx < g.Hq + n_phi) {
+        mlp_phi_q_slice<DIRECT ? 0 : 1>(g, pr, problem_block(g, ws, p), (idx - g.Hq) % g.Hq, (idx - g.Hq) / g.Hq);
+        return;
+      }
+      const int wg = idx - g.Hq - n_phi, n_wg = ((int)gridDim.x - g.Hq - n_phi) / g.Hkv, h = wg % g.Hkv;
+      const tkphi_mlp mp = pr.mlp_k[h];
+      for (size_t q = (size_t)(wg / g.Hkv) * NTHR + threadIdx.x; q < packed_pieces(g); q += (size_t)n_wg * NTHR) pack_piece(g, ws, mp, 0, h, q, true);
+      return;
+    }
+    const int gq = idx;
+    select_gather_body<D, NTHR, DIRECT, LIST>(g, probs, ws, 0, gq, p);
+    if (g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;     // (as below)
+    return;
+  } else {
   const int part = blockIdx.x, gq = blockIdx.y, p = blockIdx.z;
-  select_gather_body<D, NTHR, DIRECT>(g, probs, ws, part, gq, p);
+  select_gather_body<D, NTHR, DIRECT, LIST>(g, probs, ws, part, gq, p);
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
   // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads; the
@@ -750,12 +781,20 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   // (the handed-over bound has been read: a replay of this call from a graph, whose tag is the same, must not find it)
   if (g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;
   merge_head<true, true>(g, probs, ws, gq, p, mode);
+  }
 }
 
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
   dim3 grid(g.sg_split, g.Hq, g.n_problems);       // (Geom::n_tiles of this pipeline: one partial per workgroup)
+  if (g.list) {
+    const bool pack = g.sel_feat && g.max_K > 0 && g.max_mid > 0;
+    grid = dim3(g.Hq + g.d_emb / 64 * g.Hq + (pack ? g.Hkv * std::max(1, 192 / g.Hkv) : 0));
+  }
   const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SELECT, fn, grid, dim3(threads), 0, s, g, probs, ws, mode); };
-  if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
+  if (g.list) {
+    if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true, true>, 1024); else launch(select_gather_kernel<128, 1024, false, true>, 1024); }
+    else { if (g.direct) launch(select_gather_kernel<64, 1024, true, true>, 1024); else launch(select_gather_kernel<64, 1024, false, true>, 1024); }
+  } else if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
   else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 512, true>, 512); else launch(select_gather_kernel<64, 512, false>, 512); }
   else { if (g.direct) launch(select_gather_kernel<64, 1024, true>, 1024); else launch(select_gather_kernel<64, 1024, false>, 1024); }
 }

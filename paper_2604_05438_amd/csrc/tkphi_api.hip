@@ -158,7 +158,9 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->diag = diag ? 1 : 0;
   g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 && !(diag && n_problems <= 1) &&
                  (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
-  g->sg_split = g->filtered ? max_split : 0;
+  // MLP maps: one problem (Geom::fused, below, or short contexts), and budgets whose winners leave the packed array some room; one workgroup per head then selects in 15 us what plan, emit and resolve took 26 for (3B layer at 128K)
+  g->list = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_MLP && g->max_mid > 0 && !compact && !diag && tn.select_mode != 1 && n_problems <= 1 &&
+             (tn.select_mode == 2 || ((int64_t)max_K * 12 <= g->max_mid && max_K <= packed / 5 * 4))) ? 1 : 0;
   // matrix-core score kernel: 4 wavefronts x 64 (d = 128) or 128 (d = 64) tokens per iteration;
   // a chunk is a whole number of such units
   g->scan_unit = g->use_mfma ? (g->d == 128 ? 256 : 512) : 256;
@@ -176,8 +178,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   if (n_problems > 1)
     for (keep_chunk = 1024; keep_chunk * 1024 < units || ceil_div(g->max_mid, keep_chunk) > 128;) keep_chunk *= 2;
   keep_chunk = std::min<int64_t>(align_up((size_t)std::max<int64_t>(keep_chunk, 1), unit), keep_most);
-  g->fused = g->filtered && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
+  g->fused = (g->filtered || g->list) && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
              (tn.scan_chunk > 0 ? tn.scan_chunk <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128) ? 1 : 0;
+  if (g->list && (g->fused || short_context)) g->filtered = 1;
+  g->list = g->list && g->filtered;
   if (g->fused) {
     g->scan_unit = unit;
     sc = (int)keep_chunk;
@@ -197,6 +201,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // Short contexts, as long as every token fits one sweep and the packed array of the select kernel: one unit per chunk, all
   // scores stored, no bound and no prep launch (1B layer at 4K 34.5 -> 22.6 us, at 10K 34.9 -> 24.6; 3B layer 34.6 -> 26.0 and 37.5 -> 31.8).  Few
   // winners then, and what workgroups of a head hand each other costs more than a gather round: one per 64 of the budget
+  g->sg_split = g->filtered ? g->list ? 1 : max_split : 0;
   g->direct = g->filtered && short_context ? 1 : 0;
   if (g->direct) {
     sc = g->scan_unit;
@@ -445,9 +450,9 @@ static uint32_t next_tag() {
 }
 
 static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems, char* ws, int acct, hipStream_t s) {
-  if (g.filtered && !g.diag) {         // (the diagnostics are by-products of the spill pipeline's emit pass)
-    Geom gf = g;
-    gf.n_tiles = g.sg_split;           // one partial per workgroup of the fused select + gather kernel
+  const bool filtered = g.filtered && !g.diag;         // (the diagnostics are by-products of the spill pipeline's emit pass)
+  const auto launch_filtered = [&](Geom gf) {
+    if (!gf.list) gf.n_tiles = gf.sg_split;            // one partial per workgroup of the fused select + gather kernel
     if (gf.direct) {
       launch_score_direct(gf, problems, ws, s);
     } else if (gf.fused) {
@@ -457,7 +462,10 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
       launch_prep(gf, problems, ws, s);
       launch_score_filtered(gf, problems, ws, s);
     }
-    launch_select_gather(gf, problems, ws, acct, s);   // (its last workgroup per head merges)
+    launch_select_gather(gf, problems, ws, acct, s);   // (Geom::list aside its last workgroup per head merges)
+  };
+  if (filtered && !g.list) {
+    launch_filtered(g);
     return TKPHI_OK;
   }
   if (g.phi_kind != TKPHI_PHI_MLP) {
@@ -469,8 +477,16 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
   }
   std::lock_guard<std::mutex> lock(g_side_mutex);
   SideStream* ss = nullptr;
-  tkphi_status st = side_stream(&ss);
+  tkphi_status st = side_stream(&ss);  // (also where it is not used: any MLP call outside a capture makes later ones fit for it)
   if (st != TKPHI_OK) return st;
+  if (g.list) {                        // most of phi_q rides in the score and select launches
+    launch_filtered(g);
+    launch_mlp_phi_q(g, problems, ws, s);
+    if (g.sel_feat) launch_mlp_sel_features(g, problems, ws, s);    // no feature cache: phi_k of the retrieved keys
+    launch_gather(g, problems, ws, s);
+    launch_merge(g, problems, ws, acct, false, s);
+    return TKPHI_OK;
+  }
   st = hip_ok(hipEventRecord(ss->fork, s), "hipEventRecord");
   if (st == TKPHI_OK) st = hip_ok(hipStreamWaitEvent(ss->stream, ss->fork, 0), "hipStreamWaitEvent");
   if (st != TKPHI_OK) return st;
@@ -478,7 +494,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
   st = hip_ok(hipEventRecord(ss->join, ss->stream), "hipEventRecord");
   launch_score_mid(g, problems, ws, s);
   launch_select(g, problems, ws, s);
-  if (g.sel_feat) launch_mlp_sel_features(g, problems, ws, s);    // no feature cache: phi_k of the retrieved keys
+  if (g.sel_feat) launch_mlp_sel_features(g, problems, ws, s);
   // (the join is enqueued even after an error above: the side stream must not be left forked)
   const tkphi_status st2 = hip_ok(hipStreamWaitEvent(s, ss->join, 0), "hipStreamWaitEvent");
   if (st != TKPHI_OK) return st;

@@ -53,6 +53,8 @@ struct Geom {
   int filtered;          // 1: decode may run the filtered pipeline (prep, score_filtered, select_gather, merge):
                          // bf16 matrix-core shapes, exp-affine maps, budgets well below the mid-region size
   int direct;            // 1: filtered pipeline for short contexts: all scores stored (off_scores), no bound, no prep launch
+  int list;              // 1: filtered pipeline with MLP maps: its select kernel ends with the retrieved lists, gather and merge follow as in
+                         // the spill pipeline
   int fused;             // 1: filtered pipeline, sample and score pass in one launch: the scores wait in LDS for the bound (off_hand)
   uint32_t tag;          // fused: the bounds of this call carry it (not 0)
   int cand_T;            // filtered pipeline: entries of a candidate list kept in the compact array (multiple of 12)

@@ -148,3 +148,44 @@ def test_recomputing_decode_replays_from_a_hip_graph():
         b.decode()
         torch.cuda.synchronize()
         assert np.array_equal(b.result(0, "out"), eager)
+
+
+@pytest.mark.parametrize("d,d_emb,cache", [(128, 512, False), (128, 256, True), (64, 1024, True), (64, 128, False)])
+@pytest.mark.parametrize("n_mid,k,select_test,chunk", [(700, 9, 0, 0), (9000, 600, 0, 0),       # short: scores in rows
+                                                       (13003, 130, 0, 0), (13003, 900, 0, 0),  # bound handed over, one sweep of lists
+                                                       (6000, 300, 1, 0), (6000, 300, 2, 0),    # rescan; every token a candidate
+                                                       (2500, 0, 0, 256)])                      # nothing to retrieve
+def test_one_problem_selects_lists(d, d_emb, cache, n_mid, k, select_test, chunk):
+    """A decode step of one problem with MLP maps: filtered score pass, a workgroup per head that ends with the retrieved list, phi_q in
+    the score and select launches (or the latter only, for short contexts), packed weights in the select launch, generated tokens behind
+    the prefix.  Index sets, scores, outputs against the oracle; then the captured step, replayed with eager ones between, bit for
+    bit."""
+    import parity_utils as PU
+    import torch
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l1b_32k"], n_q_heads=6, n_kv_heads=2, d_head=d, d_phi=d, seed=733)
+    n_gen = 70
+    L = w.n_sink + w.n_tail + n_mid
+    P = I.make_layer(w, L=L + n_gen)
+    P["L"], P["n_gen"] = L, n_gen
+    P["mlp"] = I.make_mlp_phi(w, layer=0, d_emb=d_emb)
+    b = H.Batch(H.config_of(w, cache_features=cache, d_emb=d_emb, max_gen=80, tuning={"select_test": select_test, "scan_chunk": chunk}),
+                [P], [k], debug=True)
+    b.build()
+    stages = dict(zip(B.STAGES, b.decode_stage_times()))
+    assert stages["select"] > 0 and stages["select_plan"] == 0, stages
+    assert b.status() & ~2 == 0
+    PU.check_layer(w, P, k, b, 0)
+    eager = b.result(0, "out").copy()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.decode()
+    for _ in range(3):
+        b.dev[0]["out"].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(b.result(0, "out"), eager)
+        b.decode()
+        torch.cuda.synchronize()
+        assert np.array_equal(b.result(0, "out"), eager)
