@@ -567,7 +567,62 @@ void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hip
   else launch(score_fused_kernel<64, 8>);
 }
 
+// The same for fp32 caches (d = 64): scores in vector arithmetic, 128 rows per workgroup and all of them requested before the first
+// is used (16 lanes x 16 bytes to a row).  Bound by latency: one head of 4K tokens is 32 such workgroups.
+constexpr int kDirectRowsF32 = 128;
+__global__ __launch_bounds__(kThreads) void score_direct_f32_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
+  constexpr int D = 64, LPR = D / 4, RPP = kThreads / LPR, UNR = kDirectRowsF32 / RPP;
+  __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
+  const int n_side = g.G * (1 + g.n_atiles);
+  const int x = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
+  if (x == 0 && h == 0 && p == 0) write_device_status(g, probs, ws, true);
+  const tkphi_problem pr = probs[p];
+  if (pr.L < 1 || pr.L > g.max_L) return;
+  char* blk = problem_block(g, ws, p);
+  if (x < n_side) {
+    if (x < g.G) {
+      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
+      side_phi<0, float>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+    } else {
+      const int j = x - g.G;
+      side_anchor<float>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+    }
+    return;
+  }
+  const int n = mid_size(pr.L, g.n_sink, g.n_tail), row0 = (x - n_side) * kDirectRowsF32;
+  if (row0 >= n) return;
+  const int tid = threadIdx.x, seg = tid % LPR, rsub = tid / LPR;
+  const char* Kb = (const char*)pr.K + ((int64_t)h * pr.stride_head + (int64_t)g.n_sink * pr.stride_tok + seg * 4) * 4;
+  u32x4 v[UNR];
+#pragma unroll
+  for (int u = 0; u < UNR; ++u) v[u] = gload128(Kb + (int64_t)min(row0 + u * RPP + rsub, n - 1) * pr.stride_tok * 4);
+  const glb_f32 rows = (glb_f32)(blk + g.off_scores);
+  for (int gl = 0; gl < g.G; ++gl) {
+    const int gq = h * g.G + gl;
+    const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * D + seg * 4) * 4);
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(v[u][e]), __uint_as_float(qv[e]), s);
+      s = row16_sum(s);
+      const int tok = row0 + u * RPP + rsub;
+      if (seg == 0 && tok < n) {
+        s = s * g.score_scale + 0.0f;              // + 0.0f: -0 -> +0, equal scores get equal keys
+        rows[(size_t)gq * g.mid_stride + tok] = s;
+        if (pr.scores) ((glb_f32)pr.scores)[(size_t)gq * n + tok] = s;
+      }
+    }
+  }
+}
+
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
+  if (g.dtype == TKPHI_F32) {
+    static_assert(kDirectRowsF32 == direct_unit_f32, "chunks of the geometry");
+    dim3 grid(g.G * (1 + g.n_atiles) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
+    TKPHI_LAUNCH(ST_SCORE, score_direct_f32_kernel, grid, dim3(kThreads), 0, s, g, probs, ws);
+    return;
+  }
   dim3 grid((g.list ? 0 : g.G * (1 + g.n_atiles)) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
   // (the phi job's rows of S ahead of everything else: 0.3 us off one 3B layer of 4K or 9K tokens, but at 158 registers instead of
   // 73 the whole launch of 256 problems of 1.5K takes 258 us instead of 224 at d = 128, 154 instead of 128 at d = 64)

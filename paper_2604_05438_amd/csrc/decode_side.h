@@ -18,19 +18,20 @@ namespace tkphi {
 // EARLY: rows of S a thread requests before anything else (16: all it takes at d_phi = d = 128; one round trip for S and Wq
 // together, for a launch of few workgroups), 0: none, eight at a time behind phi_q (16 rows ahead cost batches two of three
 // wavefronts: decode_side_kernel over 6400 heads 99 us instead of 59).
-template <int EARLY>
+template <int EARLY, typename T = uint16_t>
 __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* sh_phiq, float* pu,
                                          float* red) {
+  constexpr int EPL = Elem<T>::per16;
   const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
   const bool act = tid < kThreads;
   // rows of Wq: LPR lanes per row (16 bytes each), rows_pp rows per pass, 8 passes in flight
-  const int LPR = d / 8, seg = tid % LPR, row_in = tid / LPR, rows_pp = kThreads / LPR;
-  const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * 8) * 2);
-  float qx[8];
-  Elem<uint16_t>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
+  const int LPR = d / EPL, seg = tid % LPR, row_in = tid / LPR, rows_pp = kThreads / LPR;
+  const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * EPL) * sizeof(T));
+  float qx[EPL];
+  Elem<T>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
   float nrm = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) nrm = fmaf(qx[e], qx[e], nrm);
+  for (int e = 0; e < EPL; ++e) nrm = fmaf(qx[e], qx[e], nrm);
   for (int o = LPR >> 1; o >= 1; o >>= 1) nrm += __shfl_xor(nrm, o);
   // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels
   const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
@@ -52,18 +53,18 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
     for (int k = 0; k < MAXP; ++k) {
       if (j0 + k * rows_pp >= dphi) break;            // (uniform)
       const int j = min(j0 + k * rows_pp + row_in, dphi - 1);
-      wv[k] = gload128((const char*)pr.Wq + (((size_t)gq * dphi + j) * d + seg * 8) * 2);
+      wv[k] = gload128((const char*)pr.Wq + (((size_t)gq * dphi + j) * d + seg * EPL) * sizeof(T));
       bj[k] = pr.bq[(size_t)gq * dphi + j];
     }
 #pragma unroll
     for (int k = 0; k < MAXP; ++k) {
       if (j0 + k * rows_pp >= dphi) break;
       const int jr = j0 + k * rows_pp + row_in;
-      float x[8];
-      Elem<uint16_t>::unpack(make_uint4(wv[k].x, wv[k].y, wv[k].z, wv[k].w), x);
+      float x[EPL];
+      Elem<T>::unpack(make_uint4(wv[k].x, wv[k].y, wv[k].z, wv[k].w), x);
       float dot = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dot = fmaf(x[e], qx[e], dot);
+      for (int e = 0; e < EPL; ++e) dot = fmaf(x[e], qx[e], dot);
       for (int o = LPR >> 1; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
       if (act && jr < dphi && seg == 0) {
         const float f = expf(g.a * dot - g.c * nrm + bj[k]);
@@ -107,8 +108,10 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
 // Anchors are the rows [0, n_sink) u [L - n_tail, L) (every row if the mid-region is empty) followed by the
 // generated tokens [L, L + n_gen).  Writes the tile's partial in the layout of the gather kernels:
 // [m_loc, Z_loc, 0, count, nu_loc[d], 0[d]].  LDS: a_s, a_w [64], red [4][128]
+template <typename T = uint16_t>
 __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int batch, float* a_s,
                                             float* a_w, float* red) {
+  constexpr int EPL = Elem<T>::per16;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, d = g.d, h = gq / g.G;
   const bool act = tid < kThreads;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -118,31 +121,31 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
   if (base >= n_anchor) return;
   const int cnt = min(64, n_anchor - base);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + g.n_tiles + batch) * g.part_stride;
-  const int LPR = d / 8, seg = tid % LPR, rsub = tid / LPR, RPP = kThreads / LPR;   // rows per pass: 16 (d = 128) or 32
-  constexpr int MAXPS = 4;                           // 64 rows / 16
+  const int LPR = d / EPL, seg = tid % LPR, rsub = tid / LPR, RPP = kThreads / LPR;   // rows per pass: 8 to 32
+  constexpr int MAXPS = EPL == 8 ? 4 : 8;            // 64 rows / 16 or 8
   const int n_pass = 64 / RPP;
   u32x4 kv[MAXPS], vv[MAXPS];
-  const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * 8) * 2);
+  const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * EPL) * sizeof(T));
 #pragma unroll
   for (int ps = 0; ps < MAXPS; ++ps) {
     if (ps < n_pass) {
       const int a = base + min(ps * RPP + rsub, cnt - 1);
       const int tok = a >= n_prefill ? pr.L + (a - n_prefill) : (n > 0 && a >= g.n_sink) ? (pr.L - g.n_tail + (a - g.n_sink)) : a;
-      const size_t off = ((size_t)h * pr.stride_head + (size_t)tok * pr.stride_tok + seg * 8) * 2;
+      const size_t off = ((size_t)h * pr.stride_head + (size_t)tok * pr.stride_tok + seg * EPL) * sizeof(T);
       kv[ps] = gload128((const char*)pr.K + off);
       vv[ps] = gload128((const char*)pr.V + off);
     }
   }
-  float qx[8];
-  Elem<uint16_t>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
+  float qx[EPL];
+  Elem<T>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
 #pragma unroll
   for (int ps = 0; ps < MAXPS; ++ps) {
     if (ps < n_pass) {
-      float kx[8];
-      Elem<uint16_t>::unpack(make_uint4(kv[ps].x, kv[ps].y, kv[ps].z, kv[ps].w), kx);
+      float kx[EPL];
+      Elem<T>::unpack(make_uint4(kv[ps].x, kv[ps].y, kv[ps].z, kv[ps].w), kx);
       float s = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s = fmaf(kx[e], qx[e], s);
+      for (int e = 0; e < EPL; ++e) s = fmaf(kx[e], qx[e], s);
       for (int o = LPR >> 1; o >= 1; o >>= 1) s += __shfl_xor(s, o);
       const int row = ps * RPP + rsub;
       if (act && seg == 0) a_s[row] = row < cnt ? s * g.score_scale + 0.0f : -INFINITY;
@@ -162,28 +165,28 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
     if (lane == 0) { part[0] = mb; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt; }
   }
   __syncthreads();
-  float acc[8];
+  float acc[EPL];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
 #pragma unroll
   for (int ps = 0; ps < MAXPS; ++ps) {
     if (ps < n_pass) {
       const int row = ps * RPP + rsub;
       const float w = row < cnt ? a_w[row] : 0.f;
-      float vx[8];
-      Elem<uint16_t>::unpack(make_uint4(vv[ps].x, vv[ps].y, vv[ps].z, vv[ps].w), vx);
+      float vx[EPL];
+      Elem<T>::unpack(make_uint4(vv[ps].x, vv[ps].y, vv[ps].z, vv[ps].w), vx);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = fmaf(w, vx[e], acc[e]);
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w, vx[e], acc[e]);
     }
   }
   // rows of one wavefront that share a segment: lanes seg, seg + LPR, ...
   for (int o = LPR; o < 64; o <<= 1) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+    for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o);
   }
   if (act && lane < LPR) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[wv * 128 + lane * 8 + e] = acc[e];
+    for (int e = 0; e < EPL; ++e) red[wv * 128 + lane * EPL + e] = acc[e];
   }
   __syncthreads();
   if (tid < d) {

@@ -16,26 +16,26 @@ union GatherFrag {
   gt_bf16x8 v;
 };
 
-constexpr int wk_row_bytes(int D) { return D * 2 + 16; }   // staged Wk rows are padded by 16 B: conflict-free 16-byte reads
+constexpr int wk_row_bytes(int D, int elem = 2) { return D * elem + 16; }   // staged Wk rows are padded by 16 B: conflict-free 16-byte reads
 
 // Stages Wk[h] ([D features][D channels] bf16) into LDS with padded rows in two steps, so that a caller with NT
 // threads can put other work between the request and the LDS stores: wk_request loads the thread's pieces
 // (piece i of the matrix = 16 bytes; thread t holds pieces t, t + NT, ...), wk_commit stores them; a barrier
 // before the first use.
-template <int D, int NT>
+template <int D, int NT, int ELEM = 2>
 struct WkPieces {
-  static constexpr int SEGS = D * 2 / 16, N = (D * SEGS + NT - 1) / NT;
+  static constexpr int SEGS = D * ELEM / 16, N = (D * SEGS + NT - 1) / NT;
   u32x4 t[N];
   __device__ __forceinline__ void request(const void* Wk, int h) {
-    const char* wsrc = (const char*)Wk + (size_t)h * D * D * 2;
+    const char* wsrc = (const char*)Wk + (size_t)h * D * D * ELEM;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       const int i = min((int)threadIdx.x + k * NT, D * SEGS - 1);
-      t[k] = gload128(wsrc + (size_t)(i / SEGS) * D * 2 + (i % SEGS) * 16);
+      t[k] = gload128(wsrc + (size_t)(i / SEGS) * D * ELEM + (i % SEGS) * 16);
     }
   }
   __device__ __forceinline__ void commit(char* wk_lds) const {
-    constexpr int WROW = wk_row_bytes(D);
+    constexpr int WROW = wk_row_bytes(D, ELEM);
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       const int i = (int)threadIdx.x + k * NT;
@@ -111,6 +111,48 @@ __device__ __forceinline__ void wave_feature_dots(const GatherFrag (&a)[D / 32],
     z[1] = fmaf(join_bf16_hi(h01, l01), pj[nt], z[1]);
     z[2] = fmaf(join_bf16_lo(h23, l23), pj[nt], z[2]);
     z[3] = fmaf(join_bf16_hi(h23, l23), pj[nt], z[3]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) z[i] += __shfl_xor(z[i], o);
+  }
+}
+
+// The same for fp32 storage, in the arithmetic of the fp32 summary build (v_mfma_f32_16x16x4_f32, four accumulator chains): a[jj] holds the channels
+// 16 jj + 4 kg .. of token r, the inner indices of step (jj, e) are the channels 16 jj + 4 kg + e.
+template <int D>
+__device__ __forceinline__ void wave_feature_dots_f32(const GatherFrag (&a)[D / 16], const char* wk_lds, const float* bk_h,
+                                                      const float* phiq, float fa, float fc, float (&z)[4]) {
+  constexpr int CT = D / 16, WROW = wk_row_bytes(D, 4);
+  const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
+  float nrm = 0.f;
+#pragma unroll
+  for (int jj = 0; jj < CT; ++jj)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) nrm = fmaf(__uint_as_float(a[jj].u[e]), __uint_as_float(a[jj].u[e]), nrm);
+  nrm += __shfl_xor(nrm, 16);
+  nrm += __shfl_xor(nrm, 32);                    // |k|^2 of token r
+  float cn[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { cn[i] = fc * __shfl(nrm, 4 * kg + i); z[i] = 0.f; }
+#pragma unroll
+  for (int nt = 0; nt < CT; ++nt) {
+    gt_floatx4 acc[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = (gt_floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int jj = 0; jj < CT; ++jj) {
+      const u32x4 w = *(const u32x4*)(wk_lds + (nt * 16 + r) * WROW + jj * 64 + kg * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[jj].u[e]), __uint_as_float(w[e]), acc[e], 0, 0, 0);
+    }
+    const float bias = bk_h[nt * 16 + r], pq = phiq[nt * 16 + r];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float dot = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+      z[i] = fmaf(expf(fa * dot - cn[i] + bias), pq, z[i]);
+    }
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {

@@ -44,7 +44,7 @@ constexpr int kSweepLoads = kSweepEntries / 2;
 // winners gathered per round: 16-token tile t of a round goes to wavefront t mod 16.  Two tiles per wavefront at
 // d = 64 (one round for most heads of a batch of short sequences); at d = 128 the second tile's rows do not fit
 // the registers
-template <int D, int NTHR> constexpr int kBatchOf = (D == 64 && NTHR == 1024) ? 512 : 256;
+template <int D, int NTHR, typename KV> constexpr int kBatchOf = (D * sizeof(KV) == 128 && NTHR == 1024) ? 512 : 256;
 // winners of a workgroup kept in LDS (the rest are re-read from the retrieved list)
 template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 
@@ -88,12 +88,12 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
 // DIRECT: Geom::direct (a row of scores per head instead of candidate lists).  LIST: Geom::list (ends with the retrieved list of the head,
-// whose only workgroup this is)
-template <int D, int NTHR, bool DIRECT, bool LIST>
+// whose only workgroup this is).  KV: storage type of keys, values and Wk (fp32 only with DIRECT, d = 64)
+template <int D, int NTHR, bool DIRECT, bool LIST, typename KV>
 __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
                                                    int part, int gq, int p) {
-  constexpr int KS = D / 32;
-  constexpr int WROW = wk_row_bytes(D);
+  constexpr int EPL = Elem<KV>::per16, KS = D * (int)sizeof(KV) / 64;        // elements of 16 bytes; 16-byte pieces of a key row per lane
+  constexpr int WROW = wk_row_bytes(D, sizeof(KV));
   // select phase: histogram (8 KB) + boundary candidates (8 KB); gather phase: reduction scratch of the value sums
   __shared__ __attribute__((aligned(16))) char lds_a[16384];
   __shared__ __attribute__((aligned(16))) char wk_lds[D * WROW];
@@ -101,7 +101,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   __shared__ uint2 dense[kDense];                   // the candidates of the head, packed (select phase)
   __shared__ int w_tok[kWinLds];
   __shared__ float w_s[kWinLds];
-  constexpr int kBatch = kBatchOf<D, NTHR>;
+  constexpr int kBatch = kBatchOf<D, NTHR, KV>;
   __shared__ float b_w[kBatch], b_z[kBatch];
   __shared__ float sh_bk[D], sh_pq[D];              // bk[h] and phi_q of the head, staged with Wk
   __shared__ int sh_scan[NWV];
@@ -228,7 +228,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // Wk[h] for the gather phase: requested now (the first sweep has arrived, nothing else is in flight), stored
   // to LDS right before the gather (the barrier after the histogram pass orders LDS only, so it does not wait
   // for these loads)
-  WkPieces<D, NTHR> wkp;
+  WkPieces<D, NTHR, sizeof(KV)> wkp;
   float bk_t = 0.f, pq_t = 0.f;
   if constexpr (!LIST) wkp.request(pr.Wk, h);
   if (!LIST && tid < D) { bk_t = pr.bk[(size_t)h * D + tid]; pq_t = ((const float*)(blk + g.off_phiq))[(size_t)gq * D + tid]; }
@@ -583,7 +583,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   // ---- gather: kBatch winners per round, one or two 16-token tiles per wavefront -----------------------------
   const int r = lane & 15, kg = lane >> 4;
   const int64_t head_off = (int64_t)h * pr.stride_head;
-  constexpr int LPR = D / 8;                        // lanes per value row (16 bytes each)
+  constexpr int LPR = D / EPL;                      // lanes per value row (16 bytes each)
   constexpr int RPP = NTHR / LPR;            // rows per pass (64 or 128)
   constexpr int NPASS = kBatch / RPP;               // value rows per thread and round (4)
   constexpr int NTW = kBatch / (16 * NWV);    // 16-token tiles per wavefront and round
@@ -613,7 +613,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       if (t16 < cnt) {
         int tk; float s;
         winner(b0, t16 + r, &tk, &s);
-        const char* rp = (const char*)pr.K + (head_off + (int64_t)tk * pr.stride_tok) * 2 + kg * 16;
+        const char* rp = (const char*)pr.K + (head_off + (int64_t)tk * pr.stride_tok) * sizeof(KV) + kg * 16;
 #pragma unroll
         for (int j = 0; j < KS; ++j) a[u][j].u = gload128(rp + j * 64);
       }
@@ -626,7 +626,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       if (ps * RPP < cnt) {
         int vtok; float vs;
         winner(b0, ps * RPP + rsub, &vtok, &vs);
-        vrow[ps] = gload128((const char*)pr.V + (head_off + (int64_t)vtok * pr.stride_tok + seg * 8) * 2);
+        vrow[ps] = gload128((const char*)pr.V + (head_off + (int64_t)vtok * pr.stride_tok + seg * EPL) * sizeof(KV));
       }
     }
   };
@@ -655,7 +655,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       const int t16 = (wv + u * NWV) * 16;
       if (t16 < cnt) {
         float z[4];
-        wave_feature_dots<D>(a[u], wk_lds, sh_bk, sh_pq, g.a, g.c, z);
+        if constexpr (sizeof(KV) == 4) wave_feature_dots_f32<D>(a[u], wk_lds, sh_bk, sh_pq, g.a, g.c, z);
+        else wave_feature_dots<D>(a[u], wk_lds, sh_bk, sh_pq, g.a, g.c, z);
         if (r == 0) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) b_z[t16 + 4 * kg + i] = (t16 + 4 * kg + i < cnt) ? z[i] : 0.f;
@@ -670,28 +671,28 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     if (tid < kBatch) b_w[tid] = tid < cnt ? __expf(b_w[tid] - mloc) : 0.f;
     lds_barrier();
     // weighted value sums: rows of one wavefront that share a segment, then the 16 wavefronts
-    float an[8], az[8];
+    float an[EPL], az[EPL];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { an[e] = 0.f; az[e] = 0.f; }
+    for (int e = 0; e < EPL; ++e) { an[e] = 0.f; az[e] = 0.f; }
 #pragma unroll
     for (int ps = 0; ps < NPASS; ++ps) {
       const int i = ps * RPP + rsub;
       if (ps * RPP < cnt && i < cnt) {
-        float x[8];
-        Elem<uint16_t>::unpack(make_uint4(vrow[ps].x, vrow[ps].y, vrow[ps].z, vrow[ps].w), x);
+        float x[EPL];
+        Elem<KV>::unpack(make_uint4(vrow[ps].x, vrow[ps].y, vrow[ps].z, vrow[ps].w), x);
         const float wi = b_w[i], zi = b_z[i];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { an[e] = fmaf(wi, x[e], an[e]); az[e] = fmaf(zi, x[e], az[e]); }
+        for (int e = 0; e < EPL; ++e) { an[e] = fmaf(wi, x[e], an[e]); az[e] = fmaf(zi, x[e], az[e]); }
       }
     }
     if (more) load_values(b0 + kBatch);
     for (int o = LPR; o < 64; o <<= 1) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { an[e] += __shfl_xor(an[e], o); az[e] += __shfl_xor(az[e], o); }
+      for (int e = 0; e < EPL; ++e) { an[e] += __shfl_xor(an[e], o); az[e] += __shfl_xor(az[e], o); }
     }
     if (lane < LPR) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { red[(wv * 2 + 0) * 128 + lane * 8 + e] = an[e]; red[(wv * 2 + 1) * 128 + lane * 8 + e] = az[e]; }
+      for (int e = 0; e < EPL; ++e) { red[(wv * 2 + 0) * 128 + lane * EPL + e] = an[e]; red[(wv * 2 + 1) * 128 + lane * EPL + e] = az[e]; }
     }
     if (wv == 1) {                                  // Z_loc and zsum of the batch, in a fixed order
       float Zb = (b_w[lane] + b_w[lane + 64]) + (b_w[lane + 128] + b_w[lane + 192]);
@@ -733,7 +734,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
 // same call: the phi jobs of decode_prep_kernel or decode_side_kernel, or, for short contexts, of score_direct_kernel.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
 // wavefronts of the workgroup that are still running.)
-template <int D, int NTHR, bool DIRECT, bool LIST = false>
+template <int D, int NTHR, bool DIRECT, bool LIST = false, typename KV = uint16_t>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
@@ -756,12 +757,12 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
       return;
     }
     const int gq = idx;
-    select_gather_body<D, NTHR, DIRECT, LIST>(g, probs, ws, 0, gq, p);
-    if (g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;     // (as below)
+    select_gather_body<D, NTHR, DIRECT, LIST, KV>(g, probs, ws, 0, gq, p);
+    if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;     // (as below)
     return;
   } else {
   const int part = blockIdx.x, gq = blockIdx.y, p = blockIdx.z;
-  select_gather_body<D, NTHR, DIRECT, LIST>(g, probs, ws, part, gq, p);
+  select_gather_body<D, NTHR, DIRECT, LIST, KV>(g, probs, ws, part, gq, p);
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
   // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads; the
@@ -779,7 +780,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   if (!sh_last || threadIdx.x >= kThreads) return;
   if (exports) __threadfence();
   // (the handed-over bound has been read: a replay of this call from a graph, whose tag is the same, must not find it)
-  if (g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;
+  if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;
   merge_head<true, true>(g, probs, ws, gq, p, mode);
   }
 }
@@ -794,7 +795,8 @@ void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, i
   if (g.list) {
     if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true, true>, 1024); else launch(select_gather_kernel<128, 1024, false, true>, 1024); }
     else { if (g.direct) launch(select_gather_kernel<64, 1024, true, true>, 1024); else launch(select_gather_kernel<64, 1024, false, true>, 1024); }
-  } else if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
+  } else if (g.dtype == TKPHI_F32) launch(select_gather_kernel<64, 1024, true, false, float>, 1024);
+  else if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
   else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 512, true>, 512); else launch(select_gather_kernel<64, 512, false>, 512); }
   else { if (g.direct) launch(select_gather_kernel<64, 1024, true>, 1024); else launch(select_gather_kernel<64, 1024, false>, 1024); }
 }

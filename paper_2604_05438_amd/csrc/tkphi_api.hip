@@ -148,7 +148,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // hide behind the other's arithmetic
   const int64_t heads = (int64_t)g->Hq * std::max(n_problems, 1);
   const int max_split = (int)std::clamp<int64_t>(256 / heads, 1, 16);
-  g->sg_threads = g->d == 64 && max_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
+  g->sg_threads = cfg->kv_dtype == TKPHI_BF16 && g->d == 64 && max_split == 1 && (int64_t)g->Hq * n_problems >= 512 && max_K <= 1024 ? 512 : 1024;
   const int sweep = g->sg_threads * kSweepEntries;   // candidate slots of a head that kernel reads in one go
   const int packed = packed_candidates(g->d, g->sg_threads);
   const bool short_context = !compact && tn.scan_chunk == 0 && tn.select_test == 0 && g->max_mid <= std::min(sweep, packed);
@@ -158,6 +158,11 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->diag = diag ? 1 : 0;
   g->filtered = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && tn.select_mode != 1 && !(diag && n_problems <= 1) &&
                  (tn.select_mode == 2 || (int64_t)max_K * min_inverse_budget <= g->max_mid)) ? 1 : 0;
+  // fp32 caches at d = d_phi = 64, short contexts: the two launches of the filtered pipeline instead of six.  (At d = 128 Wk in fp32 and the
+  // packed array do not fit LDS together.)
+  if (cfg->kv_dtype == TKPHI_F32 && g->d == 64 && g->dphi == 64 && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && !g->cache && !diag && short_context &&
+      g->max_mid > 0 && !tn.force_generic && tn.select_mode != 1 && (int64_t)max_K * 12 <= g->max_mid)
+    g->filtered = 1;
   // MLP maps: one problem (Geom::fused, below, or short contexts), and budgets whose winners leave the packed array some room; one workgroup per head then selects in 15 us what plan, emit and resolve took 26 for (3B layer at 128K)
   g->list = (g->use_mfma && cfg->phi_kind == TKPHI_PHI_MLP && g->max_mid > 0 && !compact && !diag && tn.select_mode != 1 && n_problems <= 1 &&
              (tn.select_mode == 2 || ((int64_t)max_K * 12 <= g->max_mid && max_K <= packed / 5 * 4))) ? 1 : 0;
@@ -204,6 +209,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->sg_split = g->filtered ? g->list ? 1 : max_split : 0;
   g->direct = g->filtered && short_context ? 1 : 0;
   if (g->direct) {
+    if (cfg->kv_dtype == TKPHI_F32) g->scan_unit = direct_unit_f32;
     sc = g->scan_unit;
     g->sg_split = std::min(g->sg_split, std::max(1, (int)ceil_div(std::min(max_K, g->max_mid), 64)));
   }

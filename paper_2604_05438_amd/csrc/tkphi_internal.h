@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "tkphi.h"
 
 namespace tkphi {
@@ -31,6 +33,7 @@ constexpr int kMinListHead = 24;       // smallest Geom::cand_T
 constexpr int kPairsPerWG = 64;        // gather: retrieved tokens per workgroup (16 per wavefront)
 
 // ---- launch geometry + workspace layout -------------------------------------------
+constexpr int direct_unit_f32 = 128;     // Geom::scan_unit of fp32 caches where Geom::direct
 constexpr int keep_unit(int d) { return d == 128 ? 64 : 128; }   // Geom::scan_unit where Geom::fused
 
 struct Geom {
@@ -396,6 +399,19 @@ __device__ __forceinline__ void write_device_status(const Geom& g, const tkphi_p
 #define TKPHI_PHASE(ws, slot) do {} while (0)
 #define TKPHI_PHASE_VALUE(ws, slot, v) do {} while (0)
 #endif
+
+// Sum over the 16 lanes of a row, in every lane: the butterfly of xor-shuffles by 1, 2, 4, 8 as data-parallel-primitive moves (lanes that
+// mirror each other across a quad pair / a half row hold equal partial sums after the earlier steps)
+__device__ __forceinline__ float row16_sum(float s) {
+  const auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  s += dpp(s, std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
+  s += dpp(s, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
+  s += dpp(s, std::integral_constant<int, 0x141>{});   // row_half_mirror
+  s += dpp(s, std::integral_constant<int, 0x140>{});   // row_mirror
+  return s;
+}
 
 // Inclusive prefix sum over the lanes of a wavefront by data-parallel-primitive moves (inside rows of 16 lanes, then across them)
 __device__ __forceinline__ int wave_scan_incl(int x) {

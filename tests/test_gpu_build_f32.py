@@ -55,3 +55,44 @@ def test_gather_f32_edges(dtype, d, dphi):
         assert b.status() == 0
         for i, (P, k) in enumerate(zip(layers[sel], ks[sel])):
             PU.check_layer(w, P, k, b, i, sum_tol=2e-5)
+
+
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (6, 2), (8, 1)])
+@pytest.mark.parametrize("mids,ks", [([12], [1]), ([127], [10]), ([128], [10]), ([129], [9]), ([12288], [1024]), ([12289], [300]),
+                                     ([4000, 13, 700], [257, 1, 50]), ([3100, 200, 12288], [258, 16, 100])])
+def test_short_f32_contexts(hq, hkv, mids, ks):
+    """Short fp32 contexts at d = d_phi = 64: two launches up to a budget of 1/12 and 12288 mid tokens (beyond: six), over the edges of
+    the score workgroups' 128 rows, several workgroups per head, one and several gather rounds of 256, ties, generated tokens.
+    Scores, index sets and outputs against the oracle at the bars of parity_utils; the captured step replays bit for bit."""
+    import parity_utils as PU
+    import torch
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], n_q_heads=hq, n_kv_heads=hkv, seed=93)
+    layers = []
+    for i, m in enumerate(mids):
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + m + 5, seq=i)
+        P["L"], P["n_gen"] = w.n_sink + w.n_tail + m, 5
+        if m >= 127:
+            P["K"][:, w.n_sink + m // 2:w.n_sink + m // 2 + 6] = P["K"][:, w.n_sink + 3:w.n_sink + 4]        # equal scores
+        layers.append(P)
+    b = H.Batch(H.config_of(w, max_gen=8), layers, ks, debug=True)
+    b.build()
+    stages = dict(zip(B.STAGES, b.decode_stage_times()))
+    assert (stages["select"] > 0) == (max(mids) <= 12288 and max(ks) * 12 <= max(mids)), stages
+    assert b.status() & ~2 == 0
+    for i, (P, k) in enumerate(zip(layers, ks)):
+        PU.check_layer(w, P, k, b, i, heads=sorted({0, hq // 2, hq - 1}), sum_tol=2e-5)
+    eager = [b.result(i, "out").copy() for i in range(len(mids))]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.decode()
+    for _ in range(3):
+        for i in range(len(mids)):
+            b.dev[i]["out"].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for i in range(len(mids)):
+            assert np.array_equal(b.result(i, "out"), eager[i])
+        b.decode()
+        torch.cuda.synchronize()
