@@ -8,12 +8,7 @@ namespace tkphi {
 // inclusive prefix sum over threadIdx.x; sh must hold >= 4 ints; contains two barriers
 __device__ __forceinline__ int block_scan_incl(int v, int* sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
+  const int x = wave_scan_incl(v);
   if (lane == 63) sh[w] = x;
   __syncthreads();
   int add = 0;
@@ -24,8 +19,7 @@ __device__ __forceinline__ int block_scan_incl(int v, int* sh) {
 
 // sum over the workgroup, result in every thread; sh must hold >= 4 floats; two barriers
 __device__ __forceinline__ float block_sum(float v, float* sh) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   const float r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
@@ -34,8 +28,7 @@ __device__ __forceinline__ float block_sum(float v, float* sh) {
 }
 
 __device__ __forceinline__ int block_sum_int(int v, int* sh) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   const int r = sh[0] + sh[1] + sh[2] + sh[3];
@@ -44,8 +37,7 @@ __device__ __forceinline__ int block_sum_int(int v, int* sh) {
 }
 
 __device__ __forceinline__ float block_max(float v, float* sh) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  v = wave_max(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   const float r = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));

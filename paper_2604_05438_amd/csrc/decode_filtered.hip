@@ -164,21 +164,14 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
     uint32_t sfx[8], run = 0;
 #pragma unroll
     for (int e = 7; e >= 0; --e) { run += hrow[e]; sfx[e] = run; }
-    uint32_t x = run;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_down(x, o);
-      if (lane + o < 64) x += y;
-    }
-    const uint32_t above = x - run;
+    const int incl = wave_scan_incl((int)run);
+    const uint32_t above = (uint32_t)(__builtin_amdgcn_readlane(incl, 63) - incl);      // samples in the bins of higher lanes
     int best = -1, rem = 0;                                            // highest bin b with count(>= b) >= tau; tau - count(> b)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if ((int)(sfx[e] + above) >= tau) { best = lane * 8 + e; rem = tau - (int)(sfx[e] + above - hrow[e]); }
     }
-    int top = best;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) top = max(top, __shfl_xor(top, o));
+    const int top = wave_max(best);
     if (best == top && best >= 0 && (lane * 8 <= top && top < lane * 8 + 8)) { sh_bin[wv] = top; sh_rem[wv] = rem; }
     if (top < 0 && lane == 0) { sh_bin[wv] = -1; sh_rem[wv] = 0; }
   }
@@ -209,8 +202,7 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
         // the largest key with at least rem keys >= it
         if (ge >= rem) edge = max(edge, mine);
       }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) edge = max(edge, (uint32_t)__shfl_xor((int)edge, o));
+      edge = wave_max(edge);
     }
     if (lane == 0) publish(gl, edge);
   }
@@ -252,7 +244,7 @@ __device__ __forceinline__ void prep_phi(const Geom& g, const tkphi_problem& pr,
   float nrm = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) nrm = fmaf(qx[e], qx[e], nrm);
-  for (int o = LPR >> 1; o >= 1; o >>= 1) nrm += __shfl_xor(nrm, o);
+  nrm = lanes_sum(nrm, LPR);
   float* phiq = (float*)(blk + g.off_phiq) + (size_t)gq * dphi;
 #pragma unroll
   for (int k = 0; k < MAXP; ++k) {
@@ -263,7 +255,7 @@ __device__ __forceinline__ void prep_phi(const Geom& g, const tkphi_problem& pr,
     float dot = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) dot = fmaf(x[e], qx[e], dot);
-    for (int o = LPR >> 1; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
+    dot = lanes_sum(dot, LPR);
     if (jr < dphi && seg == 0) {
       const float f = expf(g.a * dot - g.c * nrm + bj[k]);
       phiq[jr] = f;
@@ -322,19 +314,15 @@ __device__ __forceinline__ void prep_anchor(const Geom& g, const tkphi_problem& 
   float s = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) s = fmaf(kx[e], qx[e], s);
-  for (int o = LPR >> 1; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  s = lanes_sum(s, LPR);
   if (seg == 0 && row < 64) a_s[row] = live ? s * g.score_scale + 0.0f : -INFINITY;
   __syncthreads();
   if (wv == 0) {
     const float sl = a_s[lane];
-    float mb = sl;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mb = fmaxf(mb, __shfl_xor(mb, o));
+    const float mb = wave_max(sl);
     const float w = lane < cnt ? __expf(sl - mb) : 0.f;
     a_w[lane] = w;
-    float Z = w;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) Z += __shfl_xor(Z, o);
+    const float Z = wave_sum(w);
     if (lane == 0) { part[0] = mb; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt; }
   }
   __syncthreads();
@@ -343,10 +331,8 @@ __device__ __forceinline__ void prep_anchor(const Geom& g, const tkphi_problem& 
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = w * vx[e];
   // rows of one wavefront that share a segment: lanes seg, seg + LPR, ...
-  for (int o = LPR; o < 64; o <<= 1) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
-  }
+  for (int e = 0; e < 8; ++e) acc[e] = strided_sum(acc[e], LPR);
   if (lane < LPR) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[wv * 128 + lane * 8 + e] = acc[e];
@@ -605,7 +591,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_f32_kernel(Geom g, cons
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(v[u][e]), __uint_as_float(qv[e]), s);
-      s = row16_sum(s);
+      s = lanes_sum(s, LPR);
       const int tok = row0 + u * RPP + rsub;
       if (seg == 0 && tok < n) {
         s = s * g.score_scale + 0.0f;              // + 0.0f: -0 -> +0, equal scores get equal keys

@@ -32,7 +32,7 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
   float nrm = 0.f;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) nrm = fmaf(qx[e], qx[e], nrm);
-  for (int o = LPR >> 1; o >= 1; o >>= 1) nrm += __shfl_xor(nrm, o);
+  nrm = lanes_sum(nrm, LPR);
   // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels
   const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR;
@@ -65,7 +65,7 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
       float dot = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) dot = fmaf(x[e], qx[e], dot);
-      for (int o = LPR >> 1; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
+      dot = lanes_sum(dot, LPR);
       if (act && jr < dphi && seg == 0) {
         const float f = expf(g.a * dot - g.c * nrm + bj[k]);
         phiq[jr] = f;
@@ -146,7 +146,7 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) s = fmaf(kx[e], qx[e], s);
-      for (int o = LPR >> 1; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+      s = lanes_sum(s, LPR);
       const int row = ps * RPP + rsub;
       if (act && seg == 0) a_s[row] = row < cnt ? s * g.score_scale + 0.0f : -INFINITY;
     }
@@ -155,13 +155,10 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
   if (wv == 0) {
     const float sl = a_s[lane];
     float mb = sl;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mb = fmaxf(mb, __shfl_xor(mb, o));
+    mb = wave_max(mb);
     const float w = lane < cnt ? __expf(sl - mb) : 0.f;
     a_w[lane] = w;
-    float Z = w;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) Z += __shfl_xor(Z, o);
+    const float Z = wave_sum(w);
     if (lane == 0) { part[0] = mb; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt; }
   }
   __syncthreads();
@@ -180,10 +177,8 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
     }
   }
   // rows of one wavefront that share a segment: lanes seg, seg + LPR, ...
-  for (int o = LPR; o < 64; o <<= 1) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o);
-  }
+  for (int e = 0; e < EPL; ++e) acc[e] = strided_sum(acc[e], LPR);
   if (act && lane < LPR) {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) red[wv * 128 + lane * EPL + e] = acc[e];

@@ -134,7 +134,7 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) s = fmaf(x[e], qreg[e], s);
-      for (int o = LPR >> 1; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+      s = lanes_sum(s, LPR);
       const int i = ps * RPP + rsub;
       if (seg == 0 && i < cnt) a_s[i] = s * g.score_scale + 0.0f;
     }
@@ -142,8 +142,7 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
   __syncthreads();
   if (tid < 64) {
     float mb = tid < cnt ? a_s[tid] : -INFINITY;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mb = fmaxf(mb, __shfl_xor(mb, o));
+    mb = wave_max(mb);
     a_w[tid] = tid < cnt ? __expf(a_s[tid] - mb) : 0.f;
     if (tid == 0) a_m = mb;
   }
@@ -221,8 +220,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   __syncthreads();
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    m = wave_max(m);
     if (tid == 0) sh_m = m;
   }
 
@@ -311,8 +309,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   __syncthreads();
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    m = wave_max(m);
     if (tid == 0) sh_m = m;
   }
   // z_t = phi_q . phi_k(k_t) of this wavefront's 16 tokens
@@ -351,8 +348,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
 #pragma unroll
       for (int e = 0; e < 4; ++e) nrm = fmaf(a[jj][e], a[jj][e], nrm);
     }
-    nrm += __shfl_xor(nrm, 16);
-    nrm += __shfl_xor(nrm, 32);                    // |k|^2 of token r
+    nrm = strided_sum(nrm, 16);                    // |k|^2 of token r
     float cn[4], z[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) { cn[i] = g.c * __shfl(nrm, 4 * kg + i); z[i] = 0.f; }
@@ -380,8 +376,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int o = 8; o >= 1; o >>= 1) z[i] += __shfl_xor(z[i], o);
+      z[i] = lanes_sum(z[i], 16);
       if (r == 0) p_z[wv * 16 + 4 * kg + i] = wv * 16 + 4 * kg + i < cnt ? z[i] : 0.f;
     }
   }
@@ -435,8 +430,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   __syncthreads();
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    m = wave_max(m);
     if (tid == 0) sh_m = m;
   }
   {
@@ -467,7 +461,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        for (int o = LPR >> 1; o >= 1; o >>= 1) zz[k] += __shfl_xor(zz[k], o);
+        zz[k] = lanes_sum(zz[k], LPR);
         const int row = r0 + k * RPP + rsub;
         if (seg == 0 && row < kPairsPerWG) p_z[row] = row < cnt ? zz[k] : 0.f;
       }

@@ -84,8 +84,7 @@ __device__ __forceinline__ void wave_feature_dots(const GatherFrag (&a)[D / 32],
 #pragma unroll
     for (int e = 0; e < 8; ++e) nrm = fmaf(x[e], x[e], nrm);
   }
-  nrm += __shfl_xor(nrm, 16);
-  nrm += __shfl_xor(nrm, 32);
+  nrm = strided_sum(nrm, 16);
   float cn[4];                                   // c |k|^2 log2(e) of tokens 4 kg + i
 #pragma unroll
   for (int i = 0; i < 4; ++i) cn[i] = c2 * __shfl(nrm, 4 * kg + i);
@@ -113,10 +112,7 @@ __device__ __forceinline__ void wave_feature_dots(const GatherFrag (&a)[D / 32],
     z[3] = fmaf(join_bf16_hi(h23, l23), pj[nt], z[3]);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) z[i] += __shfl_xor(z[i], o);
-  }
+  for (int i = 0; i < 4; ++i) z[i] = lanes_sum(z[i], 16);
 }
 
 // The same for fp32 storage, in the arithmetic of the fp32 summary build (v_mfma_f32_16x16x4_f32, four accumulator chains): a[jj] holds the channels
@@ -131,8 +127,7 @@ __device__ __forceinline__ void wave_feature_dots_f32(const GatherFrag (&a)[D / 
   for (int jj = 0; jj < CT; ++jj)
 #pragma unroll
     for (int e = 0; e < 4; ++e) nrm = fmaf(__uint_as_float(a[jj].u[e]), __uint_as_float(a[jj].u[e]), nrm);
-  nrm += __shfl_xor(nrm, 16);
-  nrm += __shfl_xor(nrm, 32);                    // |k|^2 of token r
+  nrm = strided_sum(nrm, 16);               // |k|^2 of token r
   float cn[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) { cn[i] = fc * __shfl(nrm, 4 * kg + i); z[i] = 0.f; }
@@ -155,10 +150,7 @@ __device__ __forceinline__ void wave_feature_dots_f32(const GatherFrag (&a)[D / 
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) z[i] += __shfl_xor(z[i], o);
-  }
+  for (int i = 0; i < 4; ++i) z[i] = lanes_sum(z[i], 16);
 }
 
 }  // namespace tkphi

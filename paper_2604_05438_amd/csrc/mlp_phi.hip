@@ -884,7 +884,7 @@ __global__ __launch_bounds__(kThreads) void summary_from_cache_kernel(Geom g, co
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float x = usum[k][e];
-      x += __shfl_xor(x, 1); x += __shfl_xor(x, 2); x += __shfl_xor(x, 4); x += __shfl_xor(x, 8);
+      x = lanes_sum(x, 16);
       if (tq == 0 && q4 < dphi / 4) bp[(size_t)dphi * D + q4 * 4 + e] = x;
     }
   }

@@ -22,13 +22,8 @@ __device__ __forceinline__ void write_suffix_hist(const uint32_t* lds_hist, uint
     uint32_t run = 0;
 #pragma unroll
     for (int e = 7; e >= 0; --e) { run += hrow[e]; s[e] = run; }     // suffix sums inside the lane
-    uint32_t x = run;                                                  // inclusive suffix over lanes
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_down(x, o);
-      if (lane + o < 64) x += y;
-    }
-    const uint32_t above = x - run;                                    // tokens in the bins of higher lanes
+    const int incl = wave_scan_incl((int)run);
+    const uint32_t above = (uint32_t)(__builtin_amdgcn_readlane(incl, 63) - incl);      // tokens in the bins of higher lanes
     u32x4 v;
     v.x = (s[0] + above) | ((s[1] + above) << 16);
     v.y = (s[2] + above) | ((s[3] + above) << 16);
@@ -212,11 +207,9 @@ __global__ __launch_bounds__(NTHR) void score_mid_kernel(Geom g, const tkphi_pro
         }
         acc[gl] = s;
       }
-      for (int o = LPR >> 1; o >= 1; o >>= 1) {
 #pragma unroll
-        for (int gl = 0; gl < kMaxGroup; ++gl)
-          if (gl < G) acc[gl] += __shfl_xor(acc[gl], o);
-      }
+      for (int gl = 0; gl < kMaxGroup; ++gl)
+        if (gl < G) acc[gl] = lanes_sum(acc[gl], LPR);
       if (valid && seg < G) {           // lane `seg` of the row finishes query head `seg`
         float s = acc[0];
 #pragma unroll

@@ -357,9 +357,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
         const uint64_t mine = valid ? bcand[j] : ~0ull;
         int rank = 0;
         for (int i = sub; i < nb; i += 8) rank += bcand[i] > mine ? 1 : 0;
-        rank += __shfl_xor(rank, 1);
-        rank += __shfl_xor(rank, 2);
-        rank += __shfl_xor(rank, 4);
+        rank = lanes_sum(rank, 8);
         if (valid && sub == 0 && rank == krem - 1) sh_thr = mine;
       }
       lds_barrier();
@@ -477,9 +475,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
           rank += (x0 > mine ? 1 : 0) + (x1 > mine ? 1 : 0) + (x2 > mine ? 1 : 0) + (x3 > mine ? 1 : 0);
         }
         for (; i < nb; i += 8) rank += bcand[i] > mine ? 1 : 0;
-        rank += __shfl_xor(rank, 1);
-        rank += __shfl_xor(rank, 2);
-        rank += __shfl_xor(rank, 4);
+        rank = lanes_sum(rank, 8);
         if (valid && sub == 0 && rank == krem - 1) sh_thr = mine;
       }
       lds_barrier();
@@ -645,8 +641,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       float mloc = -INFINITY;
 #pragma unroll
       for (int k = 0; k < kBatch / 64; ++k) mloc = fmaxf(mloc, b_w[lane + 64 * k]);
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, o));
+      mloc = wave_max(mloc);
       if (lane == 0) sh_m = mloc;
     }
     // z_i of this wavefront's tokens
@@ -686,10 +681,9 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
       }
     }
     if (more) load_values(b0 + kBatch);
-    for (int o = LPR; o < 64; o <<= 1) {
+    static_assert(LPR == 8 || LPR == 16, "lanes per row");
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) { an[e] += __shfl_xor(an[e], o); az[e] += __shfl_xor(az[e], o); }
-    }
+    for (int e = 0; e < EPL; ++e) { an[e] = strided_sum(an[e], LPR); az[e] = strided_sum(az[e], LPR); }
     if (lane < LPR) {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) { red[(wv * 2 + 0) * 128 + lane * EPL + e] = an[e]; red[(wv * 2 + 1) * 128 + lane * EPL + e] = az[e]; }
@@ -702,8 +696,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
         Zb += (b_w[lane + 64 * k] + b_w[lane + 64 * (k + 1)]) + (b_w[lane + 64 * (k + 2)] + b_w[lane + 64 * (k + 3)]);
         zb += (b_z[lane + 64 * k] + b_z[lane + 64 * (k + 1)]) + (b_z[lane + 64 * (k + 2)] + b_z[lane + 64 * (k + 3)]);
       }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) { Zb += __shfl_xor(Zb, o); zb += __shfl_xor(zb, o); }
+      Zb = wave_sum(Zb); zb = wave_sum(zb);
       if (lane == 0) { sh_Z = Zb; sh_zs = zb; }
     }
     lds_barrier();
@@ -772,12 +765,13 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   const bool exports = probs[p].topk_idx != nullptr;
   if (exports) __threadfence();
   __syncthreads();
-  if (threadIdx.x == 0) {
+  // (a head's only workgroup is its last, and need not ask memory: 0.6 us)
+  if (g.sg_split > 1 && threadIdx.x == 0) {
     uint32_t* arrived = (uint32_t*)(problem_block(g, ws, p) + g.off_mcount) + gq;
     sh_last = atomicAdd(arrived, 1u) == (uint32_t)g.sg_split - 1u ? 1 : 0;
   }
-  __syncthreads();
-  if (!sh_last || threadIdx.x >= kThreads) return;
+  if (g.sg_split > 1) __syncthreads();
+  if ((g.sg_split > 1 && !sh_last) || threadIdx.x >= kThreads) return;
   if (exports) __threadfence();
   // (the handed-over bound has been read: a replay of this call from a graph, whose tag is the same, must not find it)
   if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;

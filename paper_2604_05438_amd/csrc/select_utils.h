@@ -10,21 +10,16 @@ namespace tkphi {
 
 constexpr int kSelWaves = kSelThreads / 64;
 
-// inclusive prefix sum over the threads of the workgroup; sh must hold one int per wavefront; two barriers (ordering LDS only)
+// inclusive prefix sum over the threads of the workgroup (at most 16 wavefronts); sh must hold one int per wavefront; two barriers
+// (ordering LDS only)
 __device__ __forceinline__ int sel_scan_incl(int v, int* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int x = wave_scan_incl(v);
   if (lane == 63) sh[w] = x;
   lds_barrier();
-  int add = 0;
-  for (int i = 0; i < w; ++i) add += sh[i];
+  const int before = wave_scan_incl(lane < w ? sh[lane] : 0);      // lane 63: the wavefronts ahead of this one
   lds_barrier();
-  return x + add;
+  return x + __builtin_amdgcn_readlane(before, 63);
 }
 
 __device__ __forceinline__ uint64_t composite(uint32_t key, uint32_t row) {

@@ -22,22 +22,6 @@ union Frag {
   bf16x8 v;
 };
 
-// Sum over the N (power of two, <= 16) consecutive lanes that hold one row, by data-parallel-primitive
-// moves inside a row of 16 lanes: the same butterfly as xor-shuffles by 1, 2, 4, 8 (lanes that mirror
-// each other across a quad pair / a half row hold equal partial sums after the earlier steps), every
-// lane ends with the total.
-template <int N>
-__device__ __forceinline__ float row_lanes_sum(float s) {
-  auto dpp = [](float v, auto ctrl) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
-  };
-  if (N >= 2) s += dpp(s, std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
-  if (N >= 4) s += dpp(s, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
-  if (N >= 8) s += dpp(s, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  if (N >= 16) s += dpp(s, std::integral_constant<int, 0x140>{});  // row_mirror
-  return s;
-}
-
 // ------------------------------------------------------------------------------------
 // bf16 on the matrix cores: grid (n_build_chunks, Hkv, n_problems), 4 wavefronts,
 // D == d_head == d_phi.  Wavefront w owns the features [w D/4, (w+1) D/4): its slice of Wk
@@ -183,7 +167,7 @@ void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __
       sq = dot2_bf16(w.y, w.y, sq);
       sq = dot2_bf16(w.z, w.z, sq);
       sq = dot2_bf16(w.w, w.w, sq);
-      sq = row_lanes_sum<GR>(sq);
+      sq = lanes_sum(sq, GR);
       if (lane % GR == 0) nrm_t[ld_row[i]] = t0 + ld_row[i] < c1 ? c2 * sq : INFINITY;
     }
   };

@@ -5,8 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
+#include "lane_ops.h"
 #include "tkphi.h"
 
 namespace tkphi {
@@ -299,7 +298,7 @@ __device__ __forceinline__ void phi_q_head(const Geom& g, const tkphi_problem& p
           dot = fmaf(x[e], qe, dot);
           nrm = fmaf(qe, qe, nrm);
         }
-        for (int o = LPR >> 1; o >= 1; o >>= 1) { dot += __shfl_xor(dot, o); nrm += __shfl_xor(nrm, o); }
+        dot = lanes_sum(dot, LPR); nrm = lanes_sum(nrm, LPR);
         if (jr < g.dphi && seg == 0) phiq[jr] = expf(g.a * dot - g.c * nrm + bj[k]);
       }
     }
@@ -340,7 +339,7 @@ __device__ __forceinline__ void gemv_consume(int N, int Kd, int j0, const u32x4 
 #pragma unroll
     for (int e = 0; e < 8; ++e) dot = fmaf(x[e], in[sg * 8 + e], dot);
     if (k % SPL == SPL - 1) {                                        // the row's last segment of this lane
-      for (int o = LPR >> 1; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
+      dot = lanes_sum(dot, LPR);
       const int jr = j0 + pass * rows_pp + row_in;
       if (sl == 0 && jr < N) epi(jr, dot);
       dot = 0.f;
@@ -399,30 +398,6 @@ __device__ __forceinline__ void write_device_status(const Geom& g, const tkphi_p
 #define TKPHI_PHASE(ws, slot) do {} while (0)
 #define TKPHI_PHASE_VALUE(ws, slot, v) do {} while (0)
 #endif
-
-// Sum over the 16 lanes of a row, in every lane: the butterfly of xor-shuffles by 1, 2, 4, 8 as data-parallel-primitive moves (lanes that
-// mirror each other across a quad pair / a half row hold equal partial sums after the earlier steps)
-__device__ __forceinline__ float row16_sum(float s) {
-  const auto dpp = [](float v, auto ctrl) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
-  };
-  s += dpp(s, std::integral_constant<int, 0xB1>{});    // quad_perm [1, 0, 3, 2]
-  s += dpp(s, std::integral_constant<int, 0x4E>{});    // quad_perm [2, 3, 0, 1]
-  s += dpp(s, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  s += dpp(s, std::integral_constant<int, 0x140>{});   // row_mirror
-  return s;
-}
-
-// Inclusive prefix sum over the lanes of a wavefront by data-parallel-primitive moves (inside rows of 16 lanes, then across them)
-__device__ __forceinline__ int wave_scan_incl(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
-  return x;
-}
 
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every global load the wavefront
 // has in flight (its fences cover global memory); where a barrier only hands LDS data from one wavefront to

@@ -237,13 +237,8 @@ __global__ __launch_bounds__(kThreads) void select_emit_kernel(Geom g, const tkp
       }
       // exclusive prefix over lanes of (na, nc) packed in one int (each <= 256)
       const int packed = na | (nc << 16);
-      int x = packed;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
-      const int total = __shfl(x, 63);
+      const int x = wave_scan_incl(packed);
+      const int total = __builtin_amdgcn_readlane(x, 63);
       int pa = a_pos + ((x - packed) & 0xffff), pc = c_pos + ((x - packed) >> 16);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -325,9 +320,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resolve_kernel(Geom g, con
           rank += (c0 > mine ? 1 : 0) + (c1 > mine ? 1 : 0) + (c2 > mine ? 1 : 0) + (c3 > mine ? 1 : 0);
         }
         for (; i < nb; i += 8) rank += sh_comp[i] > mine ? 1 : 0;
-        rank += __shfl_xor(rank, 1);
-        rank += __shfl_xor(rank, 2);
-        rank += __shfl_xor(rank, 4);
+        rank = lanes_sum(rank, 8);
         if (valid && sub == 0 && rank < k_cap) {
           sel_idx[c_hi + rank] = (int)(0xffffffffu - (uint32_t)mine);
           sel_score[c_hi + rank] = key_score((uint32_t)(mine >> 32));
