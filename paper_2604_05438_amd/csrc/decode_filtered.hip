@@ -95,8 +95,8 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
   TKPHI_WAVE_MARK((blk - g.off_problem0), 64);       // sample job entered
   for (int i = tid; i < G * kBins; i += NTHR) hist[i] = 0u;
   if (tid < G) nin[tid] = 0;
-  ScoreFrag bq[KS];
-  load_query_frags<D>(g, pr, h, bq);
+  ScoreFrag bq[kQueryFrags<D, false>];
+  load_query_frags<D, false>(g, pr, h, bq);
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
   const char* K0 = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + (size_t)(lane % LPRW) * 16;
   char* stage = stage_all + (size_t)wv * 16 * ROWP;
@@ -124,9 +124,7 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
       ScoreFrag a[KS];
 #pragma unroll
       for (int j = 0; j < KS; ++j) a[j].u = *(const u32x4*)(stage + r * ROWP + j * 64 + kg * 16);
-      st_floatx4 acc = (st_floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < KS; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].v, bq[j].v, acc, 0, 0, 0);
+      const st_floatx4 acc = score_tile<D, false>(a, bq);
       // lane (r, kg) holds head r's scores of samples i0 + t 16 + 4 kg + {0..3}: to LDS, so that every lane
       // takes part in what follows (12 of 64 lanes hold all the scores here)
       if (r >= gl0 && r < gl0 + G) *(st_floatx4*)(sc + (r - gl0) * 1024 + i0 + t * 16 + 4 * kg) = acc;
@@ -394,7 +392,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
 // against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
 // as large, gain nothing at 128K and lose 2 us at 32K (the first group is consumed later).  Groups of TPI / 2 for batches at
 // d = 64: within 0.6 % either way over 66 batches of 4 to 400 sequences on the same buffers.
-template <int D, int TPI, bool STRIP>
+template <int D, int TPI, bool STREAM, bool STRIP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                   char* __restrict__ ws) {
   const int p = blockIdx.z, h = blockIdx.y;
@@ -408,12 +406,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   if (chunk >= n_chunks) return;
   char* blk = problem_block(g, ws, p);
   const int r = threadIdx.x & 15;
-  ScoreFrag bq[D / 32];
-  load_query_frags<D>(g, pr, h, bq);
+  ScoreFrag bq[kQueryFrags<D, STREAM>];
+  load_query_frags<D, STREAM>(g, pr, h, bq);
   const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
   extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  scan_wave_slot<D, TPI, TPI / 4, 2, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r,
+  scan_wave_slot<D, TPI, TPI / 4, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r,
                                                        (lds_u32x2)sh_heads + (STRIP ? wv * g.G * g.cand_T : 0));
 }
 
@@ -442,7 +440,7 @@ __device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk,
 // the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10.7).  Prep + score
 // launches / this one: 11.1 + 48.7 / 52.5 us and 7.6 + 9.6 / 13.5 us.
 constexpr int kFusedThreads = 512;
-template <int D, int TPI>
+template <int D, int TPI, bool STREAM>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                                                               char* __restrict__ ws) {
   extern __shared__ __attribute__((aligned(16))) float sh_dyn[];
@@ -482,10 +480,10 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   const int h = x / g.n_scan_chunks, chunk = (x % g.n_scan_chunks + h + p * g.Hkv) % g.n_scan_chunks;
   if (chunk >= n_chunks) return;
   if (threadIdx.x == 0) sh_n = NWV;
-  ScoreFrag bq[D / 32];
-  load_query_frags<D>(g, pr, h, bq);
+  ScoreFrag bq[kQueryFrags<D, STREAM>];
+  load_query_frags<D, STREAM>(g, pr, h, bq);
   lds_barrier();
-  scan_keep<D, TPI / 4, NWV>(g, pr, h, n, n_chunks, chunk, bq, (lds_f32)sh_dyn, &sh_n);
+  scan_keep<D, TPI / 4, NWV, STREAM>(g, pr, h, n, n_chunks, chunk, bq, (lds_f32)sh_dyn, &sh_n);
   const uint32_t edge = await_bounds(g, blk, h);
   lds_barrier();
   list_kept<D, NWV>(g, pr, blk, h, n, n_chunks, chunk, (lds_f32)sh_dyn, edge);
@@ -534,10 +532,10 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int chunk = x - n_side, n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
   if (chunk >= n_chunks) return;
-  ScoreFrag bq[D / 32];
-  load_query_frags<D>(g, pr, h, bq);
+  ScoreFrag bq[kQueryFrags<D, false>];
+  load_query_frags<D, false>(g, pr, h, bq);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  scan_wave_slot<D, TPI, TPI / 4, 2, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, (lds_u32x2) nullptr);
+  scan_wave_slot<D, TPI, TPI / 4, 2, false, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, (lds_u32x2) nullptr);
 }
 
 void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
@@ -549,8 +547,8 @@ void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hip
     if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
     TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kFusedThreads), lds, s, g, probs, ws);
   };
-  if (g.d == 128) launch(score_fused_kernel<128, 4>);
-  else launch(score_fused_kernel<64, 8>);
+  if (g.d == 128) { if (g.stream_keys) launch(score_fused_kernel<128, 4, true>); else launch(score_fused_kernel<128, 4, false>); }
+  else { if (g.stream_keys) launch(score_fused_kernel<64, 8, true>); else launch(score_fused_kernel<64, 8, false>); }
 }
 
 // The same for fp32 caches (d = 64): scores in vector arithmetic, 128 rows per workgroup and all of them requested before the first
@@ -641,8 +639,12 @@ void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, 
   dim3 grid(g.n_scan_chunks, g.Hkv, g.n_problems);
   const size_t lds = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
   const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
-  if (g.d == 128) { if (g.head_strip) launch(score_filtered_kernel<128, 4, true>); else launch(score_filtered_kernel<128, 4, false>); }
-  else { if (g.head_strip) launch(score_filtered_kernel<64, 8, true>); else launch(score_filtered_kernel<64, 8, false>); }
+  const auto launch_as = [&](auto strip, auto stream) {
+    if (g.d == 128) launch(score_filtered_kernel<128, 4, decltype(stream)::value, decltype(strip)::value>);
+    else launch(score_filtered_kernel<64, 8, decltype(stream)::value, decltype(strip)::value>);
+  };
+  if (g.head_strip) { if (g.stream_keys) launch_as(std::true_type(), std::true_type()); else launch_as(std::true_type(), std::false_type()); }
+  else { if (g.stream_keys) launch_as(std::false_type(), std::true_type()); else launch_as(std::false_type(), std::false_type()); }
 }
 
 }  // namespace tkphi

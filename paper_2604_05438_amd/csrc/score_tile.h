@@ -20,16 +20,67 @@ union ScoreFrag {
   st_bf16x8 v;
 };
 
-// B operand of the score MFMA: column r = query head h G + r of the group (zero for r >= G);
-// lane (r, kg) holds channels j 32 + kg 8 .. + 8 of k-step j.
-template <int D>
-__device__ __forceinline__ void load_query_frags(const Geom& g, const tkphi_problem& pr, int h, ScoreFrag (&bq)[D / 32]) {
-  const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
+// The score contraction of 16 rows, in one of two layouts of the key loads.
+// LINES: a load instruction covers 8 rows x 128 bytes, whole cache lines: lane (r, kg) takes 16 bytes of row r mod 8, in the first
+// half of its line for r < 8, in the second for r >= 8.  As the A operand of one MFMA that makes row r of the product the first 32
+// channels (of a line's 64) of row r, and row 8 + r the other 32; the B operand holds the query heads' first 32 channels in the columns
+// 0 .. 7 and their other 32 in the columns 8 .. 15, so that the score of (row m, head c) is P[m][c] + P[8 + m][8 + c].
+// Otherwise 16 rows x 64 bytes, the plain operand layout (lane (r, kg): row r, channels 32 j + 8 kg ..), which requests every line twice.
+// Streaming 6 GB of 128- or 256-byte rows: whole lines 7.2 to 7.3 TB/s with non-temporal loads and 6.4 with plain ones, half lines 6.0
+// and 6.4; so non-temporal loads come with LINES, and where plain ones are right (keys that the caches hold until the select
+// kernel reads its share again) the plain layout saves the sum: 1B layer at 64K 33.7 us per step against 34.6.
+template <int D, bool LINES> constexpr int kQueryFrags = LINES ? D / 64 : D / 32;
+template <int D> constexpr int kTileFrags = D / 32;
+template <int D, bool LINES>
+__device__ __forceinline__ void load_query_frags(const Geom& g, const tkphi_problem& pr, int h, ScoreFrag (&bq)[kQueryFrags<D, LINES>]) {
+  const int lane = threadIdx.x & 63, c = lane & 15, kg = lane >> 4, head = LINES ? c & 7 : c;
 #pragma unroll
-  for (int j = 0; j < D / 32; ++j) {
+  for (int j = 0; j < kQueryFrags<D, LINES>; ++j) {
     bq[j].u = (u32x4){0u, 0u, 0u, 0u};
-    if (r < g.G) bq[j].u = gload128((const uint16_t*)pr.q + (size_t)(h * g.G + r) * D + j * 32 + kg * 8);
+    if (head < g.G) bq[j].u = gload128((const uint16_t*)pr.q + (size_t)(h * g.G + head) * D + (LINES ? j * 64 + (c >> 3) * 32 : j * 32) + kg * 8);
   }
+}
+// bytes that the lane adds to the address of its row
+template <bool LINES>
+__device__ __forceinline__ int score_lane_offset() {
+  return (LINES ? ((threadIdx.x >> 3) & 1) * 64 : 0) + ((threadIdx.x >> 4) & 3) * 16;
+}
+// row_of(i): address of row i of the tile plus score_lane_offset(); LINES: non-temporal
+template <int D, bool LINES, typename RowOf>
+__device__ __forceinline__ void request_tile(ScoreFrag (&f)[kTileFrags<D>], RowOf&& row_of) {
+  if constexpr (LINES) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const char* rp = row_of(u * 8 + (int)(threadIdx.x & 7));
+#pragma unroll
+      for (int j = 0; j < D / 64; ++j) f[u * (D / 64) + j].u = gload128_stream(rp + j * 128);
+    }
+  } else {
+    const char* rp = row_of((int)(threadIdx.x & 15));
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j) f[j].u = gload128(rp + j * 64);
+  }
+}
+// unscaled scores: lane (r < G, kg) gets those of head r and the rows 4 kg + {0 .. 3}
+template <int D, bool LINES>
+__device__ __forceinline__ st_floatx4 score_tile(const ScoreFrag (&f)[kTileFrags<D>], const ScoreFrag (&bq)[kQueryFrags<D, LINES>]) {
+  constexpr int NP = LINES ? 2 : 1, NJ = kQueryFrags<D, LINES>;
+  st_floatx4 p[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    p[u] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) p[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[u * NJ + j].v, bq[j].v, p[u], 0, 0, 0);
+  }
+  if constexpr (!LINES) return p[0];
+  st_floatx4 s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    // lanes kg < 2 of the first eight rows' product and of the second eight's; the same of the other 32 channels' (lanes kg >= 2)
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0][i]), __float_as_uint(p[NP - 1][i]), false, false);
+    s[i] = __uint_as_float(x[0]) + dpp_move<0x128>(__uint_as_float(x[1]));           // row_ror:8
+  }
+  return s;
 }
 
 // Candidate lists of the filtered selection.  A score chunk is scanned by four wavefront slots; slot
@@ -51,14 +102,13 @@ __device__ __forceinline__ size_t cand_region(const Geom& g, int gq, int chunk, 
 // Lane (r, kg) ends up with the scores of head r for tokens base + t 16 + 4 kg + i, so each list is
 // written by the four lanes of its column, in the order (unit, t, i, kg).
 // SUB: 16-token tiles loaded and contracted together; NB: groups of SUB tiles in registers, NB - 1 of them on their way while one
-// is contracted
+// is contracted; STREAM: non-temporal loads of whole lines
 // STRIP: `strip` is used (a template parameter, and address spaces spelled out on every pointer stored through: a store that
 // might go to LDS or to memory becomes a flat store, after which the compiler waits for every load in flight)
 // DIRECT: no bound and no lists; every score goes to the head's row of Geom::off_scores
-template <int D, int TPI, int SUB, int NB, bool STRIP, bool DIRECT = false>
+template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP, bool DIRECT = false>
 __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks,
-                                               int chunk, int wslot, const ScoreFrag (&bq)[D / 32], uint32_t edge_r, lds_u32x2 strip) {
-  constexpr int KS = D / 32;
+                                               int chunk, int wslot, const ScoreFrag (&bq)[kQueryFrags<D, STREAM>], uint32_t edge_r, lds_u32x2 strip) {
   constexpr int TOK = TPI * 16;         // tokens per wavefront and unit
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int G = g.G;
@@ -81,24 +131,17 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
   float edge_s;
   auto float_bound = [&]() { edge_s = !col_live || edge_r == 0xffffffffu ? INFINITY : edge_r == 0u ? -INFINITY : key_score(edge_r); };
 
-  ScoreFrag a[NB][SUB][KS];
-  const char* const Kl = Kb + kg * 16;
-  auto request = [&](int base, ScoreFrag (&f)[SUB][KS]) {
+  ScoreFrag a[NB][SUB][kTileFrags<D>];
+  const char* const Kl = Kb + score_lane_offset<STREAM>();
+  auto request = [&](int base, ScoreFrag (&f)[SUB][kTileFrags<D>]) {
 #pragma unroll
-    for (int t = 0; t < SUB; ++t) {
-      const char* rp = Kl + (uint64_t)(uint32_t)min(base + t * 16 + r, n - 1) * row_bytes;     // rows past the end repeat the last one
-#pragma unroll
-      for (int j = 0; j < KS; ++j) f[t][j].u = gload128(rp + j * 64);
-    }
+    for (int t = 0; t < SUB; ++t)          // (rows past the end repeat the last one)
+      request_tile<D, STREAM>(f[t], [&](int i) { return Kl + (uint64_t)(uint32_t)min(base + t * 16 + i, n - 1) * row_bytes; });
   };
-  auto contract = [&](int base, const ScoreFrag (&f)[SUB][KS]) {
+  auto contract = [&](int base, const ScoreFrag (&f)[SUB][kTileFrags<D>]) {
     st_floatx4 acc[SUB];
 #pragma unroll
-    for (int t = 0; t < SUB; ++t) {
-      acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][j].v, bq[j].v, acc[t], 0, 0, 0);
-    }
+    for (int t = 0; t < SUB; ++t) acc[t] = score_tile<D, STREAM>(f[t], bq);
     if constexpr (DIRECT) {
 #pragma unroll
       for (int t = 0; t < SUB; ++t) {
@@ -176,17 +219,16 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
 // the chunk stay in LDS, keep[head of the group][position], position = token's place in the order of the chunk's units.
 // The wavefronts draw groups of SUB tiles from a counter in LDS: of two workgroups that share a CU the older one gets its loads
 // served first, so that with a fixed share for each the second half ran alone for the last quarter of the pass (3B layer at 128K: the
-// older ones done after 33 us, the younger after 44).  Rows of 256 bytes are read with non-temporal loads: the pass itself takes as
-// long, but the lists, phi_q and the problem record are still in the caches when the select kernel starts (25.5 -> 24.9 us); of rows
-// of 128 bytes the two loads that share a cache line would fetch it twice (a batch's pass 20 % longer).
-template <int D, int SUB, int NWV>
+// older ones done after 33 us, the younger after 44).
+// Non-temporal loads (above) also leave the lists, phi_q and the problem record in the caches for the select kernel.
+template <int D, int SUB, int NWV, bool STREAM>
 __device__ __forceinline__ void scan_keep(const Geom& g, const tkphi_problem& pr, int h, int n, int n_chunks, int chunk,
-                                          const ScoreFrag (&bq)[D / 32], lds_f32 keep, int* next /*LDS, NWV*/) {
-  constexpr int KS = D / 32, GT = SUB * 16;
+                                          const ScoreFrag (&bq)[kQueryFrags<D, STREAM>], lds_f32 keep, int* next /*LDS, NWV*/) {
+  constexpr int GT = SUB * 16;
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
-  const char* const Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + kg * 16;
+  const char* const Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + score_lane_offset<STREAM>();
   constexpr int per_unit = keep_unit(D) / GT;
   const int n_groups = g.scan_chunk / GT;
   auto group_base = [&](int q) { return q < n_groups ? chunk_unit_token(g, n_chunks, chunk, q / per_unit) + (q % per_unit) * GT : n; };
@@ -195,23 +237,16 @@ __device__ __forceinline__ void scan_keep(const Geom& g, const tkphi_problem& pr
     if (lane == 0) q = atomicAdd(next, 1);
     return __builtin_amdgcn_readfirstlane(q);
   };
-  ScoreFrag a[2][SUB][KS];
-  auto request = [&](int base, ScoreFrag (&f)[SUB][KS]) {      // (unconditional: rows past the end repeat the last one)
+  ScoreFrag a[2][SUB][kTileFrags<D>];
+  auto request = [&](int base, ScoreFrag (&f)[SUB][kTileFrags<D>]) {      // (unconditional: rows past the end repeat the last one)
 #pragma unroll
-    for (int t = 0; t < SUB; ++t) {
-      const char* rp = Kl + (uint64_t)(uint32_t)min(base + t * 16 + r, n - 1) * row_bytes;
-#pragma unroll
-      for (int j = 0; j < KS; ++j) f[t][j].u = D == 128 ? gload128_stream(rp + j * 64) : gload128(rp + j * 64);
-    }
+    for (int t = 0; t < SUB; ++t)
+      request_tile<D, STREAM>(f[t], [&](int i) { return Kl + (uint64_t)(uint32_t)min(base + t * 16 + i, n - 1) * row_bytes; });
   };
-  auto contract = [&](int q, int base, const ScoreFrag (&f)[SUB][KS]) {
+  auto contract = [&](int q, int base, const ScoreFrag (&f)[SUB][kTileFrags<D>]) {
     st_floatx4 acc[SUB];
 #pragma unroll
-    for (int t = 0; t < SUB; ++t) {
-      acc[t] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < KS; ++j) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][j].v, bq[j].v, acc[t], 0, 0, 0);
-    }
+    for (int t = 0; t < SUB; ++t) acc[t] = score_tile<D, STREAM>(f[t], bq);
     if (r < g.G && base < n) {
 #pragma unroll
       for (int t = 0; t < SUB; ++t) *(lds_f32x4)(keep + r * g.scan_chunk + q * GT + t * 16 + 4 * kg) = acc[t];

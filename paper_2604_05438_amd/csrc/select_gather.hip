@@ -56,22 +56,18 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
   const int h = gq / g.G, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
-  ScoreFrag bq[D / 32];
-  load_query_frags<D>(g, pr, h, bq);
-  const char* Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + kg * 16;
+  ScoreFrag bq[kQueryFrags<D, false>];
+  load_query_frags<D, false>(g, pr, h, bq);
+  const char* Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + score_lane_offset<false>();
   for (int reg = wv; reg < n_reg; reg += NTHR / 64) {
     const size_t idx = (size_t)gq * g.n_scan_chunks * 4 + reg;
     const glb_u32x2 list = (glb_u32x2)(blk + g.off_resf) + idx * (size_t)cap;
     const glb_u32x2 head = (glb_u32x2)(blk + g.off_resc) + idx * (size_t)T;
     const int t0 = reg * cap, cnt = max(0, min(cap, n - t0));
     for (int o = 0; o < cnt; o += 16) {
-      const char* rp = Kl + (uint64_t)(uint32_t)min(t0 + o + r, n - 1) * (uint64_t)(pr.stride_tok * 2);
-      ScoreFrag a[D / 32];
-#pragma unroll
-      for (int j = 0; j < D / 32; ++j) a[j].u = gload128(rp + j * 64);
-      st_floatx4 acc = (st_floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < D / 32; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].v, bq[j].v, acc, 0, 0, 0);
+      ScoreFrag a[kTileFrags<D>];
+      request_tile<D, false>(a, [&](int i) { return Kl + (uint64_t)(uint32_t)min(t0 + o + i, n - 1) * (uint64_t)(pr.stride_tok * 2); });
+      const st_floatx4 acc = score_tile<D, false>(a, bq);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int at = o + 4 * kg + i;

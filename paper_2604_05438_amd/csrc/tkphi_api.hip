@@ -226,6 +226,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->interleave = tn.interleave ? (tn.interleave == 1 ? 1 : 0)
                                 : (g->use_mfma && g->scan_unit < g->scan_chunk && (g->fused || (g->n_scan_chunks >= 64 && (n_problems == 1 || !g->filtered)))) ? 1 : 0;
   if (!g->use_mfma || g->scan_unit >= g->scan_chunk) g->interleave = 0;
+  // The filtered score pass reads keys of more than 64 MB (by the bounds) with non-temporal loads of whole lines (score_tile.h): 256
+  // ragged sequences 2857 -> 2653 us per step, 16 208 -> 188, the 3B layer at 128K 73.4 -> 69.3, at 48K 42.3 -> 41.9; less than that is
+  // served from the caches to the select kernel's gather: 1B layer at 32K 28.2 -> 28.9.
+  g->stream_keys = units * g->d * 2 > ((int64_t)64 << 20) ? 1 : 0;
   g->sel_test = tn.select_test;
   // gather: tiles of kPairsPerWG retrieved tokens per query head
   g->n_tiles = (int)ceil_div(std::min<int64_t>(max_K, g->max_mid), kPairsPerWG);

@@ -26,6 +26,27 @@ def test_score_groups_at_every_end(shape, chunk, interleave):
         PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+@pytest.mark.parametrize("shape", ["l3b_128k", "l1b_32k"])
+def test_whole_line_loads_at_every_end(shape):
+    """The layout of the key loads that calls of more than 64 MB of keys (by their bounds) take: mid-regions that end around the 8 rows
+    of a load instruction, the 16 of a tile and the groups, far inside the bounds; one problem at a time (scores kept in LDS) and a
+    batch (lists on the way).  Scores, index sets and outputs against the oracle."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    mids = [1, 7, 8, 9, 15, 16, 17, 24, 31, 33, 65, 127, 130, 1000, 2049]
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(mids)]
+    ks = [max(1, m // 9) for m in mids]
+    for sel in ([1], [3], [6], [9], [14], range(len(mids))):
+        b = H.Batch(H.config_of(w, tuning={"select_mode": 2}), [layers[i] for i in sel], [ks[i] for i in sel], debug=True, max_L=140000,
+                    max_K=400)
+        b.build()
+        b.decode()
+        assert b.status() & ~2 == 0
+        for i, at in enumerate(sel):
+            PU.check_layer(w, layers[at], ks[at], b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
 @pytest.mark.parametrize("shape,unit", [("l3b_128k", 64), ("l1b_32k", 128)])
 @pytest.mark.parametrize("units,interleave", [(1, 0), (3, 1), (5, 2), (17, 1)])
 def test_kept_scores_at_every_end(shape, unit, units, interleave):
