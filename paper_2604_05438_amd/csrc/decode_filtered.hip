@@ -436,9 +436,9 @@ __device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk,
 // (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks.  A score workgroup keeps its scores in LDS (G scan_chunk floats) and lists those that reach the bound at
 // (With MLP maps, Geom::list, the first stage of phi_q instead of the phi and anchor jobs, behind the score chunks.)
 // its end, when the sample is long since done: the launch that only sampled had nothing to run beside it.  Bound by HBM for long
-// contexts (3B layer at 128K: 268 MB in 45 us behind 2 us of prologue; CUs that also sample end 3 us late, the lists take 1.6), by
-// the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10.7).  Prep + score
-// launches / this one: 11.1 + 48.7 / 52.5 us and 7.6 + 9.6 / 13.5 us.
+// contexts (3B layer at 128K: 268 MB; behind the last row the lists take 1.6 us, CUs that also sample end 3 us late), by the
+// sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10).  Prep + score launches /
+// this one: 11.1 + 48.7 / 47.5 us (52.5 with half-line loads) and 7.6 + 9.6 / 12.4 us.
 constexpr int kFusedThreads = 512;
 template <int D, int TPI, bool STREAM>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,
