@@ -95,8 +95,8 @@ __device__ __forceinline__ void prep_sample(const Geom& g, const tkphi_problem& 
   TKPHI_WAVE_MARK((blk - g.off_problem0), 64);       // sample job entered
   for (int i = tid; i < G * kBins; i += NTHR) hist[i] = 0u;
   if (tid < G) nin[tid] = 0;
-  ScoreFrag bq[kQueryFrags<D, false>];
-  load_query_frags<D, false>(g, pr, h, bq);
+  ScoreFrag bq[kTileFrags<D>];
+  load_query_frags<D>(g, pr, h, bq);
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
   const char* K0 = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + (size_t)(lane % LPRW) * 16;
   char* stage = stage_all + (size_t)wv * 16 * ROWP;
@@ -406,8 +406,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   if (chunk >= n_chunks) return;
   char* blk = problem_block(g, ws, p);
   const int r = threadIdx.x & 15;
-  ScoreFrag bq[kQueryFrags<D, STREAM>];
-  load_query_frags<D, STREAM>(g, pr, h, bq);
+  ScoreFrag bq[kTileFrags<D>];
+  load_query_frags<D>(g, pr, h, bq);
   const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
   extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -480,8 +480,8 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   const int h = x / g.n_scan_chunks, chunk = (x % g.n_scan_chunks + h + p * g.Hkv) % g.n_scan_chunks;
   if (chunk >= n_chunks) return;
   if (threadIdx.x == 0) sh_n = NWV;
-  ScoreFrag bq[kQueryFrags<D, STREAM>];
-  load_query_frags<D, STREAM>(g, pr, h, bq);
+  ScoreFrag bq[kTileFrags<D>];
+  load_query_frags<D>(g, pr, h, bq);
   lds_barrier();
   scan_keep<D, TPI / 4, NWV, STREAM>(g, pr, h, n, n_chunks, chunk, bq, (lds_f32)sh_dyn, &sh_n);
   const uint32_t edge = await_bounds(g, blk, h);
@@ -532,8 +532,8 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int chunk = x - n_side, n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
   if (chunk >= n_chunks) return;
-  ScoreFrag bq[kQueryFrags<D, false>];
-  load_query_frags<D, false>(g, pr, h, bq);
+  ScoreFrag bq[kTileFrags<D>];
+  load_query_frags<D>(g, pr, h, bq);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   scan_wave_slot<D, TPI, TPI / 4, 2, false, false, true>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, 0u, (lds_u32x2) nullptr);
 }

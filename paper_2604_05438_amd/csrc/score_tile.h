@@ -22,22 +22,23 @@ union ScoreFrag {
 
 // The score contraction of 16 rows, in one of two layouts of the key loads.
 // LINES: a load instruction covers 8 rows x 128 bytes, whole cache lines: lane (r, kg) takes 16 bytes of row r mod 8, in the first
-// half of its line for r < 8, in the second for r >= 8.  As the A operand of one MFMA that makes row r of the product the first 32
-// channels (of a line's 64) of row r, and row 8 + r the other 32; the B operand holds the query heads' first 32 channels in the columns
-// 0 .. 7 and their other 32 in the columns 8 .. 15, so that the score of (row m, head c) is P[m][c] + P[8 + m][8 + c].
+// half of its line for r < 8, in the second for r >= 8; eight lanes of the first eight rows' register then change places with eight of
+// the second eight rows', which makes the plain operands of both.
 // Otherwise 16 rows x 64 bytes, the plain operand layout (lane (r, kg): row r, channels 32 j + 8 kg ..), which requests every line twice.
+// Either way a score is the same sum in the same order, bit for bit: the bound that a call samples in one layout prunes what it scores in
+// the other, and a mid-region that is sampled whole has its K-th score itself for a bound.
 // Streaming 6 GB of 128- or 256-byte rows: whole lines 7.2 to 7.3 TB/s with non-temporal loads and 6.4 with plain ones, half lines 6.0
 // and 6.4; so non-temporal loads come with LINES, and where plain ones are right (keys that the caches hold until the select
-// kernel reads its share again) the plain layout saves the sum: 1B layer at 64K 33.7 us per step against 34.6.
-template <int D, bool LINES> constexpr int kQueryFrags = LINES ? D / 64 : D / 32;
+// kernel reads its share again) the plain layout saves the moves: 1B layer at 64K 33.7 us per step against 34.6.
 template <int D> constexpr int kTileFrags = D / 32;
-template <int D, bool LINES>
-__device__ __forceinline__ void load_query_frags(const Geom& g, const tkphi_problem& pr, int h, ScoreFrag (&bq)[kQueryFrags<D, LINES>]) {
-  const int lane = threadIdx.x & 63, c = lane & 15, kg = lane >> 4, head = LINES ? c & 7 : c;
+// the query heads' operand: lane (r, kg) holds the channels 32 j + 8 kg .. of head h G + r
+template <int D>
+__device__ __forceinline__ void load_query_frags(const Geom& g, const tkphi_problem& pr, int h, ScoreFrag (&bq)[kTileFrags<D>]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
 #pragma unroll
-  for (int j = 0; j < kQueryFrags<D, LINES>; ++j) {
+  for (int j = 0; j < kTileFrags<D>; ++j) {
     bq[j].u = (u32x4){0u, 0u, 0u, 0u};
-    if (head < g.G) bq[j].u = gload128((const uint16_t*)pr.q + (size_t)(h * g.G + head) * D + (LINES ? j * 64 + (c >> 3) * 32 : j * 32) + kg * 8);
+    if (r < g.G) bq[j].u = gload128((const uint16_t*)pr.q + (size_t)(h * g.G + r) * D + j * 32 + kg * 8);
   }
 }
 // bytes that the lane adds to the address of its row
@@ -53,7 +54,7 @@ __device__ __forceinline__ void request_tile(ScoreFrag (&f)[kTileFrags<D>], RowO
     for (int u = 0; u < 2; ++u) {
       const char* rp = row_of(u * 8 + (int)(threadIdx.x & 7));
 #pragma unroll
-      for (int j = 0; j < D / 64; ++j) f[u * (D / 64) + j].u = gload128_stream(rp + j * 128);
+      for (int j = 0; j < D / 64; ++j) f[2 * j + u].u = gload128_stream(rp + j * 128);
     }
   } else {
     const char* rp = row_of((int)(threadIdx.x & 15));
@@ -63,24 +64,23 @@ __device__ __forceinline__ void request_tile(ScoreFrag (&f)[kTileFrags<D>], RowO
 }
 // unscaled scores: lane (r < G, kg) gets those of head r and the rows 4 kg + {0 .. 3}
 template <int D, bool LINES>
-__device__ __forceinline__ st_floatx4 score_tile(const ScoreFrag (&f)[kTileFrags<D>], const ScoreFrag (&bq)[kQueryFrags<D, LINES>]) {
-  constexpr int NP = LINES ? 2 : 1, NJ = kQueryFrags<D, LINES>;
-  st_floatx4 p[NP];
+__device__ __forceinline__ st_floatx4 score_tile(const ScoreFrag (&f)[kTileFrags<D>], const ScoreFrag (&bq)[kTileFrags<D>]) {
+  st_floatx4 p = (st_floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int u = 0; u < NP; ++u) {
-    p[u] = (st_floatx4){0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < kTileFrags<D>; j += 2) {
+    ScoreFrag a = f[j], b = f[j + 1];
+    if constexpr (LINES) {
+      // lanes 8 .. 15 of each row of 16 of the one <-> lanes 0 .. 7 of the other (row_ror:8 into two banks of four lanes)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) p[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[u * NJ + j].v, bq[j].v, p[u], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) {
+        a.u[e] = (uint32_t)__builtin_amdgcn_update_dpp((int)f[j].u[e], (int)f[j + 1].u[e], 0x128, 0xf, 0xc, false);
+        b.u[e] = (uint32_t)__builtin_amdgcn_update_dpp((int)f[j + 1].u[e], (int)f[j].u[e], 0x128, 0xf, 0x3, false);
+      }
+    }
+    p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, bq[j].v, p, 0, 0, 0);
+    p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, bq[j + 1].v, p, 0, 0, 0);
   }
-  if constexpr (!LINES) return p[0];
-  st_floatx4 s;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // lanes kg < 2 of the first eight rows' product and of the second eight's; the same of the other 32 channels' (lanes kg >= 2)
-    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0][i]), __float_as_uint(p[NP - 1][i]), false, false);
-    s[i] = __uint_as_float(x[0]) + dpp_move<0x128>(__uint_as_float(x[1]));           // row_ror:8
-  }
-  return s;
+  return p;
 }
 
 // Candidate lists of the filtered selection.  A score chunk is scanned by four wavefront slots; slot
@@ -108,7 +108,7 @@ __device__ __forceinline__ size_t cand_region(const Geom& g, int gq, int chunk, 
 // DIRECT: no bound and no lists; every score goes to the head's row of Geom::off_scores
 template <int D, int TPI, int SUB, int NB, bool STREAM, bool STRIP, bool DIRECT = false>
 __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks,
-                                               int chunk, int wslot, const ScoreFrag (&bq)[kQueryFrags<D, STREAM>], uint32_t edge_r, lds_u32x2 strip) {
+                                               int chunk, int wslot, const ScoreFrag (&bq)[kTileFrags<D>], uint32_t edge_r, lds_u32x2 strip) {
   constexpr int TOK = TPI * 16;         // tokens per wavefront and unit
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int G = g.G;
@@ -223,7 +223,7 @@ __device__ __forceinline__ void scan_wave_slot(const Geom& g, const tkphi_proble
 // Non-temporal loads (above) also leave the lists, phi_q and the problem record in the caches for the select kernel.
 template <int D, int SUB, int NWV, bool STREAM>
 __device__ __forceinline__ void scan_keep(const Geom& g, const tkphi_problem& pr, int h, int n, int n_chunks, int chunk,
-                                          const ScoreFrag (&bq)[kQueryFrags<D, STREAM>], lds_f32 keep, int* next /*LDS, NWV*/) {
+                                          const ScoreFrag (&bq)[kTileFrags<D>], lds_f32 keep, int* next /*LDS, NWV*/) {
   constexpr int GT = SUB * 16;
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

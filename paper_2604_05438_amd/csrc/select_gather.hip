@@ -56,8 +56,8 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
   const int h = gq / g.G, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
-  ScoreFrag bq[kQueryFrags<D, false>];
-  load_query_frags<D, false>(g, pr, h, bq);
+  ScoreFrag bq[kTileFrags<D>];
+  load_query_frags<D>(g, pr, h, bq);
   const char* Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + score_lane_offset<false>();
   for (int reg = wv; reg < n_reg; reg += NTHR / 64) {
     const size_t idx = (size_t)gq * g.n_scan_chunks * 4 + reg;

@@ -47,6 +47,37 @@ def test_whole_line_loads_at_every_end(shape):
             PU.check_layer(w, layers[at], ks[at], b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+@pytest.mark.parametrize("shape", ["l3b_128k", "l1b_32k"])
+@pytest.mark.parametrize("n_problems", [1, 7])
+def test_scores_alike_in_both_layouts(shape, n_problems):
+    """A call whose bounds allow for more than 64 MB of keys loads them in the other layout: its scores are those of the same problems under
+    small bounds bit for bit, and no head of a sequence that is sampled whole (up to 1024 rows: its bound is its K-th score itself) loses
+    a candidate to it.  A rescan would list every token: the workspace, cleared before the step, must not hold a head's worst one."""
+    import numpy as np
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    mids = [1000, 9, 1024, 300, 777, 1030, 5000][:n_problems]
+    ks = [m // 60 + 1 for m in mids]
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(mids)]
+    res = []
+    for max_L in (None, 140000):
+        b = H.Batch(H.config_of(w, tuning={"select_mode": 2}), layers, ks, debug=True, max_L=max_L, max_K=400)
+        b.build()
+        b.ws.zero_()
+        b.decode()
+        assert b.status() & ~2 == 0
+        res.append([{n: b.result(i, n) for n in ("scores", "topk_idx")} for i in range(n_problems)])
+    words = b.ws[:b.ws_bytes // 8 * 8].view(torch.int64)
+    for i, (small, large) in enumerate(zip(*res)):
+        assert np.array_equal(small["scores"].view(np.uint32), large["scores"].view(np.uint32)), f"problem {i}: scores differ"
+        assert np.array_equal(small["topk_idx"], large["topk_idx"])
+        worst = large["scores"].argmin(1)
+        bits = np.take_along_axis(large["scores"], worst[:, None], 1)[:, 0].view(np.uint32).astype(np.int64)
+        listed = torch.isin(torch.from_numpy(worst.astype(np.int64) << 32 | bits).cuda(), words)
+        assert not listed.any(), f"problem {i}: heads {listed.nonzero().flatten().tolist()} rescanned"
+
+
 @pytest.mark.parametrize("shape,unit", [("l3b_128k", 64), ("l1b_32k", 128)])
 @pytest.mark.parametrize("units,interleave", [(1, 0), (3, 1), (5, 2), (17, 1)])
 def test_kept_scores_at_every_end(shape, unit, units, interleave):
