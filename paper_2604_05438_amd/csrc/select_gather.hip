@@ -754,12 +754,14 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   select_gather_body<D, NTHR, DIRECT, LIST, KV>(g, probs, ws, part, gq, p);
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
-  // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads; the
-  // barrier below waits for this workgroup's stores to complete before thread 0 counts it in.  Only the optional
-  // export of the retrieved indices reads what ordinary stores of other workgroups wrote (the retrieved list): then,
-  // and only then, device-wide fences (each writes back / invalidates a whole L2) bracket the count.
+  // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads.  Every wavefront waits
+  // for its own stores before the barrier behind which thread 0 counts the workgroup in: the barrier itself waits for LDS
+  // only, and at d = 128 the second wavefront's half of the sums could otherwise still be on its way when another XCD merges.
+  // Only the optional export of the retrieved indices reads what ordinary stores of other workgroups wrote (the retrieved list):
+  // then, and only then, device-wide fences (each writes back / invalidates a whole L2) bracket the count.
   const bool exports = probs[p].topk_idx != nullptr;
   if (exports) __threadfence();
+  else if (g.sg_split > 1) wait_stores();
   __syncthreads();
   // (a head's only workgroup is its last, and need not ask memory: 0.6 us)
   if (g.sg_split > 1 && threadIdx.x == 0) {

@@ -400,10 +400,10 @@ __device__ __forceinline__ void write_device_status(const Geom& g, const tkphi_p
 #define TKPHI_PHASE_VALUE(ws, slot, v) do {} while (0)
 #endif
 
-// Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits for every global load the wavefront
-// has in flight (its fences cover global memory); where a barrier only hands LDS data from one wavefront to
-// another, this one lets prefetched global loads stay in flight across it.  Not for data exchanged through
-// global memory.
+// Workgroup barrier that orders LDS accesses only.  The fences of __syncthreads() cover global memory too: the compiler
+// keeps global accesses on their side of it (and waits for loads whose results it needs there), where this one lets
+// prefetched global loads stay in flight across it.  Not for data exchanged through global memory.  Neither of the two makes
+// a wavefront wait for its stores (within a workgroup they take effect in order without it): wait_stores does.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
@@ -436,6 +436,9 @@ __device__ __forceinline__ void wait_vm_loads() {   // at most N vector memory o
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
   asm volatile("" ::: "memory");                    // no LDS read moves above the wait
 }
+
+// Every store and load of this wavefront so far is complete, the GPU-coherent ones below for all workgroups to see.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Stores and loads that are coherent across the whole GPU (the 8 XCDs have separate L2 caches; ordinary accesses may
 // stay in, or be served from, the L2 of the XCD they were issued on until a kernel boundary).  For the few words

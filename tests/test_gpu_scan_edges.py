@@ -78,6 +78,34 @@ def test_scores_alike_in_both_layouts(shape, n_problems):
         assert not listed.any(), f"problem {i}: heads {listed.nonzero().flatten().tolist()} rescanned"
 
 
+@pytest.mark.parametrize("shape,L,k", [("l3b_128k", 2500, 200), ("l3b_128k", 40000, 400), ("l1b_32k", 20000, 300)])
+def test_partials_of_several_workgroups(shape, L, k):
+    """Several workgroups share a head and the last one merges what the others have handed it: steps of two queries in turn, without the
+    export of the indices, on a workspace full of huge values, give the outputs of the steps with the export bit for bit (those against
+    the oracle)."""
+    import numpy as np
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    P = I.make_layer(w, L=L)
+    queries = [P["q"], I.make_layer(w, L=L, seq=1)["q"]]
+    want = []
+    for debug in (True, False):
+        b = H.Batch(H.config_of(w), [P], [k], debug=debug)
+        b.build()
+        for rep in range(2 if debug else 12):
+            b.set_query(0, queries[rep % 2])
+            b.ws.fill_(0x7f)             # (3.4e38 as a float)
+            b.dev[0]["out"].zero_()
+            b.decode()
+            if debug:
+                assert b.status() & ~2 == 0
+                PU.check_layer(w, dict(P, q=queries[rep]), k, b, 0, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+                want.append(b.result(0, "out"))
+            else:
+                assert np.array_equal(b.result(0, "out"), want[rep % 2]), f"step {rep} differs"
+
+
 @pytest.mark.parametrize("shape,unit", [("l3b_128k", 64), ("l1b_32k", 128)])
 @pytest.mark.parametrize("units,interleave", [(1, 0), (3, 1), (5, 2), (17, 1)])
 def test_kept_scores_at_every_end(shape, unit, units, interleave):
