@@ -148,7 +148,8 @@ typedef struct tkphi_tuning {
                              writes; one select kernel per step).  Ignored where only the spill pipeline applies
                              (fp32 storage, d_phi != d_head, MLP maps, TKPHI_FLAG_DIAG)                    */
   int32_t select_test;    /* filtered pipeline, tests only: 1 = the sampled bound is replaced by one no score
-                             passes (every head takes the rescan), 2 = by one every score passes           */
+                             passes, or does not arrive in time (every head takes the rescan), 2 = by one
+                             every score passes                                                           */
   int32_t reserved[4];    /* 0                                                                            */
 } tkphi_tuning;
 

@@ -416,12 +416,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
 }
 
 // ---- sample and score pass in one launch ------------------------------------------------------------------------------
-// The bounds of KV head h (lane gl < G: head h G + gl) from the sample workgroups, which lie ahead of every score workgroup in
-// the launch and wait for nothing, so the words arrive; the polls are counted all the same, and a head whose bound has not come
-// by then goes unpruned (every score a candidate: slower, nothing else).  A word is (tag, bound): tags differ from call to call,
-// and the merging workgroup of the select kernel clears the word, for replays of a captured call.
+// The bounds of KV head h (lane gl < G: head h G + gl) from the sample workgroups, which lie ahead of the score workgroups of
+// their problem in the launch and wait for nothing, so the words arrive; the polls are counted all the same, and the lists of a head
+// whose bound has not come by then are marked as not made (kNoList: the select kernel rescans that head).  False for such a
+// lane.  A word is (tag, bound): tags differ from call to call, and the merging workgroup of the select kernel clears the
+// word, for replays of a captured call.
 constexpr int kBoundPolls = 1 << 14;     // of a microsecond or so
-__device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk, int h) {
+__device__ __forceinline__ bool await_bounds(const Geom& g, const char* blk, int h, uint32_t* edge) {
   const uint64_t* word = (const uint64_t*)(blk + g.off_hand) + h * g.G + min((int)(threadIdx.x & 63), g.G - 1);
   uint64_t w = 0;
   for (int k = 0; k < kBoundPolls; ++k) {
@@ -429,7 +430,8 @@ __device__ __forceinline__ uint32_t await_bounds(const Geom& g, const char* blk,
     if (__all((uint32_t)(w >> 32) == g.tag)) break;
     __builtin_amdgcn_s_sleep(4);
   }
-  return (uint32_t)(w >> 32) == g.tag ? (uint32_t)w : 0u;
+  *edge = (uint32_t)w;
+  return (uint32_t)(w >> 32) == g.tag;
 }
 
 // grid (Hq (2 + n_atiles) + Hkv n_scan_chunks, n_problems), 512 threads: a sample job per query head, the phi and anchor jobs
@@ -484,9 +486,11 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   load_query_frags<D>(g, pr, h, bq);
   lds_barrier();
   scan_keep<D, TPI / 4, NWV, STREAM>(g, pr, h, n, n_chunks, chunk, bq, (lds_f32)sh_dyn, &sh_n);
-  const uint32_t edge = await_bounds(g, blk, h);
+  uint32_t edge;
+  bool known = await_bounds(g, blk, h, &edge);
+  if (g.sel_test == 1 && (chunk & 1)) known = false;      // (test: as if the wait had run out)
   lds_barrier();
-  list_kept<D, NWV>(g, pr, blk, h, n, n_chunks, chunk, (lds_f32)sh_dyn, edge);
+  list_kept<D, NWV>(g, pr, blk, h, n, n_chunks, chunk, (lds_f32)sh_dyn, edge, known);
 }
 
 // The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query

@@ -272,9 +272,12 @@ __device__ __forceinline__ void scan_keep(const Geom& g, const tkphi_problem& pr
 // list (head, slot) takes the positions [slot, slot + 1) scan_chunk / 4, 1024 of them at a time: a lane marks which of its 16 (4 of
 // every 256) pass, one prefix sum over the lanes places them (a ballot and a store per four positions took 5 us of the pass of
 // a 3B layer at 128K instead of 1).  A list is in the order (1024 positions, lane, position).
+// known_lane: false where the bound has not come: kNoList in the place of a count, whose head the select kernel rescans (lists without a
+// bound beside lists with one could make up K candidates that are not the K best).
+constexpr uint32_t kNoList = 0xffffffffu;
 template <int D, int NWV>
 __device__ __forceinline__ void list_kept(const Geom& g, const tkphi_problem& pr, char* blk, int h, int n, int n_chunks, int chunk,
-                                          lds_f32 keep, uint32_t edge_lane) {
+                                          lds_f32 keep, uint32_t edge_lane, bool known_lane) {
   const int lane = threadIdx.x & 63, slot = g.scan_chunk / 4, T = g.cand_T;
   constexpr int U = keep_unit(D);        // = g.scan_unit
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -290,6 +293,10 @@ __device__ __forceinline__ void list_kept(const Geom& g, const tkphi_problem& pr
     const int gl = job >> 2, ws = job & 3, gq = h * g.G + gl, pos0 = ws * slot + 4 * lane;
     const uint32_t edge = (uint32_t)__builtin_amdgcn_readlane((int)edge_lane, gl);
     const size_t idx = ((size_t)gq * g.n_scan_chunks + chunk) * 4 + ws;
+    if (!__builtin_amdgcn_readlane((int)known_lane, gl)) {
+      if (lane == 0) ((uint32_t*)(blk + g.off_ccount))[idx] = kNoList;
+      continue;
+    }
     const glb_u32x2 list = (glb_u32x2)(blk + g.off_candf) + idx * (size_t)slot;
     const glb_u32x2 head = (glb_u32x2)(blk + g.off_candc) + idx * (size_t)T;
     const lds_f32 row = keep + gl * g.scan_chunk + ws * slot;

@@ -15,9 +15,9 @@
 //   * histogram of a fine monotone binning of the score keys -> boundary bin b* (tokens in higher bins
 //     are retrieved); the candidates in b* are ranked by counting (or, beyond kBCap of them, by radix
 //     passes over the sweeps) -> the K-th best composite (score key, lower index first), `thr`
-//   * fewer than K candidates (the sampled bound was too high: a ~1e-6 event per head by design, and what
-//     tkphi_tuning::select_test = 1 forces): the workgroup first rescans its head's keys with no bound,
-//     which makes every mid token a candidate
+//   * fewer than K candidates (the sampled bound was too high: a ~1e-6 event per head by design), or a list that was not made for
+//     want of a bound (kNoList); tkphi_tuning::select_test = 1 forces both: the workgroup first rescans its head's
+//     keys with no bound, which makes every mid token a candidate
 // Short contexts (Geom::direct) come without a bound and without lists: the score pass stored a row of scores per head, which
 // is loaded whole and packed as it is.
 // Then workgroup `part` takes an equal share of the packed candidates (of the lists, where they are too many to pack): its
@@ -185,17 +185,20 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     for (int r = 0; r < rounds; ++r) {
       const int s = kSweepEntries * (tid + NTHR * r), list = s / T;
       if (s % T == 0 && list < n_reg) {               // the thread that owns the head of a list counts it
-        const uint32_t c = min((r == 0 && have_e0) ? c0 : ccount[list], cap_w);
+        const uint32_t len = (r == 0 && have_e0) ? c0 : ccount[list], c = min(len, cap_w);
         tot += c;
         if (c > (uint32_t)T) ovp = max(ovp, (c - T + T - 1) / T);
+        if (len == kNoList) ovp = kNoList;
       }
     }
     if (tot) atomicAdd(&sh_total, tot);
     if (ovp) atomicMax(&sh_ovp, ovp);
     __syncthreads();
-    max_passes = (int)sh_ovp;
-    n_sweeps = rounds + rounds * max_passes;
-    if (sh_total >= (uint32_t)Ksel || attempt > 0) break;
+    if ((sh_total >= (uint32_t)Ksel && sh_ovp != kNoList) || attempt > 0) {
+      max_passes = (int)sh_ovp;
+      n_sweeps = rounds + rounds * max_passes;
+      break;
+    }
     __syncthreads();
     // (every workgroup of the head takes this branch, the counts it depends on being the score pass's, and writes
     // the same values to the rescan set: no ordering between them is needed.  A head's only workgroup may write the first set

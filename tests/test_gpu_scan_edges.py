@@ -134,7 +134,7 @@ def test_kept_scores_at_every_end(shape, unit, units, interleave):
     ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # short contexts: no lists, the row of scores is packed as it is
     ("l3b_128k", 13000, 400, 2), ("l1b_32k", 14000, 1500, 2),     # every token a candidate, more than the packed array: boundary bin first
     ("l1b_32k", 14000, 13500, 2),                                 # a budget beyond the packed array: every phase from the lists
-    ("l3b_128k", 13000, 900, 1)])                                 # nothing passes the bound: rescan, then as above
+    ("l3b_128k", 13000, 900, 1), ("l1b_32k", 14000, 300, 1)])     # no bound for half of the chunks, and nothing passes that of the others: rescan, then as above
 def test_candidate_packing(shape, n_mid, k, select_test):
     """The select kernel's ways of bringing the candidates of a head together, where neighbouring tokens score alike (rows
     [2000, 2400) lean towards a query of their group, so their lists hold far more than the expected share).  One problem
