@@ -49,37 +49,39 @@ template <int D, int NTHR, typename KV> constexpr int kBatchOf = (D * sizeof(KV)
 template <int NTHR> constexpr int kWinLdsOf = NTHR == 1024 ? 1536 : 1024;
 
 // every mid token of query head gq becomes a candidate: list k of the rescan set takes the tokens [k cap, (k + 1) cap), cap =
-// scan_chunk / 4 (what the score pass wrote stays as it is: other workgroups of the head may still be reading it)
-// (one 16-token tile in flight per wavefront: the rare path must not cost the common one registers)
+// scan_chunk / 4, a multiple of 16 (what the score pass wrote stays as it is: other workgroups of the head may still be reading
+// it).  The wavefronts take the tiles of 16 tokens in turn, however long the lists are: a short sequence under large bounds has few
+// lists, and a wavefront to each was a chain of up to 64 round trips beside idle ones (step of a 3B layer of 1090 tokens under bounds
+// of 128K, all heads rescanning: 104 -> 58 us; of 131072 tokens 1215 -> 1133, a 1B layer 687 -> 697).  One tile in flight per wavefront: the
+// rare path must not cost the common one registers.
 template <int D, int NTHR>
 __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int n, int n_reg) {
   const int h = gq / g.G, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
   const int cap = g.scan_chunk / 4, T = g.cand_T;
+  const size_t reg0 = (size_t)gq * g.n_scan_chunks * 4;
   ScoreFrag bq[kTileFrags<D>];
   load_query_frags<D>(g, pr, h, bq);
   const char* Kl = (const char*)pr.K + ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2 + score_lane_offset<false>();
-  for (int reg = wv; reg < n_reg; reg += NTHR / 64) {
-    const size_t idx = (size_t)gq * g.n_scan_chunks * 4 + reg;
-    const glb_u32x2 list = (glb_u32x2)(blk + g.off_resf) + idx * (size_t)cap;
-    const glb_u32x2 head = (glb_u32x2)(blk + g.off_resc) + idx * (size_t)T;
-    const int t0 = reg * cap, cnt = max(0, min(cap, n - t0));
-    for (int o = 0; o < cnt; o += 16) {
-      ScoreFrag a[kTileFrags<D>];
-      request_tile<D, false>(a, [&](int i) { return Kl + (uint64_t)(uint32_t)min(t0 + o + i, n - 1) * (uint64_t)(pr.stride_tok * 2); });
-      const st_floatx4 acc = score_tile<D, false>(a, bq);
+  for (int t0 = wv * 16; t0 < n; t0 += NTHR / 4) {
+    const int reg = t0 / cap;
+    const glb_u32x2 list = (glb_u32x2)(blk + g.off_resf) + (reg0 + reg) * (size_t)cap;
+    const glb_u32x2 head = (glb_u32x2)(blk + g.off_resc) + (reg0 + reg) * (size_t)T;
+    ScoreFrag a[kTileFrags<D>];
+    request_tile<D, false>(a, [&](int i) { return Kl + (uint64_t)(uint32_t)min(t0 + i, n - 1) * (uint64_t)(pr.stride_tok * 2); });
+    const st_floatx4 acc = score_tile<D, false>(a, bq);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int at = o + 4 * kg + i;
-        const st_u32x2 e = (st_u32x2){__float_as_uint(fmaf(acc[i], g.score_scale, 0.0f)), (uint32_t)(t0 + at)};
-        if (r == gq % g.G && at < cnt) {
-          if (at < T) head[at] = e;
-          else list[at] = e;
-        }
+    for (int i = 0; i < 4; ++i) {
+      const int tok = t0 + 4 * kg + i, at = tok - reg * cap;
+      const st_u32x2 e = (st_u32x2){__float_as_uint(fmaf(acc[i], g.score_scale, 0.0f)), (uint32_t)tok};
+      if (r == gq % g.G && tok < n) {
+        if (at < T) head[at] = e;
+        else list[at] = e;
       }
     }
-    if (lane == 0) ((uint32_t*)(blk + g.off_rescount))[idx] = (uint32_t)cnt;
   }
+  for (int reg = threadIdx.x; reg < n_reg; reg += NTHR)
+    ((uint32_t*)(blk + g.off_rescount))[reg0 + reg] = (uint32_t)max(0, min(cap, n - reg * cap));
 }
 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve

@@ -317,6 +317,27 @@ def test_sampled_rows_above_all_others(shape, n_mid, n_problems):
         assert np.isin(b.result(i, "topk_idx")[hot, :k], rows).mean() > 0.9        # (the case is what it says: the bound misses)
 
 
+@pytest.mark.parametrize("shape,chunk,max_L", [("l3b_128k", 64, None), ("l3b_128k", 320, None), ("l3b_128k", 0, 140000), ("l1b_32k", 128, None),
+                                               ("l1b_32k", 1280, None), ("l1b_32k", 0, 140000)])
+def test_rescan_at_every_list_length(shape, chunk, max_L):
+    """A head that lists its keys again, in lists of 16 tokens to more than it has, mid-regions around tiles and lists: one problem (a second
+    set of lists) and seven (more than 128 heads: the first set over), against the oracle."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    mids = [1000, 1, 15, 17, 64, 1281, 2500]
+    ks = [max(1, m // 12) for m in mids]
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(mids)]
+    for sel in ([0], [3], [5], range(7)):
+        b = H.Batch(H.config_of(w, tuning={"select_mode": 2, "select_test": 1, "scan_chunk": chunk}), [layers[i] for i in sel], [ks[i] for i in sel],
+                    debug=True, max_L=max_L, max_K=400)
+        b.build()
+        b.decode()
+        assert b.status() & ~2 == 0
+        for i, at in enumerate(sel):
+            PU.check_layer(w, layers[at], ks[at], b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
+
+
 @pytest.mark.parametrize("hq,hkv,d,L,k", [(3, 1, 128, 70000, 700), (8, 1, 64, 70000, 1500), (1, 1, 128, 20000, 100), (4, 2, 64, 50000, 400)])
 def test_few_kv_heads(hq, hkv, d, L, k):
     """One or two KV heads over a long context: at most 128 chunks per head, fewer workgroups than CUs.  All heads against the
