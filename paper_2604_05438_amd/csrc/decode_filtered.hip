@@ -474,7 +474,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
     x -= g.Hq * g.n_atiles;
   } else if (x >= g.Hkv * g.n_scan_chunks) {
     x -= g.Hkv * g.n_scan_chunks;
-    mlp_phi_q_slice<0>(g, pr, blk, x % g.Hq, x / g.Hq);
+    mlp_phi_q_slice<0>(g, pr, blk, x % g.Hq, x / g.Hq, sh_dyn);
     return;
   }
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -545,6 +545,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
 void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   dim3 grid(g.Hq * (g.list ? 1 + g.d_emb / 64 : 2 + g.n_atiles) + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0), g.n_problems);
   const size_t sample = (size_t)(1024 + kBins + kInBin) * 4 + (size_t)(kFusedThreads / 64) * 16 * (g.d * 2 + 16);
+  static_assert(kQuerySliceLds <= 1024 + kBins + kInBin + 128 * (64 * 2 + 16) / 4, "the sample's share holds phi_q's as well");
   const size_t lds = std::max(sample, (size_t)g.G * g.scan_chunk * sizeof(float));       // (more than the 6 KB of the phi jobs)
   const auto launch = [&](auto fn) {
     const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -896,7 +896,8 @@ __global__ __launch_bounds__(kSelThreads) void mlp_phi_q_kernel(Geom g, const tk
                                                                 char* __restrict__ ws) {
   const tkphi_problem pr = probs[blockIdx.z];
   if (pr.L < 1 || pr.L > g.max_L) return;
-  mlp_phi_q_slice<STAGE, SPL>(g, pr, problem_block(g, ws, blockIdx.z), blockIdx.y, blockIdx.x);
+  __shared__ __attribute__((aligned(16))) float lds[kQuerySliceLds];
+  mlp_phi_q_slice<STAGE, SPL>(g, pr, problem_block(g, ws, blockIdx.z), blockIdx.y, blockIdx.x, lds);
 }
 
 // all three stages, or those that have not ridden in the score and select launches (Geom::list); one timed stage

@@ -15,11 +15,10 @@ namespace tkphi {
 // ------------------------------------------------------------------------------------
 // Every global load of a workgroup (weights of its first row groups, biases, input vector) is
 // issued before anything is consumed: one memory round trip per stage.
+constexpr int kQuerySliceLds = 128 + 2 * 1024 + 2 * 64;        // floats of LDS, the caller's
 template <int STAGE, int SPL>   // SPL = 1 for d_emb <= 512, 2 for 1024
-__device__ __forceinline__ void mlp_phi_q_slice(const Geom& g, const tkphi_problem& pr, char* __restrict__ blk, int gq, int slice) {
-  __shared__ float xs[128];
-  __shared__ float vin[1024], sb[1024];
-  __shared__ float sb2[64], sg[64];
+__device__ __forceinline__ void mlp_phi_q_slice(const Geom& g, const tkphi_problem& pr, char* __restrict__ blk, int gq, int slice, float* lds) {
+  float *xs = lds, *vin = xs + 128, *sb = vin + 1024, *sb2 = sb + 1024, *sg = sb2 + 64;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int E = g.d_emb;
   float* gbuf = (float*)(blk + g.off_mlpq) + (size_t)gq * 2 * E;
@@ -56,9 +55,9 @@ __device__ __forceinline__ void mlp_phi_q_slice(const Geom& g, const tkphi_probl
 }
 // the same for the d_emb of the configuration
 template <int STAGE>
-__device__ __forceinline__ void mlp_phi_q_slice(const Geom& g, const tkphi_problem& pr, char* __restrict__ blk, int gq, int slice) {
-  if (g.d_emb <= 512) mlp_phi_q_slice<STAGE, 1>(g, pr, blk, gq, slice);
-  else mlp_phi_q_slice<STAGE, 2>(g, pr, blk, gq, slice);
+__device__ __forceinline__ void mlp_phi_q_slice(const Geom& g, const tkphi_problem& pr, char* __restrict__ blk, int gq, int slice, float* lds) {
+  if (g.d_emb <= 512) mlp_phi_q_slice<STAGE, 1>(g, pr, blk, gq, slice, lds);
+  else mlp_phi_q_slice<STAGE, 2>(g, pr, blk, gq, slice, lds);
 }
 
 }  // namespace tkphi

@@ -742,7 +742,8 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
       const tkphi_problem& pr = probs[p];
       if (pr.L < 1 || pr.L > g.max_L) return;
       if (idx < g.Hq + n_phi) {
-        mlp_phi_q_slice<DIRECT ? 0 : 1>(g, pr, problem_block(g, ws, p), (idx - g.Hq) % g.Hq, (idx - g.Hq) / g.Hq);
+        __shared__ __attribute__((aligned(16))) float sh_q[kQuerySliceLds];
+        mlp_phi_q_slice<DIRECT ? 0 : 1>(g, pr, problem_block(g, ws, p), (idx - g.Hq) % g.Hq, (idx - g.Hq) / g.Hq, sh_q);
         return;
       }
       const int wg = idx - g.Hq - n_phi, n_wg = ((int)gridDim.x - g.Hq - n_phi) / g.Hkv, h = wg % g.Hkv;

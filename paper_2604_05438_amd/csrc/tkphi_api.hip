@@ -172,7 +172,9 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // spill pipeline: about 1024 workgroups, 256..8192 tokens each (uint16 chunk histograms: < 65536)
   int sc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 1024), 256, 8192), 256);
   // Filtered pipeline, one or a few problems: sample and score pass in one launch, whose workgroups hold the scores of their chunk in
-  // LDS (at most half of it: two workgroups per CU).  One problem: the pass lasts as long as its busiest CU and wants one
+  // LDS (two workgroups per CU: half of it, of which 2 KB are left for what else the kernel holds; with one per CU the sample, phi and
+  // anchor workgroups hold CUs that as many score workgroups wait for: 1B layer at 128000 tokens 48 us instead of 45, 64 / 8 heads
+  // of 64 at 100000 tokens 55 instead of 48).  One problem: the pass lasts as long as its busiest CU and wants one
   // workgroup on each.  A few (ragged: up to half of the chunks that the bounds allow for are empty): about 1024 workgroups.  At most
   // 128 chunks per KV head (one sweep of the select kernel).  Two launches / one, us per step: 3B layer at 16K 41 / 35, 50K 56 / 48,
   // 128K 84 / 77; 1B layer at 32K 37.5 / 34, 96K 52 / 43; 1B sequences of 4K to 16K, 2 of them 35 / 32, 4 of them 50 / 42; 2 3B

@@ -129,6 +129,27 @@ def test_kept_scores_at_every_end(shape, unit, units, interleave):
                 PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+@pytest.mark.parametrize("d,tiles", [(64, 8), (128, 4)])
+@pytest.mark.parametrize("stream", [0, 1])
+def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream):
+    """The one-launch score pass keeps up to 79872 bytes of scores per workgroup so that two share the 160 KB of a CU: what its kernel
+    holds besides must fit the 2 KB left of each half."""
+    import ctypes
+    from paper_2604_05438_amd import binding as B
+    lib = B.lib()
+
+    class Attributes(ctypes.Structure):                     # hipFuncAttributes
+        _fields_ = [("binaryVersion", ctypes.c_int), ("cacheModeCA", ctypes.c_int), ("constSizeBytes", ctypes.c_size_t),
+                    ("localSizeBytes", ctypes.c_size_t), ("maxDynamicSharedSizeBytes", ctypes.c_int), ("maxThreadsPerBlock", ctypes.c_int),
+                    ("numRegs", ctypes.c_int), ("preferredShmemCarveout", ctypes.c_int), ("ptxVersion", ctypes.c_int),
+                    ("sharedSizeBytes", ctypes.c_size_t)]
+
+    attr = Attributes()
+    name = f"_ZN5tkphi18score_fused_kernelILi{d}ELi{tiles}ELb{stream}EEEvNS_4GeomEPK13tkphi_problemPc"
+    assert lib.hipFuncGetAttributes(ctypes.byref(attr), ctypes.byref(ctypes.c_void_p.in_dll(lib, name))) == 0
+    assert attr.sharedSizeBytes <= 81920 - 79872, attr.sharedSizeBytes
+
+
 @pytest.mark.parametrize("shape,n_mid,k,select_test", [
     ("l3b_128k", 11000, 100, 0), ("l1b_32k", 13000, 700, 0),      # a hot stretch overflows the compact heads of its lists: several sweeps
     ("l3b_128k", 9000, 100, 0), ("l1b_32k", 9000, 700, 0),        # short contexts: no lists, the row of scores is packed as it is
