@@ -463,12 +463,12 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   if (!g.list) {
     if (x < g.Hq) {
       if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
-      side_phi<0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+      side_phi<D, 0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
       return;
     }
     x -= g.Hq;
     if (x < g.Hq * g.n_atiles) {
-      side_anchor(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
+      side_anchor<D>(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
       return;
     }
     x -= g.Hq * g.n_atiles;
@@ -495,6 +495,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
 
 // The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query
 // head h G + j (and that head's arrival counter <- 0), then n_atiles anchor tiles per query head.
+template <int D>
 __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
   const int job = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
@@ -503,10 +504,10 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
   char* blk = problem_block(g, ws, p);
   if (job < g.G) {
     if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + job] = 0u;
-    side_phi<0>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+    side_phi<D, 0>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
   } else {
     const int j = job - g.G;
-    side_anchor(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+    side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
   }
 }
 
@@ -526,10 +527,10 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   if (x < n_side) {
     if (x < g.G) {
       if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
-      side_phi<EARLY>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+      side_phi<D, EARLY>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
     } else {
       const int j = x - g.G;
-      side_anchor(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+      side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
     }
     return;
   }
@@ -571,10 +572,10 @@ __global__ __launch_bounds__(kThreads) void score_direct_f32_kernel(Geom g, cons
   if (x < n_side) {
     if (x < g.G) {
       if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
-      side_phi<0, float>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+      side_phi<D, 0, float>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
     } else {
       const int j = x - g.G;
-      side_anchor<float>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+      side_anchor<D, float>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
     }
     return;
   }
@@ -613,8 +614,9 @@ void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hi
     return;
   }
   dim3 grid((g.list ? 0 : g.G * (1 + g.n_atiles)) + (g.max_mid > 0 ? g.n_scan_chunks : 0), g.Hkv, g.n_problems);
-  // (the phi job's rows of S ahead of everything else: 0.3 us off one 3B layer of 4K or 9K tokens, but at 158 registers instead of
-  // 73 the whole launch of 256 problems of 1.5K takes 258 us instead of 224 at d = 128, 154 instead of 128 at d = 64)
+  // (the phi job's rows of S ahead of everything else: 0.3 us off one 3B layer of 4K or 9K tokens, but at twice the
+  // registers the whole launch of 256 problems of 1.5K took 258 us instead of 224 at d = 128, 154 instead of 128 at d = 64, when both were
+  // measured; now 215 and 116 without)
   if (g.d == 128 && g.n_problems == 1) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4, 16>), grid, dim3(kThreads), 0, s, g, probs, ws);
   else if (g.d == 128) TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<128, 4, 0>), grid, dim3(kThreads), 0, s, g, probs, ws);
   else TKPHI_LAUNCH(ST_SCORE, (score_direct_kernel<64, 8, 0>), grid, dim3(kThreads), 0, s, g, probs, ws);
@@ -636,7 +638,8 @@ void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_
   dim3 grid_a(1, g.Hkv, g.n_problems), grid_b(n_jobs - 1, g.Hkv, g.n_problems);
   if (g.d == 128) TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
   else TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<64, 8>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-  TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel, grid_b, dim3(kThreads), 0, s, g, probs, ws);
+  if (g.d == 128) TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<128>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
+  else TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<64>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
 }
 
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {

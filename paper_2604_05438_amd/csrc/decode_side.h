@@ -17,15 +17,20 @@ namespace tkphi {
 // order.    LDS: sh_phiq, pu [kMaxDim], red [1024]
 // EARLY: rows of S a thread requests before anything else (16: all it takes at d_phi = d = 128; one round trip for S and Wq
 // together, for a launch of few workgroups), 0: none, eight at a time behind phi_q (16 rows ahead cost batches two of three
-// wavefronts: decode_side_kernel over 6400 heads 99 us instead of 59).
-template <int EARLY, typename T = uint16_t>
+// wavefronts: decode_side_kernel over 6400 heads 99 us instead of 59, in the form with d at run time).
+// D at compile time: with it at run time the unrolled lane sums, which branch on the lanes of a row, took 88 registers instead of 72, five
+// wavefronts to a SIMD instead of seven: decode_side_kernel over 8192 heads of 64 76 us instead of 53, over 4800 heads of 128 78 instead
+// of 70; score_direct_kernel over 256 problems of 1.5K at d = 64 137 instead of 116.
+template <int D, int EARLY, typename T = uint16_t>
 __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* sh_phiq, float* pu,
                                          float* red) {
   constexpr int EPL = Elem<T>::per16;
-  const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
+  constexpr int d = D;
+  const int tid = threadIdx.x, dphi = g.dphi, h = gq / g.G;
   const bool act = tid < kThreads;
   // rows of Wq: LPR lanes per row (16 bytes each), rows_pp rows per pass, 8 passes in flight
-  const int LPR = d / EPL, seg = tid % LPR, row_in = tid / LPR, rows_pp = kThreads / LPR;
+  constexpr int LPR = d / EPL, rows_pp = kThreads / LPR;
+  const int seg = tid % LPR, row_in = tid / LPR;
   const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * EPL) * sizeof(T));
   float qx[EPL];
   Elem<T>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
@@ -34,7 +39,7 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
   for (int e = 0; e < EPL; ++e) nrm = fmaf(qx[e], qx[e], nrm);
   nrm = lanes_sum(nrm, LPR);
   // S^T phi_q below: thread (jg, c4) takes the features of group jg for 4 value channels
-  const int QPR = d / 4, NG = kThreads / QPR;         // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
+  constexpr int QPR = d / 4, NG = kThreads / QPR;     // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR;
   const int per = (dphi + NG - 1) / NG, sj0 = jg * per, sj1 = min(dphi, sj0 + per);
   const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
@@ -108,11 +113,12 @@ __device__ __forceinline__ void side_phi(const Geom& g, const tkphi_problem& pr,
 // Anchors are the rows [0, n_sink) u [L - n_tail, L) (every row if the mid-region is empty) followed by the
 // generated tokens [L, L + n_gen).  Writes the tile's partial in the layout of the gather kernels:
 // [m_loc, Z_loc, 0, count, nu_loc[d], 0[d]].  LDS: a_s, a_w [64], red [4][128]
-template <typename T = uint16_t>
+template <int D, typename T = uint16_t>
 __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& pr, char* blk, int gq, int batch, float* a_s,
                                             float* a_w, float* red) {
   constexpr int EPL = Elem<T>::per16;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, d = g.d, h = gq / g.G;
+  constexpr int d = D;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = gq / g.G;
   const bool act = tid < kThreads;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int n_prefill = n > 0 ? g.n_sink + g.n_tail : pr.L;
@@ -121,35 +127,30 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
   if (base >= n_anchor) return;
   const int cnt = min(64, n_anchor - base);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + g.n_tiles + batch) * g.part_stride;
-  const int LPR = d / EPL, seg = tid % LPR, rsub = tid / LPR, RPP = kThreads / LPR;   // rows per pass: 8 to 32
-  constexpr int MAXPS = EPL == 8 ? 4 : 8;            // 64 rows / 16 or 8
-  const int n_pass = 64 / RPP;
-  u32x4 kv[MAXPS], vv[MAXPS];
+  constexpr int LPR = d / EPL, RPP = kThreads / LPR, n_pass = 64 / RPP;   // rows per pass: 16 or 32
+  const int seg = tid % LPR, rsub = tid / LPR;
+  u32x4 kv[n_pass], vv[n_pass];
   const u32x4 qv = gload128((const char*)pr.q + ((size_t)gq * d + seg * EPL) * sizeof(T));
 #pragma unroll
-  for (int ps = 0; ps < MAXPS; ++ps) {
-    if (ps < n_pass) {
-      const int a = base + min(ps * RPP + rsub, cnt - 1);
-      const int tok = a >= n_prefill ? pr.L + (a - n_prefill) : (n > 0 && a >= g.n_sink) ? (pr.L - g.n_tail + (a - g.n_sink)) : a;
-      const size_t off = ((size_t)h * pr.stride_head + (size_t)tok * pr.stride_tok + seg * EPL) * sizeof(T);
-      kv[ps] = gload128((const char*)pr.K + off);
-      vv[ps] = gload128((const char*)pr.V + off);
-    }
+  for (int ps = 0; ps < n_pass; ++ps) {
+    const int a = base + min(ps * RPP + rsub, cnt - 1);
+    const int tok = a >= n_prefill ? pr.L + (a - n_prefill) : (n > 0 && a >= g.n_sink) ? (pr.L - g.n_tail + (a - g.n_sink)) : a;
+    const size_t off = ((size_t)h * pr.stride_head + (size_t)tok * pr.stride_tok + seg * EPL) * sizeof(T);
+    kv[ps] = gload128((const char*)pr.K + off);
+    vv[ps] = gload128((const char*)pr.V + off);
   }
   float qx[EPL];
   Elem<T>::unpack(make_uint4(qv.x, qv.y, qv.z, qv.w), qx);
 #pragma unroll
-  for (int ps = 0; ps < MAXPS; ++ps) {
-    if (ps < n_pass) {
-      float kx[EPL];
-      Elem<T>::unpack(make_uint4(kv[ps].x, kv[ps].y, kv[ps].z, kv[ps].w), kx);
-      float s = 0.f;
+  for (int ps = 0; ps < n_pass; ++ps) {
+    float kx[EPL];
+    Elem<T>::unpack(make_uint4(kv[ps].x, kv[ps].y, kv[ps].z, kv[ps].w), kx);
+    float s = 0.f;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) s = fmaf(kx[e], qx[e], s);
-      s = lanes_sum(s, LPR);
-      const int row = ps * RPP + rsub;
-      if (act && seg == 0) a_s[row] = row < cnt ? s * g.score_scale + 0.0f : -INFINITY;
-    }
+    for (int e = 0; e < EPL; ++e) s = fmaf(kx[e], qx[e], s);
+    s = lanes_sum(s, LPR);
+    const int row = ps * RPP + rsub;
+    if (act && seg == 0) a_s[row] = row < cnt ? s * g.score_scale + 0.0f : -INFINITY;
   }
   __syncthreads();
   if (wv == 0) {
@@ -166,15 +167,13 @@ __device__ __forceinline__ void side_anchor(const Geom& g, const tkphi_problem& 
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
 #pragma unroll
-  for (int ps = 0; ps < MAXPS; ++ps) {
-    if (ps < n_pass) {
-      const int row = ps * RPP + rsub;
-      const float w = row < cnt ? a_w[row] : 0.f;
-      float vx[EPL];
-      Elem<T>::unpack(make_uint4(vv[ps].x, vv[ps].y, vv[ps].z, vv[ps].w), vx);
+  for (int ps = 0; ps < n_pass; ++ps) {
+    const int row = ps * RPP + rsub;
+    const float w = row < cnt ? a_w[row] : 0.f;
+    float vx[EPL];
+    Elem<T>::unpack(make_uint4(vv[ps].x, vv[ps].y, vv[ps].z, vv[ps].w), vx);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w, vx[e], acc[e]);
-    }
+    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w, vx[e], acc[e]);
   }
   // rows of one wavefront that share a segment: lanes seg, seg + LPR, ...
 #pragma unroll

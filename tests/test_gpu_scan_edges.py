@@ -129,14 +129,9 @@ def test_kept_scores_at_every_end(shape, unit, units, interleave):
                 PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
-@pytest.mark.parametrize("d,tiles", [(64, 8), (128, 4)])
-@pytest.mark.parametrize("stream", [0, 1])
-def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream):
-    """The one-launch score pass keeps up to 79872 bytes of scores per workgroup so that two share the 160 KB of a CU: what its kernel
-    holds besides must fit the 2 KB left of each half."""
+def _kernel_attributes(name):
     import ctypes
     from paper_2604_05438_amd import binding as B
-    lib = B.lib()
 
     class Attributes(ctypes.Structure):                     # hipFuncAttributes
         _fields_ = [("binaryVersion", ctypes.c_int), ("cacheModeCA", ctypes.c_int), ("constSizeBytes", ctypes.c_size_t),
@@ -145,9 +140,25 @@ def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream):
                     ("sharedSizeBytes", ctypes.c_size_t)]
 
     attr = Attributes()
-    name = f"_ZN5tkphi18score_fused_kernelILi{d}ELi{tiles}ELb{stream}EEEvNS_4GeomEPK13tkphi_problemPc"
-    assert lib.hipFuncGetAttributes(ctypes.byref(attr), ctypes.byref(ctypes.c_void_p.in_dll(lib, name))) == 0
-    assert attr.sharedSizeBytes <= 81920 - 79872, attr.sharedSizeBytes
+    kernel = ctypes.c_void_p.in_dll(B.lib(), f"_ZN5tkphi{name}EvNS_4GeomEPK13tkphi_problemPc")
+    assert B.lib().hipFuncGetAttributes(ctypes.byref(attr), ctypes.byref(kernel)) == 0
+    return attr
+
+
+@pytest.mark.parametrize("d,tiles", [(64, 8), (128, 4)])
+@pytest.mark.parametrize("stream", [0, 1])
+def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream):
+    """The one-launch score pass keeps up to 79872 bytes of scores per workgroup so that two share the 160 KB of a CU: what its kernel
+    holds besides must fit the 2 KB left of each half."""
+    assert _kernel_attributes(f"18score_fused_kernelILi{d}ELi{tiles}ELb{stream}EE").sharedSizeBytes <= 81920 - 79872
+
+
+@pytest.mark.parametrize("name,wavefronts", [("18decode_side_kernelILi64EE", 7), ("18decode_side_kernelILi128EE", 7),
+                                             ("19score_direct_kernelILi64ELi8ELi0EE", 5), ("19score_direct_kernelILi128ELi4ELi0EE", 6)])
+def test_batch_jobs_keep_their_wavefronts(name, wavefronts):
+    """The launches that carry the phi and anchor jobs of batches are throughput work: the wavefronts per SIMD that they were measured with
+    (512 registers, dealt in eights)."""
+    assert 0 < _kernel_attributes(name).numRegs <= 512 // wavefronts // 8 * 8
 
 
 @pytest.mark.parametrize("shape,n_mid,k,select_test", [
