@@ -185,8 +185,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   if (n_problems > 1)
     for (keep_chunk = 1024; keep_chunk * 1024 < units || ceil_div(g->max_mid, keep_chunk) > 128;) keep_chunk *= 2;
   keep_chunk = std::min<int64_t>(align_up((size_t)std::max<int64_t>(keep_chunk, 1), unit), keep_most);
+  int64_t given = (int64_t)align_up((size_t)tn.scan_chunk, unit);        // (one too short for the bounds grows, below)
+  while (tn.scan_chunk > 0 && ceil_div(g->max_mid, given) > kMaxScanChunks && given < 32768) given *= 2;
   g->fused = (g->filtered || g->list) && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
-             (tn.scan_chunk > 0 ? tn.scan_chunk <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128) ? 1 : 0;
+             (tn.scan_chunk > 0 ? given <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128) ? 1 : 0;
   if (g->list && (g->fused || short_context)) g->filtered = 1;
   g->list = g->list && g->filtered;
   if (g->fused) {

@@ -129,6 +129,22 @@ def test_kept_scores_at_every_end(shape, unit, units, interleave):
                 PU.check_layer(w, P, k, b, i, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+@pytest.mark.parametrize("hq,hkv,d,chunk,max_L", [(8, 1, 128, 1024, 9000000), (4, 1, 64, 256, 700000), (8, 1, 128, 1024, 2000000)])
+def test_given_chunk_too_short_for_the_bounds(hq, hkv, d, chunk, max_L):
+    """A given chunk grows until 2048 of them hold the bounds: where its scores then pass what a workgroup can keep in LDS (the first case)
+    the call takes the pass that does not keep them."""
+    import dataclasses
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l3b_128k" if d == 128 else "l1b_32k"], n_q_heads=hq, n_kv_heads=hkv)
+    P = I.make_layer(w, L=3000)
+    b = H.Batch(H.config_of(w, tuning={"select_mode": 2, "scan_chunk": chunk}), [P], [40], debug=True, max_L=max_L, max_K=400)
+    b.build()
+    b.decode()
+    assert b.status() & ~2 == 0
+    PU.check_layer(w, P, 40, b, 0)
+
+
 def _kernel_attributes(name):
     import ctypes
     from paper_2604_05438_amd import binding as B
