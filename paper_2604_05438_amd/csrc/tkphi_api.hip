@@ -59,11 +59,14 @@ static int filtered_min_inverse_budget(bool short_context, int64_t heads, int sp
   return wgs * 4 >= slots * 3 ? 16 : wgs * 5 >= slots * 3 && max_mid > 32768 ? 25 : 64;
 }
 
-// compact: the geometry for scratch memory that the faster one does not fit in.  Its needs grow with max_L, max_K and the
+// What a call tries in turn until one fits its scratch memory.  kFast: the fastest.  kSeparate: where that is the one-launch score pass
+// (Geom::fused), sample and score pass in two, whose chunks may fit where those do not.  kCompact: its needs grow with max_L, max_K and the
 // number of problems (one chunk rule for all lengths, the filtered pipeline with its two full-length lists per head for budgets
 // up to 1/64 only), so a workspace sized for larger bounds serves the smaller calls (but for a budget of at most 1/64 where the
 // workspace was sized for one beyond 1/12).
-static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, bool compact, bool diag, Geom* g) {
+enum Fit { kFast, kSeparate, kCompact };
+static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Fit fit, bool diag, Geom* g) {
+  const bool compact = fit == kCompact;
   if (!cfg) { set_error("cfg is null"); return TKPHI_EINVAL; }
   if (n_problems < 0 || max_L < 1 || max_K < 0) {
     set_error("n_problems=%d max_L=%d max_K=%d out of range", n_problems, max_L, max_K);
@@ -187,13 +190,28 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   keep_chunk = std::min<int64_t>(align_up((size_t)std::max<int64_t>(keep_chunk, 1), unit), keep_most);
   int64_t given = (int64_t)align_up((size_t)tn.scan_chunk, unit);        // (one too short for the bounds grows, below)
   while (tn.scan_chunk > 0 && ceil_div(g->max_mid, given) > kMaxScanChunks && given < 32768) given *= 2;
-  g->fused = (g->filtered || g->list) && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
-             (tn.scan_chunk > 0 ? given <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128) ? 1 : 0;
+  const bool fusable = (g->filtered || g->list) && !compact && !diag && !short_context && (n_problems <= 1 || (int64_t)g->Hkv * n_problems <= 32) &&
+                       (tn.scan_chunk > 0 ? given <= keep_most : ceil_div(g->max_mid, keep_chunk) <= 128);
+  g->fused = fusable && fit == kFast ? 1 : 0;
   if (g->list && (g->fused || short_context)) g->filtered = 1;
   g->list = g->list && g->filtered;
   if (g->fused) {
     g->scan_unit = unit;
     sc = (int)keep_chunk;
+  } else if (g->filtered && fusable && n_problems <= 1) {
+    // (kSeparate) the pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (score pass of a 3B
+    // layer at 50 K tokens: 232 workgroups of 1792 tokens 22.4 us, 400 of 1024 25.0, 312 of 1280 29.2); one workgroup per CU
+    // streams 7 % slower at d = 128 and, with 2.7 times the score work per byte, 40 % at d = 64.  Against that stands what the
+    // select kernel pays for more lists: 0.35 us per 1000 slots of their compact heads.
+    const double ideal_us = (double)units * g->d * 2 / 6.2e6;
+    double best = 0.0;
+    for (int c = g->scan_unit; c <= 8192; c += g->scan_unit) {
+      const int64_t chunks = std::max<int64_t>(1, ceil_div(g->max_mid, c)), rounds = ceil_div(chunks * g->Hkv, 256);
+      if (chunks * 4 * kMinListHead > sweep && c + g->scan_unit <= 8192) continue;
+      const double eff = (double)units / ((double)rounds * 256 * c) * (rounds > 1 ? 1.0 : g->d == 128 ? 0.93 : 0.7);
+      const double cost = ideal_us / eff + 0.35e-3 * (double)(chunks * 4 * list_head(c, std::min<int64_t>(max_K, g->max_mid), g->max_mid, sweep, chunks));
+      if (best == 0.0 || cost <= best) { best = cost; sc = c; }
+    }
   } else if (g->filtered && !compact) {
     // Filtered pipeline, batches: 4096 workgroups by the bounds of the call, a power of two of tokens each.  Ragged batches have
     // far fewer, which then still even out over the CUs (8 sequences of 8K to 32K at d = 128: score pass 74 -> 58 us against a
@@ -355,9 +373,11 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
 
 // have / need: the scratch bytes that the caller has and the member that says what its call takes (null: no limit)
 tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have, size_t Geom::*need, bool diag) {
-  const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, false, diag, g);
-  if (st != TKPHI_OK || !need || g->*need <= have) return st;
-  return make_geom_as(cfg, n_problems, max_L, max_K, true, diag, g);
+  for (const Fit fit : {kFast, kSeparate, kCompact}) {
+    const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, fit, diag, g);
+    if (st != TKPHI_OK || !need || g->*need <= have) return st;
+  }
+  return TKPHI_OK;                     // (the caller sees what the last one needs)
 }
 
 static tkphi_status check_call(const tkphi_problem* problems, int n_problems, const void* ws,
@@ -390,14 +410,16 @@ size_t tkphi_workspace_bytes(const tkphi_config* cfg, int32_t n_problems, int32_
   Geom g;
   if (make_geom(cfg, n_problems, max_L, max_K, &g) != TKPHI_OK) return 0;
   size_t bytes = 0;
-  // enough for the compact geometry too, which a call with smaller bounds may fall back to, and for the largest number of problems
-  // whose heads have two workgroups (and two sets of candidate lists): it may need more than a few problems beyond it
+  // enough for the compact geometry too, which a call with smaller bounds may fall back to, for a step with the diagnostics (other
+  // chunks), and for the largest number of problems whose heads have two workgroups (and two sets of candidate lists): it may need
+  // more than a few problems beyond it
   const int fewer = std::min(n_problems, 128 / cfg->n_q_heads);
   for (int n : {n_problems, fewer})
-    for (bool compact : {false, true}) {
-      if (make_geom_as(cfg, n, max_L, max_K, compact, false, &g) != TKPHI_OK) return 0;
-      bytes = std::max(bytes, g.total_bytes);
-    }
+    for (bool diag : {false, true})
+      for (Fit fit : {kFast, kCompact}) {
+        if (make_geom_as(cfg, n, max_L, max_K, fit, diag, &g) != TKPHI_OK) return 0;
+        bytes = std::max(bytes, g.total_bytes);
+      }
   return bytes;
 }
 

@@ -282,6 +282,40 @@ def test_static_scratch_budgets(shape, L, k):
     PU.check_layer(w, P, k, b, 0, heads=[0, w.n_q_heads // 2 + 1, w.n_q_heads - 1])
 
 
+def test_static_scratch_holds_the_two_launch_pass():
+    """16 heads over 2 KV heads, 109000 tokens: the chunks of the one-launch score pass need more than the 32 MiB of static scratch, those of
+    the pass with a launch for the sample fit."""
+    import dataclasses
+    import torch
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l1b_32k"], n_q_heads=16, n_kv_heads=2)
+    P = I.make_layer(w, L=109000)
+    b = H.Batch(H.config_of(w), [P], [270], debug=True)
+    b.build()
+    B.tkphi_decode_static(b.cfg, b.table.data_ptr(), 1, b.max_L, b.max_K, 0, B.current_stream_ptr())
+    torch.cuda.synchronize()
+    PU.check_layer(w, P, 270, b, 0, heads=[0, 7, 15])
+
+
+def test_diagnostics_in_a_workspace_sized_for_a_larger_budget():
+    """A step with the diagnostics takes other chunks than one without: a workspace sized for a budget of 2 % serves one of 5 tokens."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS["l1b_32k"]
+    layers = [I.make_layer(w, L=L, seq=i) for i, L in enumerate((13753, 9000))]
+    b = H.Batch(H.config_of(w), layers, [5, 5], debug=True)
+    b.ws_bytes = B.tkphi_workspace_bytes(b.cfg, 2, 13753, 275)
+    b.ws = B.alloc_workspace(b.ws_bytes, "cuda")
+    b.build()
+    b.decode(B.TKPHI_MODE_SUB | B.TKPHI_FLAG_DIAG)
+    assert b.status() & ~2 == 0
+    for i, P in enumerate(layers):
+        PU.check_layer(w, P, 5, b, i, heads=[0, 17, 31])
+
+
 @pytest.mark.parametrize("shape,L,k", [("l3b_128k", 14000, 139), ("l1b_32k", 5000, 49)])
 def test_each_decode_route_replays_from_a_hip_graph(shape, L, k):
     """The sampled-bound route (three launches) and the short-context one (two), captured and replayed with eager work between."""
