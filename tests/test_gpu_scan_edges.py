@@ -78,6 +78,47 @@ def test_scores_alike_in_both_layouts(shape, n_problems):
         assert not listed.any(), f"problem {i}: heads {listed.nonzero().flatten().tolist()} rescanned"
 
 
+@pytest.mark.parametrize("shape", ["l3b_128k", "l1b_32k"])
+@pytest.mark.parametrize("layout", ["token_major", "padded"])
+def test_whole_line_loads_of_strided_and_undefined_keys(shape, layout):
+    """Whole-line loads over rows that do not adjoin (all heads of a token in a row; rows padded by 16 bytes, so that most straddle cache
+    lines), with an infinite channel in some rows of KV head 1 and a row of NaN in KV head 2: the scores of the plain layout over
+    contiguous rows bit for bit (undefined ones where those are), the same index sets for the heads that see no NaN.  One problem and seven."""
+    import numpy as np
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = I.WORKLOADS[shape]
+    mids = [5000, 15, 1000, 1025, 64, 2050, 130]
+    layers, strided = [], []
+    for i, m in enumerate(mids):
+        P = I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i)
+        P["K"][1, [w.n_sink, w.n_sink + m // 2, w.n_sink + m - 1], 5 + 40 * (i % 2)] = 0x7F80
+        P["K"][2, w.n_sink + m // 3, :] = 0x7FC0
+        layers.append(P)
+        dev = dict(P)
+        for name in ("K", "V"):
+            hm = H.to_device(P[name])
+            if layout == "token_major":
+                dev[name] = hm.permute(1, 0, 2).contiguous().permute(1, 0, 2)
+            else:
+                dev[name] = torch.zeros(*hm.shape[:2], w.d_head + 8, dtype=hm.dtype, device="cuda")[:, :, :w.d_head]
+                dev[name].copy_(hm)
+        strided.append(dev)
+    plain = [g for g in range(w.n_q_heads) if g // w.group != 2]
+    for n in (1, 7):
+        res = []
+        for inputs, max_L in ((layers, None), (strided, 140000)):
+            b = H.Batch(H.config_of(w, tuning={"select_mode": 2}), inputs[:n], [m // 60 + 1 for m in mids[:n]], debug=True, max_L=max_L, max_K=400)
+            b.build()
+            b.decode()
+            res.append([{x: b.result(i, x) for x in ("scores", "topk_idx")} for i in range(n)])
+        for i, (want, got) in enumerate(zip(*res)):
+            defined = ~np.isnan(want["scores"])
+            assert np.array_equal(defined, ~np.isnan(got["scores"])) and not defined.all()
+            assert np.array_equal(want["scores"][defined].view(np.uint32), got["scores"][defined].view(np.uint32)), f"problem {i}: scores differ"
+            assert np.array_equal(want["topk_idx"][plain], got["topk_idx"][plain]), f"problem {i}: index sets differ"
+
+
 @pytest.mark.parametrize("shape,L,k", [("l3b_128k", 2500, 200), ("l3b_128k", 40000, 400), ("l1b_32k", 20000, 300)])
 def test_partials_of_several_workgroups(shape, L, k):
     """Several workgroups share a head and the last one merges what the others have handed it: steps of two queries in turn, without the
@@ -316,17 +357,18 @@ def test_diagnostics_in_a_workspace_sized_for_a_larger_budget():
         PU.check_layer(w, P, 5, b, i, heads=[0, 17, 31])
 
 
-@pytest.mark.parametrize("shape,L,k", [("l3b_128k", 14000, 139), ("l1b_32k", 5000, 49)])
-def test_each_decode_route_replays_from_a_hip_graph(shape, L, k):
-    """The sampled-bound route (three launches) and the short-context one (two), captured and replayed with eager work between."""
+@pytest.mark.parametrize("shape,L,k,n", [("l3b_128k", 14000, 139, 1), ("l1b_32k", 5000, 49, 1), ("l3b_128k", 14000, 139, 5)])
+def test_each_decode_route_replays_from_a_hip_graph(shape, L, k, n):
+    """The sampled-bound route of one problem (two launches; the bounds handed over inside the first) and of a batch of 40 KV heads (three),
+    and the short-context one (two), captured and replayed with eager work between."""
     import numpy as np
     import torch
     from paper_2604_05438_amd import harness as H
     w = I.WORKLOADS[shape]
-    b = H.Batch(H.config_of(w), [I.make_layer(w, L=L)], [k], debug=True)
+    b = H.Batch(H.config_of(w), [I.make_layer(w, L=L, seq=i) for i in range(n)], [k] * n, debug=True)
     b.build(); b.decode()
     torch.cuda.synchronize()
-    eager = {n: b.result(0, n).copy() for n in ("out", "topk_idx")}
+    eager = {(i, x): b.result(i, x).copy() for i in range(n) for x in ("out", "topk_idx")}
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
         b.decode()
@@ -335,12 +377,13 @@ def test_each_decode_route_replays_from_a_hip_graph(shape, L, k):
             b.decode()
     torch.cuda.synchronize()
     for rep in range(3):
-        b.dev[0]["out"].zero_()
+        for dev in b.dev:
+            dev["out"].zero_()
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        for n, y in eager.items():
-            assert np.array_equal(b.result(0, n), y), f"replay {rep}: {n} differs from the eager result"
+        for (i, x), y in eager.items():
+            assert np.array_equal(b.result(i, x), y), f"replay {rep}: {x} of problem {i} differs from the eager result"
         b.decode()
         torch.cuda.synchronize()
 
