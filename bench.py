@@ -229,8 +229,12 @@ def main() -> int:
     bytes_const = probs_per_step * (w.n_kv_heads * w.d_phi * (w.d_head + 1) * 4          # S, u
                                     + (w.n_q_heads + w.n_kv_heads) * w.d_phi * w.d_head * esz)   # Wq, Wk
     bytes_step = bytes_scan + bytes_gather + bytes_anchor + bytes_const
+    # short contexts, whose scores are all stored, end where the select kernel's array of candidates does (packed_candidates)
+    short_mid = 10240 if w.d_head == 128 else 4096 if w.dtype == "bf16" and w.n_q_heads * probs_per_step >= 512 and max(Ks) <= 1024 else 12288
     scan_kernel = ("score_mid_kernel" if stage_us.get("select", 0.0) == 0 else
-                   "score_filtered_kernel" if stage_us.get("prep", 0.0) > 0 else "score_fused_kernel")
+                   "score_filtered_kernel" if stage_us.get("prep", 0.0) > 0 else
+                   "score_fused_kernel" if max(Ls) - w.n_sink - w.n_tail > short_mid else
+                   "score_direct_kernel" if w.dtype == "bf16" else "score_direct_f32_kernel")
     scan_s = stage_us["score_mid"] * 1e-6
     achieved = bytes_scan / scan_s / 1e9
 

@@ -145,8 +145,10 @@ typedef struct tkphi_tuning {
                              1 = spill (score_mid writes
                              every score and chunk histograms; plan / emit / resolve select from them),
                              2 = filtered (a sampled lower bound of the K-th score prunes what the score pass
-                             writes; one select kernel per step).  Ignored where only the spill pipeline applies
-                             (fp32 storage, d_phi != d_head, MLP maps, TKPHI_FLAG_DIAG)                    */
+                             writes; one select kernel per step).  1 also holds for short fp32 contexts and
+                             for one problem with MLP maps, 2 also for the latter; ignored where only the spill
+                             pipeline applies (other fp32 storage, d_phi != d_head, several problems with MLP
+                             maps, an exp-affine feature cache, TKPHI_FLAG_DIAG)                          */
   int32_t select_test;    /* filtered pipeline, tests only: 1 = the sampled bound is replaced by one no score
                              passes, or does not arrive in time (every head takes the rescan), 2 = by one
                              every score passes                                                           */

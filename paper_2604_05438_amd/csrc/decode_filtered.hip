@@ -1,8 +1,9 @@
-// Decode front end of the filtered pipeline (bf16 caches on the matrix cores).
+// Decode front end of the filtered pipeline (bf16 caches on the matrix cores; fp32 ones of short contexts in vector arithmetic).
 //
 // The exhaustive Top-K over the mid-region (Sec. "Models, tasks, and protocol") needs every score
 // s_i = q . k_i / sqrt(d_h) once, but only the scores that can still reach the top K have to
-// leave the chip.  Two kernels (for batches; one otherwise):
+// leave the chip.  Two kernels and, from a few sequences on, a third for the phi and anchor jobs (decode_side_kernel) for
+// batches; one otherwise:
 //
 //   decode_prep     one small launch of independent jobs that need no selection:
 //                   * sample: per KV head, the scores of an evenly spaced sample of mid-region rows
@@ -435,12 +436,14 @@ __device__ __forceinline__ bool await_bounds(const Geom& g, const char* blk, int
 }
 
 // grid (Hq (2 + n_atiles) + Hkv n_scan_chunks, n_problems), 512 threads: a sample job per query head, the phi and anchor jobs
-// (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks.  A score workgroup keeps its scores in LDS (G scan_chunk floats) and lists those that reach the bound at
-// (With MLP maps, Geom::list, the first stage of phi_q instead of the phi and anchor jobs, behind the score chunks.)
-// its end, when the sample is long since done: the launch that only sampled had nothing to run beside it.  Bound by HBM for long
-// contexts (3B layer at 128K: 268 MB; behind the last row the lists take 1.6 us, CUs that also sample end 3 us late), by the
-// sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10).  Prep + score launches /
-// this one: 11.1 + 48.7 / 47.5 us (52.5 with half-line loads) and 7.6 + 9.6 / 12.4 us.
+// (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks; with MLP
+// maps (Geom::list) no phi and anchor jobs but the first stage of phi_q, behind the score chunks.  A score workgroup keeps its scores in
+// LDS (G scan_chunk floats) and lists those that reach the bound at its end, when the sample is long since done: the launch that only
+// sampled had nothing to run beside it.  Of several problems each one's samples lie ahead of its own chunks, but behind the
+// chunks of the problems before it.
+// Bound by HBM for long contexts (3B layer at 128K: 268 MB; behind the last row the lists take 1.6 us, CUs that also sample end 3 us
+// late), by the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10).  Prep +
+// score launches / this one: 11.1 + 48.7 / 47.5 us (52.5 with half-line loads) and 7.6 + 9.6 / 12.4 us.
 constexpr int kFusedThreads = 512;
 template <int D, int TPI, bool STREAM>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,

@@ -1,6 +1,7 @@
-// The phi and anchor jobs of the filtered pipeline's prep stage as 256-thread workgroups, for batches: with many
-// (problem, head) pairs in a call the jobs are throughput work, and small workgroups (eight per CU) run them four
-// times as densely as the 1024-thread ones that a single layer uses for the shortest latency.
+// The phi and anchor jobs of the filtered pipeline as the work of 256 threads: workgroups of a launch of their own for batches (with
+// many (problem, head) pairs in a call the jobs are throughput work, and small workgroups run them four times as densely as the
+// 1024-thread ones of decode_prep_kernel, which a few problems take), workgroups of the short-context score launches, and the
+// first half of a 512-thread workgroup in the launch that samples and scores one problem or a few.
 //   phi job     phi_q(q) of a query head (App. "Head-wise phi architecture": per query head, once per step)
 //               and the summary terms S_M^T phi_q, phi_q . u_M that eq. (subtraction) and eq. (hybrid_merge)
 //               start from

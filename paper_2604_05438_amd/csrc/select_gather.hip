@@ -1,4 +1,4 @@
-// Fused Top-K select + gather of the filtered pipeline (bf16 caches on the matrix cores):
+// Fused Top-K select + gather of the filtered pipeline (bf16 caches, and fp32 ones of short contexts at d = 64, on the matrix cores):
 // topk_select, exact_branch and residual_correct for the retrieved tokens in one launch.
 // grid (split, Hq, n_problems), NTHR = 1024 or 512 threads: `split` workgroups share a query head.
 //
@@ -726,17 +726,18 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // grid (sg_split, Hq, n_problems).  After its own share every workgroup of a head counts itself in (its partial made
 // visible first); the one that arrives last finds all partials of the head complete and merges them (merge_head.h)
 // with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
-// same call: the phi jobs of decode_prep_kernel or decode_side_kernel, or, for short contexts, of score_direct_kernel.  (The other wavefronts of that workgroup end before the merge's barriers: a barrier waits only for the
-// wavefronts of the workgroup that are still running.)
+// same call: the phi jobs of whichever launch carries them.  (The other wavefronts of that workgroup end before the merge's
+// barriers: a barrier waits only for the wavefronts of the workgroup that are still running.)
 template <int D, int NTHR, bool DIRECT, bool LIST = false, typename KV = uint16_t>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
   if constexpr (LIST) {
-    // grid (Hq + Hq d_emb / 64 + ..): behind a workgroup per head, on the CUs that the selection leaves idle, a stage of phi_q (the second, where
-    // the first rode in a score launch long enough for it) and, for a step that recomputes features, the weights of the chain over the retrieved keys (a single problem: slot
-    // 0).  As a launch between select and chain the packing took 9 us of a 3B layer's step; phi_q on a second stream, joined before the
-    // gather, held a step with a feature cache at 65 us at any context length (now 45 at 4K).
+    // grid (Hq + Hq d_emb / 64 + ..): behind a workgroup per head, on the CUs that the selection leaves idle, a stage of phi_q (the
+    // second, where the first rode in a score launch long enough for it) and, for a step that recomputes features, the weights of
+    // the chain over the retrieved keys (a single problem: slot 0).  As a launch between select and chain the packing took 9 us of a
+    // 3B layer's step; phi_q on a second stream, joined before the gather, held a step with a feature cache at 65 us up to 16K
+    // tokens (now 40 at 4K, 49 at 16K).
     const int idx = blockIdx.x, n_phi = g.d_emb / 64 * g.Hq, p = 0;
     if (idx >= g.Hq) {
       const tkphi_problem& pr = probs[p];

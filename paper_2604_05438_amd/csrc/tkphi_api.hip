@@ -40,7 +40,9 @@ static int list_head(int scan_chunk, int64_t K, int64_t n, int sweep, int64_t n_
 
 // The filtered pipeline runs for budgets of at most 1 / (this number) of the mid-region.  Against the spill pipeline it saves the
 // write-back of the scores, and pays for a larger budget with what one workgroup of its select kernel gathers alone.  Measured
-// over 1000 combinations of shape, batch, length and budget (spill / filtered, us):
+// over 1000 combinations of shape, batch, length and budget (spill / filtered, us; the filtered side before sample and scores of one
+// problem or a few went into one launch and the reductions off the LDS pipe, 12 to 18 us of a single layer: the lines may lie
+// higher for those now):
 //   * short contexts: always faster (1.07 to 1.6x)
 //   * up to 1/64: as it always was (faster wherever the score pass lasts)
 //   * beyond, where the select kernel's workgroups fill the last of their rounds over the 256 CUs to 4/5: up to 1/12 (3B layer
@@ -439,9 +441,9 @@ tkphi_status tkphi_build_summaries(const tkphi_config* cfg, const tkphi_problem*
 }
 
 // The kernels of one decode call in stream order.  With the MLP feature maps the three phi_q
-// launches (a chain of small cold-weight matrix-vector products, ~30 us if serialised) go to a
+// launches of several problems (a chain of small cold-weight matrix-vector products, ~30 us if serialised) go to a
 // second stream of the library's own that forks from `s` at the start of the call and joins
-// before the gather, so that they run beside the score pass.  One such stream and event pair per
+// before the gather, so that they run beside the score pass (one problem: Geom::list).  One such stream and event pair per
 // device, created on first use at the default priority and kept until the process ends; MLP decode
 // calls hold a mutex while they enqueue (the events are shared).
 struct SideStream {

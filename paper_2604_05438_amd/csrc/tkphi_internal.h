@@ -40,8 +40,8 @@ struct Geom {
   int use_mfma;          // bf16 storage with d_phi == d_head: matrix-core kernels
   int n_problems, max_L, max_K, max_mid;
   int mid_stride;        // floats per score row (multiple of 64)
-  int scan_chunk, n_scan_chunks;     // score_mid: mid tokens per workgroup
-  int scan_unit;         // tokens a score_mid workgroup takes per iteration (scan_chunk is a multiple)
+  int scan_chunk, n_scan_chunks;     // score pass: mid tokens per workgroup
+  int scan_unit;         // tokens a score workgroup takes per iteration (scan_chunk is a multiple)
   int phi_kind, d_emb;   // tkphi_phi_kind; MLP width
   int max_gen;           // bound of tkphi_problem::n_gen (generated tokens, exact)
   int mlp_mode;          // MLP build: tkphi_tuning::mlp_mode
@@ -52,8 +52,8 @@ struct Geom {
   int diag;              // 1: the select emit pass also reduces the entropy / mass diagnostics
   int interleave;        // 1: chunk c owns the units c, c + n_chunks, c + 2 n_chunks, ... of its problem
                          // (all workgroups sweep the key cache together); 0: one contiguous range
-  int filtered;          // 1: decode may run the filtered pipeline (prep, score_filtered, select_gather, merge):
-                         // bf16 matrix-core shapes, exp-affine maps, budgets well below the mid-region size
+  int filtered;          // 1: decode may run the filtered pipeline (score and select launches, before them a prep launch in batches):
+                         // bf16 matrix-core shapes, fp32 ones where Geom::direct, budgets well below the mid-region size
   int direct;            // 1: filtered pipeline for short contexts: all scores stored (off_scores), no bound, no prep launch
   int list;              // 1: filtered pipeline with MLP maps: its select kernel ends with the retrieved lists, gather and merge follow as in
                          // the spill pipeline
@@ -61,7 +61,7 @@ struct Geom {
   uint32_t tag;          // fused: the bounds of this call carry it (not 0)
   int cand_T;            // filtered pipeline: entries of a candidate list kept in the compact array (multiple of 12)
   int head_strip;        // 1: the score pass collects the compact list heads in LDS (4 G cand_T entries fit 32 KB)
-  int stream_keys;       // 1: the filtered score pass reads the keys with non-temporal loads
+  int stream_keys;       // 1: the filtered score pass reads the keys with non-temporal loads of whole lines
   int sel_test;          // tkphi_tuning::select_test (0 unless a test forces the rescan or the no-pruning path)
   int n_tiles;           // gather: ceil(max_K / kPairsPerWG) retrieved-token tiles per query head; one partial each
   int sg_split;          // filtered pipeline: workgroups per query head of the fused select + gather kernel (0 if it cannot run);
@@ -76,7 +76,7 @@ struct Geom {
   size_t off_problem0;   // first per-problem block
   size_t per_problem;    // bytes per problem block
   // offsets inside a per-problem block
-  size_t off_scores;     // float    [Hq][mid_stride]            mid-region scores (spill pipeline)
+  size_t off_scores;     // float    [Hq][mid_stride]            mid-region scores (spill pipeline, Geom::direct)
   size_t off_candf;      // uint2    [Hq][n_scan_chunks][4][scan_chunk/4]  candidate lists (score bits, mid index) of the filtered
                          //                                       pipeline at full capacity (entries past the first cand_T of a
                          //                                       list land here); shares its memory with off_scores
