@@ -200,8 +200,9 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   if (g->fused) {
     g->scan_unit = unit;
     sc = (int)keep_chunk;
-  } else if (g->filtered && fusable && n_problems <= 1) {
-    // (kSeparate) the pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (score pass of a 3B
+  } else if (g->filtered && !compact && n_problems <= 1) {
+    // One problem of more than 128 kept chunks per KV head (64 / 8 heads from 320 K tokens, 24 / 8 from 850 K), or kSeparate: the
+    // pass takes as long as its busiest CU, so the chunk is chosen for full rounds of 256 workgroups (score pass of a 3B
     // layer at 50 K tokens: 232 workgroups of 1792 tokens 22.4 us, 400 of 1024 25.0, 312 of 1280 29.2); one workgroup per CU
     // streams 7 % slower at d = 128 and, with 2.7 times the score work per byte, 40 % at d = 64.  Against that stands what the
     // select kernel pays for more lists: 0.35 us per 1000 slots of their compact heads.

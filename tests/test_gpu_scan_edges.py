@@ -442,6 +442,22 @@ def test_sampled_rows_above_all_others(shape, n_mid, n_problems):
         assert np.isin(b.result(i, "topk_idx")[hot, :k], rows).mean() > 0.9        # (the case is what it says: the bound misses)
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 64), (16, 2, 128)])
+def test_contexts_beyond_the_kept_chunks(hq, hkv, d):
+    """A single sequence of more than 128 chunks of kept scores per KV head: sample and score pass as two launches, heads against the oracle."""
+    import dataclasses
+    import parity_utils as PU
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["l3b_128k" if d == 128 else "l1b_32k"], n_q_heads=hq, n_kv_heads=hkv)
+    P = I.make_layer(w, L=321000)
+    b = H.Batch(H.config_of(w), [P], [900], debug=True)
+    b.build()
+    stages = dict(zip(B.STAGES, b.decode_stage_times()))
+    assert stages["prep"] > 0 and stages["select"] > 0 and b.status() == 0
+    PU.check_layer(w, P, 900, b, 0, heads=[0, hq - 1])
+
+
 @pytest.mark.parametrize("shape,chunk,max_L", [("l3b_128k", 64, None), ("l3b_128k", 320, None), ("l3b_128k", 0, 140000), ("l1b_32k", 128, None),
                                                ("l1b_32k", 1280, None), ("l1b_32k", 0, 140000)])
 def test_rescan_at_every_list_length(shape, chunk, max_L):
