@@ -417,8 +417,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
 }
 
 // ---- sample and score pass in one launch ------------------------------------------------------------------------------
-// The bounds of KV head h (lane gl < G: head h G + gl) from the sample workgroups, which lie ahead of the score workgroups of
-// their problem in the launch and wait for nothing, so the words arrive; the polls are counted all the same, and the lists of a head
+// The bounds of KV head h (lane gl < G: head h G + gl) from the sample workgroups, which lie ahead of every score workgroup in
+// the launch and wait for nothing, so the words arrive; the polls are counted all the same, and the lists of a head
 // whose bound has not come by then are marked as not made (kNoList: the select kernel rescans that head).  False for such a
 // lane.  A word is (tag, bound): tags differ from call to call, and the merging workgroup of the select kernel clears the
 // word, for replays of a captured call.
@@ -435,12 +435,15 @@ __device__ __forceinline__ bool await_bounds(const Geom& g, const char* blk, int
   return (uint32_t)(w >> 32) == g.tag;
 }
 
-// grid (Hq (2 + n_atiles) + Hkv n_scan_chunks, n_problems), 512 threads: a sample job per query head, the phi and anchor jobs
+// n_problems (Hq (2 + n_atiles) + Hkv n_scan_chunks) workgroups of 512 threads: a sample job per query head, the phi and anchor jobs
 // (behind the score chunks their loads are served last: they ended with the pass instead of after 10 us), the score chunks; with MLP
 // maps (Geom::list) no phi and anchor jobs but the first stage of phi_q, behind the score chunks.  A score workgroup keeps its scores in
 // LDS (G scan_chunk floats) and lists those that reach the bound at its end, when the sample is long since done: the launch that only
-// sampled had nothing to run beside it.  Of several problems each one's samples lie ahead of its own chunks, but behind the
-// chunks of the problems before it.
+// sampled had nothing to run beside it.  The jobs of a kind of all problems come before those of the next kind: problem by problem, a
+// problem's samples started behind the chunks of those before it and its own chunks held CUs waiting for them (3 3B sequences of 2K to
+// 30K under bounds of 128K 75 us instead of 55, 4 of 60K to 128K 194 instead of 184, 32 single heads of 128 of 1K to 60K 79 instead of
+// 66, which the two launches took 70 for; the other way round, 4 1B sequences of 16K to 64K 56 instead of 58, 20 of 3 / 1 heads of up
+// to 20K 37 instead of 38).
 // Bound by HBM for long contexts (3B layer at 128K: 268 MB; behind the last row the lists take 1.6 us, CUs that also sample end 3 us
 // late), by the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10).  Prep +
 // score launches / this one: 11.1 + 48.7 / 47.5 us (52.5 with half-line loads) and 7.6 + 9.6 / 12.4 us.
@@ -451,32 +454,39 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   extern __shared__ __attribute__((aligned(16))) float sh_dyn[];
   __shared__ int sh_n;
   constexpr int NWV = kFusedThreads / 64;
-  const int p = blockIdx.y;
   int x = blockIdx.x;
-  if (x == 0 && p == 0) write_device_status(g, probs, ws, true);
+  if (x == 0) write_device_status(g, probs, ws, true);
+  // the jobs of one kind of every problem, then those of the next kind: problem p, job x of its kind
+  int p = 0, kind = 0;
+  const auto is_kind = [&](int k, int per) {
+    if (kind != k) return;
+    const int all = per * g.n_problems;
+    if (x >= all) { x -= all; kind = k + 1; }
+    else if (g.n_problems > 1) { p = x / per; x -= p * per; }
+  };
+  const int n_side = g.list ? 0 : g.Hq;
+  is_kind(0, g.Hq);
+  is_kind(1, n_side);
+  is_kind(2, n_side * g.n_atiles);
+  is_kind(3, g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0);     // (kind 4, behind them: Geom::list, one problem)
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   char* blk = problem_block(g, ws, p);
-  if (x < g.Hq) {
+  if (kind == 0) {
     uint32_t* hist = (uint32_t*)(sh_dyn + 1024);
     prep_sample<D, TPI, kFusedThreads, true>(g, pr, blk, x / g.G, x % g.G, 1, sh_dyn, hist, hist + kBins, &sh_n, (char*)(hist + kBins + kInBin));
     return;
   }
-  x -= g.Hq;
-  if (!g.list) {
-    if (x < g.Hq) {
-      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
-      side_phi<D, 0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
-      return;
-    }
-    x -= g.Hq;
-    if (x < g.Hq * g.n_atiles) {
-      side_anchor<D>(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
-      return;
-    }
-    x -= g.Hq * g.n_atiles;
-  } else if (x >= g.Hkv * g.n_scan_chunks) {
-    x -= g.Hkv * g.n_scan_chunks;
+  if (kind == 1) {
+    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
+    side_phi<D, 0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+    return;
+  }
+  if (kind == 2) {
+    side_anchor<D>(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
+    return;
+  }
+  if (kind == 4) {
     mlp_phi_q_slice<0>(g, pr, blk, x % g.Hq, x / g.Hq, sh_dyn);
     return;
   }
@@ -547,7 +557,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
 }
 
 void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(g.Hq * (g.list ? 1 + g.d_emb / 64 : 2 + g.n_atiles) + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0), g.n_problems);
+  dim3 grid(g.n_problems * (g.Hq * (g.list ? 1 + g.d_emb / 64 : 2 + g.n_atiles) + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0)));
   const size_t sample = (size_t)(1024 + kBins + kInBin) * 4 + (size_t)(kFusedThreads / 64) * 16 * (g.d * 2 + 16);
   static_assert(kQuerySliceLds <= 1024 + kBins + kInBin + 128 * (64 * 2 + 16) / 4, "the sample's share holds phi_q's as well");
   const size_t lds = std::max(sample, (size_t)g.G * g.scan_chunk * sizeof(float));       // (more than the 6 KB of the phi jobs)
