@@ -233,7 +233,7 @@ def main() -> int:
     short_mid = 10240 if w.d_head == 128 else 4096 if w.dtype == "bf16" and w.n_q_heads * probs_per_step >= 512 and max(Ks) <= 1024 else 12288
     scan_kernel = ("score_mid_kernel" if stage_us.get("select", 0.0) == 0 else
                    "score_filtered_kernel" if stage_us.get("prep", 0.0) > 0 else
-                   "score_fused_kernel" if max(Ls) - w.n_sink - w.n_tail > short_mid else
+                   ("score_fused_kernel" if probs_per_step == 1 else "score_fused_few_kernel") if max(Ls) - w.n_sink - w.n_tail > short_mid else
                    "score_direct_kernel" if w.dtype == "bf16" else "score_direct_f32_kernel")
     scan_s = stage_us["score_mid"] * 1e-6
     achieved = bytes_scan / scan_s / 1e9

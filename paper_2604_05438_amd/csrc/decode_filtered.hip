@@ -19,8 +19,8 @@
 //   score_filtered  the streaming pass over all mid-region keys, each KV head read once for its G
 //                   query heads; a score goes to memory only if its key is >= the head's bound
 //                   (about 2-3 K tokens per head instead of |M|), appended to per-wavefront lists.
-//   score_fused     both in one launch for one problem or a few (Geom::fused): the scan keeps its scores in LDS until the sample's
-//                   bound, which the sample workgroups hand over inside the launch, has come.
+//   score_fused     both in one launch for one problem or a few (score_fused_few; Geom::fused): the scan keeps its scores in LDS until
+//                   the sample's bound, which the sample workgroups hand over inside the launch, has come.
 //   score_direct    instead of both where contexts are short (Geom::direct): every score stored, one row per head,
 //                   with the phi and anchor jobs in the same launch.
 #include <algorithm>
@@ -441,52 +441,43 @@ __device__ __forceinline__ bool await_bounds(const Geom& g, const char* blk, int
 // LDS (G scan_chunk floats) and lists those that reach the bound at its end, when the sample is long since done: the launch that only
 // sampled had nothing to run beside it.  The jobs of a kind of all problems come before those of the next kind: problem by problem, a
 // problem's samples started behind the chunks of those before it and its own chunks held CUs waiting for them (3 3B sequences of 2K to
-// 30K under bounds of 128K 75 us instead of 55, 4 of 60K to 128K 194 instead of 184, 32 single heads of 128 of 1K to 60K 79 instead of
-// 66, which the two launches took 70 for; the other way round, 4 1B sequences of 16K to 64K 56 instead of 58, 20 of 3 / 1 heads of up
+// 30K under bounds of 128K 75 us instead of 55, 4 of 60K to 128K 195 instead of 184, 32 single heads of 128 of 1K to 60K 79 instead of
+// 66, which the two launches took 70 for; the other way round, 4 1B sequences of 16K to 64K 56 instead of 57, 20 of 3 / 1 heads of up
 // to 20K 37 instead of 38).
 // Bound by HBM for long contexts (3B layer at 128K: 268 MB; behind the last row the lists take 1.6 us, CUs that also sample end 3 us
 // late), by the sample's round trips for short ones (1B layer at 32K: scores complete after 6.6 us, bounds there after 10).  Prep +
 // score launches / this one: 11.1 + 48.7 / 47.5 us (52.5 with half-line loads) and 7.6 + 9.6 / 12.4 us.
 constexpr int kFusedThreads = 512;
-template <int D, int TPI, bool STREAM>
-__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                                                              char* __restrict__ ws) {
+// job x of problem p.  LIST: with MLP maps (one problem)
+template <int D, int TPI, bool STREAM, bool LIST>
+__device__ __forceinline__ void score_fused_job(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws, int x, int p) {
   extern __shared__ __attribute__((aligned(16))) float sh_dyn[];
   __shared__ int sh_n;
   constexpr int NWV = kFusedThreads / 64;
-  int x = blockIdx.x;
-  if (x == 0) write_device_status(g, probs, ws, true);
-  // the jobs of one kind of every problem, then those of the next kind: problem p, job x of its kind
-  int p = 0, kind = 0;
-  const auto is_kind = [&](int k, int per) {
-    if (kind != k) return;
-    const int all = per * g.n_problems;
-    if (x >= all) { x -= all; kind = k + 1; }
-    else if (g.n_problems > 1) { p = x / per; x -= p * per; }
-  };
-  const int n_side = g.list ? 0 : g.Hq;
-  is_kind(0, g.Hq);
-  is_kind(1, n_side);
-  is_kind(2, n_side * g.n_atiles);
-  is_kind(3, g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0);     // (kind 4, behind them: Geom::list, one problem)
+  if (blockIdx.x == 0) write_device_status(g, probs, ws, true);
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   char* blk = problem_block(g, ws, p);
-  if (kind == 0) {
+  if (x < g.Hq) {
     uint32_t* hist = (uint32_t*)(sh_dyn + 1024);
     prep_sample<D, TPI, kFusedThreads, true>(g, pr, blk, x / g.G, x % g.G, 1, sh_dyn, hist, hist + kBins, &sh_n, (char*)(hist + kBins + kInBin));
     return;
   }
-  if (kind == 1) {
-    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
-    side_phi<D, 0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
-    return;
-  }
-  if (kind == 2) {
-    side_anchor<D>(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
-    return;
-  }
-  if (kind == 4) {
+  x -= g.Hq;
+  if (!LIST || !g.list) {
+    if (x < g.Hq) {
+      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[x] = 0u;
+      side_phi<D, 0>(g, pr, blk, x, sh_dyn, sh_dyn + kMaxDim, sh_dyn + 2 * kMaxDim);
+      return;
+    }
+    x -= g.Hq;
+    if (x < g.Hq * g.n_atiles) {
+      side_anchor<D>(g, pr, blk, x / g.n_atiles, x % g.n_atiles, sh_dyn, sh_dyn + 64, sh_dyn + 128);
+      return;
+    }
+    x -= g.Hq * g.n_atiles;
+  } else if (x >= g.Hkv * g.n_scan_chunks) {
+    x -= g.Hkv * g.n_scan_chunks;
     mlp_phi_q_slice<0>(g, pr, blk, x % g.Hq, x / g.Hq, sh_dyn);
     return;
   }
@@ -504,6 +495,33 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   if (g.sel_test == 1 && (chunk & 1)) known = false;      // (test: as if the wait had run out)
   lds_barrier();
   list_kept<D, NWV>(g, pr, blk, h, n, n_chunks, chunk, (lds_f32)sh_dyn, edge, known);
+}
+
+// one problem
+template <int D, int TPI, bool STREAM>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+                                                                                                              char* __restrict__ ws) {
+  score_fused_job<D, TPI, STREAM, true>(g, probs, ws, blockIdx.x, 0);
+}
+
+// a few: the jobs of one kind of every problem, then those of the next kind (in the kernel for one problem this sorting would cost a layer's
+// step 0.4 us)
+struct FusedJobs { int n_problems, per_problem[4]; };    // sample, phi, anchor, score jobs of a problem (beside probs in the arguments: the
+                                                         // record's address waits for no other line of them)
+template <int D, int TPI, bool STREAM>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void score_fused_few_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+                                                                                                                  char* __restrict__ ws, FusedJobs jobs) {
+  int x = blockIdx.x, ahead = 0, per = 0;  // jobs of a problem of the kinds before this one's, of this one's
+  bool found = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (found) continue;
+    per = jobs.per_problem[k];
+    found = x < per * jobs.n_problems;
+    if (!found) { x -= per * jobs.n_problems; ahead += per; }
+  }
+  const int p = x / per;
+  score_fused_job<D, TPI, STREAM, false>(g, probs, ws, x - p * per + ahead, p);
 }
 
 // The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query
@@ -557,17 +575,21 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
 }
 
 void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(g.n_problems * (g.Hq * (g.list ? 1 + g.d_emb / 64 : 2 + g.n_atiles) + (g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0)));
+  const FusedJobs jobs = {g.n_problems, {g.Hq, g.Hq, g.Hq * g.n_atiles, g.max_mid > 0 ? g.Hkv * g.n_scan_chunks : 0}};
+  const int n_score = jobs.per_problem[3], n_jobs = g.list ? g.Hq * (1 + g.d_emb / 64) + n_score : g.Hq * (2 + g.n_atiles) + n_score;
   const size_t sample = (size_t)(1024 + kBins + kInBin) * 4 + (size_t)(kFusedThreads / 64) * 16 * (g.d * 2 + 16);
   static_assert(kQuerySliceLds <= 1024 + kBins + kInBin + 128 * (64 * 2 + 16) / 4, "the sample's share holds phi_q's as well");
   const size_t lds = std::max(sample, (size_t)g.G * g.scan_chunk * sizeof(float));       // (more than the 6 KB of the phi jobs)
-  const auto launch = [&](auto fn) {
+  const auto launch = [&](auto fn, auto... more) {
     const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
-    TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kFusedThreads), lds, s, g, probs, ws);
+    TKPHI_LAUNCH(ST_SCORE, fn, dim3(g.n_problems * n_jobs), dim3(kFusedThreads), lds, s, g, probs, ws, more...);
   };
-  if (g.d == 128) { if (g.stream_keys) launch(score_fused_kernel<128, 4, true>); else launch(score_fused_kernel<128, 4, false>); }
-  else { if (g.stream_keys) launch(score_fused_kernel<64, 8, true>); else launch(score_fused_kernel<64, 8, false>); }
+  if (g.n_problems == 1) {
+    if (g.d == 128) { if (g.stream_keys) launch(score_fused_kernel<128, 4, true>); else launch(score_fused_kernel<128, 4, false>); }
+    else { if (g.stream_keys) launch(score_fused_kernel<64, 8, true>); else launch(score_fused_kernel<64, 8, false>); }
+  } else if (g.d == 128) { if (g.stream_keys) launch(score_fused_few_kernel<128, 4, true>, jobs); else launch(score_fused_few_kernel<128, 4, false>, jobs); }
+  else { if (g.stream_keys) launch(score_fused_few_kernel<64, 8, true>, jobs); else launch(score_fused_few_kernel<64, 8, false>, jobs); }
 }
 
 // The same for fp32 caches (d = 64): scores in vector arithmetic, 128 rows per workgroup and all of them requested before the first

@@ -186,7 +186,7 @@ def test_given_chunk_too_short_for_the_bounds(hq, hkv, d, chunk, max_L):
     PU.check_layer(w, P, 40, b, 0)
 
 
-def _kernel_attributes(name):
+def _kernel_attributes(name, more=""):
     import ctypes
     from paper_2604_05438_amd import binding as B
 
@@ -197,17 +197,18 @@ def _kernel_attributes(name):
                     ("sharedSizeBytes", ctypes.c_size_t)]
 
     attr = Attributes()
-    kernel = ctypes.c_void_p.in_dll(B.lib(), f"_ZN5tkphi{name}EvNS_4GeomEPK13tkphi_problemPc")
+    kernel = ctypes.c_void_p.in_dll(B.lib(), f"_ZN5tkphi{name}EvNS_4GeomEPK13tkphi_problemPc{more}")
     assert B.lib().hipFuncGetAttributes(ctypes.byref(attr), ctypes.byref(kernel)) == 0
     return attr
 
 
 @pytest.mark.parametrize("d,tiles", [(64, 8), (128, 4)])
 @pytest.mark.parametrize("stream", [0, 1])
-def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream):
+@pytest.mark.parametrize("name,more", [("18score_fused_kernel", ""), ("22score_fused_few_kernel", "NS_9FusedJobsE")])
+def test_kept_scores_leave_room_for_two_workgroups(d, tiles, stream, name, more):
     """The one-launch score pass keeps up to 79872 bytes of scores per workgroup so that two share the 160 KB of a CU: what its kernel
     holds besides must fit the 2 KB left of each half."""
-    assert _kernel_attributes(f"18score_fused_kernelILi{d}ELi{tiles}ELb{stream}EE").sharedSizeBytes <= 81920 - 79872
+    assert _kernel_attributes(f"{name}ILi{d}ELi{tiles}ELb{stream}EE", more).sharedSizeBytes <= 81920 - 79872
 
 
 @pytest.mark.parametrize("name,wavefronts", [("18decode_side_kernelILi64EE", 7), ("18decode_side_kernelILi128EE", 7),
