@@ -462,18 +462,23 @@ __global__ __launch_bounds__(kThreads) void build_f32_kernel(Geom g, const tkphi
 }
 
 // sums the chunk partials of each (problem, KV head) in a fixed order.
-// grid (ceil(dphi*(d+1)/4 / 64), Hkv, n_problems), 256 threads = 64 float4 elements x 4 chunk
+// grid (ceil(dphi*(d+1)/4 / 64) + 1, Hkv, n_problems), 256 threads = 64 float4 elements x 4 chunk
 // groups: group q sums chunks q*16 .. q*16+15 of every 64 (16 loads in flight), then the four
-// group sums are added in group order.
+// group sums are added in group order.  The last workgroup of the first row writes the device status.
+// What bounds it at one problem is a chain of round trips (arguments, problem record, partials, result): so the record's pointers
+// are asked for with the length, and the first partials of a single problem before the length is there (its chunks nearly always
+// fill the bounds; what lies behind them is not added): one fp32 head of 4K tokens 12.3 -> 11.4 us per call.
 __global__ __launch_bounds__(kThreads) void build_reduce_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                 char* __restrict__ ws) {
   __shared__ float4 sh[4][64];
   const int h = blockIdx.y, p = blockIdx.z;
-  if (blockIdx.x == 0 && h == 0 && p == 0) write_device_status(g, probs, ws, false);
+  if (blockIdx.x == gridDim.x - 1) {
+    if (h == 0 && p == 0) write_device_status(g, probs, ws, false);
+    return;
+  }
   const int L = probs[p].L;
-  if (L < 1 || L > g.max_L) return;
-  const int n = mid_size(L, g.n_sink, g.n_tail);
-  const int n_chunks = (n + g.build_chunk - 1) / g.build_chunk;
+  float* S = probs[p].S;
+  float* u = probs[p].u;
   const int d = g.d, dphi = g.dphi;
   const size_t per = (size_t)dphi * (d + 1);          // floats per partial (a multiple of 4)
   const int el = threadIdx.x & 63, grp = threadIdx.x >> 6;
@@ -482,14 +487,20 @@ __global__ __launch_bounds__(kThreads) void build_reduce_kernel(Geom g, const tk
   const float4* bp = (const float4*)((const float*)(ws + g.off_bpart) + ((size_t)(p * g.Hkv + h) * g.n_build_chunks) * per) +
                      (live ? e4 : 0);
   const size_t per4 = per / 4;
+  auto request = [&](int c0, int last, float4 (&v)[16]) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = bp[(size_t)min(c0 + grp * 16 + k, last) * per4];
+  };
+  float4 v[16];
+  if (g.n_problems == 1) request(0, g.n_build_chunks - 1, v);
+  asm volatile("" : : "s"(L), "s"(S), "s"(u));
+  if (L < 1 || L > g.max_L) return;
+  const int n = mid_size(L, g.n_sink, g.n_tail);
+  const int n_chunks = (n + g.build_chunk - 1) / g.build_chunk;
+  if (g.n_problems != 1 && n_chunks > 0) request(0, n_chunks - 1, v);
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int c0 = 0; c0 < n_chunks; c0 += 64) {
-    float4 v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int c = c0 + grp * 16 + k;
-      v[k] = bp[(size_t)min(c, n_chunks - 1) * per4];
-    }
+    if (c0 > 0) request(c0, n_chunks - 1, v);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       if (c0 + grp * 16 + k < n_chunks) { acc.x += v[k].x; acc.y += v[k].y; acc.z += v[k].z; acc.w += v[k].w; }
@@ -502,8 +513,8 @@ __global__ __launch_bounds__(kThreads) void build_reduce_kernel(Geom g, const tk
 #pragma unroll
   for (int q = 1; q < 4; ++q) { s.x += sh[q][el].x; s.y += sh[q][el].y; s.z += sh[q][el].z; s.w += sh[q][el].w; }
   const size_t e = e4 * 4;
-  if (e < (size_t)dphi * d) *(float4*)(probs[p].S + (size_t)h * dphi * d + e) = s;
-  else *(float4*)(probs[p].u + (size_t)h * dphi + (e - (size_t)dphi * d)) = s;
+  if (e < (size_t)dphi * d) *(float4*)(S + (size_t)h * dphi * d + e) = s;
+  else *(float4*)(u + (size_t)h * dphi + (e - (size_t)dphi * d)) = s;
 }
 
 template <int D, bool CACHE, int NS>
@@ -552,7 +563,7 @@ void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream
     }
   }
   const int per4 = g.dphi * (g.d + 1) / 4;
-  dim3 rgrid((per4 + 63) / 64, g.Hkv, g.n_problems);
+  dim3 rgrid((per4 + 63) / 64 + 1, g.Hkv, g.n_problems);
   TKPHI_LAUNCH(ST_UNTIMED, build_reduce_kernel, rgrid, dim3(kThreads), 0, s, g, probs, ws);
 }
 
