@@ -23,9 +23,8 @@ union Frag {
 };
 
 // ------------------------------------------------------------------------------------
-// bf16 on the matrix cores: grid (n_build_chunks, Hkv, n_problems), 4 wavefronts,
-// D == d_head == d_phi.  Wavefront w owns the features [w D/4, (w+1) D/4): its slice of Wk
-// stays in registers for the whole chunk.
+// bf16 on the matrix cores, d_head == d_phi == D = 128: grid (n_build_chunks, Hkv, n_problems), 4 wavefronts.
+// Wavefront w owns the features [w D/4, (w+1) D/4): its slice of Wk stays in registers for the whole chunk.
 //
 // The chunk is cut into tiles of 32 tokens.  A stage of LDS holds one tile of keys and one of
 // values, both row-major as they lie in the cache, brought in by loads that write LDS
@@ -44,10 +43,8 @@ union Frag {
 // r holds granule s ^ f(r) of that row, with f chosen per tensor so that the reads spread
 // over all banks:
 //   keys    read as the A operand of GEMM1 (16 lanes = 16 rows, same granule): f = row mod 16
-//           (rows of 256 bytes), (row / 2) mod 8 (rows of 128 bytes)
 //   values  read by the transposing LDS read (16 lanes take 8 bytes each of 4 rows x 16
-//           channels; lane j receives the 4 tokens of channel j): f = 2 (row mod 8) resp.
-//           2 ((row / 2) mod 4)
+//           channels; lane j receives the 4 tokens of channel j): f = 2 (row mod 8)
 // |k|^2: a wavefront reads back the rows its own loads brought (its own wait covers them), sums
 // the squares with 16-bit dot products and leaves c |k|^2 per row in LDS before the tile's
 // barrier: one barrier per tile.
@@ -61,10 +58,10 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {   
   return __builtin_amdgcn_fdot2_f32_bf16(x.v, y.v, c, false);
 }
 
-template <int D, bool CACHE, int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2, D == 64 ? 4 : 2)))
+template <bool CACHE, int NS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
-  constexpr int NW = 4;
+  constexpr int D = 128, NW = 4;
   constexpr int KS = D / 32;            // k-steps of GEMM1 (over channels)
   constexpr int FT = D / (16 * NW);     // feature tiles per wavefront
   constexpr int CT = D / 16;            // channel tiles of S
@@ -116,8 +113,8 @@ void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __
   const char* Vt = (const char*)pr.V + base_off;
   const uint32_t ring_addr = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)ring;
 
-  auto f_key = [](int row) { return GR == 16 ? (row & 15) : ((row >> 1) & 7); };
-  auto f_val = [](int row) { return GR == 16 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1); };
+  auto f_key = [](int row) { return row & 15; };
+  auto f_val = [](int row) { return (row & 7) << 1; };
   // loads: instruction i of wavefront wv fills rows (wv * NLD + i) * RPI .. + RPI of a tile
   int ld_row[NLD], ld_kg[NLD], ld_vg[NLD];
 #pragma unroll
@@ -278,6 +275,243 @@ void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __
     x += __shfl_xor(x, 16);
     x += __shfl_xor(x, 32);
     if (kg == 0) bp[(size_t)D * D + wv * (D / NW) + ft * 16 + r] = x;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// bf16, d_head == d_phi == 64: grid (n_build_chunks, Hkv, n_problems), NW wavefronts, wavefront w with tokens of its own (the tiles
+// w, w + NW, ... of the chunk) and all 64 features of them: S (64 registers), Wk (32) and a tile's features (32) of one
+// wavefront fit the registers.  So the tiles of a wavefront are its own business: it waits for its own loads only, there is no barrier
+// in the loop, a key row is read from LDS once instead of once per feature slice, and |k|^2 costs a wavefront eight dot products per 16
+// tokens: their sums over a row's four lanes come from one fp32 matrix product with c in every element of B, which leaves
+// c |k|^2 of the tokens 4 kg + i in every lane (r, kg), where the exponents need it.  The wavefronts' S and u are added at the
+// end, through LDS, in wavefront order.  Contractions and operand layouts as in the kernel above (values: f = 2 ((row / 2) mod 4), keys:
+// f = (row / 2) mod 8, rows of 128 bytes).  Two stages of 8 KB per wavefront; the keys' half of a stage is refilled as soon as
+// its fragments are in registers.
+// What bounds it: the memory pipeline.  16 sequences of 64K (2.1 GB): 371 us per call, 343 without the arithmetic, with slices of
+// 16 features per wavefront and a barrier per tile (the form of the kernel above, 4 workgroups per CU) 395; 16 ragged ones of 16K..64K 317 ->
+// 300; one of 128K 57 -> 52, of 32K 21.8 -> 20.0, of 12K 14.6 -> 12.7.  8 wavefronts per workgroup: 32K 26.6, ragged 321.
+// ------------------------------------------------------------------------------------
+template <int NW, bool CACHE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void build_mfma64_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
+  constexpr int D = 64, KS = 2, FT = 4, CT = 4, TT = 32, ROWB = 128, TILEB = TT * ROWB, NLD = 4, STAGE = 2 * TILEB;
+  extern __shared__ __attribute__((aligned(1024))) char ring[];   // [NW][2][keys, values][TT][ROWB], then Wk [D][ROWB], bias [D]
+  const int ch = blockIdx.x, h = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
+  const tkphi_problem pr = probs[p];
+  if (pr.L < 1 || pr.L > g.max_L) return;
+  const int n = mid_size(pr.L, g.n_sink, g.n_tail);
+  const int c0 = ch * g.build_chunk;
+  if (c0 >= n) return;
+  const int c1 = min(n, c0 + g.build_chunk);
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, kg = lane >> 4;
+  const float a2 = g.a * kLog2e, c2 = g.c * kLog2e;
+  char* my = ring + wv * 2 * STAGE;      // this wavefront's stages
+  char* w_s = ring + NW * 2 * STAGE;
+  float* bias_s = (float*)(w_s + D * ROWB);
+  const uint32_t ring_addr = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)ring;
+  const uint32_t my_addr = ring_addr + wv * 2 * STAGE;
+
+  // Wk and the biases by way of LDS, ahead of the first tiles: no wait of their own
+  {
+    const char* wsrc = (const char*)pr.Wk + (size_t)h * D * ROWB;
+#pragma unroll
+    for (int i = 0; i < 8 / NW; ++i) {
+      const uint32_t o = (wv * (8 / NW) + i) * 1024;
+      load_to_lds16(wsrc, o + lane * 16, ring_addr + NW * 2 * STAGE + o);
+    }
+    if (lane < D / 4) load_to_lds16((const char*)(pr.bk + (size_t)h * D), lane * 16, ring_addr + NW * 2 * STAGE + D * ROWB);
+  }
+  const size_t row_bytes = (size_t)pr.stride_tok * 2;
+  const size_t base_off = ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2;
+  const char* Kt = (const char*)pr.K + base_off;
+  const char* Vt = (const char*)pr.V + base_off;
+  auto f_key = [](int row) { return (row >> 1) & 7; };
+  auto f_val = [](int row) { return ((row >> 1) & 3) << 1; };
+  const int n_tiles = (c1 - c0 + TT - 1) / TT;
+  const int n_my = n_tiles > wv ? (n_tiles - wv + NW - 1) / NW : 0;
+  const bool near = (uint64_t)TT * row_bytes < (1ull << 31);
+  // load instruction i of a tile: rows 8 i .. 8 i + 7
+  const int lrow = lane >> 3;
+  uint32_t ko[NLD], vo[NLD];
+#pragma unroll
+  for (int i = 0; i < NLD; ++i) {
+    const int row = i * 8 + lrow;
+    ko[i] = (near ? (uint32_t)(row * row_bytes) : 0u) + (((lane & 7) ^ f_key(row)) * 16);
+    vo[i] = (near ? (uint32_t)(row * row_bytes) : 0u) + (((lane & 7) ^ f_val(row)) * 16);
+  }
+  auto issue = [&](int j, const char* T, const uint32_t (&off)[NLD], uint32_t dst) {      // this wavefront's tile j of K or V
+    const int t0 = c0 + (wv + j * NW) * TT;
+    if (near && t0 + TT <= c1) {
+      const char* b = T + (size_t)t0 * row_bytes;
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) load_to_lds16_stream(b, off[i], dst + i * 1024);
+    } else {                             // rows past the end re-read the last row
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        const int row = i * 8 + lrow;
+        const size_t ro = (size_t)min(t0 + row, c1 - 1) * row_bytes;
+        load_to_lds16_stream(T + ro + (off[i] - (near ? (uint32_t)(row * row_bytes) : 0u)), dst + i * 1024);
+      }
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if (j < n_my) {
+      issue(j, Kt, ko, my_addr + j * STAGE);
+      issue(j, Vt, vo, my_addr + j * STAGE + TILEB);
+    }
+  if (n_my >= 2) wait_vm_loads<4 * NLD>();
+  else if (n_my == 1) wait_vm_loads<2 * NLD>();
+  else wait_vm_loads<0>();
+  lds_barrier();
+  Frag wk[FT][KS];
+  float bias[FT];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) {
+#pragma unroll
+    for (int j = 0; j < KS; ++j) wk[ft][j].u = *(const u32x4*)(w_s + (ft * 16 + r) * ROWB + j * 64 + kg * 16);
+    bias[ft] = bias_s[ft * 16 + r] * kLog2e;
+  }
+  floatx4 sacc[FT][CT];
+  float uacc[FT];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) {
+    uacc[ft] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) sacc[ft][ct] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  }
+  uint32_t a_off[KS], v_off[CT];
+#pragma unroll
+  for (int j = 0; j < KS; ++j) a_off[j] = (uint32_t)(r * ROWB + (((j * 4 + kg) ^ f_key(r)) * 16));
+  {
+    const int vrow = 4 * kg + (r >> 2), b = r & 3, fv2 = f_val(vrow) >> 1;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) v_off[ct] = (uint32_t)(vrow * ROWB + ((ct ^ fv2) << 5) + b * 8);
+  }
+  float* cache_h = CACHE ? pr.phi_cache + (size_t)h * n * D : nullptr;   // [token of M][feature]
+
+  for (int j = 0; j < n_my; ++j) {
+    const uint32_t so = (uint32_t)(j & 1) * STAGE;
+    const char* k_t = my + so;
+    const char* v_t = k_t + TILEB;
+    const int t0 = c0 + (wv + j * NW) * TT;
+    if (j + 1 < n_my) wait_vm_loads<3 * NLD>();
+    else wait_vm_loads<NLD>();
+    Frag a[2][KS];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a[mt][s].u = *(const u32x4*)(k_t + mt * 16 * ROWB + a_off[s]);
+    floatx4 cn[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      float sq = 0.f;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq = dot2_bf16(a[mt][s].u[e], a[mt][s].u[e], sq);
+      asm volatile("s_nop 4" : "+v"(sq));     // (a dot product's result needs wait states before a matrix instruction reads it)
+      cn[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(sq, c2, (floatx4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+    // (the key fragments have left LDS: their stage takes the tile after the next)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (j + 2 < n_my) issue(j + 2, Kt, ko, my_addr + so);
+    if (t0 + TT > c1) {                  // no features past the end
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (t0 + mt * 16 + 4 * kg + i >= c1) cn[mt][i] = INFINITY;
+    }
+    u32x2 phi_hi[2][FT], phi_lo[2][FT];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      floatx4 acc[FT];                   // (all tiles' products ahead of the first exponential)
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft)
+          acc[ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt][s].v, wk[ft][s].v, s ? acc[ft] : (floatx4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) {
+        float f[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = phi_exp2(acc[ft][i], a2, bias[ft] - cn[mt][i]);
+        uacc[ft] += (f[0] + f[1]) + (f[2] + f[3]);
+        uint32_t h01, l01, h23, l23;
+        split_bf16_pair(f[0], f[1], &h01, &l01);
+        split_bf16_pair(f[2], f[3], &h23, &l23);
+        phi_hi[mt][ft] = (u32x2){h01, h23};
+        phi_lo[mt][ft] = (u32x2){l01, l23};
+        if (CACHE) {                     // the 16-bit values GEMM2 contracts, as fp32
+          const int tok = t0 + mt * 16 + 4 * kg;
+          float* cp = cache_h + (size_t)tok * D + ft * 16 + r;
+          if (tok + 0 < c1) cp[0] = join_bf16_lo(h01, l01);
+          if (tok + 1 < c1) cp[D] = join_bf16_hi(h01, l01);
+          if (tok + 2 < c1) cp[2 * D] = join_bf16_lo(h23, l23);
+          if (tok + 3 < c1) cp[3 * D] = join_bf16_hi(h23, l23);
+        }
+      }
+    }
+    if (CACHE) wait_vm_loads<0>();       // (stores count too)
+    else if (j + 2 < n_my) wait_vm_loads<3 * NLD>();
+    else if (j + 1 < n_my) wait_vm_loads<2 * NLD>();
+    else wait_vm_loads<0>();
+    Frag vb[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      typedef short4v __attribute__((address_space(3)))* lds_s4;
+      union { short4v s; u32x2 u; } b0, b1;
+      b0.s = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(v_t + v_off[ct]));
+      b1.s = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(v_t + 16 * ROWB + v_off[ct]));
+      vb[ct].u = (u32x4){b0.u.x, b0.u.y, b1.u.x, b1.u.y};
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (so have the values)
+    if (j + 2 < n_my) issue(j + 2, Vt, vo, my_addr + so + TILEB);
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) {
+      Frag ahi, alo;
+      ahi.u = (u32x4){phi_hi[0][ft].x, phi_hi[0][ft].y, phi_hi[1][ft].x, phi_hi[1][ft].y};
+      alo.u = (u32x4){phi_lo[0][ft].x, phi_lo[0][ft].y, phi_lo[1][ft].x, phi_lo[1][ft].y};
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) sacc[ft][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo.v, vb[ct].v, sacc[ft][ct], 0, 0, 0);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) sacc[ft][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi.v, vb[ct].v, sacc[ft][ct], 0, 0, 0);
+    }
+  }
+
+  // the wavefronts' sums through LDS, added in wavefront order
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) *(floatx4*)(my + (ft * CT + ct) * 1024 + lane * 16) = sacc[ft][ct];
+  float* u_s = (float*)w_s;              // [NW][D], over Wk
+  lds_barrier();                         // every wavefront has taken its Wk and bias
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) {
+    float x = uacc[ft];
+    x += __shfl_xor(x, 16);
+    x += __shfl_xor(x, 32);
+    if (kg == 0) u_s[wv * D + ft * 16 + r] = x;
+  }
+  lds_barrier();
+  float* bp = (float*)(ws + g.off_bpart) + ((size_t)(p * g.Hkv + h) * g.n_build_chunks + ch) * ((size_t)D * (D + 1));
+#pragma unroll
+  for (int k = 0; k < FT * CT / NW; ++k) {
+    const int t = wv * (FT * CT / NW) + k, ft = t / CT, ct = t % CT;
+    floatx4 x = *(const floatx4*)(ring + t * 1024 + lane * 16);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) x += *(const floatx4*)(ring + w * 2 * STAGE + t * 1024 + lane * 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bp[(size_t)(ft * 16 + 4 * kg + i) * D + ct * 16 + r] = x[i];
+  }
+  if (tid < D) {
+    float x = u_s[tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) x += u_s[w * D + tid];
+    bp[(size_t)D * D + tid] = x;
   }
 }
 
@@ -517,19 +751,26 @@ __global__ __launch_bounds__(kThreads) void build_reduce_kernel(Geom g, const tk
   else *(float4*)(u + (size_t)h * dphi + (e - (size_t)dphi * d)) = s;
 }
 
-template <int D, bool CACHE, int NS>
+template <bool CACHE, int NS>
 static void launch_build_mfma_as(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
-  const size_t lds = (size_t)NS * (2 * 32 * D * 2 + 32 * 4);
-  const hipError_t e = hipFuncSetAttribute((const void*)build_mfma_kernel<D, CACHE, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const size_t lds = (size_t)NS * (2 * 32 * 128 * 2 + 32 * 4);
+  const hipError_t e = hipFuncSetAttribute((const void*)build_mfma_kernel<CACHE, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
-  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma_kernel<D, CACHE, NS>), grid, dim3(256), lds, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma_kernel<CACHE, NS>), grid, dim3(256), lds, s, g, probs, ws);
+}
+template <int NW, bool CACHE>
+static void launch_build_mfma64(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
+  constexpr size_t lds = NW * 16384 + 64 * 128 + 64 * 4;
+  const hipError_t e = hipFuncSetAttribute((const void*)build_mfma64_kernel<NW, CACHE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
+  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma64_kernel<NW, CACHE>), grid, dim3(64 * NW), lds, s, g, probs, ws);
 }
 static void launch_build_mfma(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
   constexpr int NS = 4;                  // ring stages: three tiles on their way while one is contracted
-  if (g.d == 128 && g.cache) launch_build_mfma_as<128, true, NS>(g, probs, ws, grid, s);
-  else if (g.d == 128) launch_build_mfma_as<128, false, NS>(g, probs, ws, grid, s);
-  else if (g.cache) launch_build_mfma_as<64, true, NS>(g, probs, ws, grid, s);
-  else launch_build_mfma_as<64, false, NS>(g, probs, ws, grid, s);
+  if (g.d == 128 && g.cache) launch_build_mfma_as<true, NS>(g, probs, ws, grid, s);
+  else if (g.d == 128) launch_build_mfma_as<false, NS>(g, probs, ws, grid, s);
+  else if (g.cache) launch_build_mfma64<4, true>(g, probs, ws, grid, s);
+  else launch_build_mfma64<4, false>(g, probs, ws, grid, s);
 }
 
 template <typename T, int D>

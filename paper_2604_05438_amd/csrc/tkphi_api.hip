@@ -263,14 +263,18 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // least 2048 tokens so that the last, partly filled round of workgroups stays a small share.  The fp32-arithmetic
   // kernel spends 32 times the bf16 one's time on a token: there a workgroup takes as little as one tile of 64
   const bool f32_build = !g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE;
-  const int64_t bc_small = std::clamp<int64_t>(ceil_div(units, 512), f32_build && !compact ? 64 : 256, 2048);
+  // One problem at d = 64: one workgroup per CU (the wavefronts have no barrier to hide, and half the workgroups leave half the
+  // partials: 20K 17.2 -> 15.2 us, 32K 21.3 -> 20.0, 128K 51.7 -> 49.5; two and four per CU are better where sequences differ in length)
+  const bool one_per_cu = g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->d == 64 && n_problems == 1;
+  const int64_t bc_small = one_per_cu ? std::clamp<int64_t>(ceil_div(units, 256), 256, 4096)
+                                      : std::clamp<int64_t>(ceil_div(units, 512), f32_build && !compact ? 64 : 256, 2048);
   int bc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 2048), bc_small, 1 << 20), 64);
   if (!g->use_mfma) bc = std::min(bc, 4096);    // fp32 FMA chains stay short on the generic kernel
-  // Several resident rounds of the matrix-core kernel (512 workgroup slots at d = 128, 1024 at d = 64): among the
+  // Several resident rounds of the matrix-core kernel (512 workgroup slots): among the
   // chunk counts within two of that guess, the one whose last round is fullest (28 layers of 128K: 9 chunks per head
   // = 2016 workgroups = 3.94 rounds instead of 10 = 4.375, which pays for 5)
   if (g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->max_mid > 0) {
-    const int64_t slots = g->d == 64 ? 1024 : 512, heads = (int64_t)g->Hkv * std::max(n_problems, 1);
+    const int64_t slots = one_per_cu ? 256 : 512, heads = (int64_t)g->Hkv * std::max(n_problems, 1);
     const int64_t c0 = ceil_div(g->max_mid, bc);
     if (c0 * heads > slots) {
       double best_fill = -1.0;

@@ -1,0 +1,62 @@
+"""The bf16 matrix-core summary build at the edges of its tiles (32 tokens, dealt to the wavefronts of a workgroup in turn) and chunks, both
+head dimensions, with strides of its own and rows that lie apart."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2604_05438_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+MIDS = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 97, 127, 128, 129, 255, 257, 300, 383, 385, 1000]
+
+
+@pytest.mark.parametrize("cache", [False, True])
+@pytest.mark.parametrize("d,chunk", [(64, 0), (64, 64), (64, 192), (64, 512), (128, 0), (128, 64)])
+def test_build_bf16_edges(d, chunk, cache):
+    """S, u (and the cached features) against the float64 oracle.  A feature enters S as 16 bits (2^-17) and its exponent carries
+    |logit| 2^-23 of the fp32 products: 2e-5 of either, the bar of the other builds."""
+    import parity_utils as PU
+    from oracle import tkphi_oracle as orc
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=4, n_kv_heads=2, d_head=d, d_phi=d, seed=95)
+    layers = [I.make_layer(w, L=w.n_sink + w.n_tail + m, seq=i) for i, m in enumerate(MIDS)]
+    for sel in ([slice(0, len(MIDS))] if cache else [slice(0, len(MIDS)), slice(7, 8), slice(20, 21)]):
+        b = H.Batch(H.config_of(w, cache_features=cache, tuning={"build_chunk": chunk}), layers[sel], [1] * len(layers[sel]), debug=True)
+        b.build()
+        assert b.status() == 0
+        for i, P in enumerate(layers[sel]):
+            O = PU.oracle_inputs(P)
+            S, u = orc.build_summaries(O["K"], O["V"], O["Wk"], O["bk"], w.phi_in_scale, w.phi_norm_coef, w.n_sink, w.n_tail)
+            PU.check_summaries(b.result(i, "S"), b.result(i, "u"), S, u, 2e-5)
+            if cache:
+                _, M = orc.partition(int(P["L"]), w.n_sink, w.n_tail)
+                for h in range(w.n_kv_heads):
+                    F = orc.phi(O["K"][h, M], O["Wk"][h], O["bk"][h], w.phi_in_scale, w.phi_norm_coef)
+                    rel = np.abs(b.result(i, "phi_cache")[h].astype(np.float64) - F) / F
+                    assert rel.max() <= 2e-5, f"mid {MIDS[i]} head {h}: feature rel err {rel.max():.3e}"
+
+
+@pytest.mark.parametrize("c", [0.0, 0.05])
+def test_build_bf16_strided(c):
+    """Rows of three times their length (K and V interleaved with a third tensor, heads behind each other) give what contiguous
+    rows give, bit for bit, and a norm coefficient of 0 is no special case."""
+    import torch
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=2, n_kv_heads=2, d_head=64, d_phi=64, seed=96)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 701)
+    cfg = H.config_of(w)
+    cfg.phi_norm_coef = c
+    plain = H.Batch(cfg, [P], [1])
+    plain.build()
+    K, V = plain.dev[0]["K"], plain.dev[0]["V"]
+    big = torch.full((K.shape[0], K.shape[1], 3, 64), float("nan"), dtype=K.dtype, device="cuda")
+    big[:, :, 0], big[:, :, 2] = K, V
+    apart = H.Batch(cfg, [dict(P, K=big[:, :, 0], V=big[:, :, 2])], [1])
+    apart.build()
+    assert plain.status() == 0 and apart.status() == 0
+    for name in ("S", "u"):
+        x = plain.result(0, name)
+        assert np.isfinite(x).all() and np.array_equal(x, apart.result(0, name))
