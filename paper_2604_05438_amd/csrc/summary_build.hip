@@ -406,11 +406,14 @@ void build_mfma64_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* 
     floatx4 cn[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      float sq = 0.f;
+      float part[KS];                    // (a chain per half row, as short as its rounding is then small)
 #pragma unroll
-      for (int s = 0; s < KS; ++s)
+      for (int s = 0; s < KS; ++s) {
+        part[s] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sq = dot2_bf16(a[mt][s].u[e], a[mt][s].u[e], sq);
+        for (int e = 0; e < 4; ++e) part[s] = dot2_bf16(a[mt][s].u[e], a[mt][s].u[e], part[s]);
+      }
+      float sq = part[0] + part[1];
       asm volatile("s_nop 4" : "+v"(sq));     // (a dot product's result needs wait states before a matrix instruction reads it)
       cn[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(sq, c2, (floatx4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
     }
