@@ -257,4 +257,47 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
   }
 }
 
+// The same for a head whose partials are all in LDS, `parts` = [n_parts][2 D + 4], anchor tiles first, the retrieved tokens' last: thread
+// c < D takes value channel c (no barrier).  There are retrieved tokens and no indices to export.  pre_n: S_M^T phi_q of the channel.
+// The sums of merge_head, in its order.
+struct LocalMerge {
+  float* out;
+  float* aux;
+  int n_at;              // anchor tiles; 0: the head is not merged this way
+  int residual, sub;     // there is a residual branch; the retrieved tokens are subtracted from it
+  float pre_z;           // phi_q . u_M
+};
+template <int D>
+__device__ __forceinline__ void merge_head_local(const LocalMerge& lm, int n_parts, const float* parts, float pre_n, uint32_t* status, int gq) {
+  constexpr int PS = 2 * D + 4;
+  const int c = threadIdx.x;
+  float m = -INFINITY;
+  for (int k = 0; k < n_parts; ++k) m = fmaxf(m, parts[k * PS]);
+  if (!(m > -INFINITY)) m = 0.f;
+  float nu = 0.f, zv = 0.f, Z = 0.f, zsum = 0.f;
+  for (int k = 0; k < n_parts; ++k) {
+    const float* pp = parts + k * PS;
+    const float r = __expf(pp[0] - m);
+    Z = fmaf(r, pp[1], Z);
+    nu = fmaf(r, pp[4 + c], nu);
+    zsum += pp[2];
+    zv += pp[4 + D + c];
+  }
+  float nuR = 0.f, ZR = 0.f;
+  bool clamped = false;
+  if (lm.residual) {
+    nuR = pre_n; ZR = lm.pre_z;
+    if (lm.sub) { nuR -= zv; ZR -= zsum; }
+    if (!(ZR > 0.f)) { clamped = true; nuR = 0.f; ZR = 0.f; }
+  }
+  const float ms = fmaxf(m, 0.f), eE = __expf(m - ms), eR = __expf(-ms);
+  lm.out[(size_t)gq * D + c] = (eE * nu + eR * nuR) / (eE * Z + eR * ZR);
+  if (lm.aux) {
+    float* ax = lm.aux + (size_t)gq * TKPHI_AUX_STRIDE(D);
+    if (c == 0) { ax[0] = m; ax[1] = Z; ax[2] = ZR; ax[3] = clamped ? 1.f : 0.f; }
+    ax[4 + c] = nu; ax[4 + D + c] = nuR;
+  }
+  if (clamped && c == 0) atomicOr(status, TKPHI_DEV_CLAMPED);
+}
+
 }  // namespace tkphi

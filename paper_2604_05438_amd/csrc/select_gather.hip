@@ -41,6 +41,7 @@ namespace tkphi {
 
 constexpr int kBCap = 1024;            // boundary-bin candidates ranked in LDS
 constexpr int kSweepLoads = kSweepEntries / 2;
+constexpr int kLocalTiles = 6;         // anchor tiles of a head that its only workgroup merges out of LDS
 // winners gathered per round: 16-token tile t of a round goes to wavefront t mod 16.  Two tiles per wavefront at
 // d = 64 (one round for most heads of a batch of short sequences); at d = 128 the second tile's rows do not fit
 // the registers
@@ -87,16 +88,18 @@ __device__ __forceinline__ void rescan_head(const Geom& g, const tkphi_problem& 
 // The selecting and gathering work of workgroup (part, gq, p); returns early where there is nothing to retrieve
 // DIRECT: Geom::direct (a row of scores per head instead of candidate lists).  LIST: Geom::list (ends with the retrieved list of the head,
 // whose only workgroup this is).  KV: storage type of keys, values and Wk (fp32 only with DIRECT, d = 64)
-template <int D, int NTHR, bool DIRECT, bool LIST, typename KV>
-__device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
-                                                   int part, int gq, int p) {
+// True: the head is merged and its output written (a head's only workgroup, see below)
+template <int D, int NTHR, bool DIRECT, bool LIST, bool LOCAL, typename KV>
+__device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws,
+                                                   int part, int gq, int p, int mode) {
   constexpr int EPL = Elem<KV>::per16, KS = D * (int)sizeof(KV) / 64;        // elements of 16 bytes; 16-byte pieces of a key row per lane
   constexpr int WROW = wk_row_bytes(D, sizeof(KV));
   // select phase: histogram (8 KB) + boundary candidates (8 KB); gather phase: reduction scratch of the value sums
   __shared__ __attribute__((aligned(16))) char lds_a[16384];
   __shared__ __attribute__((aligned(16))) char wk_lds[D * WROW];
   constexpr int kDense = packed_candidates(D, NTHR), kWinLds = kWinLdsOf<NTHR>, NWV = NTHR / 64;
-  __shared__ uint2 dense[kDense];                   // the candidates of the head, packed (select phase)
+  __shared__ __attribute__((aligned(16))) uint2 dense[kDense];   // the candidates of the head, packed (select phase)
+  float* sh_parts = (float*)dense;                  // then [kLocalTiles + 1][2 D + 4], the partials of a head that is merged here
   __shared__ int w_tok[kWinLds];
   __shared__ float w_s[kWinLds];
   constexpr int kBatch = kBatchOf<D, NTHR, KV>;
@@ -108,6 +111,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   __shared__ int sh_bstar, sh_krem, sh_chi, sh_nb, sh_nbc;
   __shared__ uint32_t sh_total, sh_ovp;
   __shared__ float sh_m, sh_Z, sh_zs;
+  __shared__ LocalMerge sh_lm;
   uint32_t* sh_hist = (uint32_t*)lds_a;
   uint64_t* bcand = (uint64_t*)(lds_a + 8192);
   float* red = (float*)lds_a;                       // [16 wavefronts][2][128]
@@ -142,13 +146,13 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     }
   }
   const tkphi_problem pr = probs[p];
-  if (pr.L < 1 || pr.L > g.max_L) return;
+  if (pr.L < 1 || pr.L > g.max_L) return false;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int Ksel = max(0, min(min(pr.topk, n), g.max_K));
   SelPlan* plan = (SelPlan*)(blk + g.off_plan) + gq;
   if (Ksel == 0) {
     if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
-    return;
+    return false;
   }
   const int h = gq / g.G;
   const int n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
@@ -224,7 +228,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   if (total < (uint32_t)Ksel) {                     // cannot happen after a rescan (every mid token is a candidate)
     if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
     empty_partial();
-    return;
+    return false;
   }
   // Wk[h] for the gather phase: requested now (the first sweep has arrived, nothing else is in flight), stored
   // to LDS right before the gather (the barrier after the histogram pass orders LDS only, so it does not wait
@@ -233,6 +237,30 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   float bk_t = 0.f, pq_t = 0.f;
   if constexpr (!LIST) wkp.request(pr.Wk, h);
   if (!LIST && tid < D) { bk_t = pr.bk[(size_t)h * D + tid]; pq_t = ((const float*)(blk + g.off_phiq))[(size_t)gq * D + tid]; }
+
+  // A head's only workgroup merges it on the spot: its partial stays in LDS, and the anchors' partials and the summary terms, which an
+  // earlier launch left, are requested here, long before they are needed.  By way of memory, as from workgroup to workgroup, the
+  // merge of a short context was 3 us of 12.5 (two round trips at the end of the chain): 1B layer at 4K 19.4 -> 18.0 us per step, 3B layer at
+  // 2K 19.1 -> 17.8, one fp32 head of 4K 17.1 -> 15.9, 256 ragged sequences 2630 -> 2587.
+  // (what the end needs of the record waits in LDS: as scalars they would have to be spilled)
+  if (LOCAL && tid == 0) {
+    const int n_at = (g.n_sink + g.n_tail + min(max(pr.n_gen, 0), g.max_gen) + 63) / 64;
+    const bool local = !pr.topk_idx && n_at <= kLocalTiles;
+    const bool residual = mode != TKPHI_MODE_TOPK_ONLY && !(mode == TKPHI_MODE_SUB && Ksel == n);
+    sh_lm = LocalMerge{pr.out, pr.aux, local ? n_at : 0, residual ? 1 : 0, mode == TKPHI_MODE_SUB ? 1 : 0};
+  }
+  u32x4 anc;
+  float pre_n = 0.f, pre_z = 0.f;
+  auto request_local = [&]() {                      // (behind at least one barrier)
+    if constexpr (!LOCAL) return;
+    const int n_at = sh_lm.n_at;
+    if (4 * tid < n_at * (2 * D + 4))
+      anc = gload128((const float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + g.n_tiles) * (2 * D + 4) + 4 * tid);
+    if (n_at > 0 && tid < D) {
+      pre_n = ((const float*)(blk + g.off_sphi))[(size_t)gq * D + tid];
+      pre_z = ((const float*)(blk + g.off_uphi))[gq];
+    }
+  };
 
   // (have_e0 is false exactly after a rescan: those lists were written without a bound)
   const SelBins bin_of{edge0, have_e0 && edge0 != 0u && edge0 != 0xffffffffu};
@@ -337,9 +365,10 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     if (bstar < 0) {                                  // cannot happen: total >= Ksel
       if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
       empty_partial();
-      return;
+      return false;
     }
     TKPHI_PHASE(ws, 13);
+    request_local();
     // ---- thr: the K_rem-th best composite of the boundary bin -------------------------------------------------
     if (nb <= kBCap) {
       for (int idx = tid; idx < n_cand; idx += NTHR) {
@@ -439,9 +468,10 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     if (bstar < 0) {                                  // cannot happen: total >= Ksel
       if (tid == 0 && part == 0) *plan = SelPlan{-1, 0, 0, 0, 0};
       empty_partial();
-      return;
+      return false;
     }
     TKPHI_PHASE(ws, 13);
+    request_local();
 
     // ---- thr: the K_rem-th best composite of the boundary bin ------------------------------------------------
     if (nb <= kBCap) {
@@ -575,7 +605,7 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     }
   }
   TKPHI_PHASE(ws, 15);
-  if constexpr (LIST) return;
+  if constexpr (LIST) return false;
 
   // ---- gather: kBatch winners per round, one or two 16-token tiles per wavefront -----------------------------
   const int r = lane & 15, kg = lane >> 4;
@@ -588,6 +618,11 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
   float run_m = -INFINITY, run_Z = 0.f, run_zs = 0.f, run_nu = 0.f, run_zv = 0.f;   // (nu, zv: channel tid < D)
   wkp.commit(wk_lds);                               // (requested before the histogram pass: long since arrived)
   if (tid < D) { sh_bk[tid] = bk_t; sh_pq[tid] = pq_t; }
+  if constexpr (LOCAL) {
+    const int n_at = sh_lm.n_at;
+    if (4 * tid < n_at * (2 * D + 4)) *(u32x4*)(sh_parts + 4 * tid) = anc;
+    if (n_at > 0 && tid < D) { sh_parts[(kLocalTiles + 1) * (2 * D + 4) + tid] = pre_n; if (tid == 0) sh_lm.pre_z = pre_z; }
+  }
   __syncthreads();                                  // lds_a changes hands; the staged Wk is complete
   // (inside the loop the wavefronts exchange data through LDS only: its barriers leave the key and value loads in flight)
   // winner j of the round that starts at b0 (thread t < kBatch <-> winner b0 + t)
@@ -717,10 +752,19 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
     }
     lds_barrier();                                // red, b_w, b_z are rewritten by the next batch
   }
+  if (const int n_at = LOCAL ? sh_lm.n_at : 0) {
+    float* own = sh_parts + n_at * (2 * D + 4);
+    if (tid == 0) { own[0] = run_m; own[1] = run_Z; own[2] = run_zs; }
+    if (tid < D) { own[4 + tid] = run_nu; own[4 + D + tid] = run_zv; }
+    lds_barrier();
+    if (tid < D) merge_head_local<D>(sh_lm, n_at + 1, sh_parts, sh_parts[(kLocalTiles + 1) * (2 * D + 4) + tid], (uint32_t*)(ws + g.off_status), gq);
+    return true;
+  }
   // (GPU-coherent stores: the workgroup that merges the head may run on another XCD)
   if (tid == 0) { store_agent(partial, run_m); store_agent(partial + 1, run_Z); store_agent(partial + 2, run_zs); store_agent(partial + 3, (float)my_count); }
   if (tid < D) { store_agent(partial + 4 + tid, run_nu); store_agent(partial + 4 + D + tid, run_zv); }
   TKPHI_PHASE(ws, 16);
+  return false;
 }
 
 // grid (sg_split, Hq, n_problems).  After its own share every workgroup of a head counts itself in (its partial made
@@ -728,7 +772,8 @@ __device__ __forceinline__ void select_gather_body(const Geom& g, const tkphi_pr
 // with its first 256 threads: no separate merge launch.  The counters are cleared by a launch before this one in the
 // same call: the phi jobs of whichever launch carries them.  (The other wavefronts of that workgroup end before the merge's
 // barriers: a barrier waits only for the wavefronts of the workgroup that are still running.)
-template <int D, int NTHR, bool DIRECT, bool LIST = false, typename KV = uint16_t>
+// LOCAL: sg_split is 1
+template <int D, int NTHR, bool DIRECT, bool LIST, bool LOCAL, typename KV = uint16_t>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                     char* __restrict__ ws, int mode) {
   __shared__ int sh_last;
@@ -753,12 +798,15 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
       return;
     }
     const int gq = idx;
-    select_gather_body<D, NTHR, DIRECT, LIST, KV>(g, probs, ws, 0, gq, p);
+    select_gather_body<D, NTHR, DIRECT, LIST, LOCAL, KV>(g, probs, ws, 0, gq, p, mode);
     if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;     // (as below)
     return;
   } else {
   const int part = blockIdx.x, gq = blockIdx.y, p = blockIdx.z;
-  select_gather_body<D, NTHR, DIRECT, LIST, KV>(g, probs, ws, part, gq, p);
+  if (select_gather_body<D, NTHR, DIRECT, LIST, LOCAL, KV>(g, probs, ws, part, gq, p, mode)) {
+    if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;     // (as below)
+    return;
+  }
   const int L = probs[p].L;
   if (L < 1 || L > g.max_L) return;                 // (the merge writes nothing for such a problem either)
   // The partial went out with GPU-coherent stores and the merge reads the partials with GPU-coherent loads.  Every wavefront waits
@@ -791,13 +839,26 @@ void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, i
     grid = dim3(g.Hq + g.d_emb / 64 * g.Hq + (pack ? g.Hkv * std::max(1, 192 / g.Hkv) : 0));
   }
   const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SELECT, fn, grid, dim3(threads), 0, s, g, probs, ws, mode); };
+  // (the kernel of a head's only workgroup is one of its own: the scalars of its merge would be spilled in the other)
+  const bool direct = g.direct, local = g.sg_split == 1;
+#define TKPHI_SELECT(D, NTHR)                                                                                              \
+  do {                                                                                                                     \
+    if (direct && local) launch(select_gather_kernel<D, NTHR, true, false, true>, NTHR);                                   \
+    else if (direct) launch(select_gather_kernel<D, NTHR, true, false, false>, NTHR);                                      \
+    else if (local) launch(select_gather_kernel<D, NTHR, false, false, true>, NTHR);                                       \
+    else launch(select_gather_kernel<D, NTHR, false, false, false>, NTHR);                                                 \
+  } while (0)
   if (g.list) {
-    if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true, true>, 1024); else launch(select_gather_kernel<128, 1024, false, true>, 1024); }
-    else { if (g.direct) launch(select_gather_kernel<64, 1024, true, true>, 1024); else launch(select_gather_kernel<64, 1024, false, true>, 1024); }
-  } else if (g.dtype == TKPHI_F32) launch(select_gather_kernel<64, 1024, true, false, float>, 1024);
-  else if (g.d == 128) { if (g.direct) launch(select_gather_kernel<128, 1024, true>, 1024); else launch(select_gather_kernel<128, 1024, false>, 1024); }
-  else if (g.sg_threads == 512) { if (g.direct) launch(select_gather_kernel<64, 512, true>, 512); else launch(select_gather_kernel<64, 512, false>, 512); }
-  else { if (g.direct) launch(select_gather_kernel<64, 1024, true>, 1024); else launch(select_gather_kernel<64, 1024, false>, 1024); }
+    if (g.d == 128) { if (direct) launch(select_gather_kernel<128, 1024, true, true, false>, 1024); else launch(select_gather_kernel<128, 1024, false, true, false>, 1024); }
+    else { if (direct) launch(select_gather_kernel<64, 1024, true, true, false>, 1024); else launch(select_gather_kernel<64, 1024, false, true, false>, 1024); }
+  } else if (g.dtype == TKPHI_F32) {
+    if (local) launch(select_gather_kernel<64, 1024, true, false, true, float>, 1024);
+    else launch(select_gather_kernel<64, 1024, true, false, false, float>, 1024);
+  } else if (g.d == 128) TKPHI_SELECT(128, 1024);
+  else if (g.sg_threads == 1024) TKPHI_SELECT(64, 1024);
+  else if (direct) launch(select_gather_kernel<64, 512, true, false, true>, 512);        // (512 threads: sg_split is 1)
+  else launch(select_gather_kernel<64, 512, false, false, true>, 512);
+#undef TKPHI_SELECT
 }
 
 }  // namespace tkphi

@@ -230,13 +230,17 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   if (tn.scan_chunk > 0) sc = tn.scan_chunk;
   // Short contexts, as long as every token fits one sweep and the packed array of the select kernel: one unit per chunk, all
   // scores stored, no bound and no prep launch (1B layer at 4K 34.5 -> 22.6 us, at 10K 34.9 -> 24.6; 3B layer 34.6 -> 26.0 and 37.5 -> 31.8).  Few
-  // winners then, and what workgroups of a head hand each other costs more than a gather round: one per 64 of the budget
+  // winners then, and what workgroups of a head hand each other costs more than a gather round: one per 64 of the budget, and a single
+  // one, which merges its head out of LDS, up to 128 of a bf16 cache (1B layer at 4K 3 % 18.1 -> 16.7 us, at 12K 1 % 23.7 -> 23.1, 3B layer at
+  // 2K 4 % 19.6 -> 18.6, at 5K 2 % 22.0 -> 21.2; 170 of the 3B layer at 8.5K would lose: 25.0 -> 25.6, and 75 fp32 rows of four
+  // times the matrix instructions: 24.2 -> 24.8)
   g->sg_split = g->filtered ? g->list ? 1 : max_split : 0;
   g->direct = g->filtered && short_context ? 1 : 0;
   if (g->direct) {
     if (cfg->kv_dtype == TKPHI_F32) g->scan_unit = direct_unit_f32;
     sc = g->scan_unit;
-    g->sg_split = std::min(g->sg_split, std::max(1, (int)ceil_div(std::min(max_K, g->max_mid), 64)));
+    const int most_K = (int)std::min<int64_t>(max_K, g->max_mid), alone = cfg->kv_dtype == TKPHI_F32 ? 64 : 128;
+    g->sg_split = most_K <= alone ? 1 : std::min(g->sg_split, (int)ceil_div(most_K, 64));
   }
   g->scan_chunk = std::clamp((int)align_up((size_t)std::max(sc, 1), g->scan_unit), g->scan_unit, 32768);
   while (ceil_div(g->max_mid, g->scan_chunk) > kMaxScanChunks && g->scan_chunk < 32768) g->scan_chunk *= 2;

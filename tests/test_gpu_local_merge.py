@@ -1,0 +1,42 @@
+"""A head's only select workgroup merges it out of LDS; where retrieved indices are exported, or anchors fill more than six tiles of 64, the
+merge goes by way of the workspace.  Both add the same partials in the same order: outputs agree bit for bit."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2604_05438_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("dtype,d,mids,ks,tail,gen", [
+    ("bf16", 64, [700], [50], 60, 0), ("bf16", 128, [700], [58], 60, 3), ("f32", 64, [700], [58], 60, 3),     # one tile and the edge of a second
+    ("bf16", 64, [2000], [128], 317, 63), ("bf16", 64, [2000], [129], 317, 64),       # six tiles and one more; the edges of the split
+    ("bf16", 128, [1600, 13, 90], [128, 1, 0], 60, 0),                                  # no retrieved tokens in one problem
+    ("bf16", 64, [40000] * 9, [400] * 9, 60, 0), ("bf16", 128, [15000] * 12, [180] * 12, 60, 2)])      # lists, one workgroup per head
+def test_local_merge(dtype, d, mids, ks, tail, gen, mode):
+    import parity_utils as PU
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype=dtype, n_q_heads=32, n_kv_heads=8, d_head=d, d_phi=d, n_sink=4, n_tail=tail, seed=97)
+    layers = []
+    for i, m in enumerate(mids):
+        P = I.make_layer(w, L=4 + tail + m + gen, seq=i) if i < 3 else layers[i % 3]
+        P["L"], P["n_gen"] = 4 + tail + m, gen
+        layers.append(P)
+    plain = H.Batch(H.config_of(w, max_gen=gen), layers, ks, max_K=max(ks))
+    export = H.Batch(H.config_of(w, max_gen=gen), layers, ks, debug=True, max_K=max(ks))
+    for b in (plain, export):
+        b.build()
+        b.decode(mode)
+        b.decode(mode)                              # (the handed-over words are cleared as well)
+        torch.cuda.synchronize()
+        assert b.status() & ~2 == 0
+    for i in range(len(mids)):
+        y = plain.result(i, "out")
+        assert np.isfinite(y).all() and np.array_equal(y, export.result(i, "out")), i
+    if mode == 0 and max(mids) <= 2000:
+        for i, (P, k) in enumerate(zip(layers, ks)):
+            PU.check_layer(w, P, k, export, i, heads=[0, 31], sum_tol=2e-5)
