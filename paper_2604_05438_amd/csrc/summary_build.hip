@@ -22,6 +22,18 @@ union Frag {
   bf16x8 v;
 };
 
+// What the build kernels need of Geom: a launch that copies all of it (0.5 KB of arguments) costs the host 3.3 us, and the next launch
+// follows after 3.8, with 64 bytes 2.8 both (short builds are bound by that: two launches with 4 and 7 us of work).
+struct BuildGeom {
+  int Hkv, d, dphi, n_sink, n_tail, n_problems, max_L, max_gen, build_chunk, n_build_chunks, cache;
+  float a, c;
+  size_t off_status, off_bpart;
+  explicit BuildGeom(const Geom& g)
+      : Hkv(g.Hkv), d(g.d), dphi(g.dphi), n_sink(g.n_sink), n_tail(g.n_tail), n_problems(g.n_problems), max_L(g.max_L),
+        max_gen(g.max_gen), build_chunk(g.build_chunk), n_build_chunks(g.n_build_chunks), cache(g.cache), a(g.a), c(g.c),
+        off_status(g.off_status), off_bpart(g.off_bpart) {}
+};
+
 // ------------------------------------------------------------------------------------
 // bf16 on the matrix cores, d_head == d_phi == D = 128: grid (n_build_chunks, Hkv, n_problems), 4 wavefronts.
 // Wavefront w owns the features [w D/4, (w+1) D/4): its slice of Wk stays in registers for the whole chunk.
@@ -60,7 +72,7 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {   
 
 template <bool CACHE, int NS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
+void build_mfma_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   constexpr int D = 128, NW = 4;
   constexpr int KS = D / 32;            // k-steps of GEMM1 (over channels)
   constexpr int FT = D / (16 * NW);     // feature tiles per wavefront
@@ -294,7 +306,7 @@ void build_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __
 // ------------------------------------------------------------------------------------
 template <int NW, bool CACHE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void build_mfma64_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
+void build_mfma64_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   constexpr int D = 64, KS = 2, FT = 4, CT = 4, TT = 32, ROWB = 128, TILEB = TT * ROWB, NLD = 4, STAGE = 2 * TILEB;
   extern __shared__ __attribute__((aligned(1024))) char ring[];   // [NW][2][keys, values][TT][ROWB], then Wk [D][ROWB], bias [D]
   const int ch = blockIdx.x, h = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
@@ -535,7 +547,7 @@ void build_mfma64_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* 
 // (16 workgroups); this one, 63 chunks of 64 tokens, 8.5 us, and the call 328 -> 11.4 us.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int FTW>
-__global__ __launch_bounds__(kThreads) void build_f32_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+__global__ __launch_bounds__(kThreads) void build_f32_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs,
                                                              char* __restrict__ ws) {
   constexpr int TT = 64, ROWF = D + 4, EPL = Elem<T>::per16, SEGS = D / EPL, NLD = TT * SEGS / kThreads;
   constexpr int CT = D / 16;
@@ -705,7 +717,7 @@ __global__ __launch_bounds__(kThreads) void build_f32_kernel(Geom g, const tkphi
 // What bounds it at one problem is a chain of round trips (arguments, problem record, partials, result): so the record's pointers
 // are asked for with the length, and the first partials of a single problem before the length is there (its chunks nearly always
 // fill the bounds; what lies behind them is not added): one fp32 head of 4K tokens 12.3 -> 11.4 us per call.
-__global__ __launch_bounds__(kThreads) void build_reduce_kernel(Geom g, const tkphi_problem* __restrict__ probs,
+__global__ __launch_bounds__(kThreads) void build_reduce_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs,
                                                                 char* __restrict__ ws) {
   __shared__ float4 sh[4][64];
   const int h = blockIdx.y, p = blockIdx.z;
@@ -759,14 +771,14 @@ static void launch_build_mfma_as(const Geom& g, const tkphi_problem* probs, char
   const size_t lds = (size_t)NS * (2 * 32 * 128 * 2 + 32 * 4);
   const hipError_t e = hipFuncSetAttribute((const void*)build_mfma_kernel<CACHE, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
-  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma_kernel<CACHE, NS>), grid, dim3(256), lds, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma_kernel<CACHE, NS>), grid, dim3(256), lds, s, BuildGeom(g), probs, ws);
 }
 template <int NW, bool CACHE>
 static void launch_build_mfma64(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
   constexpr size_t lds = NW * 16384 + 64 * 128 + 64 * 4;
   const hipError_t e = hipFuncSetAttribute((const void*)build_mfma64_kernel<NW, CACHE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
-  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma64_kernel<NW, CACHE>), grid, dim3(64 * NW), lds, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_UNTIMED, (build_mfma64_kernel<NW, CACHE>), grid, dim3(64 * NW), lds, s, BuildGeom(g), probs, ws);
 }
 static void launch_build_mfma(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
   constexpr int NS = 4;                  // ring stages: three tiles on their way while one is contracted
@@ -785,7 +797,7 @@ static void launch_build_f32_d(const Geom& g, const tkphi_problem* probs, char* 
     const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
   }
-  TKPHI_LAUNCH(ST_UNTIMED, fn, grid, dim3(kThreads), lds, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_UNTIMED, fn, grid, dim3(kThreads), lds, s, BuildGeom(g), probs, ws);
 }
 template <typename T>
 static void launch_build_f32(const Geom& g, const tkphi_problem* probs, char* ws, dim3 grid, hipStream_t s) {
@@ -808,7 +820,7 @@ void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream
   }
   const int per4 = g.dphi * (g.d + 1) / 4;
   dim3 rgrid((per4 + 63) / 64 + 1, g.Hkv, g.n_problems);
-  TKPHI_LAUNCH(ST_UNTIMED, build_reduce_kernel, rgrid, dim3(kThreads), 0, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_UNTIMED, build_reduce_kernel, rgrid, dim3(kThreads), 0, s, BuildGeom(g), probs, ws);
 }
 
 }  // namespace tkphi

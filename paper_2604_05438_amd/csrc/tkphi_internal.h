@@ -376,7 +376,8 @@ __device__ __forceinline__ float gelu_erf(float x) {
 
 // device status word: recomputed from the problem lengths by one workgroup per call (decode also
 // checks the generated-token counts, which the build does not read)
-__device__ __forceinline__ void write_device_status(const Geom& g, const tkphi_problem* probs, char* ws, bool check_gen) {
+template <typename G>   // Geom or what a kernel is handed of it
+__device__ __forceinline__ void write_device_status(const G& g, const tkphi_problem* probs, char* ws, bool check_gen) {
   int bad = 0;
   for (int i = threadIdx.x; i < g.n_problems; i += blockDim.x) {
     const int Li = probs[i].L, gi = probs[i].n_gen;
