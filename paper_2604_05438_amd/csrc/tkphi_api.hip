@@ -342,6 +342,10 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   g->off_selphi = p;  p = align_up(p + (g->sel_feat ? (size_t)g->Hq * std::max(max_K, 1) * g->dphi * sizeof(float) : (size_t)0), 256);
   g->off_part = p;
   p = align_up(p + (size_t)g->Hq * (std::max(g->n_tiles, g->filtered ? max_split : 0) + g->n_atiles) * g->part_stride * sizeof(float), 256);
+  if (p >> 40) {                       // (WsOffset; no GPU holds it)
+    set_error("scratch of one problem beyond 1 TB (max_L=%d max_K=%d)", max_L, max_K);
+    return TKPHI_ESHAPE;
+  }
   g->per_problem = p;
   const size_t decode_total = g->off_problem0 + (size_t)std::max(n_problems, 1) * g->per_problem;
   size_t decode_all = decode_total;

@@ -35,6 +35,14 @@ constexpr int kPairsPerWG = 64;        // gather: retrieved tokens per workgroup
 constexpr int direct_unit_f32 = 128;     // Geom::scan_unit of fp32 caches where Geom::direct
 constexpr int keep_unit(int d) { return d == 128 ? 64 : 128; }   // Geom::scan_unit where Geom::fused
 
+// An offset inside a problem's block (less than 1 TB), in 32 bits as 256-byte units: a launch copies its Geom, and every cache line of
+// arguments is one more that its first instructions wait for (0.1 to 0.2 us of a short decode step).
+struct WsOffset {
+  uint32_t units;
+  WsOffset& operator=(size_t bytes) { units = (uint32_t)(bytes >> 8); return *this; }
+  __host__ __device__ operator size_t() const { return (size_t)units << 8; }
+};
+
 struct Geom {
   int Hq, Hkv, G, d, dphi, n_sink, n_tail, dtype;
   int use_mfma;          // bf16 storage with d_phi == d_head: matrix-core kernels
@@ -72,39 +80,39 @@ struct Geom {
   int part_stride;       // floats per partial: 2*d + 4
   float score_scale, a, c;
   // byte offsets inside the workspace
-  size_t off_status;     // uint32 device status word
-  size_t off_problem0;   // first per-problem block
-  size_t per_problem;    // bytes per problem block
+  WsOffset off_status;     // uint32 device status word
+  WsOffset off_problem0;   // first per-problem block
+  WsOffset per_problem;    // bytes per problem block
   // offsets inside a per-problem block
-  size_t off_scores;     // float    [Hq][mid_stride]            mid-region scores (spill pipeline, Geom::direct)
-  size_t off_candf;      // uint2    [Hq][n_scan_chunks][4][scan_chunk/4]  candidate lists (score bits, mid index) of the filtered
+  WsOffset off_scores;     // float    [Hq][mid_stride]            mid-region scores (spill pipeline, Geom::direct)
+  WsOffset off_candf;      // uint2    [Hq][n_scan_chunks][4][scan_chunk/4]  candidate lists (score bits, mid index) of the filtered
                          //                                       pipeline at full capacity (entries past the first cand_T of a
                          //                                       list land here); shares its memory with off_scores
-  size_t off_candc;      // uint2    [Hq][n_scan_chunks][4][cand_T]  the first cand_T entries of every list
-  size_t off_ccount;     // uint32   [Hq][n_scan_chunks][4]      lengths of the candidate lists
-  size_t off_resf, off_resc, off_rescount;  // the rescan set: a second candf / candc / ccount, written when the select kernel
+  WsOffset off_candc;      // uint2    [Hq][n_scan_chunks][4][cand_T]  the first cand_T entries of every list
+  WsOffset off_ccount;     // uint32   [Hq][n_scan_chunks][4]      lengths of the candidate lists
+  WsOffset off_resf, off_resc, off_rescount;  // the rescan set: a second candf / candc / ccount, written when the select kernel
                          //                                       rescans a head without a bound, read by its second attempt; the
                          //                                       first set itself where one workgroup takes a head (sg_split 1)
-  size_t off_thr;        // uint32   [Hq]                        lower bound of the score key per query head
-  size_t off_hand;       // uint64   [Hq]                        fused: (tag, bound) of a head, handed from its sample workgroup to the
+  WsOffset off_thr;        // uint32   [Hq]                        lower bound of the score key per query head
+  WsOffset off_hand;       // uint64   [Hq]                        fused: (tag, bound) of a head, handed from its sample workgroup to the
                          //                                       score workgroups of the running launch (shares off_hist's memory)
-  size_t off_mcount;     // uint32   [Hq]                        filtered pipeline: workgroups of the fused select + gather kernel
+  WsOffset off_mcount;     // uint32   [Hq]                        filtered pipeline: workgroups of the fused select + gather kernel
                          //                                       that have finished their share of the head (cleared by the phi jobs)
-  size_t off_sphi;       // float    [Hq][d]                     S_M^T phi_q
-  size_t off_uphi;       // float    [Hq]                        phi_q . u_M
-  size_t off_hist;       // uint16   [n_scan_chunks][Hq][kBins]  per-chunk histograms
-  size_t off_plan;       // SelPlan  [Hq]
-  size_t off_diag;       // float    [n_scan_chunks][Hq][4]      per-chunk (max, sum exp, sum (s-max) exp) of the scores
-  size_t off_chunkoff;   // int32    [Hq][n_scan_chunks][2]      output offsets of each chunk (above b*, in b*)
-  size_t off_cand;       // uint2    [Hq][kCandCap]              boundary-bin candidates (key, mid index)
-  size_t off_selidx;     // int32    [Hq][max_K]                 retrieved mid indices
-  size_t off_selscore;   // float    [Hq][max_K]                 their scores
-  size_t off_phiq;       // float    [Hq][dphi]
-  size_t off_mlpq;       // float    [Hq][2][d_emb]                  MLP phi_q: stem / residual stream g, hidden h
-  size_t off_selphi;     // float    [Hq][max_K][d_phi]              MLP maps without a feature cache: phi_k of the retrieved keys,
+  WsOffset off_sphi;       // float    [Hq][d]                     S_M^T phi_q
+  WsOffset off_uphi;       // float    [Hq]                        phi_q . u_M
+  WsOffset off_hist;       // uint16   [n_scan_chunks][Hq][kBins]  per-chunk histograms
+  WsOffset off_plan;       // SelPlan  [Hq]
+  WsOffset off_diag;       // float    [n_scan_chunks][Hq][4]      per-chunk (max, sum exp, sum (s-max) exp) of the scores
+  WsOffset off_chunkoff;   // int32    [Hq][n_scan_chunks][2]      output offsets of each chunk (above b*, in b*)
+  WsOffset off_cand;       // uint2    [Hq][kCandCap]              boundary-bin candidates (key, mid index)
+  WsOffset off_selidx;     // int32    [Hq][max_K]                 retrieved mid indices
+  WsOffset off_selscore;   // float    [Hq][max_K]                 their scores
+  WsOffset off_phiq;       // float    [Hq][dphi]
+  WsOffset off_mlpq;       // float    [Hq][2][d_emb]                  MLP phi_q: stem / residual stream g, hidden h
+  WsOffset off_selphi;     // float    [Hq][max_K][d_phi]              MLP maps without a feature cache: phi_k of the retrieved keys,
                          //                                       in the order of the retrieved list
-  size_t off_part;       // float    [Hq][n_tiles + n_atiles][part_stride]  (retrieved tiles, then anchor tiles)
-  size_t off_bpart;      // float    [Hkv][n_build_chunks][dphi*(d+1)]   (build only; aliases the block)
+  WsOffset off_part;       // float    [Hq][n_tiles + n_atiles][part_stride]  (retrieved tiles, then anchor tiles)
+  WsOffset off_bpart;      // float    [Hkv][n_build_chunks][dphi*(d+1)]   (build only; aliases the block)
   size_t off_act;        // float    2 x [Hkv][mlp_block][d_emb]          (layer-wise MLP build only: activations g, h of a token block)
   size_t off_wpack;      // bf16     [mlp_group][Hkv][Ws | W1 | W2 | Wo]  (MLP maps: a group's key-side weights in MFMA-fragment order)
   size_t off_feat;       // float    [mlp_group][Hkv][max_mid][d_phi]     (MLP build without a feature cache: a group's key features)
