@@ -156,8 +156,51 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
   if (tid < d) { part[4 + tid] = a_acc[4 + tid]; part[4 + d + tid] = 0.f; }
 }
 
+// ---- summary terms: S_M^T phi_q and phi_q . u_M of a query head -> off_sphi, off_uphi ----------------------------------
+// One workgroup per head of the gather launches, beside its tiles: at the head of the merge, whose few workgroups wait for 64 KB of S
+// at d = 128, they took 4 of its 9.8 us.  Sums in a fixed order: features of a group in order, groups in order.  red: 1536 floats
+__device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* red) {
+  const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
+  float* sh_phiq = red + 1024;
+  float* pu = red + 1280;
+  const int QPR = d / 4, NG = kThreads / QPR;      // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
+  const int jg = tid / QPR, c4 = tid % QPR, per = (dphi + NG - 1) / NG, j0 = jg * per, j1 = min(dphi, j0 + per);
+  const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
+  constexpr int MAXF = kMaxDim / 8;                // features of a group (all rows of S are requested together)
+  u32x4 sv[MAXF];
+#pragma unroll
+  for (int k = 0; k < MAXF; ++k)
+    if (j0 + k < j1) sv[k] = gload128(S + (size_t)(j0 + k) * d + c4 * 4);
+  if (tid < dphi) {                                // (d_phi <= kMaxDim = the threads)
+    const float pq = ((const float*)(blk + g.off_phiq))[(size_t)gq * dphi + tid];
+    sh_phiq[tid] = pq;
+    pu[tid] = pq * pr.u[(size_t)h * dphi + tid];
+  }
+  __syncthreads();
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int k = 0; k < MAXF; ++k) {
+    if (j0 + k < j1) {
+      const float pj = sh_phiq[j0 + k];
+      a.x = fmaf(pj, __uint_as_float(sv[k].x), a.x); a.y = fmaf(pj, __uint_as_float(sv[k].y), a.y);
+      a.z = fmaf(pj, __uint_as_float(sv[k].z), a.z); a.w = fmaf(pj, __uint_as_float(sv[k].w), a.w);
+    }
+  }
+  *(float4*)(red + jg * d + c4 * 4) = a;           // (NG d = 1024 floats)
+  __syncthreads();
+  if (tid < d) {
+    float x = 0.f;
+    for (int k = 0; k < NG; ++k) x += red[k * d + tid];
+    ((float*)(blk + g.off_sphi))[(size_t)gq * d + tid] = x;
+  } else if (tid == kThreads - 64) {
+    float x = 0.f;
+    for (int j = 0; j < dphi; ++j) x += pu[j];     // feature order
+    ((float*)(blk + g.off_uphi))[gq] = x;
+  }
+}
+
 // ------------------------------------------------------------------------------------
-// gather, bf16 on the matrix cores: grid (n_tiles + n_atiles, Hq, n_problems); D == d_head == d_phi.
+// gather, bf16 on the matrix cores: grid (n_tiles + n_atiles + 1, Hq, n_problems); D == d_head == d_phi.
 // Wavefront w owns 16 retrieved tokens: their key rows are the A operand (lane (r, kg): token
 // r, 8 consecutive channels per k-step), Wk of the KV head is staged once per workgroup in
 // LDS (rows padded by 16 B: conflict-free ds_read_b128) and provides the B operand per
@@ -185,6 +228,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
+  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<uint16_t>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
@@ -267,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   constexpr int EPL = Elem<T>::per16;
   constexpr int KFS = 128 + 4;                     // padded row stride (d <= 128): conflict-free 16-byte reads
   __shared__ __attribute__((aligned(16))) float kf[kPairsPerWG * KFS];
-  __shared__ float red[2 * kThreads * 8];
+  __shared__ __attribute__((aligned(16))) float red[2 * kThreads * 8];
   __shared__ int p_tok[kPairsPerWG];
   __shared__ float p_s[kPairsPerWG], p_w[kPairsPerWG], p_z[kPairsPerWG];
   __shared__ float acc_part[2 * 128 + 4];
@@ -278,6 +322,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
+  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
@@ -402,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                  char* __restrict__ ws) {
-  __shared__ float red[2 * kThreads * 8];
+  __shared__ __attribute__((aligned(16))) float red[2 * kThreads * 8];
   __shared__ int p_tok[kPairsPerWG];
   __shared__ float p_s[kPairsPerWG], p_w[kPairsPerWG], p_z[kPairsPerWG];
   __shared__ float acc_part[2 * 128 + 4];
@@ -413,6 +458,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
+  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
@@ -483,14 +529,13 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
 // ------------------------------------------------------------------------------------
 // merge: grid (Hq, n_problems); see merge_head.h
 // ------------------------------------------------------------------------------------
-template <bool PRE>
 __global__ __launch_bounds__(kThreads) void merge_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                          char* __restrict__ ws, int mode) {
-  merge_head<PRE>(g, probs, ws, (int)blockIdx.x, (int)blockIdx.y, mode);
+  merge_head<true, false>(g, probs, ws, (int)blockIdx.x, (int)blockIdx.y, mode);
 }
 
 void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(g.n_tiles + g.n_atiles, g.Hq, g.n_problems);
+  dim3 grid(g.n_tiles + g.n_atiles + 1, g.Hq, g.n_problems);
   if (g.cache || g.sel_feat) {
     if (g.dtype == TKPHI_BF16) TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws);
     else TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws);
@@ -504,10 +549,8 @@ void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStrea
   }
 }
 
-void launch_merge(const Geom& g, const tkphi_problem* probs, char* ws, int mode, bool pre, hipStream_t s) {
-  dim3 grid(g.Hq, g.n_problems);
-  if (pre) TKPHI_LAUNCH(ST_MERGE, merge_kernel<true>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
-  else TKPHI_LAUNCH(ST_MERGE, merge_kernel<false>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
+void launch_merge(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
+  TKPHI_LAUNCH(ST_MERGE, merge_kernel, dim3(g.Hq, g.n_problems), dim3(kThreads), 0, s, g, probs, ws, mode);
 }
 
 }  // namespace tkphi

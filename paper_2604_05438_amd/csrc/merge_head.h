@@ -12,24 +12,24 @@
 
 namespace tkphi {
 
-// COHERENT: the retrieved-token partials were written (store_agent) by other workgroups of the running launch
-template <bool PRE, bool COHERENT = false>   // PRE: S_M^T phi_q and phi_q . u_M come from the prep kernel (workspace), not from S, u
+// TILES: a partial per 64 retrieved tokens (gather kernels), else one per workgroup of the fused select + gather kernel.
+// COHERENT: they were written (store_agent) by other workgroups of the running launch.  S_M^T phi_q and phi_q . u_M are in the workspace
+// (off_sphi, off_uphi)
+template <bool TILES, bool COHERENT>
 __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws, int gq,
                                            int p, int mode) {
   __shared__ float red_f[4];
-  __shared__ float sh_phiq[kMaxDim], sh_u[kMaxDim];
-  __shared__ float sh_grp[9][128];                 // [feature group][value channel]; row 8: scalars of the partial combine
+  __shared__ float sh_grp[9][128];                 // sums of the thread groups; row 8: scalars
   const int tid = threadIdx.x;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int Ksel = max(0, min(min(pr.topk, n), g.max_K));
   const int n_anchor = (n > 0 ? g.n_sink + g.n_tail : pr.L) + min(max(pr.n_gen, 0), g.max_gen);   // anchors + generated tokens
-  // partials holding retrieved tokens: tiles of 64, or (PRE) one per workgroup of the fused select + gather kernel
-  const int n_used = PRE ? (Ksel > 0 ? g.n_tiles : 0) : (Ksel + kPairsPerWG - 1) / kPairsPerWG;
+  // partials holding retrieved tokens
+  const int n_used = TILES ? (Ksel + kPairsPerWG - 1) / kPairsPerWG : (Ksel > 0 ? g.n_tiles : 0);
   const int na_used = (n_anchor + 63) / 64;                      // tiles holding anchors
-  const int d = g.d, dphi = g.dphi;
-  const int h = gq / g.G;
+  const int d = g.d;
   char* blk = problem_block(g, ws, p);
   const float* part0 = (const float*)(blk + g.off_part) + (size_t)gq * (g.n_tiles + g.n_atiles) * g.part_stride;
   const bool use_res = mode != TKPHI_MODE_TOPK_ONLY && n > 0 && !(mode == TKPHI_MODE_SUB && Ksel == n);
@@ -38,36 +38,11 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
   auto ldp = [](const float* q) { return COHERENT ? load_agent(q) : *q; };
   auto part_ptr = [&](int k) { return part0 + (size_t)(k < na_used ? g.n_tiles + k : k - na_used) * g.part_stride; };
 
-  // ---- residual branch: S^T phi_q and u . phi_q, all loads of S issued together --------------
-  // thread (jg = tid / (d/4), c4 = tid % (d/4)) takes the features of group jg for 4 value channels
-  float4 sacc = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int QPR = d / 4, NG = kThreads / QPR;      // float4 per row; feature groups (8 for d=128, 16 for d=64)
-  const int jg = tid / QPR, c4 = tid % QPR;
+  // ---- residual branch: what an earlier launch left of S and u ---------------------------------
   float pre_n = 0.f, pre_z = 0.f;
-  if (PRE && use_res) {
+  if (use_res) {
     pre_z = ((const float*)(blk + g.off_uphi))[gq];
     if (tid < d) pre_n = ((const float*)(blk + g.off_sphi))[(size_t)gq * d + tid];
-  }
-  if (!PRE && use_res) {
-    const float* phiq = (const float*)(blk + g.off_phiq) + (size_t)gq * dphi;
-    for (int j = tid; j < dphi; j += kThreads) { sh_phiq[j] = phiq[j]; sh_u[j] = pr.u[(size_t)h * dphi + j]; }
-    const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
-    const int per = (dphi + NG - 1) / NG;          // features per group (<= 32)
-    const int j0 = jg * per, j1 = min(dphi, j0 + per);
-    constexpr int MAXF = 32;
-    float4 sv[MAXF];
-#pragma unroll
-    for (int k = 0; k < MAXF; ++k)
-      if (j0 + k < j1) sv[k] = *(const float4*)(S + (size_t)(j0 + k) * d + c4 * 4);
-    __syncthreads();                               // phi_q staged
-#pragma unroll
-    for (int k = 0; k < MAXF; ++k) {
-      if (j0 + k < j1) {
-        const float pj = sh_phiq[j0 + k];
-        sacc.x = fmaf(pj, sv[k].x, sacc.x); sacc.y = fmaf(pj, sv[k].y, sacc.y);
-        sacc.z = fmaf(pj, sv[k].z, sacc.z); sacc.w = fmaf(pj, sv[k].w, sacc.w);
-      }
-    }
   }
 
   // ---- shift m = max over the exact support (all partial headers) ------------------------------
@@ -123,7 +98,7 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
     }
   }
   if (!few) {
-    // sh_grp is free until the residual sums below: [0] nu, [1] zv per (group, channel); [2] Z, zsum, ZA per group
+    // [0] nu, [1] zv per (group, channel); [2] Z, zsum, ZA per group
     float* cmb = &sh_grp[0][0];
     __syncthreads();
     cmb[grp * 128 + c] = nu;
@@ -135,39 +110,13 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
       nu += cmb[q * 128 + c]; zv += cmb[512 + q * 128 + c];
       Z += cmb[1024 + q * 4 + 0]; zsum += cmb[1024 + q * 4 + 1]; ZA += cmb[1024 + q * 4 + 2];
     }
-    __syncthreads();                               // before sh_grp is reused
   }
 
   // (with every mid token retrieved in SUB mode the residual set is empty: exactly zero)
   float nuR = 0.f, ZR = 0.f;
   bool clamped = false;
-  if (PRE && use_res) {
+  if (use_res) {
     float accn = pre_n, accz = pre_z;
-    if (mode == TKPHI_MODE_SUB) { accn -= zv; accz -= zsum; }
-    nuR = accn; ZR = accz;
-    if (!(ZR > 0.f)) {                     // numerical clamp: drop the residual branch
-      clamped = true;
-      nuR = 0.f; ZR = 0.f;
-    }
-  }
-  if (!PRE && use_res) {
-    // fixed-order sum over the feature groups
-    float* row = &sh_grp[0][0];
-    if (jg < 8) { row[jg * 128 + c4 * 4 + 0] = sacc.x; row[jg * 128 + c4 * 4 + 1] = sacc.y;
-                  row[jg * 128 + c4 * 4 + 2] = sacc.z; row[jg * 128 + c4 * 4 + 3] = sacc.w; }
-    __syncthreads();
-    if (jg >= 8) {                                 // d = 64: groups 8..15 add onto groups 0..7
-      row[(jg - 8) * 128 + 64 + c4 * 4 + 0] = sacc.x; row[(jg - 8) * 128 + 64 + c4 * 4 + 1] = sacc.y;
-      row[(jg - 8) * 128 + 64 + c4 * 4 + 2] = sacc.z; row[(jg - 8) * 128 + 64 + c4 * 4 + 3] = sacc.w;
-    }
-    float accz = 0.f;
-    for (int j = 0; j < dphi; ++j) accz = fmaf(sh_phiq[j], sh_u[j], accz);
-    __syncthreads();
-    float accn = 0.f;
-    if (c < d) {
-      for (int k = 0; k < 8; ++k) accn += row[k * 128 + c];
-      if (NG == 16) for (int k = 0; k < 8; ++k) accn += row[k * 128 + 64 + c];
-    }
     if (mode == TKPHI_MODE_SUB) { accn -= zv; accz -= zsum; }
     nuR = accn; ZR = accz;
     if (!(ZR > 0.f)) {                     // numerical clamp: drop the residual branch

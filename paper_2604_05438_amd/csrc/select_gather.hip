@@ -828,7 +828,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
   if (exports) __threadfence();
   // (the handed-over bound has been read: a replay of this call from a graph, whose tag is the same, must not find it)
   if (!DIRECT && g.fused && threadIdx.x == 0) ((uint64_t*)(problem_block(g, ws, p) + g.off_hand))[gq] = 0ull;
-  merge_head<true, true>(g, probs, ws, gq, p, mode);
+  merge_head<false, true>(g, probs, ws, gq, p, mode);
   }
 }
 

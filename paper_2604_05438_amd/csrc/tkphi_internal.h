@@ -164,8 +164,7 @@ void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hi
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);  // includes the merge
 void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
-// `pre`: the prep kernel has already produced the anchor partials and the summary terms S_M^T phi_q, phi_q . u_M
-void launch_merge(const Geom& g, const tkphi_problem* probs, char* ws, int mode, bool pre, hipStream_t s);
+void launch_merge(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);
 void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_mlp_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);        // key features + chunk partials
 void launch_mlp_sel_features(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);  // -> off_selphi
