@@ -270,8 +270,14 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // One problem at d = 64: one workgroup per CU (the wavefronts have no barrier to hide, and half the workgroups leave half the
   // partials: 20K 17.2 -> 15.2 us, 32K 21.3 -> 20.0, 128K 51.7 -> 49.5; two and four per CU are better where sequences differ in length)
   const bool one_per_cu = g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->d == 64 && n_problems == 1;
-  const int64_t bc_small = one_per_cu ? std::clamp<int64_t>(ceil_div(units, 256), 256, 4096)
-                                      : std::clamp<int64_t>(ceil_div(units, 512), f32_build && !compact ? 64 : 256, 2048);
+  // Short layers at d = 128 too, as long as its tiles of four wavefronts (0.9 us each) weigh more than its partials of 66 KB: chunks from 64
+  // up to 384, one workgroup per CU (1.5K tokens 17.3 -> 12.8 us, 3K 18.3 -> 15.1, 6K 19.3 -> 18.0, 9K 25.3 -> 21.6, 12K 28.0 -> 24.4; 16K in
+  // chunks of 384 33.1 against 32.7 with two per CU)
+  const bool short_layer = g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->d == 128 && !compact;
+  const int64_t per_cu = ceil_div(units, 256), two_per_cu = ceil_div(units, 512);
+  const int64_t bc_small = one_per_cu ? std::clamp<int64_t>(per_cu, 256, 4096)
+                           : short_layer ? (per_cu <= 384 ? std::max<int64_t>(per_cu, 64) : std::clamp<int64_t>(two_per_cu, 256, 2048))
+                                         : std::clamp<int64_t>(two_per_cu, f32_build && !compact ? 64 : 256, 2048);
   int bc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 2048), bc_small, 1 << 20), 64);
   if (!g->use_mfma) bc = std::min(bc, 4096);    // fp32 FMA chains stay short on the generic kernel
   // Several resident rounds of the matrix-core kernel (512 workgroup slots): among the
@@ -523,7 +529,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
     launch_score_mid(g, problems, ws, s);
     launch_select(g, problems, ws, s);
     launch_gather(g, problems, ws, s);
-    launch_merge(g, problems, ws, acct, false, s);
+    launch_merge(g, problems, ws, acct, s);
     return TKPHI_OK;
   }
   std::lock_guard<std::mutex> lock(g_side_mutex);
@@ -535,7 +541,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
     launch_mlp_phi_q(g, problems, ws, s);
     if (g.sel_feat) launch_mlp_sel_features(g, problems, ws, s);    // no feature cache: phi_k of the retrieved keys
     launch_gather(g, problems, ws, s);
-    launch_merge(g, problems, ws, acct, false, s);
+    launch_merge(g, problems, ws, acct, s);
     return TKPHI_OK;
   }
   st = hip_ok(hipEventRecord(ss->fork, s), "hipEventRecord");
@@ -551,7 +557,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
   if (st != TKPHI_OK) return st;
   if (st2 != TKPHI_OK) return st2;
   launch_gather(g, problems, ws, s);
-  launch_merge(g, problems, ws, acct, false, s);
+  launch_merge(g, problems, ws, acct, s);
   return TKPHI_OK;
 }
 
