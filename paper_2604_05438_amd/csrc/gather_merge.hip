@@ -31,27 +31,29 @@ typedef GatherFrag Frag;
 // nu[c] = sum_i w[i] v_i[c], zv[c] = sum_i z[i] v_i[c] over `cnt` <= 64 rows given by tok[]
 // (absolute token indices), rows of d elements.  Each row is read by LPR = d / (elements per
 // 16 bytes) lanes with one 16-byte load; 256 threads cover 256 / LPR rows per pass and all
-// passes' loads are issued together.  Results land in part[4 .. 4+d) and part[4+d .. 4+2d).
+// passes' loads are issued together, as soon as the tokens are known: the rows arrive beside the keys or features that the
+// weights are worked out from.  Results land in part[4 .. 4+d) and part[4+d .. 4+2d).
 // LDS scratch `red` must hold 2 * 256 * 8 floats.
 template <typename T>
-__device__ __forceinline__ void weighted_value_sums(const Geom& g, const tkphi_problem& pr, int64_t head_off,
-                                                    const int* tok, const float* w, const float* z, int cnt,
+struct ValueRows {
+  static constexpr int EPL = Elem<T>::per16, MAXP = 8;   // 64 rows / (256 / 32 lanes) passes at most
+  u32x4 v[MAXP];
+  __device__ __forceinline__ void request(const Geom& g, const tkphi_problem& pr, int64_t head_off, const int* tok, int cnt) {
+    const int LPR = g.d / EPL, RPP = kThreads / LPR, seg = threadIdx.x % LPR, rsub = threadIdx.x / LPR;
+#pragma unroll
+    for (int ps = 0; ps < MAXP; ++ps)
+      if (ps * RPP < cnt)
+        v[ps] = gload128((const char*)pr.V + (head_off + (int64_t)tok[min(ps * RPP + rsub, cnt - 1)] * pr.stride_tok + seg * EPL) * sizeof(T));
+  }
+};
+template <typename T>
+__device__ __forceinline__ void weighted_value_sums(const Geom& g, const ValueRows<T>& rows, const float* w, const float* z, int cnt,
                                                     float* red, float* part, bool with_z) {
-  constexpr int EPL = Elem<T>::per16;
+  constexpr int EPL = Elem<T>::per16, MAXP = ValueRows<T>::MAXP;
   const int tid = threadIdx.x, d = g.d;
   const int LPR = d / EPL, RPP = kThreads / LPR;      // rows per pass
   const int seg = tid % LPR, rsub = tid / LPR;
-  constexpr int MAXP = 8;                              // 64 rows / (256 / 32 lanes) passes at most
   const int n_pass = (cnt + RPP - 1) / RPP;
-  uint4 v[MAXP];
-#pragma unroll
-  for (int ps = 0; ps < MAXP; ++ps) {
-    if (ps < n_pass) {
-      const int i = min(ps * RPP + rsub, cnt - 1);
-      const u32x4 t = gload128((const char*)pr.V + (head_off + (int64_t)tok[i] * pr.stride_tok + seg * EPL) * sizeof(T));
-      v[ps] = make_uint4(t.x, t.y, t.z, t.w);
-    }
-  }
   float an[EPL], az[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) { an[e] = 0.f; az[e] = 0.f; }
@@ -61,7 +63,7 @@ __device__ __forceinline__ void weighted_value_sums(const Geom& g, const tkphi_p
       const int i = ps * RPP + rsub;
       if (i < cnt) {
         float x[EPL];
-        Elem<T>::unpack(v[ps], x);
+        Elem<T>::unpack(make_uint4(rows.v[ps].x, rows.v[ps].y, rows.v[ps].z, rows.v[ps].w), x);
         const float wi = w[i], zi = with_z ? z[i] : 0.f;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) { an[e] = fmaf(wi, x[e], an[e]); az[e] = fmaf(zi, x[e], az[e]); }
@@ -82,6 +84,14 @@ __device__ __forceinline__ void weighted_value_sums(const Geom& g, const tkphi_p
     part[4 + d + tid] += a1;
   }
   __syncthreads();
+}
+
+// Entry i0 + tid of a head's retrieved list, requested together with the length of the list (behind its end: any row of the
+// mid-region, which counts for nothing)
+struct ListEntry { int idx; float score; };
+__device__ __forceinline__ ListEntry list_entry(const Geom& g, const char* blk, int gq, int i0) {
+  const size_t at = (size_t)gq * g.max_K + min(i0 + min((int)threadIdx.x, kPairsPerWG - 1), g.max_K - 1);
+  return ListEntry{((const int32_t*)(blk + g.off_selidx))[at], ((const float*)(blk + g.off_selscore))[at]};
 }
 
 // ---- anchors: exact terms over [0, n_sink) u [L - n_tail, L) (or every token if M is empty) --------
@@ -114,6 +124,8 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
     a_tok[tid] = a >= n_prefill ? pr.L + (a - n_prefill) : (n > 0 && a >= g.n_sink) ? (pr.L - g.n_tail + (a - g.n_sink)) : a;
   }
   __syncthreads();
+  ValueRows<T> rows;
+  rows.request(g, pr, head_off, a_tok, cnt);
   // scores of the batch
   constexpr int MAXP = 8;
   const int n_pass = (cnt + RPP - 1) / RPP;
@@ -147,11 +159,10 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
     if (tid == 0) a_m = mb;
   }
   __syncthreads();
-  weighted_value_sums<T>(g, pr, head_off, a_tok, a_w, a_w, cnt, red, a_acc, false);
-  if (tid == 0) {
-    float Z = 0.f;
-    for (int i = 0; i < cnt; ++i) Z += a_w[i];
-    part[0] = a_m; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt;
+  weighted_value_sums<T>(g, rows, a_w, a_w, cnt, red, a_acc, false);
+  if (tid < 64) {
+    const float Z = wave_sum(a_w[tid]);
+    if (tid == 0) { part[0] = a_m; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt; }
   }
   if (tid < d) { part[4 + tid] = a_acc[4 + tid]; part[4 + d + tid] = 0.f; }
 }
@@ -166,11 +177,14 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
   const int QPR = d / 4, NG = kThreads / QPR;      // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR, per = (dphi + NG - 1) / NG, j0 = jg * per, j1 = min(dphi, j0 + per);
   const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
-  constexpr int MAXF = kMaxDim / 8;                // features of a group (all rows of S are requested together)
+  constexpr int MAXF = 16;                         // rows of S requested together (all of a thread's at d_phi = 128)
   u32x4 sv[MAXF];
+  auto request = [&](int jb) {
 #pragma unroll
-  for (int k = 0; k < MAXF; ++k)
-    if (j0 + k < j1) sv[k] = gload128(S + (size_t)(j0 + k) * d + c4 * 4);
+    for (int k = 0; k < MAXF; ++k)
+      if (jb + k < j1) sv[k] = gload128(S + (size_t)(jb + k) * d + c4 * 4);
+  };
+  request(j0);
   if (tid < dphi) {                                // (d_phi <= kMaxDim = the threads)
     const float pq = ((const float*)(blk + g.off_phiq))[(size_t)gq * dphi + tid];
     sh_phiq[tid] = pq;
@@ -178,12 +192,15 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
   }
   __syncthreads();
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int jb = j0; jb < j1; jb += MAXF) {
+    if (jb != j0) request(jb);
 #pragma unroll
-  for (int k = 0; k < MAXF; ++k) {
-    if (j0 + k < j1) {
-      const float pj = sh_phiq[j0 + k];
-      a.x = fmaf(pj, __uint_as_float(sv[k].x), a.x); a.y = fmaf(pj, __uint_as_float(sv[k].y), a.y);
-      a.z = fmaf(pj, __uint_as_float(sv[k].z), a.z); a.w = fmaf(pj, __uint_as_float(sv[k].w), a.w);
+    for (int k = 0; k < MAXF; ++k) {
+      if (jb + k < j1) {
+        const float pj = sh_phiq[jb + k];
+        a.x = fmaf(pj, __uint_as_float(sv[k].x), a.x); a.y = fmaf(pj, __uint_as_float(sv[k].y), a.y);
+        a.z = fmaf(pj, __uint_as_float(sv[k].z), a.z); a.w = fmaf(pj, __uint_as_float(sv[k].w), a.w);
+      }
     }
   }
   *(float4*)(red + jg * d + c4 * 4) = a;           // (NG d = 1024 floats)
@@ -230,8 +247,9 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
   if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<uint16_t>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
-  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
+  const ListEntry le = list_entry(g, blk, gq, i0);
+  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   if (i0 >= Ksel) return;
   const int cnt = min(kPairsPerWG, Ksel - i0);
   const int h = gq / g.G;
@@ -239,9 +257,8 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
 
   // the tile's retrieved tokens
   if (tid < kPairsPerWG) {
-    const int i = i0 + min(tid, cnt - 1);
-    p_tok[tid] = g.n_sink + min(max(((const int32_t*)(blk + g.off_selidx))[(size_t)gq * g.max_K + i], 0), n - 1);
-    p_s[tid] = tid < cnt ? ((const float*)(blk + g.off_selscore))[(size_t)gq * g.max_K + i] : -INFINITY;
+    p_tok[tid] = g.n_sink + min(max(le.idx, 0), n - 1);
+    p_s[tid] = tid < cnt ? le.score : -INFINITY;
   }
   for (int i = tid; i < 2 * D + 4; i += kThreads) acc_part[i] = 0.f;
   // stage Wk[h] ([D features][D channels] bf16) with padded rows
@@ -262,13 +279,15 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
     }
   }
   __syncthreads();
+  const int64_t head_off = (int64_t)h * pr.stride_head;
+  ValueRows<uint16_t> rows;
+  rows.request(g, pr, head_off, p_tok, cnt);
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
     m = wave_max(m);
     if (tid == 0) sh_m = m;
   }
 
-  const int64_t head_off = (int64_t)h * pr.stride_head;
   if (wv * 16 < cnt) {
     // A operand: key rows of this wavefront's 16 tokens
     const int tok = p_tok[wv * 16 + r];
@@ -288,12 +307,11 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<uint16_t>(g, pr, head_off, p_tok, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums<uint16_t>(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < D) { part[4 + tid] = acc_part[4 + tid]; part[4 + D + tid] = acc_part[4 + D + tid]; }
-  if (tid == 0) {
-    float Z = 0.f, zs = 0.f;
-    for (int i = 0; i < cnt; ++i) { Z += p_w[i]; zs += p_z[i]; }
-    part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt;
+  if (tid < 64) {
+    const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
+    if (tid == 0) { part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt; }
   }
 }
 
@@ -324,8 +342,9 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
   if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
-  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
+  const ListEntry le = list_entry(g, blk, gq, i0);
+  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   if (i0 >= Ksel) return;
   const int cnt = min(kPairsPerWG, Ksel - i0);
   const int h = gq / g.G, d = g.d, dphi = g.dphi;
@@ -333,12 +352,13 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   const int64_t head_off = (int64_t)h * pr.stride_head;
 
   if (tid < kPairsPerWG) {
-    const int i = i0 + min(tid, cnt - 1);
-    p_tok[tid] = g.n_sink + min(max(((const int32_t*)(blk + g.off_selidx))[(size_t)gq * g.max_K + i], 0), n - 1);
-    p_s[tid] = tid < cnt ? ((const float*)(blk + g.off_selscore))[(size_t)gq * g.max_K + i] : -INFINITY;
+    p_tok[tid] = g.n_sink + min(max(le.idx, 0), n - 1);
+    p_s[tid] = tid < cnt ? le.score : -INFINITY;
   }
   for (int i = tid; i < 2 * d + 4; i += kThreads) acc_part[i] = 0.f;
   __syncthreads();
+  ValueRows<T> rows;
+  rows.request(g, pr, head_off, p_tok, cnt);
   {
     // key rows -> LDS (fp32): 16-byte pieces, (row, segment) pairs dealt over the threads
     const int SEGS = d / EPL;
@@ -429,12 +449,11 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<T>(g, pr, head_off, p_tok, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums<T>(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < d) { part[4 + tid] = acc_part[4 + tid]; part[4 + d + tid] = acc_part[4 + d + tid]; }
-  if (tid == 0) {
-    float Z = 0.f, zs = 0.f;
-    for (int i = 0; i < cnt; ++i) { Z += p_w[i]; zs += p_z[i]; }
-    part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt;
+  if (tid < 64) {
+    const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
+    if (tid == 0) { part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt; }
   }
 }
 
@@ -460,20 +479,22 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
   if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
-  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   const int i0 = tile * kPairsPerWG;
+  const ListEntry le = list_entry(g, blk, gq, i0);
+  const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
   if (i0 >= Ksel) return;
   const int cnt = min(kPairsPerWG, Ksel - i0);
   const int h = gq / g.G, d = g.d, dphi = g.dphi;
   const int64_t head_off = (int64_t)h * pr.stride_head;
 
   if (tid < kPairsPerWG) {
-    const int i = i0 + min(tid, cnt - 1);
-    p_tok[tid] = g.n_sink + min(max(((const int32_t*)(blk + g.off_selidx))[(size_t)gq * g.max_K + i], 0), n - 1);
-    p_s[tid] = tid < cnt ? ((const float*)(blk + g.off_selscore))[(size_t)gq * g.max_K + i] : -INFINITY;
+    p_tok[tid] = g.n_sink + min(max(le.idx, 0), n - 1);
+    p_s[tid] = tid < cnt ? le.score : -INFINITY;
   }
   for (int i = tid; i < 2 * d + 4; i += kThreads) acc_part[i] = 0.f;
   __syncthreads();
+  ValueRows<T> rows;
+  rows.request(g, pr, head_off, p_tok, cnt);
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
     m = wave_max(m);
@@ -517,12 +538,11 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<T>(g, pr, head_off, p_tok, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums<T>(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < d) { part[4 + tid] = acc_part[4 + tid]; part[4 + d + tid] = acc_part[4 + d + tid]; }
-  if (tid == 0) {
-    float Z = 0.f, zs = 0.f;
-    for (int i = 0; i < cnt; ++i) { Z += p_w[i]; zs += p_z[i]; }
-    part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt;
+  if (tid < 64) {
+    const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
+    if (tid == 0) { part[0] = sh_m; part[1] = Z; part[2] = zs; part[3] = (float)cnt; }
   }
 }
 
