@@ -103,14 +103,13 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   __shared__ int w_tok[kWinLds];
   __shared__ float w_s[kWinLds];
   constexpr int kBatch = kBatchOf<D, NTHR, KV>;
-  __shared__ float b_w[kBatch], b_z[kBatch];
+  __shared__ float b_w[2][kBatch], b_z[2][kBatch], sh_wave[3][NWV];    // (maxima, shares of Z_loc and of zsum)
   __shared__ float sh_bk[D], sh_pq[D];              // bk[h] and phi_q of the head, staged with Wk
   __shared__ int sh_scan[NWV];
   __shared__ uint64_t sh_prefix, sh_thr;
   __shared__ int sh_want, sh_tot;
   __shared__ int sh_bstar, sh_krem, sh_chi, sh_nb, sh_nbc;
   __shared__ uint32_t sh_total, sh_ovp;
-  __shared__ float sh_m, sh_Z, sh_zs;
   __shared__ LocalMerge sh_lm;
   uint32_t* sh_hist = (uint32_t*)lds_a;
   uint64_t* bcand = (uint64_t*)(lds_a + 8192);
@@ -230,9 +229,8 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     empty_partial();
     return false;
   }
-  // Wk[h] for the gather phase: requested now (the first sweep has arrived, nothing else is in flight), stored
-  // to LDS right before the gather (the barrier after the histogram pass orders LDS only, so it does not wait
-  // for these loads)
+  // Wk[h] for the gather phase: requested now (the first sweep has arrived, nothing else is in flight; the barrier after the
+  // histogram pass orders LDS only, so it does not wait for these loads)
   WkPieces<D, NTHR, sizeof(KV)> wkp;
   float bk_t = 0.f, pq_t = 0.f;
   if constexpr (!LIST) wkp.request(pr.Wk, h);
@@ -259,6 +257,14 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     if (n_at > 0 && tid < D) {
       pre_n = ((const float*)(blk + g.off_sphi))[(size_t)gq * D + tid];
       pre_z = ((const float*)(blk + g.off_uphi))[gq];
+    }
+  };
+
+  // (to LDS once the threshold is found: the barriers of the winners' prefix sums publish it, and the gather begins with its loads)
+  auto commit_wk = [&]() {
+    if constexpr (!LIST) {
+      wkp.commit(wk_lds);
+      if (tid < D) { sh_bk[tid] = bk_t; sh_pq[tid] = pq_t; }
     }
   };
 
@@ -301,9 +307,9 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     }
     lds_barrier();                                    // (the histogram is LDS traffic; the Wk loads stay in flight)
   };
-  bool packed = total <= (uint32_t)kDense;
+  bool packed = DIRECT || total <= (uint32_t)kDense;     // (Geom::direct: the mid-region fits the array)
   int min_bin = 0;                                  // candidates in lower bins are not packed
-  if (!packed) {
+  if (!DIRECT && !packed) {
     clear_hist();
     __syncthreads();
     sweep_histogram();
@@ -312,7 +318,7 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     packed = min_bin >= 0 && sh_chi + sh_nb <= kDense;       // (else all scores (nearly) equal, or a budget beyond the array)
     lds_barrier();
   }
-  if (packed) {
+  if (DIRECT || packed) {
     int n_cand = 0;
     clear_hist();
     if constexpr (DIRECT) {                        // entry i = token i, straight from the registers of the speculative loads
@@ -404,6 +410,7 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     }
     const uint64_t thr = sh_thr;
     TKPHI_PHASE(ws, 14);
+    commit_wk();
     if (tid == 0 && part == 0) *plan = SelPlan{bstar, krem, c_hi, nb, Ksel};
     // ---- winners of the packed range [r0, r1) --------------------------------------------------------------------
     auto is_winner = [&](int idx, int lim, uint2* en) {
@@ -528,6 +535,7 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
     }
     const uint64_t thr = sh_thr;
     TKPHI_PHASE(ws, 14);
+    commit_wk();
     if (tid == 0 && part == 0) *plan = SelPlan{bstar, krem, c_hi, nb, Ksel};
 
     // ---- this workgroup's winners: lists [l0, l1), in list order -----------------------------------------------
@@ -615,22 +623,31 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   constexpr int NPASS = kBatch / RPP;               // value rows per thread and round (4)
   constexpr int NTW = kBatch / (16 * NWV);    // 16-token tiles per wavefront and round
   const int seg = tid % LPR, rsub = tid / LPR;
-  float run_m = -INFINITY, run_Z = 0.f, run_zs = 0.f, run_nu = 0.f, run_zv = 0.f;   // (nu, zv: channel tid < D)
-  wkp.commit(wk_lds);                               // (requested before the histogram pass: long since arrived)
-  if (tid < D) { sh_bk[tid] = bk_t; sh_pq[tid] = pq_t; }
-  if constexpr (LOCAL) {
-    const int n_at = sh_lm.n_at;
-    if (4 * tid < n_at * (2 * D + 4)) *(u32x4*)(sh_parts + 4 * tid) = anc;
-    if (n_at > 0 && tid < D) { sh_parts[(kLocalTiles + 1) * (2 * D + 4) + tid] = pre_n; if (tid == 0) sh_lm.pre_z = pre_z; }
-  }
-  __syncthreads();                                  // lds_a changes hands; the staged Wk is complete
-  // (inside the loop the wavefronts exchange data through LDS only: its barriers leave the key and value loads in flight)
-  // winner j of the round that starts at b0 (thread t < kBatch <-> winner b0 + t)
-  auto winner = [&](int b0, int j, int* tok, float* s) {
-    const int i = b0 + min(j, min(kBatch, my_count - b0) - 1);
-    if (i < kWinLds) { *tok = w_tok[i]; *s = w_s[i]; }
-    else { *tok = sel_idx[min(my_base + i, g.max_K - 1)]; *s = sel_score[min(my_base + i, g.max_K - 1)]; }
-    *tok = g.n_sink + min(max(*tok, 0), n - 1);
+  // mid indices of N winners of the round that starts at b0, all LDS reads together; those beyond the LDS stage (rare) from the list
+  const bool staged = my_count <= kWinLds;
+  auto winners = [&](auto& tok, int b0, int first, int step) {
+    constexpr int N = sizeof(tok) / sizeof(int);
+    const int last = min(kBatch, my_count - b0) - 1;
+#pragma unroll
+    for (int k = 0; k < N; ++k) tok[k] = w_tok[min(b0 + min(first + k * step, last), kWinLds - 1)];
+    if (!staged) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const int i = b0 + min(first + k * step, last);
+        if (i >= kWinLds) tok[k] = sel_idx[min(my_base + i, g.max_K - 1)];
+      }
+      wait_vm_loads<0>();                           // (here, or the common path would wait for its rows as well)
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) tok[k] = g.n_sink + min(max(tok[k], 0), n - 1);
+  };
+  auto score_of = [&](int i) {
+    float s = w_s[min(i, kWinLds - 1)];
+    if (!staged) {
+      if (i >= kWinLds) s = sel_score[min(my_base + i, g.max_K - 1)];
+      wait_vm_loads<0>();
+    }
+    return s;
   };
   // The key rows of this wavefront's tiles and the value rows of all passes only need the token indices.  The rows
   // of round b + 1 are requested inside round b, each set into the registers round b has just finished with (keys
@@ -639,13 +656,13 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   u32x4 vrow[NPASS];
   auto load_keys = [&](int b0) {
     const int cnt = min(kBatch, my_count - b0);
+    int tk[NTW];
+    winners(tk, b0, wv * 16 + r, NWV * 16);
 #pragma unroll
     for (int u = 0; u < NTW; ++u) {
       const int t16 = (wv + u * NWV) * 16;      // first token of this wavefront's u-th tile
       if (t16 < cnt) {
-        int tk; float s;
-        winner(b0, t16 + r, &tk, &s);
-        const char* rp = (const char*)pr.K + (head_off + (int64_t)tk * pr.stride_tok) * sizeof(KV) + kg * 16;
+        const char* rp = (const char*)pr.K + (head_off + (int64_t)tk[u] * pr.stride_tok) * sizeof(KV) + kg * 16;
 #pragma unroll
         for (int j = 0; j < KS; ++j) a[u][j].u = gload128(rp + j * 64);
       }
@@ -653,33 +670,39 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   };
   auto load_values = [&](int b0) {
     const int cnt = min(kBatch, my_count - b0);
+    int tk[NPASS];
+    winners(tk, b0, rsub, RPP);
 #pragma unroll
-    for (int ps = 0; ps < NPASS; ++ps) {
-      if (ps * RPP < cnt) {
-        int vtok; float vs;
-        winner(b0, ps * RPP + rsub, &vtok, &vs);
-        vrow[ps] = gload128((const char*)pr.V + (head_off + (int64_t)vtok * pr.stride_tok + seg * EPL) * sizeof(KV));
-      }
-    }
+    for (int ps = 0; ps < NPASS; ++ps)
+      if (ps * RPP < cnt) vrow[ps] = gload128((const char*)pr.V + (head_off + (int64_t)tk[ps] * pr.stride_tok + seg * EPL) * sizeof(KV));
   };
+  if constexpr (LOCAL) {
+    const int n_at = sh_lm.n_at;
+    if (4 * tid < n_at * (2 * D + 4)) *(u32x4*)(sh_parts + 4 * tid) = anc;
+    if (n_at > 0 && tid < D) { sh_parts[(kLocalTiles + 1) * (2 * D + 4) + tid] = pre_n; if (tid == 0) sh_lm.pre_z = pre_z; }
+  }
   if (my_count > 0) { load_keys(0); load_values(0); }
-  for (int b0 = 0; b0 < my_count; b0 += kBatch) {
+  // The scores' maximum (known behind the first round's barrier): the weights of all rounds have one shift, and the rounds no sums to rescale
+  {
+    float lm = -INFINITY;
+    for (int i = tid; i < my_count; i += NTHR) lm = fmaxf(lm, score_of(i));
+    lm = wave_max(lm);
+    if (lane == 0) sh_wave[0][wv] = lm;
+  }
+  float run_m = -INFINITY;
+  float Zt = 0.f, zst = 0.f;                        // this thread's share of Z_loc; of zsum (a lane's four tokens, the same in all of r)
+  float an[EPL], az[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) { an[e] = 0.f; az[e] = 0.f; }
+  // One barrier per round: scores and z of its tokens go through the buffers that the round before last has read.  With five barriers, and the
+  // sums over the wavefronts in every round, a round of 256 took 8 us at d = 128, now 5: 3B layer at 128K 4 % 91.1 -> 88.0 us per step, 16 ragged
+  // ones of 10K..40K at 3 % 243 -> 230, 256 ragged ones of the 1B layer at 1 % 2600 -> 2560; with one round 1B layer at 4K 18.1 -> 17.7, 32K 27.5 -> 27.0.
+#pragma unroll 1
+  for (int b0 = 0, par = 0; b0 < my_count; b0 += kBatch, par ^= 1) {
     const int cnt = min(kBatch, my_count - b0);
     const bool more = b0 + kBatch < my_count;
-    // batch maximum of the scores
-    if (tid < kBatch) {
-      int tk; float s;
-      winner(b0, tid, &tk, &s);
-      b_w[tid] = tid < cnt ? s : -INFINITY;         // (scores for now)
-    }
-    lds_barrier();
-    if (wv == 0) {
-      float mloc = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < kBatch / 64; ++k) mloc = fmaxf(mloc, b_w[lane + 64 * k]);
-      mloc = wave_max(mloc);
-      if (lane == 0) sh_m = mloc;
-    }
+    const float s_own = tid < cnt ? score_of(b0 + tid) : -INFINITY;
+    if (tid < kBatch) b_w[par][tid] = s_own;        // (scores; every reader makes its weight of one)
     // z_i of this wavefront's tokens
 #pragma unroll
     for (int u = 0; u < NTW; ++u) {
@@ -688,81 +711,66 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
         float z[4];
         if constexpr (sizeof(KV) == 4) wave_feature_dots_f32<D>(a[u], wk_lds, sh_bk, sh_pq, g.a, g.c, z);
         else wave_feature_dots<D>(a[u], wk_lds, sh_bk, sh_pq, g.a, g.c, z);
-        if (r == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) b_z[t16 + 4 * kg + i] = (t16 + 4 * kg + i < cnt) ? z[i] : 0.f;
+        for (int i = 0; i < 4; ++i) {
+          const bool in = t16 + 4 * kg + i < cnt;
+          if (in) zst += z[i];
+          if (r == 0) b_z[par][t16 + 4 * kg + i] = in ? z[i] : 0.f;
         }
-      } else if (lane < 16) {
-        b_z[t16 + lane] = 0.f;
       }
     }
     if (more) load_keys(b0 + kBatch);
     lds_barrier();
-    const float mloc = sh_m;
-    if (tid < kBatch) b_w[tid] = tid < cnt ? __expf(b_w[tid] - mloc) : 0.f;
-    lds_barrier();
-    // weighted value sums: rows of one wavefront that share a segment, then the 16 wavefronts
-    float an[EPL], az[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) { an[e] = 0.f; az[e] = 0.f; }
+    if (b0 == 0) run_m = lanes_reduce(sh_wave[0][lane & (NWV - 1)], NWV, MaxOp());
+    Zt += __expf(s_own - run_m);
+    // weighted value sums of this thread's rows
 #pragma unroll
     for (int ps = 0; ps < NPASS; ++ps) {
       const int i = ps * RPP + rsub;
       if (ps * RPP < cnt && i < cnt) {
         float x[EPL];
         Elem<KV>::unpack(make_uint4(vrow[ps].x, vrow[ps].y, vrow[ps].z, vrow[ps].w), x);
-        const float wi = b_w[i], zi = b_z[i];
+        const float wi = __expf(b_w[par][i] - run_m), zi = b_z[par][i];
 #pragma unroll
         for (int e = 0; e < EPL; ++e) { an[e] = fmaf(wi, x[e], an[e]); az[e] = fmaf(zi, x[e], az[e]); }
       }
     }
     if (more) load_values(b0 + kBatch);
-    static_assert(LPR == 8 || LPR == 16, "lanes per row");
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) { an[e] = strided_sum(an[e], LPR); az[e] = strided_sum(az[e], LPR); }
-    if (lane < LPR) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) { red[(wv * 2 + 0) * 128 + lane * EPL + e] = an[e]; red[(wv * 2 + 1) * 128 + lane * EPL + e] = az[e]; }
-    }
-    if (wv == 1) {                                  // Z_loc and zsum of the batch, in a fixed order
-      float Zb = (b_w[lane] + b_w[lane + 64]) + (b_w[lane + 128] + b_w[lane + 192]);
-      float zb = (b_z[lane] + b_z[lane + 64]) + (b_z[lane + 128] + b_z[lane + 192]);
-#pragma unroll
-      for (int k = 4; k < kBatch / 64; k += 4) {    // (all zero in a round of at most 256 winners)
-        Zb += (b_w[lane + 64 * k] + b_w[lane + 64 * (k + 1)]) + (b_w[lane + 64 * (k + 2)] + b_w[lane + 64 * (k + 3)]);
-        zb += (b_z[lane + 64 * k] + b_z[lane + 64 * (k + 1)]) + (b_z[lane + 64 * (k + 2)] + b_z[lane + 64 * (k + 3)]);
-      }
-      Zb = wave_sum(Zb); zb = wave_sum(zb);
-      if (lane == 0) { sh_Z = Zb; sh_zs = zb; }
-    }
-    lds_barrier();
-    {
-      float nu_b = 0.f, zv_b = 0.f;
-      if (tid < D) {
-        for (int k = 0; k < NWV; ++k) { nu_b += red[(k * 2 + 0) * 128 + tid]; zv_b += red[(k * 2 + 1) * 128 + tid]; }
-      }
-      // running combination with the earlier batches (log-sum-exp rescaling)
-      const float m_new = fmaxf(run_m, mloc);
-      const float so = run_m > -INFINITY ? __expf(run_m - m_new) : 0.f, sb = __expf(mloc - m_new);
-      run_nu = run_nu * so + nu_b * sb;
-      run_Z = run_Z * so + sh_Z * sb;
-      run_zv += zv_b;
-      run_zs += sh_zs;
-      run_m = m_new;
-    }
-    lds_barrier();                                // red, b_w, b_z are rewritten by the next batch
   }
-  if (const int n_at = LOCAL ? sh_lm.n_at : 0) {
-    float* own = sh_parts + n_at * (2 * D + 4);
-    if (tid == 0) { own[0] = run_m; own[1] = run_Z; own[2] = run_zs; }
-    if (tid < D) { own[4 + tid] = run_nu; own[4 + D + tid] = run_zv; }
+  // rows of one wavefront that share a segment, then the wavefronts
+  static_assert(LPR == 8 || LPR == 16, "lanes per row");
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) { an[e] = strided_sum(an[e], LPR); az[e] = strided_sum(az[e], LPR); }
+  if (lane < LPR) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) { red[(wv * 2 + 0) * 128 + lane * EPL + e] = an[e]; red[(wv * 2 + 1) * 128 + lane * EPL + e] = az[e]; }
+  }
+  Zt = wave_sum(Zt);
+  zst = strided_sum(zst, 16);
+  if (lane == 0) { sh_wave[1][wv] = Zt; sh_wave[2][wv] = zst; }
+  lds_barrier();
+  // channel tid < D; the wavefront behind those adds up Z_loc and zsum
+  float* own = sh_parts;                            // (LOCAL)
+  int n_at = 0;
+  if constexpr (LOCAL) { n_at = sh_lm.n_at; own += n_at * (2 * D + 4); }
+  auto out = [&](int k, float x) {                  // (GPU-coherent: the workgroup that merges the head may run on another XCD)
+    if (LOCAL && n_at) own[k] = x;
+    else store_agent(partial + k, x);
+  };
+  if (tid < D) {
+    float nu = 0.f, zv = 0.f;
+    for (int k = 0; k < NWV; ++k) { nu += red[(k * 2 + 0) * 128 + tid]; zv += red[(k * 2 + 1) * 128 + tid]; }
+    out(4 + tid, nu);
+    out(4 + D + tid, zv);
+  } else if (wv == D / 64) {
+    const float Z = lanes_reduce(sh_wave[1][lane & (NWV - 1)], NWV, AddOp()), zs = lanes_reduce(sh_wave[2][lane & (NWV - 1)], NWV, AddOp());
+    if (lane == 0) { out(0, run_m); out(1, Z); out(2, zs); out(3, (float)my_count); }
+  }
+  if (LOCAL && n_at) {
     lds_barrier();
     if (tid < D) merge_head_local<D>(sh_lm, n_at + 1, sh_parts, sh_parts[(kLocalTiles + 1) * (2 * D + 4) + tid], (uint32_t*)(ws + g.off_status), gq);
     return true;
   }
-  // (GPU-coherent stores: the workgroup that merges the head may run on another XCD)
-  if (tid == 0) { store_agent(partial, run_m); store_agent(partial + 1, run_Z); store_agent(partial + 2, run_zs); store_agent(partial + 3, (float)my_count); }
-  if (tid < D) { store_agent(partial + 4 + tid, run_nu); store_agent(partial + 4 + D + tid, run_zv); }
   TKPHI_PHASE(ws, 16);
   return false;
 }

@@ -40,3 +40,20 @@ def test_local_merge(dtype, d, mids, ks, tail, gen, mode):
     if mode == 0 and max(mids) <= 2000:
         for i, (P, k) in enumerate(zip(layers, ks)):
             PU.check_layer(w, P, k, export, i, heads=[0, 31], sum_tol=2e-5)
+
+
+@pytest.mark.parametrize("d,ks", [(64, [256, 257, 511, 512, 513, 1024, 1025, 1536, 1600]), (64, [255, 256, 257, 512, 513, 700, 1000, 1023, 1024]),
+                                  (128, [255, 256, 257, 511, 512, 513, 1024, 1536, 1600])])
+def test_gather_rounds(d, ks):
+    """One workgroup per head (9 problems of 32 heads), winners around the rounds of 256 and 512 and beyond those kept in LDS (1024 or 1536),
+    against the oracle at the bars of parity_utils."""
+    import parity_utils as PU
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=32, n_kv_heads=8, d_head=d, d_phi=d, seed=98)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 20001)
+    b = H.Batch(H.config_of(w), [P] * len(ks), ks, debug=True)
+    b.build()
+    b.decode()
+    assert b.status() & ~2 == 0
+    for i, k in enumerate(ks):
+        PU.check_layer(w, P, k, b, i, heads=[i], sum_tol=2e-5)
