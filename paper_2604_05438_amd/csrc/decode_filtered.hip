@@ -5,7 +5,8 @@
 // leave the chip.  Two kernels and, from a few sequences on, a third for the phi and anchor jobs (decode_side_kernel) for
 // batches; one otherwise:
 //
-//   decode_prep     one small launch of independent jobs that need no selection:
+//   decode_prep     one small launch of independent jobs that need no selection (at d = 64 the sample jobs only, the others are blocks of
+//                   score_filtered):
 //                   * sample: per KV head, the scores of an evenly spaced sample of mid-region rows
 //                     -> per query head a lower bound of the K-th largest score (a bin edge chosen so
 //                     that the sample count above it exceeds its expectation at the K-th score by five
@@ -387,7 +388,33 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
   }
 }
 
-// grid (n_scan_chunks, Hkv, n_problems), 256 threads: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
+// The phi and anchor jobs of KV head h of a problem as workgroups of 256 threads: job j < G: phi of query head h G + j (and that head's
+// arrival counter <- 0: nobody has arrived yet at its merge), then n_atiles anchor tiles per query head.
+constexpr int kSideLds = (2 * kMaxDim + 1024) * (int)sizeof(float);
+template <int D, int EARLY>
+__device__ __forceinline__ void side_job(const Geom& g, const tkphi_problem& pr, char* blk, int h, int job, float* sh_f) {
+  if (job < g.G) {
+    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + job] = 0u;
+    side_phi<D, EARLY>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+  } else {
+    const int j = job - g.G;
+    side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+  }
+}
+
+// At d = 64 the phi and anchor jobs of a batch are blocks of the score launch, behind the chunks of their KV head: they hide among the chunks (a
+// launch of their own took 55 us of 256 ragged sequences' 2558, 6.5 of 48 for 16 of 2K..8K; on the sample launch, at one 1024-thread workgroup
+// per CU, 7 of 57 for 8 of 8K..30K; now 2470, 44.9 and 51.8).  At d = 128, where a head's S is 64 KB, they hold the stream up for as long or
+// longer: 16 sequences of 10K..40K 199 -> 204, 8 of 15K..60K 127 -> 129, 11 of 6K..25K 98.7 -> 93.4; there they stay apart.
+// As many blocks as make those of a KV head an odd number in all: workgroups go to XCDs (and in them to CUs) in turn by their linear index, the
+// chunks of short sequences are empty and the side jobs light, and with an odd number a chunk's place runs through all 256 CUs from
+// head to head (with 16 + 16 blocks 256 ragged sequences took 3500 us).
+__host__ __device__ __forceinline__ int side_blocks(const Geom& g) {
+  const int jobs = g.G * (1 + g.n_atiles);
+  return g.d != 64 ? 0 : jobs + ((jobs + g.n_scan_chunks) % 2 == 0 ? 1 : 0);
+}
+
+// grid (n_scan_chunks + side_blocks, Hkv, n_problems), 256 threads: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
 // caches, by the latency of a few round trips for short ones.  A wavefront holds two groups of TPI / 4 tiles, one on its way
 // while the other is contracted: whole units at a time (16 loads, wait, 16 tiles' scores, next unit) took 49.5 us
 // against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
@@ -399,18 +426,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const int p = blockIdx.z, h = blockIdx.y;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
+  extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]; side jobs: kSideLds bytes
+  char* blk = problem_block(g, ws, p);
+  if (D == 64 && (int)blockIdx.x >= g.n_scan_chunks) {
+    const int job = (int)blockIdx.x - g.n_scan_chunks;
+    if (job < g.G * (1 + g.n_atiles)) side_job<D, 0>(g, pr, blk, h, job, (float*)sh_heads);
+    return;
+  }
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
-  // (chunk indices rotated per head and problem: workgroups go to the 8 XCDs round-robin by linear
+  // (d = 128: chunk indices rotated per head and problem: workgroups go to the 8 XCDs round-robin by linear
   // index and the short sequences of a ragged batch have no late chunks)
-  const int chunk = ((int)blockIdx.x + h + p * g.Hkv) % (int)gridDim.x;
+  const int chunk = D == 64 ? (int)blockIdx.x : ((int)blockIdx.x + h + p * g.Hkv) % (int)gridDim.x;
   if (chunk >= n_chunks) return;
-  char* blk = problem_block(g, ws, p);
   const int r = threadIdx.x & 15;
   ScoreFrag bq[kTileFrags<D>];
   load_query_frags<D>(g, pr, h, bq);
   const uint32_t edge_r = ((const uint32_t*)(blk + g.off_thr))[h * g.G + min(r, g.G - 1)];
-  extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   scan_wave_slot<D, TPI, TPI / 4, 2, STREAM, STRIP>(g, pr, blk, h, n, n_chunks, chunk, wv, bq, edge_r,
                                                        (lds_u32x2)sh_heads + (STRIP ? wv * g.G * g.cand_T : 0));
@@ -524,22 +556,14 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   score_fused_job<D, TPI, STREAM, false>(g, probs, ws, x - p * per + ahead, p);
 }
 
-// The phi and anchor jobs of a batch: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads; job j < G: phi of query
-// head h G + j (and that head's arrival counter <- 0), then n_atiles anchor tiles per query head.
+// The phi and anchor jobs of a batch as a launch (d = 128, or no mid-region to score): grid (G (1 + n_atiles), Hkv, n_problems), 256 threads
 template <int D>
 __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
-  const int job = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
+  const int h = blockIdx.y, p = blockIdx.z;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
-  char* blk = problem_block(g, ws, p);
-  if (job < g.G) {
-    if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + job] = 0u;
-    side_phi<D, 0>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
-  } else {
-    const int j = job - g.G;
-    side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
-  }
+  side_job<D, 0>(g, pr, problem_block(g, ws, p), h, blockIdx.x, sh_f);
 }
 
 // The front end of short contexts (Geom::direct) in one launch: grid (G (1 + n_atiles) + n_scan_chunks, Hkv, n_problems), 256
@@ -556,13 +580,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_kernel(Geom g, const tk
   if (pr.L < 1 || pr.L > g.max_L) return;
   char* blk = problem_block(g, ws, p);
   if (x < n_side) {
-    if (x < g.G) {
-      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
-      side_phi<D, EARLY>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
-    } else {
-      const int j = x - g.G;
-      side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
-    }
+    side_job<D, EARLY>(g, pr, blk, h, x, sh_f);
     return;
   }
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -665,22 +683,25 @@ void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_
   const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
   const int n_jobs = 1 + g.G * (1 + g.n_atiles);
+  if (g.d == 64) {                     // (the other jobs ride in the score launch, if there is one)
+    TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<64, 8>), dim3(1, g.Hkv, g.n_problems), dim3(kPrepThreads), lds, s, g, probs, ws, 0);
+    if (g.max_mid == 0) TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<64>, dim3(n_jobs - 1, g.Hkv, g.n_problems), dim3(kThreads), 0, s, g, probs, ws);
+    return;
+  }
   if ((long)n_jobs * g.Hkv * g.n_problems <= 1024) {
-    if (g.d == 128) TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-    else TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<64, 8>), grid, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
+    TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
     return;
   }
   dim3 grid_a(1, g.Hkv, g.n_problems), grid_b(n_jobs - 1, g.Hkv, g.n_problems);
-  if (g.d == 128) TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-  else TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<64, 8>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-  if (g.d == 128) TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<128>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
-  else TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<64>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
+  TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
+  TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<128>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
 }
 
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
   if (g.max_mid == 0) return;
-  dim3 grid(g.n_scan_chunks, g.Hkv, g.n_problems);
-  const size_t lds = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
+  dim3 grid(g.n_scan_chunks + side_blocks(g), g.Hkv, g.n_problems);
+  const size_t strips = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
+  const size_t lds = g.d == 64 ? std::max(strips, (size_t)kSideLds) : strips;
   const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
   const auto launch_as = [&](auto strip, auto stream) {
     if (g.d == 128) launch(score_filtered_kernel<128, 4, decltype(stream)::value, decltype(strip)::value>);
