@@ -257,8 +257,9 @@ typedef struct tkphi_problem {
 } tkphi_problem;
 
 /* Bytes of DEVICE workspace tkphi_build_summaries / tkphi_decode need for the given
- * launch bounds (the larger of the two; a decode that is handed less may still run, in a smaller and slower
- * launch geometry).  For long contexts, per problem, query head and mid token: about 5 bytes where the spill pipeline
+ * launch bounds (the larger of the two; a call that is handed less may still run, in a smaller and slower
+ * launch geometry: a decode with other chunks and candidate lists, a build with fewer and longer chunks).  Every
+ * size reported for larger bounds serves a build of exp-affine maps.  For long contexts, per problem, query head and mid token: about 5 bytes where the spill pipeline
  * runs, 10 (budgets beyond 1/64 of batches of more than 128 heads) or 20 with the candidate lists of the filtered one.  Returns 0 if the config is invalid.
  * The workspace must be 256-byte aligned.  Its contents need not be preserved between
  * calls and need not be initialised.  Two calls that overlap in time (different

@@ -65,9 +65,10 @@ static int filtered_min_inverse_budget(bool short_context, int64_t heads, int sp
 // (Geom::fused), sample and score pass in two, whose chunks may fit where those do not.  kCompact: its needs grow with max_L, max_K and the
 // number of problems (one chunk rule for all lengths, the filtered pipeline with its two full-length lists per head for budgets
 // up to 1/64 only), so a workspace sized for larger bounds serves the smaller calls (but for a budget of at most 1/64 where the
-// workspace was sized for one beyond 1/12).
+// workspace was sized for one beyond 1/12).  For summary builds see make_geom.
 enum Fit { kFast, kSeparate, kCompact };
-static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Fit fit, bool diag, Geom* g) {
+// most_build_chunks: the partials of a KV head that a summary build has room for (0: as many as it likes)
+static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Fit fit, bool diag, Geom* g, int64_t most_build_chunks = 0) {
   const bool compact = fit == kCompact;
   if (!cfg) { set_error("cfg is null"); return TKPHI_EINVAL; }
   if (n_problems < 0 || max_L < 1 || max_K < 0) {
@@ -300,6 +301,7 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
       bc = best_bc;
     }
   }
+  if (most_build_chunks > 0) bc = std::max(bc, (int)align_up((size_t)ceil_div(g->max_mid, most_build_chunks), 64));
   if (tn.build_chunk > 0) bc = tn.build_chunk;
   g->build_chunk = std::max(64, bc / 64 * 64);
   g->n_build_chunks = (int)std::max<int64_t>(1, ceil_div(g->max_mid, g->build_chunk));
@@ -392,11 +394,27 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   return TKPHI_OK;
 }
 
-// have / need: the scratch bytes that the caller has and the member that says what its call takes (null: no limit)
+// have / need: the scratch bytes that the caller has and the member that says what its call takes (null: no limit).
+// A summary build takes as many chunks as the scratch has room for, down to a quarter of the compact geometry's.  The number of chunks that its rules
+// choose (whole rounds of workgroups) goes up and down with the length and the number of problems, by less than that, so a workspace sized for
+// larger bounds serves the smaller builds too (MLP maps without a feature cache aside, whose problems per launch change as well).
 tkphi_status make_geom(const tkphi_config* cfg, int n_problems, int max_L, int max_K, Geom* g, size_t have, size_t Geom::*need, bool diag) {
+  int64_t least_chunks = 0;
   for (const Fit fit : {kFast, kSeparate, kCompact}) {
-    const tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, fit, diag, g);
+    tkphi_status st = make_geom_as(cfg, n_problems, max_L, max_K, fit, diag, g);
     if (st != TKPHI_OK || !need || g->*need <= have) return st;
+    if (need != &Geom::build_bytes) continue;
+    if (least_chunks == 0) {
+      Geom compact;
+      st = make_geom_as(cfg, n_problems, max_L, max_K, kCompact, diag, &compact);
+      if (st != TKPHI_OK) return st;
+      least_chunks = ceil_div(compact.n_build_chunks, 4);
+    }
+    const size_t chunk_bytes = (size_t)std::max(n_problems, 1) * g->Hkv * g->dphi * (g->d + 1) * sizeof(float);      // of every KV head
+    const int64_t fit_chunks = g->n_build_chunks - (int64_t)std::min<size_t>((g->build_bytes - have + chunk_bytes - 1) / chunk_bytes, g->n_build_chunks);
+    if (fit_chunks < least_chunks) continue;
+    st = make_geom_as(cfg, n_problems, max_L, max_K, fit, diag, g, fit_chunks);
+    if (st != TKPHI_OK || g->build_bytes <= have) return st;
   }
   return TKPHI_OK;                     // (the caller sees what the last one needs)
 }

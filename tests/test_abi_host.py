@@ -188,3 +188,33 @@ def test_reported_workspace_of_batches():
     for n, L, K in ((256, 50000, 1000), (256, 131072, 5242), (40, 30000, 2100), (256, 4096, 327)):
         spill = B.tkphi_workspace_bytes(_cfg(tuning={"select_mode": 1}, **w), n, L, K)
         assert B.tkphi_workspace_bytes(_cfg(**w), n, L, K) <= 1.05 * (spill + n * 32 * L * 8)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_reported_workspace_serves_shorter_builds(seed):
+    """A summary build is accepted in the workspace that tkphi_workspace_bytes reports for any larger bounds.  Few query heads per KV head and
+    small budgets: there the partials of the build decide the size, and their number goes up and down with the length and the number of
+    problems.  (Misaligned table as above: EALIGN is acceptance.)"""
+    import random
+    r = random.Random(900 + seed)
+    lib = B.lib()
+    fixed = [(8, 64, 1, 11539, 1, 10126), (8, 64, 1, 15593, 1, 8212), (8, 64, 1, 21530, 1, 12261), (1, 64, 1, 101463, 1, 93995),
+             (1, 128, 2, 12000, 2, 8000), (4, 64, 64, 4598, 51, 1503), (1, 128, 3, 199066, 2, 130670)]
+    for i in range(1500):
+        if i < len(fixed):
+            hkv, d, n, L, n2, L2 = fixed[i]
+            dtype, cache = "bf16", 0
+        else:
+            hkv, d, n = r.choice([1, 1, 2, 4, 8]), r.choice([64, 128]), r.choice([1, 1, 1, 2, 3, 4, 8, 16, 33, 64, 200])
+            L = int(2 ** r.uniform(7, 18))
+            n2, L2 = r.randint(1, n), r.randint(1, L)
+            dtype, cache = r.choice(["bf16", "bf16", "f32"]), int(r.random() < 0.3)
+        cfg = _cfg(n_q_heads=hkv * r.choice([1, 1, 2]), n_kv_heads=hkv, d_head=d, d_phi=d, dtype=dtype, cache_features=cache)
+        size = B.tkphi_workspace_bytes(cfg, n, L, L // 100)
+        for m, l in ((n2, L2), (n, L2), (n2, L), (n, L)):
+            st = lib.tkphi_build_summaries(C.byref(cfg), 4100, m, l, 4096, size, None)
+            assert st == B.TKPHI_EALIGN, (hkv, d, dtype, n, L, m, l, st, B.tkphi_last_error())
+        # one chunk's partial of every KV head is too little for all but the shortest
+        per = hkv * n * d * (d + 1) * 4
+        if L > 8 * 4096 and n * hkv <= 8:
+            assert lib.tkphi_build_summaries(C.byref(cfg), 4100, n, L, 4096, 4096 + per, None) == B.TKPHI_EWORKSPACE

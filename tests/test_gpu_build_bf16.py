@@ -60,3 +60,29 @@ def test_build_bf16_strided(c):
     for name in ("S", "u"):
         x = plain.result(0, name)
         assert np.isfinite(x).all() and np.array_equal(x, apart.result(0, name))
+
+
+@pytest.mark.parametrize("dtype,d,hkv,n,L,longer", [("bf16", 64, 8, 1, 10126, 11539), ("bf16", 64, 8, 1, 8212, 15593), ("bf16", 128, 1, 2, 8000, 12000),
+                                                      ("f32", 64, 8, 1, 6000, 0)])
+def test_build_in_a_smaller_workspace(dtype, d, hkv, n, L, longer):
+    """Builds that take fewer chunks than they would like, as their workspace is that of longer sequences (or half their own): S and u against
+    the float64 oracle at the bars of test_build_bf16_edges, and nothing behind the end of the workspace is written."""
+    import parity_utils as PU
+    import torch
+    from oracle import tkphi_oracle as orc
+    from paper_2604_05438_amd import binding as B
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype=dtype, n_q_heads=hkv, n_kv_heads=hkv, d_head=d, d_phi=d, seed=99)
+    layers = [I.make_layer(w, L=L, seq=i) for i in range(n)]
+    b = H.Batch(H.config_of(w), layers, [L // 100] * n)
+    have = B.tkphi_workspace_bytes(b.cfg, n, longer, longer // 100) if longer else b.ws_bytes // 2 // 256 * 256
+    assert 0 < have < b.ws_bytes
+    guard = 1 << 20
+    ws = torch.full((have + guard,), 0x5a, dtype=torch.uint8, device="cuda")
+    B.tkphi_build_summaries(b.cfg, b.table.data_ptr(), n, L, ws.data_ptr(), have, B.current_stream_ptr())
+    torch.cuda.synchronize()
+    assert bool((ws[have:] == 0x5a).all())
+    for i, P in enumerate(layers):
+        O = PU.oracle_inputs(P)
+        S, u = orc.build_summaries(O["K"], O["V"], O["Wk"], O["bk"], w.phi_in_scale, w.phi_norm_coef, w.n_sink, w.n_tail)
+        PU.check_summaries(b.result(i, "S"), b.result(i, "u"), S, u, 2e-5)
