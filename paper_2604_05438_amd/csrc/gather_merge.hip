@@ -225,7 +225,7 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
 // ------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                               char* __restrict__ ws) {
+                                                               char* __restrict__ ws, int mode) {
   constexpr int KS = D / 32;
   constexpr int WROW = wk_row_bytes(D);            // bytes per staged Wk row
   // the staged Wk and the reduction scratch of the value sums are never live together
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<uint16_t>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
 // ------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                          char* __restrict__ ws) {
+                                                          char* __restrict__ ws, int mode) {
   constexpr int EPL = Elem<T>::per16;
   constexpr int KFS = 128 + 4;                     // padded row stride (d <= 128): conflict-free 16-byte reads
   __shared__ __attribute__((aligned(16))) float kf[kPairsPerWG * KFS];
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
 // ------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                 char* __restrict__ ws) {
+                                                                 char* __restrict__ ws, int mode) {
   __shared__ __attribute__((aligned(16))) float red[2 * kThreads * 8];
   __shared__ int p_tok[kPairsPerWG];
   __shared__ float p_s[kPairsPerWG], p_w[kPairsPerWG], p_z[kPairsPerWG];
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (n > 0) summary_terms(g, pr, blk, gq, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
   if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
@@ -554,18 +554,18 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(Geom g, const tkphi_pro
   merge_head<true, false>(g, probs, ws, (int)blockIdx.x, (int)blockIdx.y, mode);
 }
 
-void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
+void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
   dim3 grid(g.n_tiles + g.n_atiles + 1, g.Hq, g.n_problems);
   if (g.cache || g.sel_feat) {
-    if (g.dtype == TKPHI_BF16) TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws);
-    else TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws);
+    if (g.dtype == TKPHI_BF16) TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
+    else TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
   } else if (g.use_mfma) {
-    if (g.d == 128) TKPHI_LAUNCH(ST_GATHER, gather_mfma_kernel<128>, grid, dim3(kThreads), 0, s, g, probs, ws);
-    else TKPHI_LAUNCH(ST_GATHER, gather_mfma_kernel<64>, grid, dim3(kThreads), 0, s, g, probs, ws);
+    if (g.d == 128) TKPHI_LAUNCH(ST_GATHER, gather_mfma_kernel<128>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
+    else TKPHI_LAUNCH(ST_GATHER, gather_mfma_kernel<64>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
   } else if (g.dtype == TKPHI_BF16) {
-    TKPHI_LAUNCH(ST_GATHER, gather_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws);
+    TKPHI_LAUNCH(ST_GATHER, gather_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
   } else {
-    TKPHI_LAUNCH(ST_GATHER, gather_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws);
+    TKPHI_LAUNCH(ST_GATHER, gather_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
   }
 }
 

@@ -12,6 +12,14 @@
 
 namespace tkphi {
 
+// Whether the residual branch enters the output (in SUB mode with every mid token retrieved its set is empty: exactly zero).  Where it does
+// not, the gather launches and the merge leave S and u alone.
+__device__ __forceinline__ bool has_residual(int mode, int n, int Ksel) {
+  return mode != TKPHI_MODE_TOPK_ONLY && n > 0 && !(mode == TKPHI_MODE_SUB && Ksel == n);
+}
+
+__device__ __forceinline__ int retrieved_of(const Geom& g, const tkphi_problem& pr, int n) { return max(0, min(min(pr.topk, n), g.max_K)); }
+
 // TILES: a partial per 64 retrieved tokens (gather kernels), else one per workgroup of the fused select + gather kernel.
 // COHERENT: they were written (store_agent) by other workgroups of the running launch.  S_M^T phi_q and phi_q . u_M are in the workspace
 // (off_sphi, off_uphi)
@@ -24,7 +32,7 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
-  const int Ksel = max(0, min(min(pr.topk, n), g.max_K));
+  const int Ksel = retrieved_of(g, pr, n);
   const int n_anchor = (n > 0 ? g.n_sink + g.n_tail : pr.L) + min(max(pr.n_gen, 0), g.max_gen);   // anchors + generated tokens
   // partials holding retrieved tokens
   const int n_used = TILES ? (Ksel + kPairsPerWG - 1) / kPairsPerWG : (Ksel > 0 ? g.n_tiles : 0);
@@ -32,7 +40,7 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
   const int d = g.d;
   char* blk = problem_block(g, ws, p);
   const float* part0 = (const float*)(blk + g.off_part) + (size_t)gq * (g.n_tiles + g.n_atiles) * g.part_stride;
-  const bool use_res = mode != TKPHI_MODE_TOPK_ONLY && n > 0 && !(mode == TKPHI_MODE_SUB && Ksel == n);
+  const bool use_res = has_residual(mode, n, Ksel);
   // partial k of this head, in combination order: anchor tiles first, then the retrieved tiles
   const int n_parts = na_used + n_used;
   auto ldp = [](const float* q) { return COHERENT ? load_agent(q) : *q; };
@@ -112,7 +120,6 @@ __device__ __forceinline__ void merge_head(const Geom& g, const tkphi_problem* _
     }
   }
 
-  // (with every mid token retrieved in SUB mode the residual set is empty: exactly zero)
   float nuR = 0.f, ZR = 0.f;
   bool clamped = false;
   if (use_res) {

@@ -244,8 +244,7 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   if (LOCAL && tid == 0) {
     const int n_at = (g.n_sink + g.n_tail + min(max(pr.n_gen, 0), g.max_gen) + 63) / 64;
     const bool local = !pr.topk_idx && n_at <= kLocalTiles;
-    const bool residual = mode != TKPHI_MODE_TOPK_ONLY && !(mode == TKPHI_MODE_SUB && Ksel == n);
-    sh_lm = LocalMerge{pr.out, pr.aux, local ? n_at : 0, residual ? 1 : 0, mode == TKPHI_MODE_SUB ? 1 : 0};
+    sh_lm = LocalMerge{pr.out, pr.aux, local ? n_at : 0, has_residual(mode, n, Ksel) ? 1 : 0, mode == TKPHI_MODE_SUB ? 1 : 0};
   }
   u32x4 anc;
   float pre_n = 0.f, pre_z = 0.f;

@@ -546,7 +546,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
   if (g.phi_kind != TKPHI_PHI_MLP) {
     launch_score_mid(g, problems, ws, s);
     launch_select(g, problems, ws, s);
-    launch_gather(g, problems, ws, s);
+    launch_gather(g, problems, ws, acct, s);
     launch_merge(g, problems, ws, acct, s);
     return TKPHI_OK;
   }
@@ -558,7 +558,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
     launch_filtered(g);
     launch_mlp_phi_q(g, problems, ws, s);
     if (g.sel_feat) launch_mlp_sel_features(g, problems, ws, s);    // no feature cache: phi_k of the retrieved keys
-    launch_gather(g, problems, ws, s);
+    launch_gather(g, problems, ws, acct, s);
     launch_merge(g, problems, ws, acct, s);
     return TKPHI_OK;
   }
@@ -574,7 +574,7 @@ static tkphi_status enqueue_decode(const Geom& g, const tkphi_problem* problems,
   const tkphi_status st2 = hip_ok(hipStreamWaitEvent(s, ss->join, 0), "hipStreamWaitEvent");
   if (st != TKPHI_OK) return st;
   if (st2 != TKPHI_OK) return st2;
-  launch_gather(g, problems, ws, s);
+  launch_gather(g, problems, ws, acct, s);
   launch_merge(g, problems, ws, acct, s);
   return TKPHI_OK;
 }

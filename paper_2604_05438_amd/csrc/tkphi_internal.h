@@ -163,7 +163,7 @@ void launch_score_fused(const Geom& g, const tkphi_problem* probs, char* ws, hip
 void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);      // filtered pipeline, Geom::direct
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);  // includes the merge
-void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
+void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);
 void launch_merge(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s);
 void launch_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);
 void launch_mlp_build(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s);        // key features + chunk partials
