@@ -173,7 +173,7 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
 __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* red) {
   const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
   float* sh_phiq = red + 1024;
-  float* pu = red + 1280;
+  float* sh_u = red + 1280;
   const int QPR = d / 4, NG = kThreads / QPR;      // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR, per = (dphi + NG - 1) / NG, j0 = jg * per, j1 = min(dphi, j0 + per);
   const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
@@ -186,9 +186,8 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
   };
   request(j0);
   if (tid < dphi) {                                // (d_phi <= kMaxDim = the threads)
-    const float pq = ((const float*)(blk + g.off_phiq))[(size_t)gq * dphi + tid];
-    sh_phiq[tid] = pq;
-    pu[tid] = pq * pr.u[(size_t)h * dphi + tid];
+    sh_phiq[tid] = ((const float*)(blk + g.off_phiq))[(size_t)gq * dphi + tid];
+    sh_u[tid] = pr.u[(size_t)h * dphi + tid];
   }
   __syncthreads();
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -211,7 +210,7 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
     ((float*)(blk + g.off_sphi))[(size_t)gq * d + tid] = x;
   } else if (tid == kThreads - 64) {
     float x = 0.f;
-    for (int j = 0; j < dphi; ++j) x += pu[j];     // feature order
+    for (int j = 0; j < dphi; ++j) x = fmaf(sh_phiq[j], sh_u[j], x);     // feature order, products not rounded
     ((float*)(blk + g.off_uphi))[gq] = x;
   }
 }
