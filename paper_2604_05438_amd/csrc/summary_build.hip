@@ -332,7 +332,7 @@ void build_mfma64_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs, c
       const uint32_t o = (wv * (8 / NW) + i) * 1024;
       load_to_lds16(wsrc, o + lane * 16, ring_addr + NW * 2 * STAGE + o);
     }
-    if (lane < D / 4) load_to_lds16((const char*)(pr.bk + (size_t)h * D), lane * 16, ring_addr + NW * 2 * STAGE + D * ROWB);
+    load_to_lds4((const char*)(pr.bk + (size_t)h * D), lane * 4, ring_addr + NW * 2 * STAGE + D * ROWB);     // (D floats, no more aligned than those are)
   }
   const size_t row_bytes = (size_t)pr.stride_tok * 2;
   const size_t base_off = ((size_t)h * pr.stride_head + (size_t)g.n_sink * pr.stride_tok) * 2;

@@ -438,6 +438,10 @@ __device__ __forceinline__ void load_to_lds16(const void* base, uint32_t off, ui
 __device__ __forceinline__ void load_to_lds16_stream(const void* base, uint32_t off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(base), "s"(lds_addr) : "memory");
 }
+// 64 lanes x 4 bytes, to lds_addr + 4 * lane
+__device__ __forceinline__ void load_to_lds4(const void* base, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(off), "s"(base), "s"(lds_addr) : "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_vm_loads() {   // at most N vector memory operations still in flight
   static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");

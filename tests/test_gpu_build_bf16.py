@@ -86,3 +86,34 @@ def test_build_in_a_smaller_workspace(dtype, d, hkv, n, L, longer):
         O = PU.oracle_inputs(P)
         S, u = orc.build_summaries(O["K"], O["V"], O["Wk"], O["bk"], w.phi_in_scale, w.phi_norm_coef, w.n_sink, w.n_tail)
         PU.check_summaries(b.result(i, "S"), b.result(i, "u"), S, u, 2e-5)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+def test_biases_need_no_alignment(dtype, d):
+    """bk and bq as they may lie inside a larger fp32 buffer, 4, 8 and 12 bytes past a 16-byte boundary: S, u and the step's output keep their bits."""
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype=dtype, n_q_heads=4, n_kv_heads=2, d_head=d, d_phi=d, seed=94)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 500)
+    rng = np.random.default_rng(7)
+    P["bk"] = rng.standard_normal(P["bk"].shape).astype(np.float32)
+    P["bq"] = np.repeat(P["bk"], 2, axis=0)
+    b = H.Batch(H.config_of(w), [P], [9])
+    b.build()
+    b.decode()
+    want = {name: b.result(0, name) for name in ("S", "u", "out")}
+    for off in (1, 2, 3):
+        keep = {}
+        for name in ("bk", "bq"):
+            t = b.dev[0][name].flatten()
+            keep[name] = torch.full((t.numel() + 8,), float("nan"), dtype=torch.float32, device="cuda")
+            keep[name][off:off + t.numel()] = t
+            setattr(b.host_table[0], name, keep[name].data_ptr() + 4 * off)
+        for name in want:
+            b.dev[0][name].zero_()
+        b.set_topk(0, 9)                                # (uploads the table)
+        b.build()
+        b.decode()
+        torch.cuda.synchronize()
+        for name, x in want.items():
+            assert np.isfinite(x).all() and np.array_equal(b.result(0, name), x), (off, name)
