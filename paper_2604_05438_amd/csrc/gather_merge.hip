@@ -32,11 +32,12 @@ typedef GatherFrag Frag;
 // (absolute token indices), rows of d elements.  Each row is read by LPR = d / (elements per
 // 16 bytes) lanes with one 16-byte load; 256 threads cover 256 / LPR rows per pass and all
 // passes' loads are issued together, as soon as the tokens are known: the rows arrive beside the keys or features that the
-// weights are worked out from.  Results land in part[4 .. 4+d) and part[4+d .. 4+2d).
+// weights are worked out from (64 sequences of 16K at 20 %: 866 us per step against 882 with the rows requested behind those at d = 64, 1276 against 1298
+// at d = 128).  Results land in part[4 .. 4+d) and part[4+d .. 4+2d).
 // LDS scratch `red` must hold 2 * 256 * 8 floats.
-template <typename T>
+template <typename T, int D>   // rows of at most D elements
 struct ValueRows {
-  static constexpr int EPL = Elem<T>::per16, MAXP = 8;   // 64 rows / (256 / 32 lanes) passes at most
+  static constexpr int EPL = Elem<T>::per16, MAXP = 64 * D / (kThreads * EPL);   // passes
   u32x4 v[MAXP];
   __device__ __forceinline__ void request(const Geom& g, const tkphi_problem& pr, int64_t head_off, const int* tok, int cnt) {
     const int LPR = g.d / EPL, RPP = kThreads / LPR, seg = threadIdx.x % LPR, rsub = threadIdx.x / LPR;
@@ -46,10 +47,10 @@ struct ValueRows {
         v[ps] = gload128((const char*)pr.V + (head_off + (int64_t)tok[min(ps * RPP + rsub, cnt - 1)] * pr.stride_tok + seg * EPL) * sizeof(T));
   }
 };
-template <typename T>
-__device__ __forceinline__ void weighted_value_sums(const Geom& g, const ValueRows<T>& rows, const float* w, const float* z, int cnt,
+template <typename T, int D>
+__device__ __forceinline__ void weighted_value_sums(const Geom& g, const ValueRows<T, D>& rows, const float* w, const float* z, int cnt,
                                                     float* red, float* part, bool with_z) {
-  constexpr int EPL = Elem<T>::per16, MAXP = ValueRows<T>::MAXP;
+  constexpr int EPL = Elem<T>::per16, MAXP = ValueRows<T, D>::MAXP;
   const int tid = threadIdx.x, d = g.d;
   const int LPR = d / EPL, RPP = kThreads / LPR;      // rows per pass
   const int seg = tid % LPR, rsub = tid / LPR;
@@ -97,7 +98,7 @@ __device__ __forceinline__ ListEntry list_entry(const Geom& g, const char* blk, 
 // ---- anchors: exact terms over [0, n_sink) u [L - n_tail, L) (or every token if M is empty) --------
 // One workgroup per batch of 64 anchors (`batch` = 0, 1, ...): scores with LPR lanes per key
 // row (16-byte loads, butterfly sum), then the same weighted value sums as a retrieved tile.
-template <typename T>
+template <typename T, int D>
 __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, int n, int batch, float* part,
                                float* red) {
   constexpr int EPL = Elem<T>::per16;
@@ -124,10 +125,10 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
     a_tok[tid] = a >= n_prefill ? pr.L + (a - n_prefill) : (n > 0 && a >= g.n_sink) ? (pr.L - g.n_tail + (a - g.n_sink)) : a;
   }
   __syncthreads();
-  ValueRows<T> rows;
+  ValueRows<T, D> rows;
   rows.request(g, pr, head_off, a_tok, cnt);
   // scores of the batch
-  constexpr int MAXP = 8;
+  constexpr int MAXP = ValueRows<T, D>::MAXP;
   const int n_pass = (cnt + RPP - 1) / RPP;
   uint4 kv[MAXP];
 #pragma unroll
@@ -159,7 +160,7 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
     if (tid == 0) a_m = mb;
   }
   __syncthreads();
-  weighted_value_sums<T>(g, rows, a_w, a_w, cnt, red, a_acc, false);
+  weighted_value_sums(g, rows, a_w, a_w, cnt, red, a_acc, false);
   if (tid < 64) {
     const float Z = wave_sum(a_w[tid]);
     if (tid == 0) { part[0] = a_m; part[1] = Z; part[2] = 0.f; part[3] = (float)cnt; }
@@ -170,6 +171,10 @@ __device__ void anchor_partial(const Geom& g, const tkphi_problem& pr, int gq, i
 // ---- summary terms: S_M^T phi_q and phi_q . u_M of a query head -> off_sphi, off_uphi ----------------------------------
 // One workgroup per head of the gather launches, beside its tiles: at the head of the merge, whose few workgroups wait for 64 KB of S
 // at d = 128, they took 4 of its 9.8 us.  Sums in a fixed order: features of a group in order, groups in order.  red: 1536 floats
+// MAXF: rows of S that a thread requests together, no more than the head dimension calls for: these registers are the whole kernel's (with
+// 16 at d = 64, where a thread has 4, and 8 value rows for the 2 there are, gather_mfma_kernel<64> held 5 wavefronts to a SIMD instead of 7
+// and 64 sequences of 16K at 20 % took 976 us per step instead of 866)
+template <int MAXF>
 __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem& pr, char* blk, int gq, float* red) {
   const int tid = threadIdx.x, d = g.d, dphi = g.dphi, h = gq / g.G;
   float* sh_phiq = red + 1024;
@@ -177,7 +182,6 @@ __device__ __forceinline__ void summary_terms(const Geom& g, const tkphi_problem
   const int QPR = d / 4, NG = kThreads / QPR;      // float4 per row of S; feature groups (8 for d = 128, 16 for d = 64)
   const int jg = tid / QPR, c4 = tid % QPR, per = (dphi + NG - 1) / NG, j0 = jg * per, j1 = min(dphi, j0 + per);
   const float* __restrict__ S = pr.S + (size_t)h * dphi * d;
-  constexpr int MAXF = 16;                         // rows of S requested together (all of a thread's at d_phi = 128)
   u32x4 sv[MAXF];
   auto request = [&](int jb) {
 #pragma unroll
@@ -244,8 +248,8 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
-  if (tile >= g.n_tiles) { anchor_partial<uint16_t>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms<D * D / 4 / kThreads>(g, pr, blk, gq, red); return; }
+  if (tile >= g.n_tiles) { anchor_partial<uint16_t, D>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   }
   __syncthreads();
   const int64_t head_off = (int64_t)h * pr.stride_head;
-  ValueRows<uint16_t> rows;
+  ValueRows<uint16_t, D> rows;
   rows.request(g, pr, head_off, p_tok, cnt);
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
@@ -306,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<uint16_t>(g, rows, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < D) { part[4 + tid] = acc_part[4 + tid]; part[4 + D + tid] = acc_part[4 + D + tid]; }
   if (tid < 64) {
     const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
@@ -339,8 +343,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
-  if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms<8>(g, pr, blk, gq, red); return; }
+  if (tile >= g.n_tiles) { anchor_partial<T, 128>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   }
   for (int i = tid; i < 2 * d + 4; i += kThreads) acc_part[i] = 0.f;
   __syncthreads();
-  ValueRows<T> rows;
+  ValueRows<T, 128> rows;
   rows.request(g, pr, head_off, p_tok, cnt);
   {
     // key rows -> LDS (fp32): 16-byte pieces, (row, segment) pairs dealt over the threads
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<T>(g, rows, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < d) { part[4 + tid] = acc_part[4 + tid]; part[4 + d + tid] = acc_part[4 + d + tid]; }
   if (tid < 64) {
     const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
@@ -476,8 +480,8 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   char* blk = problem_block(g, ws, p);
   float* part = (float*)(blk + g.off_part) + ((size_t)gq * (g.n_tiles + g.n_atiles) + tile) * g.part_stride;
-  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms(g, pr, blk, gq, red); return; }
-  if (tile >= g.n_tiles) { anchor_partial<T>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
+  if (tile == g.n_tiles + g.n_atiles) { if (has_residual(mode, n, retrieved_of(g, pr, n))) summary_terms<8>(g, pr, blk, gq, red); return; }
+  if (tile >= g.n_tiles) { anchor_partial<T, 128>(g, pr, gq, n, tile - g.n_tiles, part, red); return; }
   const int i0 = tile * kPairsPerWG;
   const ListEntry le = list_entry(g, blk, gq, i0);
   const int Ksel = ((const SelPlan*)(blk + g.off_plan))[gq].n_sel;
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   }
   for (int i = tid; i < 2 * d + 4; i += kThreads) acc_part[i] = 0.f;
   __syncthreads();
-  ValueRows<T> rows;
+  ValueRows<T, 128> rows;
   rows.request(g, pr, head_off, p_tok, cnt);
   if (tid < 64) {                                  // m_loc = max score of the tile
     float m = p_s[tid];
@@ -537,7 +541,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   if (tid < kPairsPerWG) p_w[tid] = tid < cnt ? __expf(p_s[tid] - sh_m) : 0.f;
   __syncthreads();
 
-  weighted_value_sums<T>(g, rows, p_w, p_z, cnt, red, acc_part, true);
+  weighted_value_sums(g, rows, p_w, p_z, cnt, red, acc_part, true);
   if (tid < d) { part[4 + tid] = acc_part[4 + tid]; part[4 + d + tid] = acc_part[4 + d + tid]; }
   if (tid < 64) {
     const float Z = wave_sum(p_w[tid]), zs = wave_sum(tid < cnt ? p_z[tid] : 0.f);
