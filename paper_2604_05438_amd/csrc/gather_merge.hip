@@ -243,6 +243,7 @@ __global__ __launch_bounds__(kThreads) void gather_mfma_kernel(Geom g, const tkp
   __shared__ float sh_m;
 
   const int tile = blockIdx.x, gq = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
+  if (tile > g.n_tiles + g.n_atiles) return;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -338,6 +339,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(Geom g, const tkphi_pr
   __shared__ float acc_part[2 * 128 + 4];
   __shared__ float sh_m;
   const int tile = blockIdx.x, gq = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
+  if (tile > g.n_tiles + g.n_atiles) return;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -475,6 +477,7 @@ __global__ __launch_bounds__(kThreads) void gather_cached_kernel(Geom g, const t
   __shared__ float acc_part[2 * 128 + 4];
   __shared__ float sh_m;
   const int tile = blockIdx.x, gq = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
+  if (tile > g.n_tiles + g.n_atiles) return;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
@@ -557,8 +560,12 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(Geom g, const tkphi_pro
   merge_head<true, false>(g, probs, ws, (int)blockIdx.x, (int)blockIdx.y, mode);
 }
 
+// Blocks of a query head: the tiles, the anchor tiles, the summary terms, and an idle one if those are an even number.  Workgroups go to the 8 XCDs in
+// turn; with 16 per head the light ones (anchors, summary terms) of all heads would share three XCDs and the others get two
+// tiles of every head (16 fp32 sequences of 20K at 4 %, us per step with 16 blocks and with 17: d = 128 664 / 623, d = 64 386 / 367).
+static int gather_blocks(const Geom& g) { return (g.n_tiles + g.n_atiles + 1) | 1; }
 void launch_gather(const Geom& g, const tkphi_problem* probs, char* ws, int mode, hipStream_t s) {
-  dim3 grid(g.n_tiles + g.n_atiles + 1, g.Hq, g.n_problems);
+  dim3 grid(gather_blocks(g), g.Hq, g.n_problems);
   if (g.cache || g.sel_feat) {
     if (g.dtype == TKPHI_BF16) TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<uint16_t>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
     else TKPHI_LAUNCH(ST_GATHER, gather_cached_kernel<float>, grid, dim3(kThreads), 0, s, g, probs, ws, mode);
