@@ -327,9 +327,9 @@ tkphi_status tkphi_decode_static(const tkphi_config* cfg /*HOST*/,
  *   score_mid (either pipeline's score pass), select_plan (+ the exp-affine phi_q), select_emit,
  *   select_resolve, gather (exact branch + subtraction sums), merge (spill pipeline), phi_q (the
  *   phi_q launches of the MLP feature maps, begin of the first to end of the last; or, for a
- *   batch on the filtered pipeline at d = 128, the phi / anchor jobs of prep as a launch of their own), and the
- *   two kernels only the filtered pipeline has: prep (sampled score bound, for some calls also phi_q,
- *   the summary terms and the anchors; runs first; for one or a few problems part of score_mid) and select (selection, gather and merge)
+ *   batch on the filtered pipeline without any mid-region, the phi / anchor jobs), and the
+ *   two kernels only the filtered pipeline has: prep (sampled score bound; runs first; for one or a few problems part of
+ *   score_mid, as phi_q, the summary terms and the anchors are) and select (selection, gather and merge)
  * (0 for a stage that the given configuration and bounds do not launch).  Same validation and results as
  * tkphi_decode; creates and destroys HIP events (no device memory). */
 #define TKPHI_N_STAGES 9

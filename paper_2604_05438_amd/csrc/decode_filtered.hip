@@ -2,11 +2,10 @@
 //
 // The exhaustive Top-K over the mid-region (Sec. "Models, tasks, and protocol") needs every score
 // s_i = q . k_i / sqrt(d_h) once, but only the scores that can still reach the top K have to
-// leave the chip.  Two kernels and, from a few sequences on, a third for the phi and anchor jobs (decode_side_kernel) for
-// batches; one otherwise:
+// leave the chip.  Two launches for batches and very long sequences, decode_prep and score_filtered; one otherwise:
 //
-//   decode_prep     one small launch of independent jobs that need no selection (at d = 64 the sample jobs only, the others are blocks of
-//                   score_filtered):
+//   decode_prep     one small launch of independent jobs that need no selection (of several problems the sample jobs only, the others are
+//                   blocks of score_filtered):
 //                   * sample: per KV head, the scores of an evenly spaced sample of mid-region rows
 //                     -> per query head a lower bound of the K-th largest score (a bin edge chosen so
 //                     that the sample count above it exceeds its expectation at the K-th score by five
@@ -346,19 +345,18 @@ __device__ __forceinline__ void prep_anchor(const Geom& g, const tkphi_problem& 
   }
 }
 
-// grid (jobs, Hkv, n_problems), 1024 threads; job = job0 + blockIdx.x of 1 + G (1 + n_atiles).  Job 0: sample; jobs
-// 1 .. G: phi of the group's query heads; then n_atiles anchor tiles per query head.  One launch for a few
-// problems; for batches the sample jobs (which need ~90 KB of LDS: one workgroup per CU) and the rest (16 KB) are
-// two launches, so that the many small jobs are not held to one workgroup per CU.
+// grid (jobs, Hkv, n_problems), 1024 threads.  Job 0: sample; of one problem also jobs 1 .. G: phi of the group's query heads, then
+// n_atiles anchor tiles per query head.  (The sample needs ~90 KB of LDS, one workgroup per CU: the many small jobs of a batch
+// would be held to that.)
 template <int D, int TPI>
 __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const tkphi_problem* __restrict__ probs,
-                                                                   char* __restrict__ ws, int job0) {
+                                                                   char* __restrict__ ws) {
   // sample job: sc [G][1024] floats + hist [G][kBins] + inb [G][kInBin] (G (4096 + 2048 + 1024) bytes), then the
   // staging strips, 16 wavefronts x 16 rows x (2 D + 16) bytes; phi / anchor jobs: 16 KB of reduction scratch
   extern __shared__ __attribute__((aligned(16))) float sh_dyn[];
   __shared__ float sh_a[kMaxDim], sh_b[kMaxDim];
   __shared__ int sh_nin[kMaxGroup];
-  const int job = job0 + (int)blockIdx.x, h = blockIdx.y, p = blockIdx.z;
+  const int job = blockIdx.x, h = blockIdx.y, p = blockIdx.z;
   TKPHI_PHASE(ws, 0);
   TKPHI_WAVE_MARK(ws, 32);                           // kernel entered
 
@@ -391,30 +389,36 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prep_kernel(Geom g, const
 // The phi and anchor jobs of KV head h of a problem as workgroups of 256 threads: job j < G: phi of query head h G + j (and that head's
 // arrival counter <- 0: nobody has arrived yet at its merge), then n_atiles anchor tiles per query head.
 constexpr int kSideLds = (2 * kMaxDim + 1024) * (int)sizeof(float);
-template <int D, int EARLY>
+template <int D, int EARLY, typename T = uint16_t>
 __device__ __forceinline__ void side_job(const Geom& g, const tkphi_problem& pr, char* blk, int h, int job, float* sh_f) {
   if (job < g.G) {
     if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + job] = 0u;
-    side_phi<D, EARLY>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
+    side_phi<D, EARLY, T>(g, pr, blk, h * g.G + job, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
   } else {
     const int j = job - g.G;
-    side_anchor<D>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
+    side_anchor<D, T>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
   }
 }
 
-// At d = 64 the phi and anchor jobs of a batch are blocks of the score launch, behind the chunks of their KV head: they hide among the chunks (a
-// launch of their own took 55 us of 256 ragged sequences' 2558, 6.5 of 48 for 16 of 2K..8K; on the sample launch, at one 1024-thread workgroup
-// per CU, 7 of 57 for 8 of 8K..30K; now 2470, 44.9 and 51.8).  At d = 128, where a head's S is 64 KB, they hold the stream up for as long or
-// longer: 16 sequences of 10K..40K 199 -> 204, 8 of 15K..60K 127 -> 129, 11 of 6K..25K 98.7 -> 93.4; there they stay apart.
-// As many blocks as make those of a KV head an odd number in all: workgroups go to XCDs (and in them to CUs) in turn by their linear index, the
-// chunks of short sequences are empty and the side jobs light, and with an odd number a chunk's place runs through all 256 CUs from
-// head to head (with 16 + 16 blocks 256 ragged sequences took 3500 us).
-__host__ __device__ __forceinline__ int side_blocks(const Geom& g) {
+// The phi and anchor jobs of several problems are blocks of the score launch, behind all its chunks: the last of those leave room on
+// the CUs (a launch of their own, us per step before / now: d = 64, 256 ragged sequences of 64K 2300 / 2200, 64 of 16K 276 / 259, 16
+// ragged ones of 20K 79 / 69; d = 128, 64 of 16K 491 / 471, 16 ragged ones of 40K 206 / 194; on the sample launch 11 of 25K 108 / 100).  Among
+// the chunks they take the places of workgroups that stream (64 ragged sequences of 17K with 8 / 8 heads of 64: 156 apart, 164 among
+// them, 149 behind them; 32 of 36K with 32 / 4 160, 163, 148).  Of a single problem the prep launch has them, whose sample leaves most CUs
+// idle (64 / 8 heads of 64 at 500K: 119, among the chunks 128), up to four of those workgroups per CU.
+__host__ __device__ __forceinline__ int side_jobs(const Geom& g) {
   const int jobs = g.G * (1 + g.n_atiles);
-  return g.d != 64 ? 0 : jobs + ((jobs + g.n_scan_chunks) % 2 == 0 ? 1 : 0);
+  return g.n_problems == 1 && (1 + jobs) * g.Hkv <= 1024 ? 0 : jobs;
 }
 
-// grid (n_scan_chunks + side_blocks, Hkv, n_problems), 256 threads: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
+// Chunk of block x of the KV head with running number `head`.  Workgroups go to the XCDs, there to the shader engines and to CUs in turn by their
+// index, and the short sequences of a ragged batch have no late chunks: rotated by the head's number, all places get early
+// and late ones alike.  For S < 32 blocks per head that comes around: after 256 workgroups the same chunk is at the same place again if S is 8 or
+// 16 (from 32 on only every fourth time), so the rotation moves on with every 256 (d = 128, 150 ragged sequences of 25K 1.29 times as
+// fast by it, 100 of 32K 1.12; d = 64, 200 of 32K 1100 -> 953 us; with S >= 32 12 of 128K at d = 128 would lose 2.4 %).
+__device__ __forceinline__ int chunk_at(uint32_t x, uint32_t head, uint32_t S) { return (int)((x + head + (S < 32 ? head * S / 256 : 0)) % S); }
+
+// 256 threads; the chunks of all KV heads, then their side jobs, numbered over a grid of one or more rows: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
 // caches, by the latency of a few round trips for short ones.  A wavefront holds two groups of TPI / 4 tiles, one on its way
 // while the other is contracted: whole units at a time (16 loads, wait, 16 tiles' scores, next unit) took 49.5 us
 // against 47.9 for the 3B layer at 128K, 13.2 against 8.7 us for the 1B layer at 32K; three or four groups ahead, or groups twice
@@ -423,21 +427,22 @@ __host__ __device__ __forceinline__ int side_blocks(const Geom& g) {
 template <int D, int TPI, bool STREAM, bool STRIP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void score_filtered_kernel(Geom g, const tkphi_problem* __restrict__ probs,
                                                                   char* __restrict__ ws) {
-  const int p = blockIdx.z, h = blockIdx.y;
+  extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]; side jobs: kSideLds bytes
+  const uint32_t S = g.n_scan_chunks, heads = (uint32_t)g.Hkv * g.n_problems, at = blockIdx.y * gridDim.x + blockIdx.x;
+  const bool side = at >= S * heads;
+  const uint32_t i = side ? at - S * heads : at, per = side ? side_jobs(g) : S, head = per ? i / per : heads;
+  if (head >= heads) return;                       // (behind the last job of a grid of several rows)
+  const int x = i - head * per, p = head / g.Hkv, h = head % g.Hkv;
   const tkphi_problem pr = probs[p];
   if (pr.L < 1 || pr.L > g.max_L) return;
-  extern __shared__ __attribute__((aligned(16))) st_u32x2 sh_heads[];      // [4 wavefronts][G][cand_T]; side jobs: kSideLds bytes
   char* blk = problem_block(g, ws, p);
-  if (D == 64 && (int)blockIdx.x >= g.n_scan_chunks) {
-    const int job = (int)blockIdx.x - g.n_scan_chunks;
-    if (job < g.G * (1 + g.n_atiles)) side_job<D, 0>(g, pr, blk, h, job, (float*)sh_heads);
+  if (side) {
+    side_job<D, 0>(g, pr, blk, h, x, (float*)sh_heads);
     return;
   }
   const int n = mid_size(pr.L, g.n_sink, g.n_tail);
   const int n_chunks = (n + g.scan_chunk - 1) / g.scan_chunk;
-  // (d = 128: chunk indices rotated per head and problem: workgroups go to the 8 XCDs round-robin by linear
-  // index and the short sequences of a ragged batch have no late chunks)
-  const int chunk = D == 64 ? (int)blockIdx.x : ((int)blockIdx.x + h + p * g.Hkv) % (int)gridDim.x;
+  const int chunk = chunk_at(x, head, S);
   if (chunk >= n_chunks) return;
   const int r = threadIdx.x & 15;
   ScoreFrag bq[kTileFrags<D>];
@@ -556,7 +561,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
   score_fused_job<D, TPI, STREAM, false>(g, probs, ws, x - p * per + ahead, p);
 }
 
-// The phi and anchor jobs of a batch as a launch (d = 128, or no mid-region to score): grid (G (1 + n_atiles), Hkv, n_problems), 256 threads
+// The phi and anchor jobs as a launch, where there is no mid-region to score: grid (G (1 + n_atiles), Hkv, n_problems), 256 threads
 template <int D>
 __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkphi_problem* __restrict__ probs, char* __restrict__ ws) {
   __shared__ __attribute__((aligned(16))) float sh_f[2 * kMaxDim + 1024];
@@ -567,7 +572,7 @@ __global__ __launch_bounds__(kThreads) void decode_side_kernel(Geom g, const tkp
 }
 
 // The front end of short contexts (Geom::direct) in one launch: grid (G (1 + n_atiles) + n_scan_chunks, Hkv, n_problems), 256
-// threads; first the phi and anchor jobs (as in decode_side_kernel), then the score chunks, which store every score: the
+// threads; first the phi and anchor jobs, then the score chunks, which store every score: the
 // select kernel takes the exact threshold from all of them, and the sample job, a launch that nothing could overlap with
 // (7-9 us), is not needed.
 template <int D, int TPI, int EARLY>
@@ -623,13 +628,7 @@ __global__ __launch_bounds__(kThreads) void score_direct_f32_kernel(Geom g, cons
   if (pr.L < 1 || pr.L > g.max_L) return;
   char* blk = problem_block(g, ws, p);
   if (x < n_side) {
-    if (x < g.G) {
-      if (threadIdx.x == 0) ((uint32_t*)(blk + g.off_mcount))[h * g.G + x] = 0u;
-      side_phi<D, 0, float>(g, pr, blk, h * g.G + x, sh_f, sh_f + kMaxDim, sh_f + 2 * kMaxDim);
-    } else {
-      const int j = x - g.G;
-      side_anchor<D, float>(g, pr, blk, h * g.G + j / g.n_atiles, j % g.n_atiles, sh_f, sh_f + 64, sh_f + 128);
-    }
+    side_job<D, 0, float>(g, pr, blk, h, x, sh_f);
     return;
   }
   const int n = mid_size(pr.L, g.n_sink, g.n_tail), row0 = (x - n_side) * kDirectRowsF32;
@@ -676,32 +675,29 @@ void launch_score_direct(const Geom& g, const tkphi_problem* probs, char* ws, hi
 }
 
 void launch_prep(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  dim3 grid(1 + g.G * (1 + g.n_atiles), g.Hkv, g.n_problems);
+  dim3 grid(side_jobs(g) ? 1 : 1 + g.G * (1 + g.n_atiles), g.Hkv, g.n_problems);
   // <= 56 KB at G = 8, plus 68 KB (d = 128) / 36 KB (d = 64) of staging strips
   const size_t lds = std::max((size_t)g.G * (1024 + kBins + kInBin) * 4 + (size_t)kPrepWaves * 16 * (g.d * 2 + 16), (size_t)16384);
-  const void* fn = g.d == 128 ? (const void*)decode_prep_kernel<128, 4> : (const void*)decode_prep_kernel<64, 8>;
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
-  const int n_jobs = 1 + g.G * (1 + g.n_atiles);
-  if (g.d == 64) {                     // (the other jobs ride in the score launch, if there is one)
-    TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<64, 8>), dim3(1, g.Hkv, g.n_problems), dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-    if (g.max_mid == 0) TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<64>, dim3(n_jobs - 1, g.Hkv, g.n_problems), dim3(kThreads), 0, s, g, probs, ws);
-    return;
-  }
-  if ((long)n_jobs * g.Hkv * g.n_problems <= 1024) {
-    TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-    return;
-  }
-  dim3 grid_a(1, g.Hkv, g.n_problems), grid_b(n_jobs - 1, g.Hkv, g.n_problems);
-  TKPHI_LAUNCH(ST_PREP, (decode_prep_kernel<128, 4>), grid_a, dim3(kPrepThreads), lds, s, g, probs, ws, 0);
-  TKPHI_LAUNCH(ST_PHIQ, decode_side_kernel<128>, grid_b, dim3(kThreads), 0, s, g, probs, ws);
+  const auto launch = [&](auto fn) {
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) { set_error("hipFuncSetAttribute(%zu bytes of LDS): %s", lds, hipGetErrorString(e)); return; }
+    TKPHI_LAUNCH(ST_PREP, fn, grid, dim3(kPrepThreads), lds, s, g, probs, ws);
+  };
+  if (g.d == 128) launch(decode_prep_kernel<128, 4>); else launch(decode_prep_kernel<64, 8>);
 }
 
 void launch_score_filtered(const Geom& g, const tkphi_problem* probs, char* ws, hipStream_t s) {
-  if (g.max_mid == 0) return;
-  dim3 grid(g.n_scan_chunks + side_blocks(g), g.Hkv, g.n_problems);
+  if (g.max_mid == 0) {
+    if (side_jobs(g) == 0) return;
+    const auto launch_side = [&](auto fn) { TKPHI_LAUNCH(ST_PHIQ, fn, dim3(side_jobs(g), g.Hkv, g.n_problems), dim3(kThreads), 0, s, g, probs, ws); };
+    if (g.d == 128) launch_side(decode_side_kernel<128>); else launch_side(decode_side_kernel<64>);
+    return;
+  }
+  const int64_t blocks = (int64_t)(g.n_scan_chunks + side_jobs(g)) * g.Hkv * g.n_problems;
+  constexpr int64_t row = 1 << 20;                   // (a row of 256-thread workgroups holds less than 2^32 threads)
+  const dim3 grid((unsigned)std::min(blocks, row), (unsigned)((blocks + row - 1) / row));
   const size_t strips = g.head_strip ? (size_t)4 * g.G * g.cand_T * sizeof(uint2) : 0;   // the wavefronts' strips of list heads
-  const size_t lds = g.d == 64 ? std::max(strips, (size_t)kSideLds) : strips;
+  const size_t lds = std::max(strips, side_jobs(g) ? (size_t)kSideLds : 0);
   const auto launch = [&](auto fn) { TKPHI_LAUNCH(ST_SCORE, fn, grid, dim3(kThreads), lds, s, g, probs, ws); };
   const auto launch_as = [&](auto strip, auto stream) {
     if (g.d == 128) launch(score_filtered_kernel<128, 4, decltype(stream)::value, decltype(strip)::value>);
