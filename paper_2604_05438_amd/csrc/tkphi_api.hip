@@ -269,15 +269,18 @@ static tkphi_status make_geom_as(const tkphi_config* cfg, int n_problems, int ma
   // kernel spends 32 times the bf16 one's time on a token: there a workgroup takes as little as one tile of 64
   const bool f32_build = !g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE;
   // One problem at d = 64: one workgroup per CU (the wavefronts have no barrier to hide, and half the workgroups leave half the
-  // partials: 20K 17.2 -> 15.2 us, 32K 21.3 -> 20.0, 128K 51.7 -> 49.5; two and four per CU are better where sequences differ in length)
+  // partials: 20K 17.2 -> 15.2 us, 32K 21.3 -> 20.0, 128K 51.7 -> 49.5).  Several: two per CU, whether their lengths differ or not, which the
+  // bounds do not tell (3 ragged ones of 5K to 20K: two per CU 24.4, one 26.6; 2 of 32K: two 31.3, one 28.2)
   const bool one_per_cu = g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->d == 64 && n_problems == 1;
-  // Short layers at d = 128 too, as long as its tiles of four wavefronts (0.9 us each) weigh more than its partials of 66 KB: chunks from 64
-  // up to 384, one workgroup per CU (1.5K tokens 17.3 -> 12.8 us, 3K 18.3 -> 15.1, 6K 19.3 -> 18.0, 9K 25.3 -> 21.6, 12K 28.0 -> 24.4; 16K in
-  // chunks of 384 33.1 against 32.7 with two per CU)
+  // Short layers at d = 128 too, as long as its tiles of four wavefronts (0.9 us each) weigh more than its partials of 66 KB: up to 384 tokens a
+  // chunk for one workgroup per CU (8 KV heads: 7K tokens 23.6 -> 22.2 us, 9K 28.6 -> 24.2, 12K 30.6 -> 27.6; 16K in chunks of 384 33.1
+  // against 32.7 with two per CU), but chunks of up to 192 for about 200 workgroups (of 64: 160), since the reduction adds a head's partials one behind
+  // the other (8 KV heads: 3K 19.4 -> 16.8, 1.5K in chunks of 64 15.0 and of 128 14.2 against 18.1; 1 KV head: 16K in chunks of 64
+  // 19.0 and of 128 15.5 against 17.9, 32K in chunks of 128 21.2 and of 192 19.7 against 20.7)
   const bool short_layer = g->use_mfma && cfg->phi_kind == TKPHI_PHI_EXP_AFFINE && g->d == 128 && !compact;
   const int64_t per_cu = ceil_div(units, 256), two_per_cu = ceil_div(units, 512);
   const int64_t bc_small = one_per_cu ? std::clamp<int64_t>(per_cu, 256, 4096)
-                           : short_layer ? (per_cu <= 384 ? std::max<int64_t>(per_cu, 64) : std::clamp<int64_t>(two_per_cu, 256, 2048))
+                           : short_layer ? (per_cu <= 384 ? std::max(per_cu, std::clamp<int64_t>(ceil_div(units, 208), units <= 160 * 64 ? 64 : 128, 192)) : std::clamp<int64_t>(two_per_cu, 256, 2048))
                                          : std::clamp<int64_t>(two_per_cu, f32_build && !compact ? 64 : 256, 2048);
   int bc = (int)align_up((size_t)std::clamp<int64_t>(ceil_div(units, 2048), bc_small, 1 << 20), 64);
   if (!g->use_mfma) bc = std::min(bc, 4096);    // fp32 FMA chains stay short on the generic kernel
