@@ -117,3 +117,62 @@ def test_biases_need_no_alignment(dtype, d):
         torch.cuda.synchronize()
         for name, x in want.items():
             assert np.isfinite(x).all() and np.array_equal(b.result(0, name), x), (off, name)
+
+
+@pytest.mark.parametrize("cache", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinite_and_undefined_rows(d, cache):
+    """What keys and values that are infinite or no numbers reach, and nothing else: a row is contracted into S and u of its own head, a value only
+    into its channel, rows outside the mid-region into nothing.  (fp32 exponents: a key whose squared norm overflows has features 0 if its products stay finite.)"""
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=3, n_kv_heads=3, d_head=d, d_phi=d, seed=93)
+    P = I.make_layer(w, L=w.n_sink + w.n_tail + 1000)
+    cfg = H.config_of(w, cache_features=cache)
+    clean = H.Batch(cfg, [P], [1])
+    clean.build()
+    S, u = clean.result(0, "S"), clean.result(0, "u")
+    assert np.isfinite(S).all() and np.isfinite(u).all()
+    inf, nan = float("inf"), float("nan")
+    last = w.n_sink + 999                               # the last row of the mid-region, which the padding of a tile repeats
+
+    def build(edit):
+        K, V = clean.dev[0]["K"].clone(), clean.dev[0]["V"].clone()
+        edit(K, V)
+        b = H.Batch(cfg, [dict(P, K=K, V=V)], [1])
+        b.build()
+        torch.cuda.synchronize()
+        assert b.status() == 0
+        return b.result(0, "S"), b.result(0, "u")
+
+    for tok in (w.n_sink, w.n_sink + 517, last):
+        for x in (inf, -inf, nan):
+            def value(K, V):
+                V[1, tok, 5] = x
+            Sx, ux = build(value)
+            assert np.array_equal(ux, u) and np.array_equal(Sx[[0, 2]], S[[0, 2]])
+            rest = [c for c in range(d) if c != 5]
+            assert np.array_equal(Sx[1][:, rest], S[1][:, rest]) and not np.isfinite(Sx[1][:, 5]).any()
+
+            def key(K, V):
+                K[1, tok, 5] = x
+            Sx, ux = build(key)
+            assert np.array_equal(ux[[0, 2]], u[[0, 2]]) and np.array_equal(Sx[[0, 2]], S[[0, 2]])
+            if x != x:
+                assert np.isnan(ux[1]).all() and np.isnan(Sx[1]).all()
+    # rows outside the mid-region
+    def outside(K, V):
+        for t in (K, V):
+            t[:, :w.n_sink] = nan
+            t[:, last + 1:] = inf
+    Sx, ux = build(outside)
+    assert np.array_equal(Sx, S) and np.array_equal(ux, u)
+
+    # a row of norm^2 beyond fp32, its products with W finite: features of exp(-inf) = 0, as if the row were not there
+    def huge(K, V):
+        K[1, w.n_sink + 517] = 2.0 ** 64
+    def gone(K, V):
+        K[1, w.n_sink + 517] = 64.0                     # (|k|^2 / (2 sqrt d) in the thousands: exp underflows)
+    Sh, uh = build(huge)
+    Sg, ug = build(gone)
+    assert np.array_equal(Sh, Sg) and np.array_equal(uh, ug) and np.isfinite(Sh).all()

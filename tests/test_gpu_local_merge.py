@@ -42,11 +42,52 @@ def test_local_merge(dtype, d, mids, ks, tail, gen, mode):
             PU.check_layer(w, P, k, export, i, heads=[0, 31], sum_tol=2e-5)
 
 
-@pytest.mark.parametrize("d,ks", [(64, [256, 257, 511, 512, 513, 1024, 1025, 1536, 1600]), (64, [255, 256, 257, 512, 513, 700, 1000, 1023, 1024]),
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("d,mid,ks,tail,gen", [
+    (64, 3000, [1, 60, 128, 250, 0, 129], 60, 2), (64, 3000, [37], 317, 64),                  # 17 problems of 32 heads: 512 threads; scores by rows, six tiles and seven
+    (64, 30000, [256, 300, 1, 511], 60, 0), (64, 30000, [300], 300, 10),                      # the same from lists
+    (128, 2000, [128, 5], 60, 2), (128, 15000, [180, 0], 60, 2)])                             # 1024 threads
+def test_local_merge_writes_aux(d, mid, ks, tail, gen, mode):
+    """The same for a call that wants `aux` but no indices, which is merged out of LDS too, and for heads of the 512-thread kernel: outputs and
+    aux agree bit for bit with the merge by way of the workspace, and with the oracle at the bars of parity_utils."""
+    import parity_utils as PU
+    import torch
+    from paper_2604_05438_amd import harness as H
+    w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=32, n_kv_heads=8, d_head=d, d_phi=d, n_sink=4, n_tail=tail, seed=97)
+    n = 17
+    base = [I.make_layer(w, L=4 + tail + mid + gen, seq=i) for i in range(2)]
+    for P in base:
+        P.update(L=4 + tail + mid, n_gen=gen)
+    layers, kk = [base[i % 2] for i in range(n)], [ks[i % len(ks)] for i in range(n)]
+    plain = H.Batch(H.config_of(w, max_gen=gen), layers, kk)
+    with_aux = H.Batch(H.config_of(w, max_gen=gen), layers, kk, debug=True)
+    export = H.Batch(H.config_of(w, max_gen=gen), layers, kk, debug=True)
+    for i in range(n):
+        with_aux.host_table[i].topk_idx = None
+        with_aux.dev[i]["topk_idx"].fill_(-5)
+        with_aux.dev[i]["aux"].fill_(float("nan"))
+    with_aux.set_topk(0, kk[0])                         # (uploads the table)
+    for b in (plain, with_aux, export):
+        b.build()
+        b.decode(mode)
+        torch.cuda.synchronize()
+        assert b.status() & ~2 == 0
+    for i in range(n):
+        y = plain.result(i, "out")
+        assert np.isfinite(y).all() and np.array_equal(y, export.result(i, "out")) and np.array_equal(y, with_aux.result(i, "out")), i
+        assert np.array_equal(with_aux.result(i, "aux"), export.result(i, "aux")), i
+        assert (with_aux.result(i, "topk_idx") == -5).all()
+    if mode == 0 and mid <= 3000:
+        for i in range(0, min(n, 2 * len(ks)), 2 if len(ks) == 1 else 1):
+            PU.check_layer(w, layers[i], kk[i], export, i, heads=[0, 31], sum_tol=2e-5)
+
+
+@pytest.mark.parametrize("d,ks", [(64, [256, 257, 511, 512, 513, 1024, 1025, 1536, 1600]), (64, [255, 256, 257, 511, 512, 513, 700, 1023, 1024] * 2),
                                   (128, [255, 256, 257, 511, 512, 513, 1024, 1536, 1600])])
 def test_gather_rounds(d, ks):
-    """One workgroup per head (9 problems of 32 heads), winners around the rounds of 256 and 512 and beyond those kept in LDS (1024 or 1536),
-    against the oracle at the bars of parity_utils."""
+    """One workgroup per head, winners around the rounds, against the oracle at the bars of parity_utils: 9 problems of 32 heads, rounds of 512
+    (d = 64) or 256, and beyond the 1536 winners kept in LDS; 18 problems at d = 64 and at most 1024 winners, all of which are kept: the
+    512-thread kernel and its rounds of 256."""
     import parity_utils as PU
     from paper_2604_05438_amd import harness as H
     w = dataclasses.replace(I.WORKLOADS["tiny_f32"], dtype="bf16", n_q_heads=32, n_kv_heads=8, d_head=d, d_phi=d, seed=98)
