@@ -240,7 +240,7 @@ __device__ __forceinline__ bool select_gather_body(const Geom& g, const tkphi_pr
   // earlier launch left, are requested here, long before they are needed.  By way of memory, as from workgroup to workgroup, the
   // merge of a short context was 3 us of 12.5 (two round trips at the end of the chain): 1B layer at 4K 19.4 -> 18.0 us per step, 3B layer at
   // 2K 19.1 -> 17.8, one fp32 head of 4K 17.1 -> 15.9, 256 ragged sequences 2630 -> 2587.
-  // (what the end needs of the record waits in LDS: as scalars they would have to be spilled)
+  // (what the end needs of the record waits in LDS: the list kernels with a merge of their own already spill 57 to 64 scalars)
   if (LOCAL && tid == 0) {
     const int n_at = (g.n_sink + g.n_tail + min(max(pr.n_gen, 0), g.max_gen) + 63) / 64;
     const bool local = !pr.topk_idx && n_at <= kLocalTiles;
@@ -846,7 +846,7 @@ void launch_select_gather(const Geom& g, const tkphi_problem* probs, char* ws, i
     grid = dim3(g.Hq + g.d_emb / 64 * g.Hq + (pack ? g.Hkv * std::max(1, 192 / g.Hkv) : 0));
   }
   const auto launch = [&](auto fn, int threads) { TKPHI_LAUNCH(ST_SELECT, fn, grid, dim3(threads), 0, s, g, probs, ws, mode); };
-  // (the kernel of a head's only workgroup is one of its own: the scalars of its merge would be spilled in the other)
+  // (the kernel of a head's only workgroup is one of its own: lists with the merge in it spill 57 to 64 scalars to vector registers, without it 15 to 17)
   const bool direct = g.direct, local = g.sg_split == 1;
 #define TKPHI_SELECT(D, NTHR)                                                                                              \
   do {                                                                                                                     \

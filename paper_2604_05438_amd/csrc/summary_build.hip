@@ -22,8 +22,9 @@ union Frag {
   bf16x8 v;
 };
 
-// What the build kernels need of Geom: a launch that copies all of it (0.5 KB of arguments) costs the host 3.3 us, and the next launch
-// follows after 3.8, with 64 bytes 2.8 both (short builds are bound by that: two launches with 4 and 7 us of work).
+// What the build kernels need of Geom, 88 bytes of arguments with the two pointers instead of 464 when they were handed all of it. A
+// launch with 720 bytes costs the host 3.3 us, and the next launch follows after 3.8, with 64 bytes 2.8 both (short builds are bound by
+// that: two launches with 4 and 7 us of work).
 struct BuildGeom {
   int Hkv, d, dphi, n_sink, n_tail, n_problems, max_L, max_gen, build_chunk, n_build_chunks, cache;
   float a, c;
@@ -300,9 +301,9 @@ void build_mfma_kernel(BuildGeom g, const tkphi_problem* __restrict__ probs, cha
 // end, through LDS, in wavefront order.  Contractions and operand layouts as in the kernel above (values: f = 2 ((row / 2) mod 4), keys:
 // f = (row / 2) mod 8, rows of 128 bytes).  Two stages of 8 KB per wavefront; the keys' half of a stage is refilled as soon as
 // its fragments are in registers.
-// What bounds it: the memory pipeline.  16 sequences of 64K (2.1 GB): 371 us per call, 343 without the arithmetic, with slices of
-// 16 features per wavefront and a barrier per tile (the form of the kernel above, 4 workgroups per CU) 395; 16 ragged ones of 16K..64K 317 ->
-// 300; one of 128K 57 -> 52, of 32K 21.8 -> 20.0, of 12K 14.6 -> 12.7.  8 wavefronts per workgroup: 32K 26.6, ragged 321.
+// What bounds it: the memory pipeline.  Per call, with slices of 16 features per wavefront and a barrier per tile (the form of the kernel above, 4
+// workgroups per CU) and so: 16 sequences of 64K (2.1 GB) 382 -> 369 us (343 without the arithmetic), 16 ragged ones of 16K..64K 314 ->
+// 298, one of 128K 56.4 -> 48.9, of 32K 21.1 -> 18.5, of 12K 14.8 -> 12.5.  8 wavefronts per workgroup: 32K 26.6, ragged 321.
 // ------------------------------------------------------------------------------------
 template <int NW, bool CACHE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))

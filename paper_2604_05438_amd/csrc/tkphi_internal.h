@@ -36,7 +36,7 @@ constexpr int direct_unit_f32 = 128;     // Geom::scan_unit of fp32 caches where
 constexpr int keep_unit(int d) { return d == 128 ? 64 : 128; }   // Geom::scan_unit where Geom::fused
 
 // An offset inside a problem's block (less than 1 TB), in 32 bits as 256-byte units: a launch copies its Geom, and every cache line of
-// arguments is one more that its first instructions wait for (0.1 to 0.2 us of a short decode step).
+// arguments is one more that its first instructions wait for (448 -> 344 bytes: 0.1 to 0.2 us of a short step at most, as much as repeated runs differ by).
 struct WsOffset {
   uint32_t units;
   WsOffset& operator=(size_t bytes) { units = (uint32_t)(bytes >> 8); return *this; }
