@@ -411,12 +411,17 @@ __host__ __device__ __forceinline__ int side_jobs(const Geom& g) {
   return g.n_problems == 1 && (1 + jobs) * g.Hkv <= 1024 ? 0 : jobs;
 }
 
-// Chunk of block x of the KV head with running number `head`.  Workgroups go to the XCDs, there to the shader engines and to CUs in turn by their
-// index, and the short sequences of a ragged batch have no late chunks: rotated by the head's number, all places get early
-// and late ones alike.  For S < 32 blocks per head that comes around: after 256 workgroups the same chunk is at the same place again if S is 8 or
-// 16 (from 32 on only every fourth time), so the rotation moves on with every 256 (d = 128, 150 ragged sequences of 25K 1.29 times as
-// fast by it, 100 of 32K 1.12; d = 64, 200 of 32K 1100 -> 953 us; with S >= 32 12 of 128K at d = 128 would lose 2.4 %).
-__device__ __forceinline__ int chunk_at(uint32_t x, uint32_t head, uint32_t S) { return (int)((x + head + (S < 32 ? head * S / 256 : 0)) % S); }
+// Chunk of block x of the KV head with running number `head`, S blocks per head.  Workgroups go to the XCDs, there to the shader engines and to CUs
+// in turn by their index, and the short sequences of a ragged batch have no late chunks: all 256 places must get early and late ones
+// alike.  With an odd S the heads' blocks run through all places by themselves (rotated by the head's number a chunk would move on by S - 1
+// places, 32 of them at S = 33: 12 sequences of 66K at d = 128 203 us per step, rotated 245; 16 of 33K with 4 / 4 heads of 64 52 and 59),
+// with an even one the rotation makes them do so.  For few blocks it comes around: after 256 workgroups the same chunk is at the same
+// place again if S is 8 or 16 (32: every fourth time), so there it moves on with every 256 (d = 128, 150 ragged sequences of 25K 1.29
+// times as fast by it, 100 of 32K 1.12; d = 64, 200 of 32K 1100 -> 953 us; with S = 32 12 of 128K at d = 128 would lose 2.4 %), odd numbers
+// as well (5 to 31 blocks: 0 to 5 % faster than unrotated).
+__device__ __forceinline__ int chunk_at(uint32_t x, uint32_t head, uint32_t S) {
+  return (int)((x + (S < 32 ? head + head * S / 256 : S % 2 ? 0 : head)) % S);
+}
 
 // 256 threads; the chunks of all KV heads, then their side jobs, numbered over a grid of one or more rows: wavefront w is slot w of the workgroup's chunk.  Bound by HBM for long
 // caches, by the latency of a few round trips for short ones.  A wavefront holds two groups of TPI / 4 tiles, one on its way
